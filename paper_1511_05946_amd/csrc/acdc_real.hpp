@@ -655,7 +655,7 @@ __host__ __device__ void real_backward_row(Ctx& ctx, const RealArgs& a, unsigned
         reinterpret_cast<float4*>(slab)[lc + cc] = make_float4(lo.x, hi.y, lo.y, hi.x);
       });
       ctx.sync_all();
-      sum_rows<ROWS, PL::SLAB, THREADS, N>(lds, GView::of(part + N + QF), tid);
+      sum_rows<ROWS, PL::SLAB, THREADS, N>(ctx, lds, GView::of(part + N + QF), tid);
       ctx.sync_all();
     }
     // h2 = DCT(u * a), gh3 = DCT(g); dL/dd image h2 * gh3; g <- pre(gh3 * d)
@@ -677,7 +677,7 @@ __host__ __device__ void real_backward_row(Ctx& ctx, const RealArgs& a, unsigned
     if constexpr (ACC)
       if (old != nullptr) lds_fetch_wait();
     ctx.sync_all();
-    sum_rows<SROWS, SSTRIDE, THREADS, QF>(lds, GView::of(part + N), tid, ACC ? old : nullptr);
+    sum_rows<SROWS, SSTRIDE, THREADS, QF>(ctx, lds, GView::of(part + N), tid, ACC ? old : nullptr);
     ctx.sync_all();
     // and its dL/da values, for the sum after the inverse transform
     if constexpr (ACC)
@@ -725,7 +725,7 @@ __host__ __device__ void real_backward_row(Ctx& ctx, const RealArgs& a, unsigned
     O::load_vec(av, ak, L);
     ACDC_SCHED_FENCE();
     ctx.sync_all();
-    sum_rows<SROWS, SSTRIDE, THREADS, N>(lds, GView::of(part), tid, ACC ? old : nullptr);
+    sum_rows<SROWS, SSTRIDE, THREADS, N>(ctx, lds, GView::of(part), tid, ACC ? old : nullptr);
     ctx.sync_all();
     // dL/du = gh1 * a, then un-permute; the next layer's u loads meanwhile
     O::scale(g, av);

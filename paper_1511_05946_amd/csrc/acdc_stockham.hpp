@@ -17,6 +17,8 @@
 // every row access is 16 bytes.
 #pragma once
 
+#include <type_traits>
+
 #include "acdc_dft.hpp"
 #include "acdc_mem.hpp"
 
@@ -284,27 +286,62 @@ __host__ __device__ __forceinline__ void stockham_fft2(Ctx& ctx, float2 (&v)[PL:
   }
 }
 
-// Sum the per-row images [rows][SLAB] of a workgroup in fixed row order and
-// write the first NFL floats to out (float4 granularity).  With `old` (LDS,
-// NFL floats) the sum is added to it afterwards: old + (row 0 + ... ).
-// Called by every thread; the trip count is a compile-time constant.
-template <int ROWS, int SLAB, int THREADS, int NFL>
-__host__ __device__ __forceinline__ void sum_rows(const float* lds, GView out, int tid,
+// Phases of sum_rows: where the image has fewer float4 entries than the
+// workgroup has threads, the rows are split over PH groups of threads.
+// Rows + phases is the serial chain of LDS reads, shortest near
+// sqrt(rows); 16 is that for the 128 to 512 rows of the narrow widths.
+// Without phases N = 32 summed 128 rows on 8 threads of 256, twice a layer.
+// Eight layers forward and backward, without and with phases: N = 8, 100
+// rows 105 and 39 us; N = 32, 100 rows 83 and 52 us; complex N = 256, 4096
+// rows 256 and 198 us; N = 512 and up has one or two phases, no change.
+template <int ROWS, int THREADS, int NFL>
+constexpr int sum_phases() {
+  int ph = 1;
+  while (ph < 16 && 2 * ph <= THREADS / (NFL / 4) && ROWS % (2 * ph) == 0) ph *= 2;
+  return ph;
+}
+
+// Sum the per-row images [rows][SLAB] of a workgroup in a fixed order and
+// write the first NFL floats to out (float4 granularity): row by row, or
+// (sum_phases) each phase's consecutive rows, then the phase sums in phase
+// order.  A phase's sum replaces its first row's entry, which no other
+// thread reads, until the second stage.  With `old` (LDS, NFL floats) the
+// sum is added to it afterwards: old + (row 0 + ... ).  Called by every
+// thread; the trip count is a compile-time constant.
+template <int ROWS, int SLAB, int THREADS, int NFL, class Ctx>
+__host__ __device__ __forceinline__ void sum_rows(Ctx& ctx, float* lds, GView out, int tid,
                                                   const float* old = nullptr) {
   constexpr int N4 = NFL / 4;
+  auto sum = [&](const float* first, unsigned e, auto rows, auto stride) {
+    float4 s = reinterpret_cast<const float4*>(first)[e];
+#pragma unroll
+    for (int r = 1; r < rows.value; ++r) {
+      const float4 u = reinterpret_cast<const float4*>(first + r * stride.value)[e];
+      s.x += u.x;
+      s.y += u.y;
+      s.z += u.z;
+      s.w += u.w;
+    }
+    return s;
+  };
+  constexpr int PH = sum_phases<ROWS, THREADS, NFL>();
+  if constexpr (PH > 1) {
+    constexpr int RP = ROWS / PH;  // rows per phase
+    const unsigned e = unsigned(tid) % N4, ph = unsigned(tid) / N4;
+    float* const first = lds + ph * unsigned(RP * SLAB);
+    if (ph < unsigned(PH))
+      reinterpret_cast<float4*>(first)[e] =
+          sum(first, e, std::integral_constant<int, RP>{}, std::integral_constant<int, SLAB>{});
+    ctx.sync_all();
+    if (ph == 0)
+      out.st4(sum(lds, e, std::integral_constant<int, PH>{}, std::integral_constant<int, RP * SLAB>{}), e * 16u, 0u);
+    return;
+  }
 #pragma unroll
   for (int e0 = 0; e0 < N4; e0 += THREADS) {
     const unsigned e = unsigned(e0 + tid);
     if (N4 % THREADS == 0 || e < unsigned(N4)) {
-      float4 s = reinterpret_cast<const float4*>(lds)[e];
-#pragma unroll
-      for (int r = 1; r < ROWS; ++r) {
-        const float4 u = reinterpret_cast<const float4*>(lds + r * SLAB)[e];
-        s.x += u.x;
-        s.y += u.y;
-        s.z += u.z;
-        s.w += u.w;
-      }
+      float4 s = sum(lds, e, std::integral_constant<int, ROWS>{}, std::integral_constant<int, SLAB>{});
       if (old != nullptr) {
         const float4 o = reinterpret_cast<const float4*>(old)[e];
         s = make_float4(o.x + s.x, o.y + s.y, o.z + s.z, o.w + s.w);
