@@ -72,11 +72,11 @@ __device__ __forceinline__ void copy_twiddles(float* dst, const char* tab, int t
 }
 
 // The forward kernel is persistent: workgroup b handles row groups (tiles)
-// b, b + gridDim.x, ...  Rows are independent, so results do not depend on
-// the grid size.
+// b, b + gridDim.x, ... of `rpw` rows (fwd_rows).  Rows are independent, so
+// results do not depend on the grid size or on rpw.
 template <class PL, bool BIAS>
 __global__ __launch_bounds__(Launch<PL>::FWD_THREADS)
-__attribute__((amdgpu_waves_per_eu(Launch<PL>::FWD_WPE))) void k_real_fwd(RealArgs a, long long ntiles) {
+__attribute__((amdgpu_waves_per_eu(Launch<PL>::FWD_WPE))) void k_real_fwd(RealArgs a, long long ntiles, int rpw) {
   using L = Launch<PL>;
   __shared__ float lds[L::FWD_LDS_FLOATS];
   DevCtx<PL::T> ctx;
@@ -92,9 +92,10 @@ __attribute__((amdgpu_waves_per_eu(Launch<PL>::FWD_WPE))) void k_real_fwd(RealAr
     float* twl = lds;
     copy_twiddles<PL>(twl, a.tab, tid, L::FWD_THREADS);
     ctx.sync_all();
+    if (r >= rpw) return;  // whole waves, which have no row: no barrier follows
     const LdsView tw = LdsView::of(twl);
     for (long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x)
-      real_forward_row<PL, BIAS>(ctx, a, t, tile * L::FWD_ROWS, unsigned(r), slab, tw);
+      real_forward_row<PL, BIAS>(ctx, a, t, tile * rpw, unsigned(r), slab, tw);
   } else {
     const GView tw = GView::of(a.tab);
     for (long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x)
@@ -380,29 +381,32 @@ int get_table(int N, bool cplx, const char** out) {
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // Workgroups of `kernel` (with `threads` threads) that fit on the current
-// device at once; the persistent kernels launch min(tiles, this).  With
-// `remember` false a value not yet cached is computed without caching it
-// (the no-allocation entry point inserts nothing).
-std::map<std::pair<const void*, int>, long long> g_resident;
-long long resident_workgroups(const void* kernel, int threads, bool remember = true) {
+// device at once (n; the persistent kernels launch min(tiles, n)) and the
+// device's CUs.  With `remember` false a value not yet cached is computed
+// without caching it (the no-allocation entry point inserts nothing).
+struct Resident {
+  long long n = 0;
+  int cus = 0;
+};
+std::map<std::pair<const void*, int>, Resident> g_resident;
+Resident resident_workgroups(const void* kernel, int threads, bool remember = true) {
+  Resident r;
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  if (hipGetDevice(&dev) != hipSuccess) return r;
   std::lock_guard<std::mutex> lock(g_mu);
   auto key = std::make_pair(kernel, dev);
   auto it = g_resident.find(key);
   if (it != g_resident.end()) return it->second;
   int per_cu = 0, cus = 0;
-  long long n = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) == hipSuccess &&
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
-    n = (long long)per_cu * cus;
-  if (remember) g_resident[key] = n;
-  return n;
+    r = Resident{(long long)per_cu * cus, cus};
+  if (remember) g_resident[key] = r;
+  return r;
 }
 
-long long persistent_grid(const void* kernel, int threads, long long tiles, bool remember = true) {
-  const long long n = resident_workgroups(kernel, threads, remember);
-  return (n > 0 && n < tiles) ? n : tiles;
+long long persistent_grid(long long resident, long long tiles) {
+  return (resident > 0 && resident < tiles) ? resident : tiles;
 }
 
 // Per-device address of `scratch`, set by acdc_prepare (the library's set-up
@@ -473,6 +477,30 @@ long long fwd_blocks(int64_t batch) {
 template <class PL>
 long long bwd_tiles(int64_t batch) {
   return (batch + Launch<PL>::BWD_ROWS - 1) / Launch<PL>::BWD_ROWS;
+}
+
+// Rows per forward workgroup of the plans with several waves per workgroup
+// (twiddles in LDS): all of FWD_ROWS once the batch gives every CU one such
+// workgroup; below that the waves are spread evenly over the CUs.  A row is
+// a serial chain through all K layers, and two waves on one SIMD take twice
+// as long for it while other CUs idle.  K = 12, without and with the spread:
+// N = 4096, 16 rows 128 and 101 us (two workgroups of 8 waves, 16 of one),
+// 700 rows 136 and 110; N = 1024, 700 rows 68 and 47; N = 64, 128 rows 46
+// and 36.  (Spreading over every resident workgroup instead, several to a
+// CU, ran N = 1024 x 4096 rows 1.6 % slower: more copies of the twiddles.)
+template <class PL>
+int fwd_rows(int64_t batch, int cus) {
+  using L = Launch<PL>;
+  if constexpr (!L::TW_LDS) {
+    return L::FWD_ROWS;
+  } else {
+    constexpr int RW = 64 / PL::T;             // rows per wave
+    constexpr int WAVES = L::FWD_ROWS / RW;
+    static_assert(PL::T <= 64 && L::FWD_ROWS % RW == 0, "whole waves of rows");
+    if (cus <= 0) return L::FWD_ROWS;
+    const long long waves = (batch + RW - 1) / RW, each = (waves + cus - 1) / cus;
+    return int(each < WAVES ? each : WAVES) * RW;
+  }
 }
 
 size_t elem_floats(uint32_t flags) { return (flags & kFlagComplex) ? 2 : 1; }
@@ -550,10 +578,12 @@ int launch_real_mq(const float* D, const float* Bias, float4* Mq, int K, const c
 
 template <class PL, bool BIAS>
 void launch_real_fwd_k(const RealArgs& a, hipStream_t s, bool remember) {
-  const long long tiles = fwd_blocks<PL>(a.batch);
-  const long long grid = persistent_grid(reinterpret_cast<const void*>(&k_real_fwd<PL, BIAS>),
-                                         Launch<PL>::FWD_THREADS, tiles, remember);
-  hipLaunchKernelGGL((k_real_fwd<PL, BIAS>), dim3(unsigned(grid)), dim3(Launch<PL>::FWD_THREADS), 0, s, a, tiles);
+  const Resident res = resident_workgroups(reinterpret_cast<const void*>(&k_real_fwd<PL, BIAS>),
+                                           Launch<PL>::FWD_THREADS, remember);
+  const int rpw = fwd_rows<PL>(a.batch, res.cus);
+  const long long tiles = (a.batch + rpw - 1) / rpw;
+  hipLaunchKernelGGL((k_real_fwd<PL, BIAS>), dim3(unsigned(persistent_grid(res.n, tiles))), dim3(Launch<PL>::FWD_THREADS), 0, s, a, tiles,
+                     rpw);
 }
 
 template <class PL>
@@ -1231,7 +1261,8 @@ extern "C" int acdc_backward(const float* x, const float* grad_y, const float* A
       // persistent (accumulating) unbiased backward
       const long long slots =
           (L::BWD_ACC && !bias_on)
-              ? persistent_grid(reinterpret_cast<const void*>(&k_real_bwd<PL, false>), L::BWD_THREADS, tiles)
+              ? persistent_grid(
+                    resident_workgroups(reinterpret_cast<const void*>(&k_real_bwd<PL, false>), L::BWD_THREADS).n, tiles)
               : tiles;
       float4* Mq = reinterpret_cast<float4*>(ws + w.off_mq);
       int4* P16 = batch > 0 ? perm16_of<PL>(Mq, K, flags) : nullptr;
