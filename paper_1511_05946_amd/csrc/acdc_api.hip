@@ -606,57 +606,53 @@ int launch_cplx_fwd(const CplxArgs& a, hipStream_t s) {
 
 // ------------------------------------------------------ multi-pass path
 
-mp::Geo mp_geo(long long N) {
-  mp::Geo g;
-  g.M = N / 2;
-  g.L = int(g.M < 8192 ? g.M : 8192);
-  const long long ratio = g.M / g.L;
-  g.R1 = ratio == 1 ? 1 : int(ratio <= 16 ? ratio : 16);
-  g.R2 = ratio <= 16 ? 1 : int(ratio / 16);
-  return g;
-}
-
 struct MpTabs {
-  const float2* tw = nullptr;
+  const float2 *tw1 = nullptr, *tw2 = nullptr;
   QuartetTabs q{};
-  const char* seg = nullptr;  // the complex plan table of the segment length
+  const char* seg = nullptr;  // the segment plan's table
 };
 std::map<std::pair<int, int>, void*> g_mp_tables;  // (device, N) -> device table
 
+// The device copy of a host-built table, made on first use.
+template <class Key, class Build>
+int device_table(std::map<Key, void*>& tables, const Key& key, Build&& build, void** out) {
+  std::lock_guard<std::mutex> lock(g_mu);
+  auto it = tables.find(key);
+  if (it == tables.end()) {
+    std::vector<unsigned char> host;
+    if (!build(host)) return ACDC_ERR_UNSUPPORTED;
+    void* d = nullptr;
+    hipError_t e = hipMalloc(&d, host.size());
+    if (e != hipSuccess) return hip_fail(e);
+    e = hipMemcpy(d, host.data(), host.size(), hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+      (void)hipFree(d);
+      return hip_fail(e);
+    }
+    it = tables.emplace(key, d).first;
+  }
+  *out = it->second;
+  return ACDC_OK;
+}
+
 int get_mp_tables(int N, MpTabs* out) {
   int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
+  const hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e);
-  const mp::Geo g = mp_geo(N);
-  int rc = get_table(g.L, true, &out->seg);
+  const mp::Geo g = mp::geo(N);
+  void *seg = nullptr, *d = nullptr;
+  // third key value 2: segment plans (0 real, 1 complex rows)
+  int rc = device_table(g_tables, std::make_tuple(dev, g.L, 2),
+                        [&](std::vector<unsigned char>& h) { return mp::build_seg_table(g.L, h); }, &seg);
   if (rc != ACDC_OK) return rc;
-  void* d = nullptr;
-  {
-    std::lock_guard<std::mutex> lock(g_mu);
-    auto it = g_mp_tables.find({dev, N});
-    if (it != g_mp_tables.end()) d = it->second;
-  }
-  if (d == nullptr) {
-    std::vector<unsigned char> host;
-    if (!build_mp_tables(N, host)) return ACDC_ERR_UNSUPPORTED;
-    std::lock_guard<std::mutex> lock(g_mu);
-    auto it = g_mp_tables.find({dev, N});
-    if (it != g_mp_tables.end()) {
-      d = it->second;
-    } else {
-      e = hipMalloc(&d, host.size());
-      if (e != hipSuccess) return hip_fail(e);
-      e = hipMemcpy(d, host.data(), host.size(), hipMemcpyHostToDevice);
-      if (e != hipSuccess) {
-        (void)hipFree(d);
-        return hip_fail(e);
-      }
-      g_mp_tables[{dev, N}] = d;
-    }
-  }
+  rc = device_table(g_mp_tables, std::make_pair(dev, N),
+                    [&](std::vector<unsigned char>& h) { return build_mp_tables(N, g.R1, g.R2, g.L, h); }, &d);
+  if (rc != ACDC_OK) return rc;
   const char* base = static_cast<const char*>(d);
-  const MpTableLayout l = mp_table_layout(N);
-  out->tw = reinterpret_cast<const float2*>(base + l.tw);
+  const MpTableLayout l = mp_table_layout(N, g.R1, g.R2, g.L);
+  out->seg = static_cast<const char*>(seg);
+  out->tw1 = reinterpret_cast<const float2*>(base + l.tw1);
+  out->tw2 = reinterpret_cast<const float2*>(base + l.tw2);
   const double qb = 1.0 / (2.0 * std::sqrt(double(N)));
   out->q = QuartetTabs{reinterpret_cast<const float4*>(base + l.mk0), reinterpret_cast<const float4*>(base + l.mk1),
                        reinterpret_cast<const int4*>(base + l.qidx), reinterpret_cast<const int*>(base + l.qmask),
@@ -664,43 +660,64 @@ int get_mp_tables(int N, MpTabs* out) {
   return ACDC_OK;
 }
 
-size_t mp_mq_bytes(long long N, int K) { return align256(size_t(K) * size_t(N / 4) * kMqRows * sizeof(float4)); }
-size_t mp_rows_bytes(int64_t batch, long long N) { return align256(size_t(batch) * size_t(N) * sizeof(float)); }
-
-// Floats per row element: 1, or 2 for complex (AFDF) rows.
+// Floats per row element (1, or 2 for complex rows), and the geometry of
+// rows of N elements.
 int mp_ew(uint32_t flags) { return (flags & kFlagComplex) ? 2 : 1; }
+mp::Geo mp_geo(int32_t N, uint32_t flags) { return mp::geo((long long)N * mp_ew(flags)); }
+
+// Bytes of the layers' coefficients: the quartet tables (real), d / N in
+// storage order (complex).
+size_t mp_coef_bytes(long long N, int K, uint32_t flags) {
+  return align256((flags & kFlagComplex) ? size_t(K) * N * sizeof(float2)
+                                         : size_t(K) * size_t(N / 4) * kMqRows * sizeof(float4));
+}
+size_t mp_rows_bytes(int64_t batch, long long row_floats) {
+  return align256(size_t(batch) * size_t(row_floats) * sizeof(float));
+}
 
 // Permutation tables: all K layers' built at once (four launches per call)
 // when they take at most 256 MB, else one layer's, rebuilt per layer.
-int mp_perm_layers(long long N, int K, int ew) {
-  const size_t per = mp::perm_table_ints(N, ew) * sizeof(int);
+int mp_perm_layers(const mp::Geo& g, int K, int ew) {
+  const size_t per = mp::perm_table_ints(g, ew) * sizeof(int);
   return per * size_t(K) <= (size_t(256) << 20) ? K : 1;
 }
-size_t mp_perm_bytes(long long N, int K, uint32_t flags) {
+size_t mp_perm_bytes(const mp::Geo& g, int K, uint32_t flags) {
   if (!(flags & kFlagPerm)) return 0;
   const int ew = mp_ew(flags);
-  return align256(mp::perm_table_ints(N, ew) * sizeof(int) * size_t(mp_perm_layers(N, K, ew)));
-}
-// Layer k's tables, building them first when they are not all built.
-hipError_t mp_perm_tabs(const int32_t* perm, long long N, int K, int k, const mp::PermTabs& pt, mp::PermTabs* out,
-                        hipStream_t s, int ew = 1) {
-  if (mp_perm_layers(N, K, ew) == K) {
-    *out = mp::perm_layer(pt, k);
-    return hipSuccess;
-  }
-  *out = pt;
-  return mp::perm_build(perm + (long long)k * N, N, 1, pt, s, ew);
-}
-hipError_t mp_perm_prebuild(const int32_t* perm, long long N, int K, const mp::PermTabs& pt, hipStream_t s,
-                            int ew = 1) {
-  return mp_perm_layers(N, K, ew) == K ? mp::perm_build(perm, N, K, pt, s, ew) : hipSuccess;
+  return align256(mp::perm_table_ints(g, ew) * sizeof(int) * size_t(mp_perm_layers(g, K, ew)));
 }
 
-// Forward workspace: quartet coefficients, the packed spectrum (also the
-// permutation's scratch), the layer output; with PERM the permuted layer
-// input (when no stash takes it) and the permutation tables.
+// The permutation tables of one call.
+struct MpPerm {
+  const int32_t* perm;
+  mp::Geo g;
+  int ew, K;
+  mp::PermTabs base;
+  bool all;  // every layer's tables are built
+  MpPerm(const int32_t* p, const mp::Geo& geo, int K_, uint32_t flags, char* ws)
+      : perm(p), g(geo), ew(mp_ew(flags)), K(K_), all(mp_perm_layers(geo, K_, mp_ew(flags)) == K_) {
+    base = mp::perm_tables_at(reinterpret_cast<int*>(ws), g, ew);
+  }
+  hipError_t prebuild(hipStream_t s) const { return all ? mp::perm_build(perm, g, ew, K, base, s) : hipSuccess; }
+  // Layer k's tables.  Not all built: they take the one place there is, so
+  // the previous layer's have been used by then.
+  hipError_t layer(int k, mp::PermTabs* out, hipStream_t s) const {
+    if (all) {
+      *out = mp::perm_layer(base, k);
+      return hipSuccess;
+    }
+    *out = base;
+    const long long N = 2 * g.M / ew;
+    return mp::perm_build(perm + k * N, g, ew, 1, base, s);
+  }
+};
+
+// Forward workspace: the layers' coefficients, the spectra, and with PERM
+// the rows between the two halves of a permutation and the tables.  The
+// total is at least that of earlier releases' layout (three buffers of rows
+// with PERM, two without), which callers may have sized by hand.
 struct MpFwdWs {
-  size_t mq = 0, z = 0, zbuf = 0, ubuf = 0, ptab = 0, total = 0;
+  size_t coef = 0, z = 0, tmp = 0, ptab = 0, total = 0;
 };
 MpFwdWs mp_fwd_ws(int64_t batch, int32_t N, int32_t K, uint32_t flags) {
   MpFwdWs w;
@@ -710,22 +727,24 @@ MpFwdWs mp_fwd_ws(int64_t batch, int32_t N, int32_t K, uint32_t flags) {
     off += align256(bytes);
     return o;
   };
-  const long long rowf = (long long)N * mp_ew(flags);  // floats per row
-  w.mq = take((flags & kFlagComplex) ? 0 : mp_mq_bytes(N, K));
-  w.z = take(mp_rows_bytes(batch, rowf));
-  w.zbuf = take(mp_rows_bytes(batch, rowf));
-  w.ubuf = take((flags & kFlagPerm) ? mp_rows_bytes(batch, rowf) : 0);
-  w.ptab = take(mp_perm_bytes(N, K, flags));
-  w.total = off;
+  const mp::Geo g = mp_geo(N, flags);
+  const bool perm_on = (flags & kFlagPerm) != 0;
+  const size_t rows = mp_rows_bytes(batch, 2 * g.M);
+  w.coef = take(mp_coef_bytes(N, K, flags));
+  w.z = take(rows);
+  w.tmp = take(perm_on ? rows : 0);
+  w.ptab = take(mp_perm_bytes(g, K, flags));
+  w.total = off + rows;
   return w;
 }
 
-// Backward workspace: quartet coefficients, the h and g spectra (contiguous,
-// transformed together), dL/dv of the current layer, the next layer's g,
-// the dL/da image, the row-block sums (dL/dd, then dL/da; dL/db), the
-// recompute stash and the permutation tables.
+// Backward workspace: the coefficients, the h and g spectra (contiguous:
+// the second-level passes take both), the rows between the halves of a
+// permutation, the row-block sums, with a bias the batch sum of g's spectra
+// and its block sums, the recompute stash and the permutation tables.  At
+// least as large as earlier releases' layout, as in the forward.
 struct MpBwdWs {
-  size_t mq = 0, zhg = 0, gh1 = 0, gbuf = 0, imgA = 0, gu = 0, part = 0, partB = 0, stash = 0, ptab = 0, total = 0;
+  size_t coef = 0, zhg = 0, tmp = 0, part = 0, zsum = 0, partB = 0, stash = 0, ptab = 0, total = 0;
 };
 MpBwdWs mp_bwd_ws(int64_t batch, int32_t N, int32_t K, uint32_t flags, bool have_saved) {
   MpBwdWs w;
@@ -735,21 +754,21 @@ MpBwdWs mp_bwd_ws(int64_t batch, int32_t N, int32_t K, uint32_t flags, bool have
     off += align256(bytes);
     return o;
   };
-  const bool cplx = (flags & kFlagComplex) != 0;
-  const size_t rowf = size_t(N) * size_t(mp_ew(flags));  // floats per row
-  const size_t rows = size_t(batch) * rowf * sizeof(float);
-  w.mq = take(cplx ? 0 : mp_mq_bytes(N, K));
+  const mp::Geo g = mp_geo(N, flags);
+  const bool cplx = (flags & kFlagComplex) != 0, perm_on = (flags & kFlagPerm) != 0, bias = (flags & kFlagBias) != 0;
+  const size_t rowb = size_t(2 * g.M) * sizeof(float), rows = size_t(batch) * rowb;
+  w.coef = take(mp_coef_bytes(N, K, flags));
   w.zhg = take(2 * rows);
-  w.gh1 = take(rows);
-  w.gbuf = take(rows);
-  w.imgA = take(rows);
-  w.gu = take(cplx && (flags & kFlagPerm) ? rows : 0);  // complex dL/du before the adjoint permutation
-  const size_t parts = size_t((batch + mp::kColRows - 1) / mp::kColRows) * rowf * sizeof(float);
-  w.part = take(parts);
-  w.partB = take((flags & kFlagBias) ? parts : 0);
+  w.tmp = take(perm_on ? rows : 0);
+  auto blocks = [&](int rb) { return size_t((batch + rb - 1) / rb); };
+  const size_t nseg = blocks(mp::seg_rows(batch, g, cplx)), ncol = blocks(mp::col_rows(batch, g, mp_ew(flags)));
+  w.part = take((nseg > ncol ? nseg : ncol) * rowb);
+  w.zsum = take(bias ? rowb : 0);
+  w.partB = take(bias ? blocks(mp::kMaxRows) * rowb : 0);
   w.stash = take(have_saved ? 0 : saved_floats(batch, N, K, flags) * sizeof(float));
-  w.ptab = take(mp_perm_bytes(N, K, flags));
-  w.total = off;
+  w.ptab = take(mp_perm_bytes(g, K, flags));
+  const size_t before = (cplx && perm_on ? 6 : 5) * rows + (have_saved ? 0 : saved_floats(batch, N, K, flags) * 4);
+  w.total = off > before ? off : align256(before);
   return w;
 }
 
@@ -759,278 +778,219 @@ MpBwdWs mp_bwd_ws(int64_t batch, int32_t N, int32_t K, uint32_t flags, bool have
     if (e_ != hipSuccess) return hip_fail(e_); \
   } while (0)
 
-// Pack rows of src (stashed, scaled by a; each may be null) and run the
-// forward FFT: the first DIF pass takes the packing.
-int mp_pack_fft(const float* src, const float* a, float* stash, float2* Z, long long rows, long long N,
-                const mp::Geo& g, const MpTabs& t, hipStream_t s) {
-  if (g.R1 > 1) {
-    MP_TRY(mp::pack_dif(src, a, stash, Z, rows, g.M, g.R1, t.tw, s));
-  } else {
-    MP_TRY(mp::pack(src, a, stash, Z, rows, N, s));
-  }
-  if (g.R2 > 1) MP_TRY(mp::dif(Z, rows, g, g.M / g.R1, g.R2, t.tw, s));
-  MP_TRY(mp::segments(Z, rows * (g.M / g.L), g.L, false, t.seg, s));
-  return ACDC_OK;
-}
-
-// Inverse FFT, then unpack (+ ReLU) into dst: the last DIT pass takes the unpacking.
-int mp_ifft_unpack(float2* Z, float* dst, long long rows, long long N, bool relu, const mp::Geo& g, const MpTabs& t,
-                   hipStream_t s) {
-  MP_TRY(mp::segments(Z, rows * (g.M / g.L), g.L, true, t.seg, s));
-  if (g.R2 > 1) MP_TRY(mp::dit(Z, rows, g, g.M / g.R1, g.R2, t.tw, s));
-  if (g.R1 > 1) {
-    MP_TRY(mp::dit_unpack(Z, dst, rows, g.M, g.R1, t.tw, relu, s));
-  } else {
-    MP_TRY(mp::unpack(Z, dst, rows, N, relu, s));
-  }
-  return ACDC_OK;
-}
-
 // Stash slot of layer input u_k (the fused path's layout): k - 1, or K - 1
 // for u_0 with PERM.
-float* mp_slot(float* saved, int k, int K, long long batch, long long N, bool perm_on) {
+float* mp_slot(float* saved, int k, int K, long long batch, long long row_floats, bool perm_on) {
   if (saved == nullptr) return nullptr;
-  if (k > 0) return saved + (long long)(k - 1) * batch * N;
-  return perm_on ? saved + (long long)(K - 1) * batch * N : nullptr;
+  if (k > 0) return saved + (long long)(k - 1) * batch * row_floats;
+  return perm_on ? saved + (long long)(K - 1) * batch * row_floats : nullptr;
 }
 
-// The K forward layers.  With PERM, the permuted input u_k goes to its
-// stash slot (or to ubuf without a stash), Z serving as the permutation's
-// scratch; without, the packing stashes z itself.
-int mp_forward_layers(const float* x, float* y, const float* A, const float4* Mq, const int32_t* perm,
-                      int64_t batch, int32_t N, int32_t K, uint32_t flags, float* saved, float2* Z, float* zbuf,
-                      float* ubuf, const mp::PermTabs& pt, bool tables_built, const MpTabs& t, hipStream_t s) {
-  const mp::Geo g = mp_geo(N);
-  const bool perm_on = (flags & kFlagPerm) != 0, relu = (flags & kFlagRelu) != 0;
-  if (perm_on && !tables_built) MP_TRY(mp_perm_prebuild(perm, N, K, pt, s));
-  for (int k = 0; k < K; ++k) {
-    const float* src = k == 0 ? x : zbuf;
-    float* slot = mp_slot(saved, k, K, batch, N, perm_on);
-    const float* u = src;
-    if (perm_on) {
-      const int32_t* pk = perm + (long long)k * N;
-      float* udst = slot != nullptr ? slot : ubuf;
-      mp::PermTabs tk;
-      MP_TRY(mp_perm_tabs(perm, N, K, k, pt, &tk, s));
-      MP_TRY(mp::permute(src, udst, reinterpret_cast<float*>(Z), pk, tk, batch, N, s));
-      u = udst;
-      slot = nullptr;  // already stashed
-    }
-    int rc = mp_pack_fft(u, A + (long long)k * N, slot, Z, batch, N, g, t, s);
-    if (rc != ACDC_OK) return rc;
-    MP_TRY(mp::mid_fwd(Z, Mq + (long long)k * (N / 4) * kMqRows, batch, g, (flags & kFlagBias) != 0, s));
-    rc = mp_ifft_unpack(Z, (k == K - 1 && y != nullptr) ? y : zbuf, batch, N, relu && k < K - 1, g, t, s);
-    if (rc != ACDC_OK) return rc;
-  }
-  return ACDC_OK;
-}
-
-// ------------------------------------------------ complex (AFDF) multi-pass
-// Rows of N complex elements are their own N-point FFT inputs (M = N, the
-// geometry and twiddles of a real width 2N).  Per layer: u = z[perm] (into
-// the stash slot), Z = FFT(u * a), Z *= d / N, z' = unnormalised IFFT(Z).
-int mp_cplx_forward_layers(const float2* x, float2* y, const float2* A, const float2* D, const int32_t* perm,
-                           int64_t batch, int32_t N, int32_t K, uint32_t flags, float* saved, float2* Z,
-                           float2* zbuf, float2* ubuf, const mp::PermTabs& pt, bool tables_built, const MpTabs& t,
-                           hipStream_t s) {
-  const mp::Geo g = mp_geo(2LL * N);
-  const bool perm_on = (flags & kFlagPerm) != 0;
-  const float invN = 1.0f / float(N);
-  if (perm_on && !tables_built) MP_TRY(mp_perm_prebuild(perm, N, K, pt, s, 2));
-  for (int k = 0; k < K; ++k) {
-    const float2* src = k == 0 ? x : zbuf;
-    float2* slot = reinterpret_cast<float2*>(mp_slot(saved, k, K, batch, 2LL * N, perm_on));
-    const float2* u = src;
-    if (perm_on) {
-      const int32_t* pk = perm + (long long)k * N;
-      float2* udst = slot != nullptr ? slot : ubuf;
-      mp::PermTabs tk;
-      MP_TRY(mp_perm_tabs(perm, N, K, k, pt, &tk, s, 2));
-      MP_TRY(mp::cpermute(src, udst, Z, pk, tk, batch, N, s));
-      u = udst;
-      slot = nullptr;  // already stashed
-    }
-    MP_TRY(mp::cfft_in(u, A + (long long)k * N, slot, Z, batch, g, t.tw, t.seg, s));
-    MP_TRY(mp::cmid_fwd(Z, D + (long long)k * N, batch, g, invN, s));
-    MP_TRY(mp::cifft_out(Z, (k == K - 1 && y != nullptr) ? y : zbuf, batch, g, t.tw, t.seg, s));
-  }
-  return ACDC_OK;
-}
-
-int mp_cplx_forward(const float* x, float* y, const float* A, const float* D, const int32_t* perm, int64_t batch,
-                    int32_t N, int32_t K, uint32_t flags, float* saved, void* workspace, hipStream_t s) {
+// One multi-pass call: geometry, constants, workspace.  The steps are those
+// of the fused rows; real and complex layers differ inside the launches.
+struct MpCall {
+  mp::Geo g;
   MpTabs t;
-  int rc = get_mp_tables(2 * N, &t);
-  if (rc != ACDC_OK) return rc;
-  const MpFwdWs w = mp_fwd_ws(batch, N, K, flags);
-  char* ws = static_cast<char*>(workspace);
-  const mp::PermTabs pt = mp::perm_tables_at(reinterpret_cast<int*>(ws + w.ptab), N, 2);
-  ProfScope prof(0, s);
-  if (batch == 0) return ACDC_OK;
-  return mp_cplx_forward_layers(reinterpret_cast<const float2*>(x), reinterpret_cast<float2*>(y),
-                                reinterpret_cast<const float2*>(A), reinterpret_cast<const float2*>(D), perm, batch,
-                                N, K, flags, saved, reinterpret_cast<float2*>(ws + w.z),
-                                reinterpret_cast<float2*>(ws + w.zbuf), reinterpret_cast<float2*>(ws + w.ubuf), pt,
-                                false, t, s);
-}
+  bool cplx, perm_on, relu, bias;
+  long long B, N, W;  // rows, elements and floats per row
+  int K;
+  float2* coef;  // quartet tables, or d / N
+  hipStream_t s;
 
-// Backward per layer (the fused complex kernels' steps): gh3 = FFT(g) / N,
-// h2 = FFT(u * a), dL/dd += gh3 conj(h2), gh1 = IFFT(gh3 conj(d)),
-// dL/da += gh1 conj(u), g_u = gh1 conj(a), scattered back through perm.
-int mp_cplx_backward(const float* x, const float* grad_y, const float* A, const float* D, const int32_t* perm,
-                     const float* saved, float* grad_x, float* grad_A, float* grad_D, int64_t batch, int32_t N,
-                     int32_t K, uint32_t flags, bool have_saved, void* workspace, hipStream_t s) {
-  MpTabs t;
-  int rc = get_mp_tables(2 * N, &t);
-  if (rc != ACDC_OK) return rc;
-  const MpBwdWs w = mp_bwd_ws(batch, N, K, flags, have_saved);
-  char* ws = static_cast<char*>(workspace);
-  float2* Zh = reinterpret_cast<float2*>(ws + w.zhg);
-  float2* Zg = Zh + batch * N;  // the g spectra follow the h spectra
-  float2* gh1 = reinterpret_cast<float2*>(ws + w.gh1);
-  float2* gbuf = reinterpret_cast<float2*>(ws + w.gbuf);
-  float2* imgA = reinterpret_cast<float2*>(ws + w.imgA);
-  float2* gu = reinterpret_cast<float2*>(ws + w.gu);
-  float* part = reinterpret_cast<float*>(ws + w.part);
-  float* stash = have_saved ? const_cast<float*>(saved) : reinterpret_cast<float*>(ws + w.stash);
-  const mp::PermTabs pt = mp::perm_tables_at(reinterpret_cast<int*>(ws + w.ptab), N, 2);
-  const mp::Geo g = mp_geo(2LL * N);
-  const bool perm_on = (flags & kFlagPerm) != 0, acc = (flags & kFlagAccumulate) != 0;
-  const float invN = 1.0f / float(N);
-  const long long W = 2LL * N;  // floats per row
-  const float2* x2 = reinterpret_cast<const float2*>(x);
-  const float2* A2 = reinterpret_cast<const float2*>(A);
-  const float2* D2 = reinterpret_cast<const float2*>(D);
-  ProfScope prof(1, s);
-  if (batch > 0) {
-    if (perm_on) MP_TRY(mp_perm_prebuild(perm, N, K, pt, s, 2));
-    if (!have_saved) {
-      // recompute the layer inputs into the workspace (Zh, gh1 are free until the layer loop)
-      rc = mp_cplx_forward_layers(x2, nullptr, A2, D2, perm, batch, N, K, flags, stash, Zh, gh1, nullptr, pt, true,
-                                  t, s);
-      if (rc != ACDC_OK) return rc;
-    }
+  const float4* mq(int k) const { return reinterpret_cast<const float4*>(coef) + (long long)k * (N / 4) * kMqRows; }
+  hipError_t coefs(const float* D, const float* Bias) const {
+    return cplx ? mp::dn(reinterpret_cast<const float2*>(D), coef, K, g, s)
+                : mp::mq(D, Bias, reinterpret_cast<float4*>(coef), K, g, t.q, s);
   }
-  for (int k = K - 1; k >= 0; --k) {
-    float* gA = grad_A + (long long)k * W;
-    float* gD = grad_D + (long long)k * W;
-    if (batch > 0) {
-      const float2* u = k > 0 || perm_on ? reinterpret_cast<const float2*>(mp_slot(stash, k, K, batch, W, perm_on))
-                                         : x2;
-      const float2* ak = A2 + (long long)k * N;
-      MP_TRY(mp::cfft_in(k == K - 1 ? reinterpret_cast<const float2*>(grad_y) : gbuf, nullptr, nullptr, Zg, batch, g,
-                         t.tw, t.seg, s));
-      MP_TRY(mp::cfft_in(u, ak, nullptr, Zh, batch, g, t.tw, t.seg, s));
-      MP_TRY(mp::cmid_bwd(Zh, Zg, D2 + (long long)k * N, batch, g, invN, reinterpret_cast<float2*>(part), s));
-      MP_TRY(mp::colsum_parts(part, batch, W, gD, nullptr, acc, s));
-      MP_TRY(mp::cifft_out(Zg, gh1, batch, g, t.tw, t.seg, s));
-      float2* gnext = reinterpret_cast<float2*>(k == 0 ? grad_x : reinterpret_cast<float*>(gbuf));
-      if (perm_on) {
-        const int32_t* pk = perm + (long long)k * N;
-        mp::PermTabs tk;
-        MP_TRY(mp_perm_tabs(perm, N, K, k, pt, &tk, s, 2));
-        MP_TRY(mp::cdA(gh1, u, ak, imgA, gu, batch, N, s));
-        MP_TRY(mp::cpermute_adjoint(gu, gnext, Zh, pk, tk, batch, N, s));  // Zh is free again
-      } else {
-        MP_TRY(mp::cdA(gh1, u, ak, imgA, gnext, batch, N, s));
-      }
-      MP_TRY(mp::colsum(reinterpret_cast<const float*>(imgA), batch, W, part, gA, nullptr, acc, s));
+  hipError_t cols(mp::Src a, mp::Sink b, const mp::Cols& c) const { return mp::cols(a, b, cplx, c, B, g, t.tw1, s); }
+  // the segment launch of layer k, between the second-level passes
+  hipError_t forward_middle(float2* Z, int k) const {
+    hipError_t e = mp::dif2(Z, B, g, t.tw2, s);
+    if (e != hipSuccess) return e;
+    e = cplx ? mp::cseg_fwd(Z, coef + (long long)k * N, B, g, t.seg, s)
+             : mp::seg_fwd(Z, mq(k), B, g, bias, t.seg, s);
+    return e != hipSuccess ? e : mp::dit2(Z, B, g, t.tw2, s);
+  }
+};
+
+// The K forward layers.  Without y (the backward's recompute) only the layer
+// inputs are wanted: they end with u_{K-1}'s store.
+int mp_forward_layers(const MpCall& m, const float* x, float* y, const float* A, const MpPerm& pm, float* saved,
+                      float2* Z, float* tmp) {
+  using mp::Sink;
+  using mp::Src;
+  mp::PermTabs tk;
+  if (m.perm_on) {
+    MP_TRY(pm.layer(0, &tk, m.s));
+    mp::Cols c;
+    c.src = x;
+    c.dst = tmp;
+    c.pt = &tk;
+    MP_TRY(m.cols(Src::rows, Sink::send, c));
+  }
+  for (int k = 0; k < m.K; ++k) {
+    const bool last = k == m.K - 1;
+    if (m.perm_on || k == 0) {
+      mp::Cols c;  // u_k, its stash, * a, the first DIF pass
+      c.src = m.perm_on ? tmp : x;
+      c.pt = m.perm_on ? &tk : nullptr;
+      c.Z = Z;
+      c.a = A + (long long)k * m.W;
+      c.stash = mp_slot(saved, k, m.K, m.B, m.W, m.perm_on);
+      MP_TRY(m.cols(m.perm_on ? Src::gather : Src::rows, Sink::dif, c));
+    }
+    if (last && y == nullptr) break;
+    MP_TRY(m.forward_middle(Z, k));
+    mp::Cols c;
+    c.Z = Z;
+    c.relu = m.relu && !last ? 1 : 0;
+    if (last) {
+      c.dst = y;
+      MP_TRY(m.cols(Src::dit, Sink::rows, c));
+    } else if (m.perm_on) {
+      MP_TRY(pm.layer(k + 1, &tk, m.s));
+      c.dst = tmp;
+      c.pt = &tk;
+      MP_TRY(m.cols(Src::dit, Sink::send, c));
     } else {
-      // no rows: zero (or unchanged, accumulating) parameter gradients
-      MP_TRY(mp::colsum(nullptr, 0, W, part, gD, nullptr, acc, s));
-      MP_TRY(mp::colsum(nullptr, 0, W, part, gA, nullptr, acc, s));
+      c.a = A + (long long)(k + 1) * m.W;
+      c.stash = mp_slot(saved, k + 1, m.K, m.B, m.W, false);
+      MP_TRY(m.cols(Src::dit, Sink::dif, c));
     }
   }
   return ACDC_OK;
+}
+
+int mp_call(MpCall* m, int64_t batch, int32_t N, int32_t K, uint32_t flags, void* coef, hipStream_t s) {
+  m->g = mp_geo(N, flags);
+  m->cplx = (flags & kFlagComplex) != 0;
+  m->perm_on = (flags & kFlagPerm) != 0;
+  m->relu = (flags & kFlagRelu) != 0;
+  m->bias = (flags & kFlagBias) != 0;
+  m->B = batch;
+  m->N = N;
+  m->W = 2 * m->g.M;
+  m->K = K;
+  m->coef = static_cast<float2*>(coef);
+  m->s = s;
+  return get_mp_tables(int(m->W), &m->t);
 }
 
 int mp_forward(const float* x, float* y, const float* A, const float* D, const float* bias, const int32_t* perm,
                int64_t batch, int32_t N, int32_t K, uint32_t flags, float* saved, void* workspace, hipStream_t s) {
-  if (flags & kFlagComplex) return mp_cplx_forward(x, y, A, D, perm, batch, N, K, flags, saved, workspace, s);
-  MpTabs t;
-  int rc = get_mp_tables(N, &t);
-  if (rc != ACDC_OK) return rc;
   const MpFwdWs w = mp_fwd_ws(batch, N, K, flags);
   char* ws = static_cast<char*>(workspace);
-  float4* Mq = reinterpret_cast<float4*>(ws + w.mq);
-  float2* Z = reinterpret_cast<float2*>(ws + w.z);
-  float* zbuf = reinterpret_cast<float*>(ws + w.zbuf);
-  float* ubuf = reinterpret_cast<float*>(ws + w.ubuf);
-  const mp::PermTabs pt = mp::perm_tables_at(reinterpret_cast<int*>(ws + w.ptab), N);
+  MpCall m;
+  const int rc = mp_call(&m, batch, N, K, flags, ws + w.coef, s);
+  if (rc != ACDC_OK) return rc;
+  const MpPerm pm(perm, m.g, K, flags, ws + w.ptab);
   ProfScope prof(0, s);
-  MP_TRY(mp::mq(D, bias, Mq, K, N / 4, t.q, s));
-  if (batch == 0) return ACDC_OK;
-  return mp_forward_layers(x, y, A, Mq, perm, batch, N, K, flags, saved, Z, zbuf, ubuf, pt, false, t, s);
+  MP_TRY(m.coefs(D, bias));
+  if (m.perm_on) MP_TRY(pm.prebuild(s));
+  return mp_forward_layers(m, x, y, A, pm, saved, reinterpret_cast<float2*>(ws + w.z),
+                           reinterpret_cast<float*>(ws + w.tmp));
 }
 
+// Backward, layer by layer from the last: Zg holds the first-level spectrum
+// of g (dL/dv_k) at the top of layer k.  Zh = that of u_k * a_k; the segment
+// launch sums the dL/dd images and leaves the inverse's segments in Zg; the
+// column launch after it sums the dL/da images and takes g * a through the
+// adjoint permutation to the next layer's Zg.  dL/db_k is the DCT-II of the
+// batch sum of g, taken on its spectrum.
 int mp_backward(const float* x, const float* grad_y, const float* A, const float* D, const float* bias,
                 const int32_t* perm, const float* saved, float* grad_x, float* grad_A, float* grad_D,
                 float* grad_bias, int64_t batch, int32_t N, int32_t K, uint32_t flags, bool have_saved,
                 void* workspace, hipStream_t s) {
-  if (flags & kFlagComplex)
-    return mp_cplx_backward(x, grad_y, A, D, perm, saved, grad_x, grad_A, grad_D, batch, N, K, flags, have_saved,
-                            workspace, s);
-  MpTabs t;
-  int rc = get_mp_tables(N, &t);
-  if (rc != ACDC_OK) return rc;
+  using mp::Order;
+  using mp::Sink;
+  using mp::Src;
   const MpBwdWs w = mp_bwd_ws(batch, N, K, flags, have_saved);
   char* ws = static_cast<char*>(workspace);
-  float4* Mq = reinterpret_cast<float4*>(ws + w.mq);
+  MpCall m;
+  int rc = mp_call(&m, batch, N, K, flags, ws + w.coef, s);
+  if (rc != ACDC_OK) return rc;
+  const mp::Geo& g = m.g;
   float2* Zh = reinterpret_cast<float2*>(ws + w.zhg);
-  float2* Zg = Zh + batch * (N / 2);  // the g spectra follow the h spectra
-  float* gh1 = reinterpret_cast<float*>(ws + w.gh1);
-  float* gbuf = reinterpret_cast<float*>(ws + w.gbuf);
-  float* imgA = reinterpret_cast<float*>(ws + w.imgA);
+  float2* Zg = Zh + batch * g.M;  // the g spectra follow the h spectra
+  float* tmp = reinterpret_cast<float*>(ws + w.tmp);
   float* part = reinterpret_cast<float*>(ws + w.part);
-  float* partB = (flags & kFlagBias) ? reinterpret_cast<float*>(ws + w.partB) : nullptr;
+  float* zsum = reinterpret_cast<float*>(ws + w.zsum);
+  float* partB = reinterpret_cast<float*>(ws + w.partB);
   float* stash = have_saved ? const_cast<float*>(saved) : reinterpret_cast<float*>(ws + w.stash);
-  const mp::PermTabs pt = mp::perm_tables_at(reinterpret_cast<int*>(ws + w.ptab), N);
-  const mp::Geo g = mp_geo(N);
-  const bool perm_on = (flags & kFlagPerm) != 0, relu = (flags & kFlagRelu) != 0;
+  const MpPerm pm(perm, g, K, flags, ws + w.ptab);
   const bool acc = (flags & kFlagAccumulate) != 0;
+  const Order order = m.cplx ? Order::spectrum : Order::quartets;
   ProfScope prof(1, s);
-  if (batch > 0) {
-    MP_TRY(mp::mq(D, bias, Mq, K, N / 4, t.q, s));
-    if (perm_on) MP_TRY(mp_perm_prebuild(perm, N, K, pt, s));
-    if (!have_saved) {
-      // recompute the layer inputs into the workspace (Zh, gh1 are free until the layer loop)
-      rc = mp_forward_layers(x, nullptr, A, Mq, perm, batch, N, K, flags, stash, Zh, gh1, nullptr, pt, true, t, s);
-      if (rc != ACDC_OK) return rc;
-    }
+  if (batch == 0) {
+    // no rows: zero (or unchanged, accumulating) parameter gradients
+    for (int k = 0; k < K; ++k)
+      for (float* o : {grad_A, grad_D, grad_bias})
+        if (o != nullptr)
+          MP_TRY(mp::colsum_parts(part, 0, m.W, o + k * m.W, Order::natural, g, nullptr, acc, s));
+    return ACDC_OK;
+  }
+  MP_TRY(m.coefs(D, bias));
+  if (m.perm_on) MP_TRY(pm.prebuild(s));
+  if (!have_saved) {
+    rc = mp_forward_layers(m, x, nullptr, A, pm, stash, Zh, tmp);
+    if (rc != ACDC_OK) return rc;
+  }
+  const long long pseg = (batch + mp::seg_rows(batch, g, m.cplx) - 1) / mp::seg_rows(batch, g, m.cplx);
+  const long long pcol = (batch + mp::col_rows(batch, g, mp_ew(flags)) - 1) / mp::col_rows(batch, g, mp_ew(flags));
+  {
+    mp::Cols c;
+    c.src = grad_y;
+    c.Z = Zg;
+    MP_TRY(m.cols(Src::rows, Sink::dif, c));
   }
   for (int k = K - 1; k >= 0; --k) {
-    float* gA = grad_A + (long long)k * N;
-    float* gD = grad_D + (long long)k * N;
-    float* gB = grad_bias ? grad_bias + (long long)k * N : nullptr;
-    if (batch > 0) {
-      const float* u = k > 0 || perm_on ? mp_slot(stash, k, K, batch, N, perm_on) : x;
-      const float* ak = A + (long long)k * N;
-      rc = mp_pack_fft(k == K - 1 ? grad_y : gbuf, nullptr, nullptr, Zg, batch, N, g, t, s);
-      if (rc != ACDC_OK) return rc;
-      rc = mp_pack_fft(u, ak, nullptr, Zh, batch, N, g, t, s);
-      if (rc != ACDC_OK) return rc;
-      MP_TRY(mp::mid_bwd(Zh, Zg, Mq + (long long)k * (N / 4) * kMqRows, batch, g, part, partB, s));
-      MP_TRY(mp::colsum_parts(part, batch, N, gD, &t.q, acc, s));
-      if (gB) MP_TRY(mp::colsum_parts(partB, batch, N, gB, &t.q, acc, s));
-      rc = mp_ifft_unpack(Zg, gh1, batch, N, false, g, t, s);
-      if (rc != ACDC_OK) return rc;
-      float* gnext = k == 0 ? grad_x : gbuf;
-      if (perm_on) {
-        // Zh and Zg are free again: the permutation's scratch
-        const int32_t* pk = perm + (long long)k * N;
-        mp::PermTabs tk;
-        MP_TRY(mp_perm_tabs(perm, N, K, k, pt, &tk, s));
-        MP_TRY(mp::dA_permute(gh1, u, ak, relu && k > 0, imgA, gnext, reinterpret_cast<float*>(Zh), pk, tk, batch,
-                              N, s));
-      } else {
-        MP_TRY(mp::dA(gh1, u, ak, relu && k > 0, imgA, gnext, batch, N, s));
-      }
-      MP_TRY(mp::colsum(imgA, batch, N, part, gA, nullptr, acc, s));
+    float* gA = grad_A + (long long)k * m.W;
+    float* gD = grad_D + (long long)k * m.W;
+    const float* u = k > 0 || m.perm_on ? mp_slot(stash, k, K, batch, m.W, m.perm_on) : x;
+    const float* ak = A + (long long)k * m.W;
+    {
+      mp::Cols c;
+      c.src = u;
+      c.Z = Zh;
+      c.a = ak;
+      MP_TRY(m.cols(Src::rows, Sink::dif, c));
+    }
+    MP_TRY(mp::dif2(Zh, 2 * batch, g, m.t.tw2, s));
+    if (m.bias) {
+      MP_TRY(mp::colsum(reinterpret_cast<const float*>(Zg), batch, m.W, partB, zsum, s));
+      MP_TRY(mp::seg_dct(reinterpret_cast<const float2*>(zsum), m.mq(k), g, m.t.q, grad_bias + k * m.W, acc, m.t.seg,
+                         s));
+    }
+    if (m.cplx) MP_TRY(mp::cseg_bwd(Zh, Zg, m.coef + (long long)k * N, batch, g, part, m.t.seg, s));
+    else MP_TRY(mp::seg_bwd(Zh, Zg, m.mq(k), batch, g, part, m.t.seg, s));
+    MP_TRY(mp::colsum_parts(part, pseg, m.W, gD, order, g, &m.t.q, acc, s));
+    MP_TRY(mp::dit2(Zg, batch, g, m.t.tw2, s));
+    mp::Cols c;
+    c.Z = Zg;
+    c.u = u;
+    c.a = ak;
+    c.part = part;
+    c.relu = m.relu && k > 0 ? 1 : 0;
+    mp::PermTabs tk;
+    if (m.perm_on) {
+      MP_TRY(pm.layer(k, &tk, s));
+      c.dst = tmp;
+      c.pt = &tk;
+      MP_TRY(m.cols(Src::dit, Sink::ret, c));
+    } else if (k == 0) {
+      c.dst = grad_x;
+      MP_TRY(m.cols(Src::dit, Sink::rows, c));
     } else {
-      // no rows: zero (or unchanged, accumulating) parameter gradients
-      MP_TRY(mp::colsum(nullptr, 0, N, part, gD, &t.q, acc, s));
-      if (gB) MP_TRY(mp::colsum(nullptr, 0, N, part, gB, &t.q, acc, s));
-      MP_TRY(mp::colsum(nullptr, 0, N, part, gA, nullptr, acc, s));
+      MP_TRY(m.cols(Src::dit, Sink::dif, c));
+    }
+    MP_TRY(mp::colsum_parts(part, pcol, m.W, gA, Order::natural, g, nullptr, acc, s));
+    if (m.perm_on) {
+      mp::Cols d;
+      d.src = tmp;
+      d.dst = grad_x;
+      d.Z = Zg;
+      d.pt = &tk;
+      MP_TRY(m.cols(Src::scatter, k == 0 ? Sink::rows : Sink::dif, d));
     }
   }
   return ACDC_OK;

@@ -1,7 +1,9 @@
 // Kernels of the multi-pass ACDC layers (declarations and the pass structure
-// in acdc_multipass.hpp).  Elementwise passes use grid-stride loops over
-// 64-bit indices; the segment FFTs reuse the complex row machinery.
+// in acdc_multipass.hpp).
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
+#include <vector>
 
 #include "acdc_devctx.hpp"
 #include "acdc_multipass.hpp"
@@ -13,11 +15,9 @@ namespace {
 constexpr int kThreads = 256;
 
 // Workgroups go to the 8 XCDs (each with its own L2) in turn: workgroup w
-// runs on XCD w mod 8.  Grids are a multiple of 8 workgroups, and gindex()
-// hands XCD x the x-th contiguous eighth of the grid, so the workgroups
-// that gather from one row share that XCD's L2.
+// runs on XCD w mod 8.  Elementwise grids are a multiple of 8 workgroups, and
+// gindex() hands XCD x the x-th contiguous eighth of the grid.
 constexpr int kXcds = 8;
-constexpr int kPermThreads = 512;
 
 dim3 grid_for(long long n) {
   long long blocks = (n + kThreads - 1) / kThreads;
@@ -44,320 +44,64 @@ __device__ __forceinline__ float4 scale4(float4 h, float4 a) {
 }
 __device__ __forceinline__ float4 relu4(float4 h) { return make_float4(relu1(h.x), relu1(h.y), relu1(h.z), relu1(h.w)); }
 
-// Chunk q (q < M/2) of row b: Z[q] and Z[M-1-q], scaled by a, stashed.
-__global__ __launch_bounds__(kThreads) void k_pack(const float* __restrict__ src, const float* __restrict__ a,
-                                                   float* __restrict__ stash, float2* __restrict__ Z, long long B,
-                                                   long long N) {
-  const long long M = N / 2, H = M / 2, total = B * H;
-  for (long long i = gindex(); i < total; i += gstride()) {
-    const long long b = i / H, q = i % H;
-    float4 h = reinterpret_cast<const float4*>(src + b * N)[q];
-    if (stash) reinterpret_cast<float4*>(stash + b * N)[q] = h;
-    if (a) h = scale4(h, reinterpret_cast<const float4*>(a)[q]);
-    Z[b * M + q] = chunk_even(h);
-    Z[b * M + M - 1 - q] = chunk_odd(h);
-  }
-}
-
-// Radix-R decimation in frequency on segments of length S (the row itself
-// for the first pass): butterfly n of segment s reads x[n + j Q], Q = S/R,
-// and writes y_r[n] = W_M^(n r M/S) sum_j x[n + j Q] W_R^(j r) to r Q + n.
-template <int R>
-__global__ __launch_bounds__(kThreads) void k_dif(float2* __restrict__ Z, long long B, long long M, long long S,
-                                                  const float2* __restrict__ twM) {
-  const long long Q = S / R, per_row = M / R, total = B * per_row, tws = M / S;
-  for (long long i = gindex(); i < total; i += gstride()) {
-    const long long b = i / per_row, q = i % per_row;
-    const long long base = b * M + (q / Q) * S, n = q % Q;
-    float2 x[R];
-#pragma unroll
-    for (int j = 0; j < R; ++j) x[j] = Z[base + n + j * Q];
-    Dft<R, false>::run(x);
-#pragma unroll
-    for (int r = 1; r < R; ++r) x[r] = cmul(x[r], twM[n * r * tws]);
-#pragma unroll
-    for (int r = 0; r < R; ++r) Z[base + r * Q + n] = x[r];
-  }
-}
-
-// The unnormalised inverse of k_dif: x'[n + j Q] = sum_r W_R^(-j r) W_M^(-n r M/S) y'_r[n].
-template <int R>
-__global__ __launch_bounds__(kThreads) void k_dit(float2* __restrict__ Z, long long B, long long M, long long S,
-                                                  const float2* __restrict__ twM) {
-  const long long Q = S / R, per_row = M / R, total = B * per_row, tws = M / S;
-  for (long long i = gindex(); i < total; i += gstride()) {
-    const long long b = i / per_row, q = i % per_row;
-    const long long base = b * M + (q / Q) * S, n = q % Q;
-    float2 y[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) y[r] = Z[base + r * Q + n];
-#pragma unroll
-    for (int r = 1; r < R; ++r) y[r] = cmulc(y[r], twM[n * r * tws]);
-    Dft<R, true>::run(y);
-#pragma unroll
-    for (int j = 0; j < R; ++j) Z[base + n + j * Q] = y[j];
-  }
-}
-
-// The first DIF pass (on whole rows, S = M) with the packing folded in.
-// Butterfly n takes m = n + j Q (Q = M/R); for j < R/2 that is the even
-// part of chunk n + j Q, for j >= R/2 the odd part of chunk
-// nb + (R-1-j) Q, nb = Q-1-n.  So butterflies n and nb read the same R
-// chunks, and one thread runs both (n < Q/2): every access contiguous.
-template <int R>
-__global__ __launch_bounds__(kThreads) void k_pack_dif(const float* __restrict__ src, const float* __restrict__ a,
-                                                       float* __restrict__ stash, float2* __restrict__ Z, long long B,
-                                                       long long M, const float2* __restrict__ twM) {
-  const long long N = 2 * M, Q = M / R, H = Q / 2, total = B * H;
-  for (long long i = gindex(); i < total; i += gstride()) {
-    const long long b = i / H, n = i % H, nb = Q - 1 - n;
-    const float4* row4 = reinterpret_cast<const float4*>(src + b * N);
-    float4* st4 = stash ? reinterpret_cast<float4*>(stash + b * N) : nullptr;
-    const float4* a4 = reinterpret_cast<const float4*>(a);
-    float2 x[R], xb[R];
-#pragma unroll
-    for (int j = 0; j < R / 2; ++j) {
-      const long long q = n + j * Q, qb = nb + j * Q;
-      float4 h = row4[q], hb = row4[qb];
-      if (st4) {
-        st4[q] = h;
-        st4[qb] = hb;
-      }
-      if (a4) {
-        h = scale4(h, a4[q]);
-        hb = scale4(hb, a4[qb]);
-      }
-      x[j] = chunk_even(h);
-      xb[R - 1 - j] = chunk_odd(h);
-      xb[j] = chunk_even(hb);
-      x[R - 1 - j] = chunk_odd(hb);
-    }
-    Dft<R, false>::run(x);
-    Dft<R, false>::run(xb);
-#pragma unroll
-    for (int r = 1; r < R; ++r) {
-      x[r] = cmul(x[r], twM[n * r]);
-      xb[r] = cmul(xb[r], twM[nb * r]);
-    }
-    float2* zrow = Z + b * M;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      zrow[r * Q + n] = x[r];
-      zrow[r * Q + nb] = xb[r];
-    }
-  }
-}
-
-// The last DIT pass (S = M) with the unpacking (and ReLU) folded in: the
-// mirror image of k_pack_dif, butterflies n and Q-1-n writing R chunks.
-template <int R>
-__global__ __launch_bounds__(kThreads) void k_dit_unpack(const float2* __restrict__ Z, float* __restrict__ dst,
-                                                         long long B, long long M, const float2* __restrict__ twM,
-                                                         int relu) {
-  const long long N = 2 * M, Q = M / R, H = Q / 2, total = B * H;
-  for (long long i = gindex(); i < total; i += gstride()) {
-    const long long b = i / H, n = i % H, nb = Q - 1 - n;
-    const float2* zrow = Z + b * M;
-    float2 y[R], yb[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      y[r] = zrow[r * Q + n];
-      yb[r] = zrow[r * Q + nb];
-    }
-#pragma unroll
-    for (int r = 1; r < R; ++r) {
-      y[r] = cmulc(y[r], twM[n * r]);
-      yb[r] = cmulc(yb[r], twM[nb * r]);
-    }
-    Dft<R, true>::run(y);
-    Dft<R, true>::run(yb);
-    float4* out4 = reinterpret_cast<float4*>(dst + b * N);
-#pragma unroll
-    for (int j = 0; j < R / 2; ++j) {
-      float4 h = chunk_of(y[j], yb[R - 1 - j]), hb = chunk_of(yb[j], y[R - 1 - j]);
-      if (relu) {
-        h = relu4(h);
-        hb = relu4(hb);
-      }
-      out4[n + j * Q] = h;
-      out4[nb + j * Q] = hb;
-    }
-  }
-}
-
-// Segment FFTs of L = CP::N points, in place, Launch<CP>::FWD_ROWS segments
-// per workgroup.  Forward: natural-order input (spatial layout) to
-// natural-order output (frequency layout); the inverse runs the mirror.
-template <class CP, bool INV>
-__global__ __launch_bounds__(Launch<CP>::FWD_THREADS) void k_seg(float2* __restrict__ Z, long long nseg,
-                                                                 const char* __restrict__ tab) {
-  using L = Launch<CP>;
-  using O = CplxOps<CP>;
-  constexpr int T = CP::T, P = CP::P;
-  __shared__ float lds[L::FWD_ROWS * L::FWD_SLAB];
-  const int tid = threadIdx.x;
-  const unsigned t = unsigned(tid) % T;
-  int r = tid / T;
-  if constexpr (T >= 64) r = __builtin_amdgcn_readfirstlane(r);
-  const long long seg0 = (long long)blockIdx.x * L::FWD_ROWS;
-  const bool valid = seg0 + r < nseg;
-  const unsigned roff = valid ? unsigned(r) * unsigned(CP::N) : 0u;
-  const GView g = GView::of(Z + seg0 * CP::N);
-  float2* slab = reinterpret_cast<float2*>(lds + r * L::FWD_SLAB);
-  DevCtx<T> ctx;
-  float2 v[P];
-  O::template ld_row<INV>(g, roff, v, t);
-  O::template fft<INV>(ctx, v, t, slab, GView::of(tab));
-  if (valid) O::template st_row<!INV>(g, roff, v, t);
-}
-
-// Per-layer quartet coefficients [K][NQ][kMqRows] (entry-major).
-__global__ __launch_bounds__(kThreads) void k_mq(const float* __restrict__ D, const float* __restrict__ Bias,
-                                                 float4* __restrict__ Mq, int K, long long NQ, QuartetTabs q,
-                                                 long long N) {
-  const long long total = (long long)K * NQ;
-  for (long long i = gindex(); i < total; i += gstride()) {
-    const long long k = i / NQ;
-    const int e = int(i % NQ);
-    float4 row[kMqRows];
-    quartet_coeffs(D + k * N, Bias ? Bias + k * N : nullptr, q, e, row);
-#pragma unroll
-    for (int r = 0; r < kMqRows; ++r) Mq[i * kMqRows + r] = row[r];
-  }
-}
-
-// Positions of quartet entry e's pair: (Z[e], Z[M-e]), or (Z[0], Z[M/2]) for e = 0.
-__device__ __forceinline__ void pair_pos(const Geo& g, long long e, long long& pa, long long& pb) {
-  pa = pos(g, e);
-  pb = pos(g, e == 0 ? g.M / 2 : g.M - e);
-}
-
-// Forward middle, kColRows rows per thread and quartet entry (the
-// coefficients loaded once for them).
-__global__ __launch_bounds__(kThreads) void k_mid_fwd(float2* __restrict__ Z, const float4* __restrict__ Mq,
-                                                      long long B, Geo g, int bias) {
-  const long long NQ = g.M / 2, P = (B + kColRows - 1) / kColRows, total = P * NQ;
-  for (long long i = gindex(); i < total; i += gstride()) {
-    const long long p = i / NQ, e = i % NQ;
-    long long pa, pb;
-    pair_pos(g, e, pa, pb);
-    const float4 c0 = Mq[e * kMqRows], c1 = Mq[e * kMqRows + 1];
-    const float4 c3 = bias ? Mq[e * kMqRows + 3] : make_float4(0.f, 0.f, 0.f, 0.f);
-    const long long b0 = p * kColRows, b1 = b0 + kColRows < B ? b0 + kColRows : B;
-    for (long long b = b0; b < b1; ++b) {
-      float2* row = Z + b * g.M;
-      float2 zk = row[pa], zm = row[pb];
-      quartet_back(quartet_split(zk, zm, make_float2(c1.z, c1.w)), c0, c1, zk, zm);
-      if (bias) {
-        zk = make_float2(zk.x + c3.x, zk.y + c3.y);
-        zm = make_float2(zm.x + c3.z, zm.y + c3.w);
-      }
-      row[pa] = zk;
-      row[pb] = zm;
-    }
-  }
-}
-
-// Backward middle over a block of kColRows rows (in row order) per thread
-// and quartet entry e: the images H*G (dL/dd) and, with a bias, G (dL/db),
-// summed over the block's rows into partD/partB[p][4e + j] (quartet order);
-// g's spectrum is replaced by the DCT-III pre-twiddle of G*d.  The
-// coefficients are loaded once per block.
-__global__ __launch_bounds__(kThreads) void k_mid_bwd(const float2* __restrict__ Zh, float2* __restrict__ Zg,
-                                                      const float4* __restrict__ Mq, long long B, Geo g,
-                                                      float* __restrict__ partD, float* __restrict__ partB) {
-  const long long NQ = g.M / 2, P = (B + kColRows - 1) / kColRows, total = P * NQ, W = 2 * g.M;
-  for (long long i = gindex(); i < total; i += gstride()) {
-    const long long p = i / NQ, e = i % NQ;
-    long long pa, pb;
-    pair_pos(g, e, pa, pb);
-    const float4 c0 = Mq[e * kMqRows], c1 = Mq[e * kMqRows + 1], c2 = Mq[e * kMqRows + 2];
-    const float2 w = make_float2(c1.z, c1.w), qa = make_float2(c2.x, c2.y), qbr = make_float2(c2.z, c2.w);
-    float4 sD = make_float4(0.f, 0.f, 0.f, 0.f), sB = sD;
-    const long long b0 = p * kColRows, b1 = b0 + kColRows < B ? b0 + kColRows : B;
-    for (long long b = b0; b < b1; ++b) {
-      const float2* hrow = Zh + b * g.M;
-      float2* grow = Zg + b * g.M;
-      float2 gk = grow[pa], gm = grow[pb];
-      float H[4], G[4];
-      quartet_post(quartet_split(hrow[pa], hrow[pb], w), qa, qbr, H);
-      const Split sg = quartet_split(gk, gm, w);
-      quartet_post(sg, qa, qbr, G);
-      sD = make_float4(sD.x + H[0] * G[0], sD.y + H[1] * G[1], sD.z + H[2] * G[2], sD.w + H[3] * G[3]);
-      sB = make_float4(sB.x + G[0], sB.y - G[1], sB.z + G[2], sB.w + G[3]);
-      quartet_back(sg, c0, c1, gk, gm);
-      grow[pa] = gk;
-      grow[pb] = gm;
-    }
-    reinterpret_cast<float4*>(partD + p * W)[e] = sD;
-    if (partB) reinterpret_cast<float4*>(partB + p * W)[e] = sB;
-  }
-}
-
-__global__ __launch_bounds__(kThreads) void k_unpack(const float2* __restrict__ Z, float* __restrict__ dst,
-                                                     long long B, long long N, int relu) {
-  const long long M = N / 2, H = M / 2, total = B * H;
-  for (long long i = gindex(); i < total; i += gstride()) {
-    const long long b = i / H, q = i % H;
-    float4 h = chunk_of(Z[b * M + q], Z[b * M + M - 1 - q]);
-    if (relu) h = relu4(h);
-    reinterpret_cast<float4*>(dst + b * N)[q] = h;
-  }
-}
-
-// dL/da image u * gh1 (gh1 masked where the previous layer's ReLU was off:
-// u = 0 there), and dL/du = gh1 * a (no permutation).
-__global__ __launch_bounds__(kThreads) void k_dA(const float* __restrict__ gh1, const float* __restrict__ u,
-                                                 const float* __restrict__ a, int mask, float* __restrict__ imgA,
-                                                 float* __restrict__ gnext, long long B, long long N) {
-  const long long total = B * N;
-  for (long long i = gindex(); i < total; i += gstride()) {
-    const long long n = i % N;
-    const float uu = u[i];
-    float gh = gh1[i];
-    if (mask && !(uu > 0.f)) gh = 0.f;
-    imgA[i] = uu * gh;
-    gnext[i] = gh * a[n];
-  }
-}
-
 // ------------------------------------------------------------ permutations
-// out[b][n] = in[b][src[n]] in chunks of C = min(N, kPermChunk) floats held
-// in LDS (see acdc_multipass.hpp).  Pass A: workgroup (b, c) loads source
-// chunk c and writes the C values it sources to tmp[b][cC + i], ordered by
-// destination chunk, then destination.  Pass B: workgroup (b, d) reads the
-// nC runs of tmp bound for chunk d into LDS (run-contiguous loads), then
-// writes chunk d in order.  The backward runs the adjoint: the same tables
-// with each pass's reads and writes exchanged.  Table entries are masked
-// into range, so a malformed perm yields wrong values, never a stray access.
 
-// Pass A table build, step 1: per block of kThreads destinations (all in
-// one chunk d, as C is a multiple of kThreads), the count of each source
-// chunk: cntS[blk][c].
-__global__ __launch_bounds__(kThreads) void k_pt_count(const int* __restrict__ src, long long N, int C, int nC,
+// Set and local position of row element i, and the element at local
+// position l of set d.
+__device__ __forceinline__ void part_of(const PermGeo& p, long long i, int& d, int& l) {
+  const long long Q = 1LL << p.lQ;
+  if (p.ew == 1) {
+    const long long q = i >> 2, j = q >> p.lQ, n = q & (Q - 1);
+    const int side = n >= Q / 2 ? 1 : 0;
+    const long long col = side ? Q - 1 - n : n;
+    d = int(col >> p.lw);
+    l = int(((((2 * j + side) << p.lw) + (col & ((1 << p.lw) - 1))) << 2) + (i & 3));
+  } else {
+    const long long j = i >> p.lQ, n = i & (Q - 1);
+    d = int(n >> p.lw);
+    l = int((j << p.lw) + (n & ((1 << p.lw) - 1)));
+  }
+}
+__device__ __forceinline__ long long elem_of(const PermGeo& p, int d, int l) {
+  const long long Q = 1LL << p.lQ;
+  if (p.ew == 1) {
+    const int l4 = l >> 2, js = l4 >> p.lw;
+    const long long col = ((long long)d << p.lw) + (l4 & ((1 << p.lw) - 1));
+    const long long n = (js & 1) ? Q - 1 - col : col;
+    return ((((long long)(js >> 1) << p.lQ) + n) << 2) + (l & 3);
+  }
+  return ((long long)(l >> p.lw) << p.lQ) + ((long long)d << p.lw) + (l & ((1 << p.lw) - 1));
+}
+
+// Table build, a counting sort of the destinations by source set.  Step 1:
+// per block of kThreads destinations (all of one set d), the count of each
+// source set: cntS[blk][c].  Every step handles layer blockIdx.y (step 3: x).
+__global__ __launch_bounds__(kThreads) void k_pt_count(const int* __restrict__ src, long long N, PermGeo pg,
                                                        int* __restrict__ cntS, long long stride) {
   __shared__ int h[kPermMaxChunks];
-  src += blockIdx.y * N;  // layer blockIdx.y
+  src += blockIdx.y * N;
   cntS += blockIdx.y * stride;
-  for (int c = threadIdx.x; c < nC; c += kThreads) h[c] = 0;
+  for (int c = threadIdx.x; c < pg.nC; c += kThreads) h[c] = 0;
   __syncthreads();
-  const long long n = (long long)blockIdx.x * kThreads + threadIdx.x;
-  atomicAdd(&h[int((src[n] & (N - 1)) / C)], 1);
+  const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
+  int c, ls;
+  part_of(pg, src[elem_of(pg, int(idx >> pg.lC), int(idx & ((1 << pg.lC) - 1)))] & (N - 1), c, ls);
+  atomicAdd(&h[c], 1);
   __syncthreads();
-  for (int c = threadIdx.x; c < nC; c += kThreads) cntS[(long long)blockIdx.x * nC + c] = h[c];
+  for (int k = threadIdx.x; k < pg.nC; k += kThreads) cntS[(long long)blockIdx.x * pg.nC + k] = h[k];
 }
 
-// Step 2, one thread per (d, c): the running count over chunk d's blocks
+// Step 2, one thread per (d, c): the running count over set d's blocks
 // (bpre[blk][c], exclusive) and the total cnt[d][c].
-__global__ __launch_bounds__(kThreads) void k_pt_blocks(const int* __restrict__ cntS, int C, int nC,
+__global__ __launch_bounds__(kThreads) void k_pt_blocks(const int* __restrict__ cntS, PermGeo pg,
                                                         int* __restrict__ bpre, int* __restrict__ cnt,
                                                         long long stride) {
-  const int i = blockIdx.x * kThreads + threadIdx.x;
+  const int i = blockIdx.x * kThreads + threadIdx.x, nC = pg.nC;
   if (i >= nC * nC) return;
   cntS += blockIdx.y * stride;
   bpre += blockIdx.y * stride;
   cnt += blockIdx.y * stride;
-  const int d = i / nC, c = i % nC, per = C / kThreads;
+  const int d = i / nC, c = i % nC, per = (1 << pg.lC) / kThreads;
   int run = 0;
   for (int j = 0; j < per; ++j) {
     const long long blk = (long long)d * per + j;
@@ -367,22 +111,17 @@ __global__ __launch_bounds__(kThreads) void k_pt_blocks(const int* __restrict__ 
   cnt[i] = run;
 }
 
-// Step 3, one workgroup: off[d][c] = c C + sum over d' < d of cnt[d'][c]
-// (the tmp position of run (c, d)) and lst[d][c] = sum over c' < c of
-// cnt[d][c'] (its LDS position in pass B).
-__global__ __launch_bounds__(kThreads) void k_pt_offsets(const int* __restrict__ cnt, int C, int nC,
-                                                         int* __restrict__ off, int* __restrict__ lst,
-                                                         long long stride) {
-  cnt += blockIdx.x * stride;  // one workgroup per layer
-  off += blockIdx.x * stride;
+// Step 3, one workgroup: start[d][c], where the entries bound for d begin in
+// set c's list; lst[d][c], where those sourced from c begin in d's values of
+// tmp; and delta[c][d] = d C + lst - start.
+__global__ __launch_bounds__(kThreads) void k_pt_offsets(const int* __restrict__ cnt, PermGeo pg,
+                                                         int* __restrict__ start, int* __restrict__ lst,
+                                                         int* __restrict__ delta, long long stride) {
+  const int nC = pg.nC;
+  cnt += blockIdx.x * stride;
+  start += blockIdx.x * stride;
   lst += blockIdx.x * stride;
-  for (int c = threadIdx.x; c < nC; c += kThreads) {
-    long long run = (long long)c * C;
-    for (int d = 0; d < nC; ++d) {
-      off[d * nC + c] = int(run);
-      run += cnt[d * nC + c];
-    }
-  }
+  delta += blockIdx.x * stride;
   for (int d = threadIdx.x; d < nC; d += kThreads) {
     int run = 0;
     for (int c = 0; c < nC; ++c) {
@@ -390,329 +129,603 @@ __global__ __launch_bounds__(kThreads) void k_pt_offsets(const int* __restrict__
       run += cnt[d * nC + c];
     }
   }
+  __syncthreads();
+  for (int c = threadIdx.x; c < nC; c += kThreads) {
+    int run = 0;
+    for (int d = 0; d < nC; ++d) {
+      start[d * nC + c] = run;
+      delta[c * nC + d] = (d << pg.lC) + lst[d * nC + c] - run;
+      run += cnt[d * nC + c];
+    }
+  }
 }
 
-// Step 4: every destination n takes a place in its run (the order inside a
+// Step 4: every destination takes a place in its run (the order inside a
 // block's share of a run is whatever the LDS counter hands out; the tables
-// stay consistent, and the permuted values do not depend on it):
-// srcA[tpos] = src[n] - c C, gposB[d C + slot] = tpos, locB[n] = slot.
-__global__ __launch_bounds__(kThreads) void k_pt_place(const int* __restrict__ src, long long N, int C, int nC,
-                                                       const int* __restrict__ bpre, const int* __restrict__ off,
-                                                       const int* __restrict__ lst, int* __restrict__ srcA,
-                                                       int* __restrict__ gposB, int* __restrict__ locB,
-                                                       long long stride) {
+// stay consistent, and the permuted values do not depend on it).
+__global__ __launch_bounds__(kThreads) void k_pt_place(const int* __restrict__ src, long long N, PermGeo pg,
+                                                       const int* __restrict__ bpre, const int* __restrict__ start,
+                                                       const int* __restrict__ lst, unsigned* __restrict__ item,
+                                                       unsigned short* __restrict__ loc, long long stride) {
   __shared__ int h[kPermMaxChunks];
-  const long long ls = blockIdx.y * stride;
+  const long long ls0 = blockIdx.y * stride;
+  const int nC = pg.nC, mask = (1 << pg.lC) - 1;
   src += blockIdx.y * N;
-  bpre += ls;
-  off += ls;
-  lst += ls;
-  srcA += ls;
-  gposB += ls;
-  locB += ls;
+  bpre += ls0;
+  start += ls0;
+  lst += ls0;
+  item += ls0;
+  loc += 2 * ls0;
   for (int c = threadIdx.x; c < nC; c += kThreads) h[c] = 0;
   __syncthreads();
-  const long long n = (long long)blockIdx.x * kThreads + threadIdx.x;
-  const int sv = int(src[n] & (N - 1)), c = sv / C, d = int(n / C);
+  const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
+  const int d = int(idx >> pg.lC);
+  int c, ls;
+  part_of(pg, src[elem_of(pg, d, int(idx & mask))] & (N - 1), c, ls);
   const int p = bpre[(long long)blockIdx.x * nC + c] + atomicAdd(&h[c], 1);
-  const long long tpos = ((long long)off[d * nC + c] + p) & (N - 1);
-  const int slot = (lst[d * nC + c] + p) & (C - 1);
-  srcA[tpos] = sv & (C - 1);
-  gposB[(long long)d * C + slot] = int(tpos);
-  locB[n] = slot;
+  loc[idx] = (unsigned short)((lst[d * nC + c] + p) & mask);
+  item[((long long)c << pg.lC) + ((start[d * nC + c] + p) & mask)] = (unsigned(ls) << 8) | unsigned(d);
 }
 
-// The pass kernels keep kPermBatch loads in flight per thread: with two
-// 64 KB workgroups per CU, one load at a time would leave them bound by
-// memory latency.  Element i of a chunk goes to thread i mod kPermThreads.
-constexpr int kPermBatch = 8;
-constexpr int kPermStep = kPermBatch * kPermThreads;
-// With more than one chunk, C = kPermChunk and the loops of pass B and of
-// the adjoint passes run whole steps; k_pt_a and k_pt_bt also serve a
-// single chunk (C = N, any power of two from 256) and take plain loops when
-// C is not a whole number of steps.
-static_assert(kPermChunk % kPermStep == 0, "whole steps per chunk");
+// ----------------------------------------------------------------- columns
 
-// Chunk copy HBM -> LDS (float4, contiguous).
-__device__ __forceinline__ void chunk_to_lds(float4* __restrict__ lds4, const float4* __restrict__ g4, int C) {
-  if ((C / 4) % kPermStep == 0) {
-    for (int i0 = threadIdx.x; i0 < C / 4; i0 += kPermStep) {
-      float4 v[kPermBatch];
+struct ColArgs {
+  const float* src;
+  float* dst;
+  float2* Z;
+  const float* a;
+  float* stash;
+  const float* u;
+  float* part;
+  const float2* tw;  // [R1-1][Q]: W_M^(n r) at [r-1][n]
+  const unsigned* item;
+  const unsigned short* loc;
+  const int* delta;
+  long long B, M;
+  int rb, relu;
+  PermGeo pg;
+};
+
+// Loads in flight per thread where a thread follows a table: each waits for
+// its table entry, so one at a time would be bound by memory latency.
+constexpr int kBatch = 8;
+
+// f(i) for the entries i of one set's list that this thread takes: first
+// get(i) for a batch, then put(i, value) for it.
+template <int THREADS, class T, class Get, class Put>
+__device__ __forceinline__ void for_entries(int C, Get&& get, Put&& put) {
+  if (C % (THREADS * kBatch) == 0) {
+    for (int i0 = threadIdx.x; i0 < C; i0 += THREADS * kBatch) {
+      T v[kBatch];
 #pragma unroll
-      for (int u = 0; u < kPermBatch; ++u) v[u] = g4[i0 + u * kPermThreads];
+      for (int q = 0; q < kBatch; ++q) v[q] = get(i0 + q * THREADS);
 #pragma unroll
-      for (int u = 0; u < kPermBatch; ++u) lds4[i0 + u * kPermThreads] = v[u];
+      for (int q = 0; q < kBatch; ++q) put(i0 + q * THREADS, v[q]);
     }
   } else {
-    for (int i = threadIdx.x; i < C / 4; i += kPermThreads) lds4[i] = g4[i];
+    for (int i = threadIdx.x; i < C; i += THREADS) put(i, get(i));
   }
 }
-// Chunk copy LDS -> HBM (float4, contiguous).
-__device__ __forceinline__ void chunk_from_lds(float4* __restrict__ g4, const float4* __restrict__ lds4, int C) {
-  for (int i = threadIdx.x; i < C / 4; i += kPermThreads) g4[i] = lds4[i];
-}
 
-// Forward pass A (or, with one chunk, the whole permutation with tab = perm):
-// out[b][cC + i] = in[b][cC + tab[cC + i]].  E is the element (float for
-// real rows, float2 for complex ones); N and C count elements.
+// Entry of a set's list with what it refers to.
 template <class E>
-__global__ __launch_bounds__(kPermThreads) void k_pt_a(const E* __restrict__ in, E* __restrict__ out,
-                                                       const int* __restrict__ tab, long long N, int C, int nC,
-                                                       long long work) {
-  constexpr int EW = int(sizeof(E) / sizeof(float));
-  __shared__ float4 lds4[kPermChunk / 4];
-  const E* lds = reinterpret_cast<const E*>(lds4);
-  for (long long w = blockIdx.x; w < work; w += gridDim.x) {
-    const long long b = w / nC, c = w % nC, base = b * N + c * C;
-    chunk_to_lds(lds4, reinterpret_cast<const float4*>(in + base), C * EW);
-    __syncthreads();
-    const int* t = tab + c * C;
-    if (C % kPermStep == 0) {
-      for (int i0 = threadIdx.x; i0 < C; i0 += kPermStep) {
-        int id[kPermBatch];
-#pragma unroll
-        for (int u = 0; u < kPermBatch; ++u) id[u] = t[i0 + u * kPermThreads] & (C - 1);
-#pragma unroll
-        for (int u = 0; u < kPermBatch; ++u) out[base + i0 + u * kPermThreads] = lds[id[u]];
-      }
-    } else {
-      for (int i = threadIdx.x; i < C; i += kPermThreads) out[base + i] = lds[t[i] & (C - 1)];
-    }
-    __syncthreads();
-  }
+struct Entry {
+  unsigned it;
+  E v;
+};
+
+// What a column launch does between its source and its sink, and whether it
+// needs the LDS chunk.
+template <Src SRC, Sink SINK>
+constexpr bool needs_lds() {
+  return SRC == Src::gather || SRC == Src::scatter || SINK == Sink::send || SINK == Sink::ret;
 }
 
-// Forward pass B: out[b][dC + j] = L[locB[dC + j]], L[j] = tmp[b][gposB[dC + j]].
-template <class E>
-__global__ __launch_bounds__(kPermThreads) void k_pt_b(const E* __restrict__ tmp, E* __restrict__ out,
-                                                       const int* __restrict__ gposB, const int* __restrict__ locB,
-                                                       long long N, int C, int nC, long long work) {
-  __shared__ float4 lds4[kPermChunk / 4];
-  E* lds = reinterpret_cast<E*>(lds4);
-  for (long long w = blockIdx.x; w < work; w += gridDim.x) {
-    const long long b = w / nC, d = w % nC, base = b * N + d * C;
-    const int* gp = gposB + d * C;
-    const int* lc = locB + d * C;
-    const E* trow = tmp + b * N;
-    for (int j0 = threadIdx.x; j0 < C; j0 += kPermStep) {
-      int id[kPermBatch];
-      E v[kPermBatch];
-#pragma unroll
-      for (int u = 0; u < kPermBatch; ++u) id[u] = gp[j0 + u * kPermThreads] & (N - 1);
-#pragma unroll
-      for (int u = 0; u < kPermBatch; ++u) v[u] = trow[id[u]];
-#pragma unroll
-      for (int u = 0; u < kPermBatch; ++u) lds[j0 + u * kPermThreads] = v[u];
-    }
-    __syncthreads();
-    for (int j0 = threadIdx.x; j0 < C; j0 += kPermStep) {
-      int id[kPermBatch];
-#pragma unroll
-      for (int u = 0; u < kPermBatch; ++u) id[u] = lc[j0 + u * kPermThreads] & (C - 1);
-#pragma unroll
-      for (int u = 0; u < kPermBatch; ++u) out[base + j0 + u * kPermThreads] = lds[id[u]];
-    }
-    __syncthreads();
-  }
-}
-
-// The plain adjoint of pass B (or, with one chunk, of the whole
-// permutation: loc = perm, no gpos): L[loc[dC + j]] = in[b][dC + j], then
-// out[b][gpos[dC + j]] = L[j] (out[b][dC + j] without gpos).
-template <class E>
-__global__ __launch_bounds__(kPermThreads) void k_pt_btp(const E* __restrict__ in, E* __restrict__ out,
-                                                         const int* __restrict__ gpos, const int* __restrict__ loc,
-                                                         long long N, int C, int nC, long long work) {
-  constexpr int EW = int(sizeof(E) / sizeof(float));
-  __shared__ float4 lds4[kPermChunk / 4];
-  E* lds = reinterpret_cast<E*>(lds4);
-  for (long long w = blockIdx.x; w < work; w += gridDim.x) {
-    const long long b = w / nC, d = w % nC, base = b * N + d * C;
-    const int* lc = loc + d * C;
-    if (C % kPermStep == 0) {
-      for (int j0 = threadIdx.x; j0 < C; j0 += kPermStep) {
-        int id[kPermBatch];
-        E v[kPermBatch];
-#pragma unroll
-        for (int u = 0; u < kPermBatch; ++u) {
-          id[u] = lc[j0 + u * kPermThreads] & (C - 1);
-          v[u] = in[base + j0 + u * kPermThreads];
-        }
-#pragma unroll
-        for (int u = 0; u < kPermBatch; ++u) lds[id[u]] = v[u];
-      }
-    } else {
-      for (int j = threadIdx.x; j < C; j += kPermThreads) lds[lc[j] & (C - 1)] = in[base + j];
-    }
-    __syncthreads();
-    if (gpos) {
-      const int* gp = gpos + d * C;
-      E* orow = out + b * N;
-      for (int j0 = threadIdx.x; j0 < C; j0 += kPermStep) {
-        int id[kPermBatch];
-#pragma unroll
-        for (int u = 0; u < kPermBatch; ++u) id[u] = gp[j0 + u * kPermThreads] & (N - 1);
-#pragma unroll
-        for (int u = 0; u < kPermBatch; ++u) orow[id[u]] = lds[j0 + u * kPermThreads];
-      }
-    } else {
-      chunk_from_lds(reinterpret_cast<float4*>(out + base), lds4, C * EW);
-    }
-    __syncthreads();
-  }
-}
-
-// Backward, first pass (the adjoint of pass B, or with one chunk of the
-// whole permutation, loc = perm and no gpos), with the dL/da step folded
-// in: for n in chunk d, gm = gh1 (0 where mask and u <= 0), imgA = u gm,
-// L[loc[n]] = gm a[n]; then out[b][gpos[dC + j]] = L[j] (out[b][dC + j]
-// without gpos).
-__global__ __launch_bounds__(kPermThreads) void k_pt_bt(const float* __restrict__ gh1, const float* __restrict__ u,
-                                                        const float* __restrict__ a, int mask,
-                                                        float* __restrict__ imgA, float* __restrict__ out,
-                                                        const int* __restrict__ gpos, const int* __restrict__ loc,
-                                                        long long N, int C, int nC, long long work) {
-  __shared__ float4 lds4[kPermChunk / 4];
-  float* lds = reinterpret_cast<float*>(lds4);
-  for (long long w = blockIdx.x; w < work; w += gridDim.x) {
-    const long long b = w / nC, d = w % nC, base = b * N + d * C;
-    const int* lc = loc + d * C;
-    const float* ad = a + d * C;
-    auto one = [&](int j, float uu, float gh, float av, int id) {
-      const float g = (mask && !(uu > 0.f)) ? 0.f : gh;
-      imgA[base + j] = uu * g;
-      lds[id & (C - 1)] = g * av;
-    };
-    if (C % kPermStep == 0) {
-      for (int j0 = threadIdx.x; j0 < C; j0 += kPermStep) {
-        float uu[kPermBatch], gh[kPermBatch], av[kPermBatch];
-        int id[kPermBatch];
-#pragma unroll
-        for (int q = 0; q < kPermBatch; ++q) {
-          const int j = j0 + q * kPermThreads;
-          uu[q] = u[base + j];
-          gh[q] = gh1[base + j];
-          av[q] = ad[j];
-          id[q] = lc[j];
-        }
-#pragma unroll
-        for (int q = 0; q < kPermBatch; ++q) one(j0 + q * kPermThreads, uu[q], gh[q], av[q], id[q]);
-      }
-    } else {
-      for (int j = threadIdx.x; j < C; j += kPermThreads) one(j, u[base + j], gh1[base + j], ad[j], lc[j]);
-    }
-    __syncthreads();
-    if (gpos) {
-      const int* gp = gpos + d * C;
-      float* orow = out + b * N;
-      for (int j0 = threadIdx.x; j0 < C; j0 += kPermStep) {
-        int id[kPermBatch];
-#pragma unroll
-        for (int q = 0; q < kPermBatch; ++q) id[q] = gp[j0 + q * kPermThreads] & (N - 1);
-#pragma unroll
-        for (int q = 0; q < kPermBatch; ++q) orow[id[q]] = lds[j0 + q * kPermThreads];
-      }
-    } else {
-      chunk_from_lds(reinterpret_cast<float4*>(out + base), lds4, C);
-    }
-    __syncthreads();
-  }
-}
-
-// Backward, second pass (the adjoint of pass A): L[srcA[cC + i]] =
-// tmp[b][cC + i], then out[b][cC + i] = L[i].
-template <class E>
-__global__ __launch_bounds__(kPermThreads) void k_pt_at(const E* __restrict__ tmp, E* __restrict__ out,
-                                                        const int* __restrict__ srcA, long long N, int C, int nC,
-                                                        long long work) {
-  constexpr int EW = int(sizeof(E) / sizeof(float));
-  __shared__ float4 lds4[kPermChunk / 4];
-  E* lds = reinterpret_cast<E*>(lds4);
-  for (long long w = blockIdx.x; w < work; w += gridDim.x) {
-    const long long b = w / nC, c = w % nC, base = b * N + c * C;
-    const int* t = srcA + c * C;
-    for (int i0 = threadIdx.x; i0 < C; i0 += kPermStep) {
-      int id[kPermBatch];
-      E v[kPermBatch];
-#pragma unroll
-      for (int q = 0; q < kPermBatch; ++q) {
-        id[q] = t[i0 + q * kPermThreads] & (C - 1);
-        v[q] = tmp[base + i0 + q * kPermThreads];
-      }
-#pragma unroll
-      for (int q = 0; q < kPermBatch; ++q) lds[id[q]] = v[q];
-    }
-    __syncthreads();
-    chunk_from_lds(reinterpret_cast<float4*>(out + base), lds4, C * EW);
-    __syncthreads();
-  }
-}
-
-// ------------------------------------------------------- complex (AFDF) rows
-// A complex row is its own M = N point FFT input: no packing.  The steps
-// follow the fused complex kernels' arithmetic (u * a, X * d / N, the
-// unnormalised inverse; backward images g * conj(h) and gh1 * conj(u)).
-
-// First DIF pass (S = M) on u * a, read from the layer input out of place
-// (a may be null; with stash the input is stashed too).
+// Real rows.  A thread holds CI column pairs, R float4 chunks each: ha[j]
+// is chunk n + jQ, hb[j] chunk (Q-1-n) + jQ.  512 threads at R <= 8 (four
+// waves per SIMD with two workgroups a CU); at R = 16 a pair is 64 values
+// and a set of 16384 floats has 256 pairs.
 template <int R>
-__global__ __launch_bounds__(kThreads) void k_cdif_in(const float2* __restrict__ src, const float2* __restrict__ a,
-                                                      float2* __restrict__ stash, float2* __restrict__ Z, long long B,
-                                                      long long M, const float2* __restrict__ twM) {
-  const long long Q = M / R, total = B * Q;
-  for (long long i = gindex(); i < total; i += gstride()) {
-    const long long b = i / Q, n = i % Q;
+constexpr int col_threads() {
+  return R <= 8 ? 512 : 256;
+}
+
+// DWELL: rb rows in turn (the backward's image sums)
+template <int R, Src SRC, Sink SINK, bool BWD>
+__global__ __launch_bounds__(col_threads<R>()) void k_cols(ColArgs A) {
+  constexpr int THREADS = col_threads<R>(), H = R / 2;
+  constexpr int CI = kPermChunk / 4 / (R * THREADS);
+  static_assert(CI >= 1 && CI * R * THREADS * 4 == kPermChunk, "a set's chunks over the threads");
+  __shared__ float4 lds4[needs_lds<SRC, SINK>() ? kPermChunk / 4 : 1];
+  __shared__ int dl[kPermMaxChunks];
+  float* lds = reinterpret_cast<float*>(lds4);
+  const PermGeo pg = A.pg;
+  const int C = 1 << pg.lC, w = 1 << pg.lw, mask = C - 1;
+  const long long M = A.M, N = 2 * M, Q = 1LL << pg.lQ;
+  const int c = int(blockIdx.x % unsigned(pg.nC));
+  const long long p = blockIdx.x / unsigned(pg.nC);
+  if constexpr (SRC == Src::scatter || SINK == Sink::send) {
+    for (int d = threadIdx.x; d < pg.nC; d += THREADS) dl[d] = A.delta[c * pg.nC + d];
+    __syncthreads();
+  }
+  const unsigned* item = A.item + ((long long)c << pg.lC);
+  const ushort4* loc4 = reinterpret_cast<const ushort4*>(A.loc + ((long long)c << pg.lC));
+  float4 ha[CI][H], hb[CI][H], sa[CI][H], sb[CI][H];
+  if constexpr (BWD) {
+#pragma unroll
+    for (int ci = 0; ci < CI; ++ci)
+#pragma unroll
+      for (int j = 0; j < H; ++j) sa[ci][j] = sb[ci][j] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  // f(ci, col, n, nb): this thread's column pairs
+  auto pairs = [&](auto&& f) {
+#pragma unroll
+    for (int ci = 0; ci < CI; ++ci) {
+      const int col = int(threadIdx.x) + ci * THREADS;
+      if (col < w) {
+        const long long n = ((long long)c << pg.lw) + col;
+        f(ci, col, n, Q - 1 - n);
+      }
+    }
+  };
+  const long long b0 = p * A.rb, b1 = b0 + A.rb < A.B ? b0 + A.rb : A.B;
+  for (long long b = b0; b < b1; ++b) {
+    if constexpr (SRC == Src::rows) {
+      const float4* row4 = reinterpret_cast<const float4*>(A.src + b * N);
+      pairs([&](int ci, int, long long n, long long nb) {
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+          ha[ci][j] = row4[n + j * Q];
+          hb[ci][j] = row4[nb + j * Q];
+        }
+      });
+    } else if constexpr (SRC == Src::gather) {
+      const float4* t4 = reinterpret_cast<const float4*>(A.src + b * N + ((long long)c << pg.lC));
+      for_entries<THREADS, float4>(
+          C / 4, [&](int i) { return t4[i]; }, [&](int i, float4 v) { lds4[i] = v; });
+      __syncthreads();
+      pairs([&](int ci, int col, long long, long long) {
+        auto at = [&](int l4) {
+          const ushort4 s = loc4[l4];
+          return make_float4(lds[s.x & mask], lds[s.y & mask], lds[s.z & mask], lds[s.w & mask]);
+        };
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+          ha[ci][j] = at(((2 * j) << pg.lw) + col);
+          hb[ci][j] = at(((2 * j + 1) << pg.lw) + col);
+        }
+      });
+      if (b + 1 < b1) __syncthreads();
+    } else if constexpr (SRC == Src::scatter) {
+      const float* trow = A.src + b * N;
+      for_entries<THREADS, Entry<float>>(
+          C,
+          [&](int i) {
+            const unsigned it = item[i];
+            return Entry<float>{it, trow[(i + dl[it & 255]) & (N - 1)]};
+          },
+          [&](int, const Entry<float>& e) { lds[(e.it >> 8) & mask] = e.v; });
+      __syncthreads();
+      pairs([&](int ci, int col, long long, long long) {
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+          ha[ci][j] = lds4[((2 * j) << pg.lw) + col];
+          hb[ci][j] = lds4[((2 * j + 1) << pg.lw) + col];
+        }
+      });
+      if (b + 1 < b1) __syncthreads();
+    } else {
+      const float2* zrow = A.Z + b * M;
+      pairs([&](int ci, int, long long n, long long nb) {
+        float2 y[R], yb[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          y[r] = zrow[(r << pg.lQ) + n];
+          yb[r] = zrow[(r << pg.lQ) + nb];
+        }
+#pragma unroll
+        for (int r = 1; r < R; ++r) {
+          y[r] = cmulc(y[r], A.tw[((r - 1) << pg.lQ) + n]);
+          yb[r] = cmulc(yb[r], A.tw[((r - 1) << pg.lQ) + nb]);
+        }
+        Dft<R, true>::run(y);
+        Dft<R, true>::run(yb);
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+          ha[ci][j] = chunk_of(y[j], yb[R - 1 - j]);
+          hb[ci][j] = chunk_of(yb[j], y[R - 1 - j]);
+        }
+      });
+      if constexpr (!BWD) {
+        if (A.relu) {
+          pairs([&](int ci, int, long long, long long) {
+#pragma unroll
+            for (int j = 0; j < H; ++j) {
+              ha[ci][j] = relu4(ha[ci][j]);
+              hb[ci][j] = relu4(hb[ci][j]);
+            }
+          });
+        }
+      }
+    }
+    if constexpr (BWD) {
+      const float4* u4 = reinterpret_cast<const float4*>(A.u + b * N);
+      const float4* a4 = reinterpret_cast<const float4*>(A.a);
+      // u = 0 exactly where the mask is off, so masking g first leaves u * g unchanged
+      auto one = [&](float4& g, float4& s, float4 u, float4 av) {
+        if (A.relu)
+          g = make_float4(u.x > 0.f ? g.x : 0.f, u.y > 0.f ? g.y : 0.f, u.z > 0.f ? g.z : 0.f, u.w > 0.f ? g.w : 0.f);
+        s = make_float4(s.x + u.x * g.x, s.y + u.y * g.y, s.z + u.z * g.z, s.w + u.w * g.w);
+        g = scale4(g, av);
+      };
+      pairs([&](int ci, int, long long n, long long nb) {
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+          one(ha[ci][j], sa[ci][j], u4[n + j * Q], a4[n + j * Q]);
+          one(hb[ci][j], sb[ci][j], u4[nb + j * Q], a4[nb + j * Q]);
+        }
+      });
+    }
+    if constexpr (SINK == Sink::dif && !BWD) {
+      if (A.stash != nullptr) {
+        float4* st4 = reinterpret_cast<float4*>(A.stash + b * N);
+        pairs([&](int ci, int, long long n, long long nb) {
+#pragma unroll
+          for (int j = 0; j < H; ++j) {
+            st4[n + j * Q] = ha[ci][j];
+            st4[nb + j * Q] = hb[ci][j];
+          }
+        });
+      }
+      if (A.a != nullptr) {
+        const float4* a4 = reinterpret_cast<const float4*>(A.a);
+        pairs([&](int ci, int, long long n, long long nb) {
+#pragma unroll
+          for (int j = 0; j < H; ++j) {
+            ha[ci][j] = scale4(ha[ci][j], a4[n + j * Q]);
+            hb[ci][j] = scale4(hb[ci][j], a4[nb + j * Q]);
+          }
+        });
+      }
+    }
+    if constexpr (SINK == Sink::rows) {
+      float4* out4 = reinterpret_cast<float4*>(A.dst + b * N);
+      pairs([&](int ci, int, long long n, long long nb) {
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+          out4[n + j * Q] = ha[ci][j];
+          out4[nb + j * Q] = hb[ci][j];
+        }
+      });
+    } else if constexpr (SINK == Sink::send) {
+      pairs([&](int ci, int col, long long, long long) {
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+          lds4[((2 * j) << pg.lw) + col] = ha[ci][j];
+          lds4[((2 * j + 1) << pg.lw) + col] = hb[ci][j];
+        }
+      });
+      __syncthreads();
+      float* trow = A.dst + b * N;
+      for_entries<THREADS, unsigned>(
+          C, [&](int i) { return item[i]; },
+          [&](int i, unsigned it) { trow[(i + dl[it & 255]) & (N - 1)] = lds[(it >> 8) & mask]; });
+      if (b + 1 < b1) __syncthreads();
+    } else if constexpr (SINK == Sink::ret) {
+      pairs([&](int ci, int col, long long, long long) {
+        auto put = [&](int l4, float4 h) {
+          const ushort4 s = loc4[l4];
+          lds[s.x & mask] = h.x;
+          lds[s.y & mask] = h.y;
+          lds[s.z & mask] = h.z;
+          lds[s.w & mask] = h.w;
+        };
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+          put(((2 * j) << pg.lw) + col, ha[ci][j]);
+          put(((2 * j + 1) << pg.lw) + col, hb[ci][j]);
+        }
+      });
+      __syncthreads();
+      float4* t4 = reinterpret_cast<float4*>(A.dst + b * N + ((long long)c << pg.lC));
+      for (int i = threadIdx.x; i < C / 4; i += THREADS) t4[i] = lds4[i];
+      if (b + 1 < b1) __syncthreads();
+    } else {
+      float2* zrow = A.Z + b * M;
+      pairs([&](int ci, int, long long n, long long nb) {
+        float2 x[R], xb[R];
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+          x[j] = chunk_even(ha[ci][j]);
+          xb[R - 1 - j] = chunk_odd(ha[ci][j]);
+          xb[j] = chunk_even(hb[ci][j]);
+          x[R - 1 - j] = chunk_odd(hb[ci][j]);
+        }
+        Dft<R, false>::run(x);
+        Dft<R, false>::run(xb);
+#pragma unroll
+        for (int r = 1; r < R; ++r) {
+          x[r] = cmul(x[r], A.tw[((r - 1) << pg.lQ) + n]);
+          xb[r] = cmul(xb[r], A.tw[((r - 1) << pg.lQ) + nb]);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          zrow[(r << pg.lQ) + n] = x[r];
+          zrow[(r << pg.lQ) + nb] = xb[r];
+        }
+      });
+    }
+  }
+  if constexpr (BWD) {
+    float4* out4 = reinterpret_cast<float4*>(A.part + p * N);
+    pairs([&](int ci, int, long long n, long long nb) {
+#pragma unroll
+      for (int j = 0; j < H; ++j) {
+        out4[n + j * Q] = sa[ci][j];
+        out4[nb + j * Q] = sb[ci][j];
+      }
+    });
+  }
+}
+
+// Complex rows: columns n, elements n + jQ.  Images gh1 * conj(u), and
+// dL/du = gh1 * conj(a).
+template <int R, Src SRC, Sink SINK, bool BWD>
+__global__ __launch_bounds__(512) void k_ccols(ColArgs A) {
+  constexpr int THREADS = 512, EC = kPermChunk / 2;  // elements of a whole set
+  constexpr int CI = EC / (R * THREADS);
+  static_assert(CI >= 1 && CI * R * THREADS == EC, "a set's elements over the threads");
+  __shared__ float4 lds4[needs_lds<SRC, SINK>() ? kPermChunk / 4 : 1];
+  __shared__ int dl[kPermMaxChunks];
+  float2* lds = reinterpret_cast<float2*>(lds4);
+  const PermGeo pg = A.pg;
+  const int C = 1 << pg.lC, w = 1 << pg.lw, mask = C - 1;
+  const long long M = A.M, Q = 1LL << pg.lQ;
+  const int c = int(blockIdx.x % unsigned(pg.nC));
+  const long long p = blockIdx.x / unsigned(pg.nC);
+  if constexpr (SRC == Src::scatter || SINK == Sink::send) {
+    for (int d = threadIdx.x; d < pg.nC; d += THREADS) dl[d] = A.delta[c * pg.nC + d];
+    __syncthreads();
+  }
+  const unsigned* item = A.item + ((long long)c << pg.lC);
+  const unsigned short* loc = A.loc + ((long long)c << pg.lC);
+  const float2* a2 = reinterpret_cast<const float2*>(A.a);
+  float2 h[CI][R], s[CI][R];
+  if constexpr (BWD) {
+#pragma unroll
+    for (int ci = 0; ci < CI; ++ci)
+#pragma unroll
+      for (int j = 0; j < R; ++j) s[ci][j] = make_float2(0.f, 0.f);
+  }
+  auto columns = [&](auto&& f) {
+#pragma unroll
+    for (int ci = 0; ci < CI; ++ci) {
+      const int col = int(threadIdx.x) + ci * THREADS;
+      if (col < w) f(ci, col, ((long long)c << pg.lw) + col);
+    }
+  };
+  const long long b0 = p * A.rb, b1 = b0 + A.rb < A.B ? b0 + A.rb : A.B;
+  for (long long b = b0; b < b1; ++b) {
+    if constexpr (SRC == Src::rows) {
+      const float2* row = reinterpret_cast<const float2*>(A.src) + b * M;
+      columns([&](int ci, int, long long n) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) h[ci][j] = row[n + j * Q];
+      });
+    } else if constexpr (SRC == Src::gather) {
+      const float4* t4 = reinterpret_cast<const float4*>(A.src + 2 * (b * M + ((long long)c << pg.lC)));
+      for_entries<THREADS, float4>(
+          C / 2, [&](int i) { return t4[i]; }, [&](int i, float4 v) { lds4[i] = v; });
+      __syncthreads();
+      columns([&](int ci, int col, long long) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) h[ci][j] = lds[loc[(j << pg.lw) + col] & mask];
+      });
+      if (b + 1 < b1) __syncthreads();
+    } else if constexpr (SRC == Src::scatter) {
+      const float2* trow = reinterpret_cast<const float2*>(A.src) + b * M;
+      for_entries<THREADS, Entry<float2>>(
+          C,
+          [&](int i) {
+            const unsigned it = item[i];
+            return Entry<float2>{it, trow[(i + dl[it & 255]) & (M - 1)]};
+          },
+          [&](int, const Entry<float2>& e) { lds[(e.it >> 8) & mask] = e.v; });
+      __syncthreads();
+      columns([&](int ci, int col, long long) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) h[ci][j] = lds[(j << pg.lw) + col];
+      });
+      if (b + 1 < b1) __syncthreads();
+    } else {
+      const float2* zrow = A.Z + b * M;
+      columns([&](int ci, int, long long n) {
+        float2 y[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) y[r] = zrow[(r << pg.lQ) + n];
+#pragma unroll
+        for (int r = 1; r < R; ++r) y[r] = cmulc(y[r], A.tw[((r - 1) << pg.lQ) + n]);
+        Dft<R, true>::run(y);
+#pragma unroll
+        for (int j = 0; j < R; ++j) h[ci][j] = y[j];
+      });
+    }
+    if constexpr (BWD) {
+      const float2* u2 = reinterpret_cast<const float2*>(A.u) + b * M;
+      columns([&](int ci, int, long long n) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+          const float2 img = cmulc(h[ci][j], u2[n + j * Q]);
+          s[ci][j] = make_float2(s[ci][j].x + img.x, s[ci][j].y + img.y);
+          h[ci][j] = cmulc(h[ci][j], a2[n + j * Q]);
+        }
+      });
+    }
+    if constexpr (SINK == Sink::dif && !BWD) {
+      if (A.stash != nullptr) {
+        float2* st = reinterpret_cast<float2*>(A.stash) + b * M;
+        columns([&](int ci, int, long long n) {
+#pragma unroll
+          for (int j = 0; j < R; ++j) st[n + j * Q] = h[ci][j];
+        });
+      }
+      if (A.a != nullptr) {
+        columns([&](int ci, int, long long n) {
+#pragma unroll
+          for (int j = 0; j < R; ++j) h[ci][j] = cmul(h[ci][j], a2[n + j * Q]);
+        });
+      }
+    }
+    if constexpr (SINK == Sink::rows) {
+      float2* out = reinterpret_cast<float2*>(A.dst) + b * M;
+      columns([&](int ci, int, long long n) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) out[n + j * Q] = h[ci][j];
+      });
+    } else if constexpr (SINK == Sink::send) {
+      columns([&](int ci, int col, long long) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) lds[(j << pg.lw) + col] = h[ci][j];
+      });
+      __syncthreads();
+      float2* trow = reinterpret_cast<float2*>(A.dst) + b * M;
+      for_entries<THREADS, unsigned>(
+          C, [&](int i) { return item[i]; },
+          [&](int i, unsigned it) { trow[(i + dl[it & 255]) & (M - 1)] = lds[(it >> 8) & mask]; });
+      if (b + 1 < b1) __syncthreads();
+    } else if constexpr (SINK == Sink::ret) {
+      columns([&](int ci, int col, long long) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) lds[loc[(j << pg.lw) + col] & mask] = h[ci][j];
+      });
+      __syncthreads();
+      float4* t4 = reinterpret_cast<float4*>(A.dst + 2 * (b * M + ((long long)c << pg.lC)));
+      for (int i = threadIdx.x; i < C / 2; i += THREADS) t4[i] = lds4[i];
+      if (b + 1 < b1) __syncthreads();
+    } else {
+      float2* zrow = A.Z + b * M;
+      columns([&](int ci, int, long long n) {
+        float2 x[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) x[j] = h[ci][j];
+        Dft<R, false>::run(x);
+#pragma unroll
+        for (int r = 1; r < R; ++r) x[r] = cmul(x[r], A.tw[((r - 1) << pg.lQ) + n]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) zrow[(r << pg.lQ) + n] = x[r];
+      });
+    }
+  }
+  if constexpr (BWD) {
+    float2* out = reinterpret_cast<float2*>(A.part) + p * M;
+    columns([&](int ci, int, long long n) {
+#pragma unroll
+      for (int j = 0; j < R; ++j) out[n + j * Q] = s[ci][j];
+    });
+  }
+}
+
+// Second-level radix-R passes on the R1 parts of a row (S = M / R1 = R L):
+// butterfly n of a part takes x[n + j L]; tw2 [R-1][L] holds W_S^(n r).
+template <int R, bool INV>
+__global__ __launch_bounds__(kThreads) void k_part(float2* __restrict__ Z, long long n_bfly, int lL,
+                                                   const float2* __restrict__ tw2) {
+  for (long long i = gindex(); i < n_bfly; i += gstride()) {
+    const long long L = 1LL << lL, n = i & (L - 1);
+    float2* z = Z + (i >> lL) * (R * L) + n;
     float2 x[R];
 #pragma unroll
-    for (int j = 0; j < R; ++j) {
-      const long long m = b * M + n + j * Q;
-      const float2 u = src[m];
-      if (stash) stash[m] = u;
-      x[j] = a ? cmul(u, a[n + j * Q]) : u;
+    for (int j = 0; j < R; ++j) x[j] = z[j << lL];
+    if constexpr (INV) {
+#pragma unroll
+      for (int r = 1; r < R; ++r) x[r] = cmulc(x[r], tw2[((r - 1) << lL) + n]);
     }
-    Dft<R, false>::run(x);
+    Dft<R, INV>::run(x);
+    if constexpr (!INV) {
 #pragma unroll
-    for (int r = 1; r < R; ++r) x[r] = cmul(x[r], twM[n * r]);
+      for (int r = 1; r < R; ++r) x[r] = cmul(x[r], tw2[((r - 1) << lL) + n]);
+    }
 #pragma unroll
-    for (int r = 0; r < R; ++r) Z[b * M + r * Q + n] = x[r];
+    for (int r = 0; r < R; ++r) z[r << lL] = x[r];
   }
 }
 
-// Last DIT pass (S = M), written out of place to the layer output.
-template <int R>
-__global__ __launch_bounds__(kThreads) void k_cdit_out(const float2* __restrict__ Z, float2* __restrict__ dst,
-                                                       long long B, long long M, const float2* __restrict__ twM) {
-  const long long Q = M / R, total = B * Q;
-  for (long long i = gindex(); i < total; i += gstride()) {
-    const long long b = i / Q, n = i % Q;
-    float2 y[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) y[r] = Z[b * M + r * Q + n];
-#pragma unroll
-    for (int r = 1; r < R; ++r) y[r] = cmulc(y[r], twM[n * r]);
-    Dft<R, true>::run(y);
-#pragma unroll
-    for (int j = 0; j < R; ++j) dst[b * M + n + j * Q] = y[j];
+// ---------------------------------------------------------------- segments
+// Segment plans: 16 (8) values per thread, one butterfly per thread in the
+// first and last pass, so that frequency k2 = t + T s sits in register s of
+// lane t.  Small register arrays keep four waves per SIMD where the complex
+// rows of the fused kernels (32 values) run two.
+using SP64 = ComplexPlan<64, 8, 8, 8>;
+using SP128 = ComplexPlan<128, 16, 8, 2, 8>;
+using SP256 = ComplexPlan<256, 16, 16, 16>;
+using SP512 = ComplexPlan<512, 32, 16, 2, 16>;
+using SP1024 = ComplexPlan<1024, 64, 16, 4, 16>;
+using SP2048 = ComplexPlan<2048, 128, 16, 8, 16>;
+using SP4096 = ComplexPlan<4096, 256, 16, 16, 16>;
+
+template <class F>
+bool with_seg_plan(int L, F&& f) {
+  switch (L) {
+    case 64: f.template operator()<SP64>(); return true;
+    case 128: f.template operator()<SP128>(); return true;
+    case 256: f.template operator()<SP256>(); return true;
+    case 512: f.template operator()<SP512>(); return true;
+    case 1024: f.template operator()<SP1024>(); return true;
+    case 2048: f.template operator()<SP2048>(); return true;
+    case 4096: f.template operator()<SP4096>(); return true;
+    default: return false;
   }
 }
 
-// Without DIF passes (one segment per row): Z = u * a (stashed), dst = Z.
-__global__ __launch_bounds__(kThreads) void k_cscale(const float2* __restrict__ src, const float2* __restrict__ a,
-                                                     float2* __restrict__ stash, float2* __restrict__ Z, long long B,
-                                                     long long M) {
-  const long long total = B * M;
-  for (long long i = gindex(); i < total; i += gstride()) {
-    const float2 u = src[i];
-    if (stash) stash[i] = u;
-    Z[i] = a ? cmul(u, a[i % M]) : u;
+template <class PL>
+struct Seg {
+  using O = CplxOps<PL>;
+  static constexpr int T = PL::T, P = PL::P, L = PL::N;
+  static_assert(O::B0 == 1 && O::BL == 1 && O::KIND == 0, "register s of lane t holds t + T s at both ends");
+  static constexpr int GROUPS = T < 64 ? 64 / T : 1;  // segments (pairs) per workgroup
+  static constexpr int THREADS = T < 64 ? 64 : T;
+  static constexpr int SLAB = PL::SLAB;
+};
+
+// Pair p (of S/2) of a real row's segments: Z[k] in one has its Makhoul
+// partner Z[M-k] in the other, at L-1-k2.  Pair 0 is the two segments that
+// hold their own partners, segment 0 (at L-k2) and one more (at L-1-k2).
+__host__ __device__ __forceinline__ void seg_pair(const Geo& g, int p, int& sa, int& sb) {
+  if (p == 0) {
+    sa = 0;
+    sb = g.R2 == 1 ? g.R1 / 2 : g.R2 / 2;
+    return;
   }
-}
-__global__ __launch_bounds__(kThreads) void k_ccopy(const float2* __restrict__ Z, float2* __restrict__ dst,
-                                                    long long total) {
-  for (long long i = gindex(); i < total; i += gstride()) dst[i] = Z[i];
+  int x = p - 1;
+  if (x < (g.R1 / 2 - 1) * g.R2) {
+    const int r1 = 1 + x / g.R2, r2 = x % g.R2;
+    sa = r1 * g.R2 + r2;
+    sb = (g.R1 - r1) * g.R2 + (g.R2 - 1 - r2);
+    return;
+  }
+  x -= (g.R1 / 2 - 1) * g.R2;
+  if (x < g.R2 / 2) {
+    sa = (g.R1 / 2) * g.R2 + x;
+    sb = (g.R1 / 2) * g.R2 + (g.R2 - 1 - x);
+    return;
+  }
+  x -= g.R2 / 2;
+  sa = 1 + x;
+  sb = g.R2 - 1 - x;
 }
 
-// Spectrum index of storage position q (the inverse of pos()).
+// Quartet of lane t, slot s (of P) of pair p: its number e, where e = 0 is
+// the self-paired (Z[0], Z[M/2]) and otherwise Z[e] pairs with Z[M-e].
+__host__ __device__ __forceinline__ long long quartet_of(const Geo& g, int p, int s, int t, int T, int P) {
+  const long long S = (long long)g.R1 * g.R2;
+  if (p == 0) return s < P / 2 ? S * (t + T * s) : S / 2 + S * (t + T * (s - P / 2));
+  int sa, sb;
+  seg_pair(g, p, sa, sb);
+  const long long k = sa / g.R2 + (long long)g.R1 * (sa % g.R2 + (long long)g.R2 * (t + T * s));
+  return k < g.M / 2 ? k : g.M - k;
+}
+
+// Spectrum index of storage position q.
 __device__ __forceinline__ long long spec_index(const Geo& g, long long q) {
   const long long S1 = g.M / g.R1;
   const long long r1 = q / S1, rem = q % S1;
@@ -720,420 +733,699 @@ __device__ __forceinline__ long long spec_index(const Geo& g, long long q) {
   return r1 + (long long)g.R1 * (r2 + (long long)g.R2 * k2);
 }
 
-// Forward middle: X[k] *= d[k] / N, kColRows rows per thread and position.
-__global__ __launch_bounds__(kThreads) void k_cmid_fwd(float2* __restrict__ Z, const float2* __restrict__ d,
-                                                       long long B, Geo g, float invN) {
-  const long long M = g.M, P = (B + kColRows - 1) / kColRows, total = P * M;
-  for (long long i = gindex(); i < total; i += gstride()) {
-    const long long p = i / M, q = i % M;
-    const float2 dk = d[spec_index(g, q)];
-    const float2 w = make_float2(dk.x * invN, dk.y * invN);
-    const long long b0 = p * kColRows, b1 = b0 + kColRows < B ? b0 + kColRows : B;
-    for (long long b = b0; b < b1; ++b) Z[b * M + q] = cmul(Z[b * M + q], w);
+// The lanes of one pair: segment A in v (lane t), segment B in w with the
+// lanes reversed (lane T-1-t).  Then register s of v and register P-1-s of w
+// hold k2 and L-1-k2, Makhoul partners in a generic pair.  Slot s has
+// (Z[e], Z[M-e]) = (v[s], w[P-1-s]) for s < P/2 and the other way round from
+// there on, where k > M/2.
+template <class PL>
+struct PairOps {
+  using G = Seg<PL>;
+  static constexpr int T = PL::T, P = PL::P, L = PL::N;
+  template <bool INV, class Ctx>
+  __device__ __forceinline__ static void fft(Ctx& ctx, float2 (&v)[P], float2 (&w)[P], unsigned t, float2* slab,
+                                             GView tab) {
+    G::O::template fft<INV>(ctx, v, t, slab, tab);
+    G::O::template fft<INV>(ctx, w, T - 1 - t, slab, tab);
   }
-}
-
-// Backward middle: gh3 = FFT(g) / N, the dL/dd image gh3 * conj(h2) summed
-// over blocks of kColRows rows into part[p][k] (complex, spectrum order),
-// and g's spectrum replaced by gh3 * conj(d).
-__global__ __launch_bounds__(kThreads) void k_cmid_bwd(const float2* __restrict__ Zh, float2* __restrict__ Zg,
-                                                       const float2* __restrict__ d, long long B, Geo g, float invN,
-                                                       float2* __restrict__ part) {
-  const long long M = g.M, P = (B + kColRows - 1) / kColRows, total = P * M;
-  for (long long i = gindex(); i < total; i += gstride()) {
-    const long long p = i / M, q = i % M, k = spec_index(g, q);
-    const float2 dk = d[k];
-    float2 acc = make_float2(0.f, 0.f);
-    const long long b0 = p * kColRows, b1 = b0 + kColRows < B ? b0 + kColRows : B;
-    for (long long b = b0; b < b1; ++b) {
-      const float2 gz = Zg[b * M + q];
-      const float2 gh3 = make_float2(gz.x * invN, gz.y * invN);
-      const float2 img = cmulc(gh3, Zh[b * M + q]);
-      acc = make_float2(acc.x + img.x, acc.y + img.y);
-      Zg[b * M + q] = cmulc(gh3, dk);
+  __device__ __forceinline__ static void load(const float2* row, int sa, int sb, float2 (&v)[P], float2 (&w)[P],
+                                              unsigned t) {
+    G::O::template ld_row<false>(GView::of(row + (long long)sa * L), 0u, v, t);
+    G::O::template ld_row<false>(GView::of(row + (long long)sb * L), 0u, w, T - 1 - t);
+  }
+  __device__ __forceinline__ static void store(float2* row, int sa, int sb, float2 (&v)[P], float2 (&w)[P],
+                                               unsigned t) {
+    G::O::template st_row<true>(GView::of(row + (long long)sa * L), 0u, v, t);
+    G::O::template st_row<true>(GView::of(row + (long long)sb * L), 0u, w, T - 1 - t);
+  }
+  static __device__ __forceinline__ float2& zk(float2 (&v)[P], float2 (&w)[P], int s) {
+    return s < P / 2 ? v[s] : w[P - 1 - s];
+  }
+  static __device__ __forceinline__ float2& zm(float2 (&v)[P], float2 (&w)[P], int s) {
+    return s < P / 2 ? w[P - 1 - s] : v[s];
+  }
+  // Pair 0: the partners lie in other lanes of the same segment.  Through
+  // the slab, one segment after the other: segment 0's quartets q = t + T s
+  // (k2 = q, L-q; q = 0: 0, L/2) into slots s < P/2, segment B's (q, L-1-q)
+  // into the others; and back.
+  template <class Ctx>
+  __device__ __forceinline__ static void to_quartets(Ctx& ctx, float2 (&v)[P], float2 (&w)[P], unsigned t,
+                                                     float2* slab) {
+    float2 a[P / 2], b[P / 2], c[P / 2], d[P / 2];
+    ctx.sync_row();
+#pragma unroll
+    for (int s = 0; s < P; ++s) slab[t + T * s] = v[s];
+    ctx.sync_row();
+#pragma unroll
+    for (int s = 0; s < P / 2; ++s) {
+      const unsigned q = t + T * s;
+      a[s] = slab[q];
+      b[s] = slab[q == 0 ? L / 2 : L - q];
     }
-    part[p * M + k] = acc;
+    ctx.sync_row();
+#pragma unroll
+    for (int s = 0; s < P; ++s) slab[T - 1 - t + T * s] = w[s];
+    ctx.sync_row();
+#pragma unroll
+    for (int s = 0; s < P / 2; ++s) {
+      const unsigned q = t + T * s;
+      c[s] = slab[q];
+      d[s] = slab[L - 1 - q];
+    }
+#pragma unroll
+    for (int s = 0; s < P / 2; ++s) {
+      zk(v, w, s) = a[s];
+      zm(v, w, s) = b[s];
+    }
+#pragma unroll
+    for (int s = P / 2; s < P; ++s) {
+      zk(v, w, s) = c[s - P / 2];
+      zm(v, w, s) = d[s - P / 2];
+    }
+  }
+  template <class Ctx>
+  __device__ __forceinline__ static void from_quartets(Ctx& ctx, float2 (&v)[P], float2 (&w)[P], unsigned t,
+                                                       float2* slab) {
+    float2 nv[P], nw[P];
+    ctx.sync_row();
+#pragma unroll
+    for (int s = 0; s < P / 2; ++s) {
+      const unsigned q = t + T * s;
+      slab[q] = zk(v, w, s);
+      slab[q == 0 ? L / 2 : L - q] = zm(v, w, s);
+    }
+    ctx.sync_row();
+#pragma unroll
+    for (int s = 0; s < P; ++s) nv[s] = slab[t + T * s];
+    ctx.sync_row();
+#pragma unroll
+    for (int s = P / 2; s < P; ++s) {
+      const unsigned q = t + T * (s - P / 2);
+      slab[q] = zk(v, w, s);
+      slab[L - 1 - q] = zm(v, w, s);
+    }
+    ctx.sync_row();
+#pragma unroll
+    for (int s = 0; s < P; ++s) nw[s] = slab[T - 1 - t + T * s];
+#pragma unroll
+    for (int s = 0; s < P; ++s) {
+      v[s] = nv[s];
+      w[s] = nw[s];
+    }
+  }
+};
+
+// Forward: segment FFTs of a pair, the quartet maps, segment IFFTs.
+template <class PL>
+__global__ __launch_bounds__(Seg<PL>::THREADS) void k_seg_fwd(float2* __restrict__ Z, const float4* __restrict__ Mq,
+                                                              long long B, Geo g, int bias,
+                                                              const char* __restrict__ tab) {
+  using G = Seg<PL>;
+  using Q = PairOps<PL>;
+  constexpr int T = PL::T, P = PL::P;
+  __shared__ float lds[G::GROUPS * G::SLAB];
+  const unsigned t = threadIdx.x % T, grp = threadIdx.x / T;
+  float2* slab = reinterpret_cast<float2*>(lds + grp * G::SLAB);
+  const int np = g.R1 * g.R2 / 2;
+  const long long id = (long long)blockIdx.x * G::GROUPS + grp;
+  const bool valid = id < B * np;
+  const long long b = valid ? id / np : 0;
+  const int p = valid ? int(id % np) : 0;
+  int sa, sb;
+  seg_pair(g, p, sa, sb);
+  float2* row = Z + b * g.M;
+  DevCtx<T> ctx;
+  const GView tw = GView::of(tab);
+  float2 v[P], w[P];
+  Q::load(row, sa, sb, v, w, t);
+  Q::template fft<false>(ctx, v, w, t, slab, tw);
+  if (p == 0) Q::to_quartets(ctx, v, w, t, slab);
+  const GView mq = GView::of(Mq + (long long)p * PL::N * kMqRows);
+#pragma unroll
+  for (int s = 0; s < P; ++s) {
+    float2& zk = Q::zk(v, w, s);
+    float2& zm = Q::zm(v, w, s);
+    const float4 c0 = mq.ld4(t * 16u, unsigned((s * kMqRows + 0) * T * 16));
+    const float4 c1 = mq.ld4(t * 16u, unsigned((s * kMqRows + 1) * T * 16));
+    quartet_back(quartet_split(zk, zm, make_float2(c1.z, c1.w)), c0, c1, zk, zm);
+    if (bias) {
+      const float4 c3 = mq.ld4(t * 16u, unsigned((s * kMqRows + 3) * T * 16));
+      zk = make_float2(zk.x + c3.x, zk.y + c3.y);
+      zm = make_float2(zm.x + c3.z, zm.y + c3.w);
+    }
+  }
+  if (p == 0) Q::from_quartets(ctx, v, w, t, slab);
+  Q::template fft<true>(ctx, v, w, t, slab, tw);
+  if (valid) Q::store(row, sa, sb, v, w, t);
+}
+
+// Backward: rb rows in turn.  Segment FFTs of h and g, the images H*G (dL/dd)
+// summed over the rows, g's quartets through the D maps, its segment IFFTs.
+template <class PL>
+__global__ __launch_bounds__(Seg<PL>::THREADS) void k_seg_bwd(const float2* __restrict__ Zh, float2* __restrict__ Zg,
+                                                              const float4* __restrict__ Mq, long long B, Geo g,
+                                                              int rb, float* __restrict__ part,
+                                                              const char* __restrict__ tab) {
+  using G = Seg<PL>;
+  using Q = PairOps<PL>;
+  constexpr int T = PL::T, P = PL::P;
+  __shared__ float lds[G::GROUPS * G::SLAB];
+  const unsigned t = threadIdx.x % T, grp = threadIdx.x / T;
+  float2* slab = reinterpret_cast<float2*>(lds + grp * G::SLAB);
+  const int np = g.R1 * g.R2 / 2;
+  const long long nblk = (B + rb - 1) / rb, id = (long long)blockIdx.x * G::GROUPS + grp;
+  const bool valid = id < nblk * np;
+  const long long blk = valid ? id / np : 0;
+  const int p = valid ? int(id % np) : 0;
+  int sa, sb;
+  seg_pair(g, p, sa, sb);
+  DevCtx<T> ctx;
+  const GView tw = GView::of(tab);
+  const GView mq = GView::of(Mq + (long long)p * PL::N * kMqRows);
+  float4 sum[P];
+#pragma unroll
+  for (int s = 0; s < P; ++s) sum[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+  const long long b0 = blk * rb, b1 = b0 + rb < B ? b0 + rb : B;
+  for (long long b = b0; b < b1; ++b) {
+    float2 hv[P], hw[P], gv[P], gw[P];
+    Q::load(Zh + b * g.M, sa, sb, hv, hw, t);
+    Q::load(Zg + b * g.M, sa, sb, gv, gw, t);
+    Q::template fft<false>(ctx, hv, hw, t, slab, tw);
+    Q::template fft<false>(ctx, gv, gw, t, slab, tw);
+    if (p == 0) {
+      Q::to_quartets(ctx, hv, hw, t, slab);
+      Q::to_quartets(ctx, gv, gw, t, slab);
+    }
+#pragma unroll
+    for (int s = 0; s < P; ++s) {
+      const float4 c0 = mq.ld4(t * 16u, unsigned((s * kMqRows + 0) * T * 16));
+      const float4 c1 = mq.ld4(t * 16u, unsigned((s * kMqRows + 1) * T * 16));
+      const float4 c2 = mq.ld4(t * 16u, unsigned((s * kMqRows + 2) * T * 16));
+      const float2 wt = make_float2(c1.z, c1.w), qa = make_float2(c2.x, c2.y), qbr = make_float2(c2.z, c2.w);
+      float2& gk = Q::zk(gv, gw, s);
+      float2& gm = Q::zm(gv, gw, s);
+      float H[4], X[4];
+      quartet_post(quartet_split(Q::zk(hv, hw, s), Q::zm(hv, hw, s), wt), qa, qbr, H);
+      const Split sg = quartet_split(gk, gm, wt);
+      quartet_post(sg, qa, qbr, X);
+      sum[s] = make_float4(sum[s].x + H[0] * X[0], sum[s].y + H[1] * X[1], sum[s].z + H[2] * X[2],
+                           sum[s].w + H[3] * X[3]);
+      quartet_back(sg, c0, c1, gk, gm);
+    }
+    if (p == 0) Q::from_quartets(ctx, gv, gw, t, slab);
+    Q::template fft<true>(ctx, gv, gw, t, slab, tw);
+    if (valid) Q::store(Zg + b * g.M, sa, sb, gv, gw, t);
+  }
+  if (!valid) return;
+  float4* out = reinterpret_cast<float4*>(part + blk * 2 * g.M) + (long long)p * PL::N;
+#pragma unroll
+  for (int s = 0; s < P; ++s) out[T * s + t] = sum[s];
+}
+
+// DCT-II outputs of one row whose DIF passes are done (the bias gradient).
+template <class PL>
+__global__ __launch_bounds__(Seg<PL>::THREADS) void k_seg_dct(const float2* __restrict__ Z,
+                                                              const float4* __restrict__ Mq, Geo g, QuartetTabs q,
+                                                              float* __restrict__ out, int accumulate,
+                                                              const char* __restrict__ tab) {
+  using G = Seg<PL>;
+  using Q = PairOps<PL>;
+  constexpr int T = PL::T, P = PL::P;
+  __shared__ float lds[G::GROUPS * G::SLAB];
+  const unsigned t = threadIdx.x % T, grp = threadIdx.x / T;
+  float2* slab = reinterpret_cast<float2*>(lds + grp * G::SLAB);
+  const int np = g.R1 * g.R2 / 2, id = int(blockIdx.x) * G::GROUPS + int(grp);
+  const bool valid = id < np;
+  const int p = valid ? id : 0;
+  int sa, sb;
+  seg_pair(g, p, sa, sb);
+  DevCtx<T> ctx;
+  float2 v[P], w[P];
+  Q::load(Z, sa, sb, v, w, t);
+  Q::template fft<false>(ctx, v, w, t, slab, GView::of(tab));
+  if (p == 0) Q::to_quartets(ctx, v, w, t, slab);
+  const GView mq = GView::of(Mq + (long long)p * PL::N * kMqRows);
+#pragma unroll
+  for (int s = 0; s < P; ++s) {
+    const float4 c1 = mq.ld4(t * 16u, unsigned((s * kMqRows + 1) * T * 16));
+    const float4 c2 = mq.ld4(t * 16u, unsigned((s * kMqRows + 2) * T * 16));
+    float X[4];
+    quartet_post(quartet_split(Q::zk(v, w, s), Q::zm(v, w, s), make_float2(c1.z, c1.w)), make_float2(c2.x, c2.y),
+                 make_float2(c2.z, c2.w), X);
+    X[1] = -X[1];
+    const long long e = quartet_of(g, p, s, int(t), T, P);
+    const int4 idx = q.qidx[e];
+    const int sm = (q.qmask[e] >> 4) & 0xF;
+    const int id4[4] = {idx.x, idx.y, idx.z, idx.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (valid && (sm & (1 << j))) put1(out + id4[j], X[j], accumulate != 0);
   }
 }
 
-// The dL/da image gh1 * conj(u) and dL/du = gh1 * conj(a).
-__global__ __launch_bounds__(kThreads) void k_cdA(const float2* __restrict__ gh1, const float2* __restrict__ u,
-                                                  const float2* __restrict__ a, float2* __restrict__ imgA,
-                                                  float2* __restrict__ gu, long long B, long long N) {
-  const long long total = B * N;
+// Complex rows: segment FFT, * d / N (Dn in storage order), segment IFFT.
+template <class PL>
+__global__ __launch_bounds__(Seg<PL>::THREADS) void k_cseg_fwd(float2* __restrict__ Z, const float2* __restrict__ Dn,
+                                                               long long B, Geo g, const char* __restrict__ tab) {
+  using G = Seg<PL>;
+  using O = typename G::O;
+  constexpr int T = PL::T, P = PL::P;
+  __shared__ float lds[G::GROUPS * G::SLAB];
+  const unsigned t = threadIdx.x % T, grp = threadIdx.x / T;
+  float2* slab = reinterpret_cast<float2*>(lds + grp * G::SLAB);
+  const int ns = g.R1 * g.R2;
+  const long long id = (long long)blockIdx.x * G::GROUPS + grp;
+  const bool valid = id < B * ns;
+  const long long seg = valid ? id : 0;
+  const GView z = GView::of(Z + seg * PL::N), tw = GView::of(tab);
+  const GView dn = GView::of(Dn + (seg % ns) * PL::N);
+  DevCtx<T> ctx;
+  float2 v[P];
+  O::template ld_row<false>(z, 0u, v, t);
+  O::template fft<false>(ctx, v, t, slab, tw);
+#pragma unroll
+  for (int s = 0; s < P; ++s) v[s] = cmul(v[s], dn.ld2(t * 8u, unsigned(T * s) * 8u));
+  O::template fft<true>(ctx, v, t, slab, tw);
+  if (valid) O::template st_row<true>(z, 0u, v, t);
+}
+
+// Backward, rb rows in turn: gh3 = FFT(g) / N, images gh3 * conj(h2) summed
+// over the rows (storage order), then gh3 * conj(d) and its segment IFFT.
+// N is a power of two, so dividing the sum is exact.
+template <class PL>
+__global__ __launch_bounds__(Seg<PL>::THREADS) void k_cseg_bwd(const float2* __restrict__ Zh, float2* __restrict__ Zg,
+                                                               const float2* __restrict__ Dn, long long B, Geo g,
+                                                               int rb, float2* __restrict__ part,
+                                                               const char* __restrict__ tab) {
+  using G = Seg<PL>;
+  using O = typename G::O;
+  constexpr int T = PL::T, P = PL::P;
+  __shared__ float lds[G::GROUPS * G::SLAB];
+  const unsigned t = threadIdx.x % T, grp = threadIdx.x / T;
+  float2* slab = reinterpret_cast<float2*>(lds + grp * G::SLAB);
+  const int ns = g.R1 * g.R2;
+  const long long nblk = (B + rb - 1) / rb, id = (long long)blockIdx.x * G::GROUPS + grp;
+  const bool valid = id < nblk * ns;
+  const long long blk = valid ? id / ns : 0;
+  const int sg = valid ? int(id % ns) : 0;
+  const GView tw = GView::of(tab), dn = GView::of(Dn + (long long)sg * PL::N);
+  DevCtx<T> ctx;
+  float2 sum[P];
+#pragma unroll
+  for (int s = 0; s < P; ++s) sum[s] = make_float2(0.f, 0.f);
+  const long long b0 = blk * rb, b1 = b0 + rb < B ? b0 + rb : B;
+  for (long long b = b0; b < b1; ++b) {
+    const long long at = b * g.M + (long long)sg * PL::N;
+    float2 h[P], v[P];
+    O::template ld_row<false>(GView::of(Zh + at), 0u, h, t);
+    O::template ld_row<false>(GView::of(Zg + at), 0u, v, t);
+    O::template fft<false>(ctx, h, t, slab, tw);
+    O::template fft<false>(ctx, v, t, slab, tw);
+#pragma unroll
+    for (int s = 0; s < P; ++s) {
+      const float2 img = cmulc(v[s], h[s]);
+      sum[s] = make_float2(sum[s].x + img.x, sum[s].y + img.y);
+      v[s] = cmulc(v[s], dn.ld2(t * 8u, unsigned(T * s) * 8u));
+    }
+    O::template fft<true>(ctx, v, t, slab, tw);
+    if (valid) O::template st_row<true>(GView::of(Zg + at), 0u, v, t);
+  }
+  if (!valid) return;
+  const float inv = 1.0f / float(g.M);
+  float2* out = part + blk * g.M + (long long)sg * PL::N;
+#pragma unroll
+  for (int s = 0; s < P; ++s) out[T * s + t] = make_float2(sum[s].x * inv, sum[s].y * inv);
+}
+
+// Per-layer quartet coefficients, [K][pair][slot][kMqRows][T].
+__global__ __launch_bounds__(kThreads) void k_mq(const float* __restrict__ D, const float* __restrict__ Bias,
+                                                 float4* __restrict__ Mq, int K, Geo g, QuartetTabs q, int T, int P) {
+  const long long NQ = g.M / 2, total = (long long)K * NQ, N = 2 * g.M;
   for (long long i = gindex(); i < total; i += gstride()) {
-    const float2 gg = gh1[i];
-    imgA[i] = cmulc(gg, u[i]);
-    gu[i] = cmulc(gg, a[i % N]);
+    const long long k = i / NQ, r = i % NQ;
+    const int p = int(r / g.L), s = int(r % g.L) / T, t = int(r % T);
+    const int e = int(quartet_of(g, p, s, t, T, P));
+    float4 row[kMqRows];
+    quartet_coeffs(D + k * N, Bias ? Bias + k * N : nullptr, q, e, row);
+    float4* out = Mq + (i - t) * kMqRows + t;
+#pragma unroll
+    for (int c = 0; c < kMqRows; ++c) out[c * T] = row[c];
   }
 }
 
-// Column sums, stage 1: part[p][w] = sum of rows p*kColRows ... of img, in
-// row order, four columns per thread.
+// d / N of every layer in storage order.
+__global__ __launch_bounds__(kThreads) void k_dn(const float2* __restrict__ D, float2* __restrict__ Dn, int K, Geo g,
+                                                 float inv) {
+  const long long total = (long long)K * g.M;
+  for (long long i = gindex(); i < total; i += gstride()) {
+    const float2 d = D[(i / g.M) * g.M + spec_index(g, i % g.M)];
+    Dn[i] = make_float2(d.x * inv, d.y * inv);
+  }
+}
+
+// -------------------------------------------------------------------- sums
+
+// part[p][w] = sum of rows p*kMaxRows ... of img, in row order, four columns
+// per thread.
 __global__ __launch_bounds__(kThreads) void k_colsum1(const float* __restrict__ img, long long B, long long W,
                                                       float* __restrict__ part) {
-  const long long W4 = W / 4, P = (B + kColRows - 1) / kColRows, total = P * W4;
+  const long long W4 = W / 4, P = (B + kMaxRows - 1) / kMaxRows, total = P * W4;
   for (long long i = gindex(); i < total; i += gstride()) {
     const long long p = i / W4, w4 = i % W4;
-    const long long b0 = p * kColRows, b1 = b0 + kColRows < B ? b0 + kColRows : B;
+    const long long b0 = p * kMaxRows, b1 = b0 + kMaxRows < B ? b0 + kMaxRows : B;
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
     const float4* col = reinterpret_cast<const float4*>(img) + w4;
 #pragma unroll 4
-    for (long long b = b0; b < b1; ++b) {
-      const float4 v = col[b * W4];
-      s = make_float4(s.x + v.x, s.y + v.y, s.z + v.z, s.w + v.w);
-    }
+    for (long long b = b0; b < b1; ++b) s = add4(s, col[b * W4]);
     reinterpret_cast<float4*>(part)[p * W4 + w4] = s;
   }
 }
 
-// Stage 2: the block sums in block order, stored (or added) to the output.
+// The block sums in block order: kSumPh phases of consecutive blocks, one
+// thread each, added in phase order (a column is a serial chain of P loads;
+// W / 4 threads alone would leave the chip idle).
+constexpr int kSumPh = 8, kSumCols = kThreads / kSumPh;
+template <Order HOW>
 __global__ __launch_bounds__(kThreads) void k_colsum2(const float* __restrict__ part, long long P, long long W,
-                                                      float* __restrict__ out, QuartetTabs q, int quartet,
+                                                      float* __restrict__ out, Geo g, QuartetTabs q, int T, int PT,
                                                       int accumulate) {
-  for (long long w = gindex(); w < W; w += gstride()) {
-    float s = 0.f;
-    for (long long p = 0; p < P; ++p) s += part[p * W + w];
-    long long o = w;
-    if (quartet) {
-      const long long e = w / 4;
-      const int j = int(w % 4);
-      if (!((q.qmask[e] >> (4 + j)) & 1)) continue;
-      const int4 idx = q.qidx[e];
-      o = j == 0 ? idx.x : j == 1 ? idx.y : j == 2 ? idx.z : idx.w;
-    }
-    out[o] = accumulate ? out[o] + s : s;
+  __shared__ float4 ph[kSumPh][kSumCols];
+  const int lane = threadIdx.x % kSumCols, f = threadIdx.x / kSumCols;
+  const long long w4 = (long long)blockIdx.x * kSumCols + lane, W4 = W / 4;
+  const long long per = (P + kSumPh - 1) / kSumPh, p0 = f * per, p1 = p0 + per < P ? p0 + per : P;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (w4 < W4) {
+    const float4* col = reinterpret_cast<const float4*>(part) + w4;
+#pragma unroll 4
+    for (long long p = p0; p < p1; ++p) s = add4(s, col[p * W4]);
+  }
+  ph[f][lane] = s;
+  __syncthreads();
+  if (f != 0 || w4 >= W4) return;
+#pragma unroll
+  for (int r = 1; r < kSumPh; ++r) s = add4(s, ph[r][lane]);
+  const bool acc = accumulate != 0;
+  if constexpr (HOW == Order::natural) {
+    put4(reinterpret_cast<float4*>(out) + w4, s, acc);
+  } else if constexpr (HOW == Order::quartets) {
+    const int p = int(w4 / g.L), sl = int(w4 % g.L) / T, t = int(w4 % T);
+    const long long e = quartet_of(g, p, sl, t, T, PT);
+    const int m = (q.qmask[e] >> 4) & 0xF;
+    const int4 idx = q.qidx[e];
+    if (m & 1) put1(out + idx.x, s.x, acc);
+    if (m & 2) put1(out + idx.y, s.y, acc);
+    if (m & 4) put1(out + idx.z, s.z, acc);
+    if (m & 8) put1(out + idx.w, s.w, acc);
+  } else {
+    float2* o = reinterpret_cast<float2*>(out);
+    const long long k0 = spec_index(g, 2 * w4), k1 = spec_index(g, 2 * w4 + 1);
+    const float2 z = make_float2(0.f, 0.f);
+    const float2 o0 = acc ? o[k0] : z, o1 = acc ? o[k1] : z;
+    o[k0] = make_float2(o0.x + s.x, o0.y + s.y);
+    o[k1] = make_float2(o1.x + s.z, o1.y + s.w);
   }
 }
 
+int log2_of(long long v) {
+  int l = 0;
+  while ((1LL << (l + 1)) <= v) ++l;
+  return l;
+}
+
+// T and P of the segment plan of L points.
+void seg_shape(int L, int& T, int& P) {
+  T = P = 1;
+  (void)with_seg_plan(L, [&]<class PL>() {
+    T = PL::T;
+    P = PL::P;
+  });
+}
+
+template <class K>
+hipError_t launch(K&& k) {
+  k();
+  return hipGetLastError();
+}
+
 template <class F>
-bool with_seg_plan(int L, F&& f) {
-  switch (L) {
-    case 128: f.template operator()<CP128>(); return true;
-    case 256: f.template operator()<CP256>(); return true;
-    case 512: f.template operator()<CP512>(); return true;
-    case 1024: f.template operator()<CP1024>(); return true;
-    case 2048: f.template operator()<CP2048>(); return true;
-    case 4096: f.template operator()<CP4096>(); return true;
-    case 8192: f.template operator()<CP8192>(); return true;
+bool with_r1(int R1, F&& f) {
+  switch (R1) {
+    case 2: f.template operator()<2>(); return true;
+    case 4: f.template operator()<4>(); return true;
+    case 8: f.template operator()<8>(); return true;
+    case 16: f.template operator()<16>(); return true;
     default: return false;
   }
 }
 
+template <Src SRC, Sink SINK, bool BWD>
+bool launch_cols(bool cplx, int R1, dim3 grid, const ColArgs& a, hipStream_t s) {
+  return with_r1(R1, [&]<int R>() {
+    if (cplx) hipLaunchKernelGGL((k_ccols<R, SRC, SINK, BWD>), grid, dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((k_cols<R, SRC, SINK, BWD>), grid, dim3(col_threads<R>()), 0, s, a);
+  });
+}
+
+template <bool INV>
+hipError_t part_pass(float2* Z, long long B, const Geo& g, const float2* tw2, hipStream_t s) {
+  if (g.R2 == 1) return hipSuccess;
+  const long long n = B * (g.M / g.R2);
+  const dim3 grid = grid_for(n), block(kThreads);
+  const int lL = log2_of(g.L);
+  switch (g.R2) {
+    case 2: hipLaunchKernelGGL((k_part<2, INV>), grid, block, 0, s, Z, n, lL, tw2); break;
+    case 4: hipLaunchKernelGGL((k_part<4, INV>), grid, block, 0, s, Z, n, lL, tw2); break;
+    case 8: hipLaunchKernelGGL((k_part<8, INV>), grid, block, 0, s, Z, n, lL, tw2); break;
+    case 16: hipLaunchKernelGGL((k_part<16, INV>), grid, block, 0, s, Z, n, lL, tw2); break;
+    case 32: hipLaunchKernelGGL((k_part<32, INV>), grid, block, 0, s, Z, n, lL, tw2); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+// Workgroups for `units` segments or pairs of the plan.
+template <class PL>
+dim3 seg_grid(long long units) {
+  return dim3(unsigned((units + Seg<PL>::GROUPS - 1) / Seg<PL>::GROUPS));
+}
+
+int clamp_rows(long long n) { return n < 1 ? 1 : n > kMaxRows ? kMaxRows : int(n); }
+
 }  // namespace
 
-hipError_t pack(const float* src, const float* a, float* stash, float2* Z, long long B, long long N, hipStream_t s) {
-  hipLaunchKernelGGL(k_pack, grid_for(B * (N / 4)), dim3(kThreads), 0, s, src, a, stash, Z, B, N);
-  return hipGetLastError();
+Geo geo(long long N) {
+  Geo g;
+  g.M = N / 2;
+  g.L = int(g.M / 2 < 4096 ? g.M / 2 : 4096);
+  const long long ratio = g.M / g.L;
+  g.R1 = int(ratio <= 16 ? ratio : 16);
+  g.R2 = int(ratio / g.R1);
+  return g;
 }
 
-hipError_t dif(float2* Z, long long B, const Geo& g, long long S, int R, const float2* twM, hipStream_t s) {
-  const dim3 grid = grid_for(B * (g.M / R)), block(kThreads);
-  switch (R) {
-    case 2: hipLaunchKernelGGL(k_dif<2>, grid, block, 0, s, Z, B, g.M, S, twM); break;
-    case 4: hipLaunchKernelGGL(k_dif<4>, grid, block, 0, s, Z, B, g.M, S, twM); break;
-    case 8: hipLaunchKernelGGL(k_dif<8>, grid, block, 0, s, Z, B, g.M, S, twM); break;
-    case 16: hipLaunchKernelGGL(k_dif<16>, grid, block, 0, s, Z, B, g.M, S, twM); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-hipError_t dit(float2* Z, long long B, const Geo& g, long long S, int R, const float2* twM, hipStream_t s) {
-  const dim3 grid = grid_for(B * (g.M / R)), block(kThreads);
-  switch (R) {
-    case 2: hipLaunchKernelGGL(k_dit<2>, grid, block, 0, s, Z, B, g.M, S, twM); break;
-    case 4: hipLaunchKernelGGL(k_dit<4>, grid, block, 0, s, Z, B, g.M, S, twM); break;
-    case 8: hipLaunchKernelGGL(k_dit<8>, grid, block, 0, s, Z, B, g.M, S, twM); break;
-    case 16: hipLaunchKernelGGL(k_dit<16>, grid, block, 0, s, Z, B, g.M, S, twM); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-hipError_t pack_dif(const float* src, const float* a, float* stash, float2* Z, long long B, long long M, int R,
-                    const float2* twM, hipStream_t s) {
-  const dim3 grid = grid_for(B * (M / R / 2)), block(kThreads);
-  switch (R) {
-    case 2: hipLaunchKernelGGL(k_pack_dif<2>, grid, block, 0, s, src, a, stash, Z, B, M, twM); break;
-    case 4: hipLaunchKernelGGL(k_pack_dif<4>, grid, block, 0, s, src, a, stash, Z, B, M, twM); break;
-    case 8: hipLaunchKernelGGL(k_pack_dif<8>, grid, block, 0, s, src, a, stash, Z, B, M, twM); break;
-    case 16: hipLaunchKernelGGL(k_pack_dif<16>, grid, block, 0, s, src, a, stash, Z, B, M, twM); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-hipError_t dit_unpack(const float2* Z, float* dst, long long B, long long M, int R, const float2* twM, bool relu,
-                      hipStream_t s) {
-  const dim3 grid = grid_for(B * (M / R / 2)), block(kThreads);
-  const int rl = relu ? 1 : 0;
-  switch (R) {
-    case 2: hipLaunchKernelGGL(k_dit_unpack<2>, grid, block, 0, s, Z, dst, B, M, twM, rl); break;
-    case 4: hipLaunchKernelGGL(k_dit_unpack<4>, grid, block, 0, s, Z, dst, B, M, twM, rl); break;
-    case 8: hipLaunchKernelGGL(k_dit_unpack<8>, grid, block, 0, s, Z, dst, B, M, twM, rl); break;
-    case 16: hipLaunchKernelGGL(k_dit_unpack<16>, grid, block, 0, s, Z, dst, B, M, twM, rl); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-hipError_t segments(float2* Z, long long nseg, int L, bool inverse, const char* seg_tab, hipStream_t s) {
-  bool ok = with_seg_plan(L, [&]<class CP>() {
-    using LC = Launch<CP>;
-    const dim3 grid(unsigned((nseg + LC::FWD_ROWS - 1) / LC::FWD_ROWS));
-    if (inverse) hipLaunchKernelGGL((k_seg<CP, true>), grid, dim3(LC::FWD_THREADS), 0, s, Z, nseg, seg_tab);
-    else hipLaunchKernelGGL((k_seg<CP, false>), grid, dim3(LC::FWD_THREADS), 0, s, Z, nseg, seg_tab);
-  });
-  if (!ok) return hipErrorInvalidValue;
-  return hipGetLastError();
-}
-
-hipError_t mq(const float* D, const float* Bias, float4* Mq, int K, long long NQ, const QuartetTabs& q,
-              hipStream_t s) {
-  hipLaunchKernelGGL(k_mq, grid_for((long long)K * NQ), dim3(kThreads), 0, s, D, Bias, Mq, K, NQ, q, 4 * NQ);
-  return hipGetLastError();
-}
-
-hipError_t mid_fwd(float2* Z, const float4* Mq, long long B, const Geo& g, bool bias, hipStream_t s) {
-  const long long P = (B + kColRows - 1) / kColRows;
-  hipLaunchKernelGGL(k_mid_fwd, grid_for(P * (g.M / 2)), dim3(kThreads), 0, s, Z, Mq, B, g, bias ? 1 : 0);
-  return hipGetLastError();
-}
-
-hipError_t mid_bwd(const float2* Zh, float2* Zg, const float4* Mq, long long B, const Geo& g, float* partD,
-                   float* partB, hipStream_t s) {
-  const long long P = (B + kColRows - 1) / kColRows;
-  hipLaunchKernelGGL(k_mid_bwd, grid_for(P * (g.M / 2)), dim3(kThreads), 0, s, Zh, Zg, Mq, B, g, partD, partB);
-  return hipGetLastError();
-}
-
-hipError_t unpack(const float2* Z, float* dst, long long B, long long N, bool relu, hipStream_t s) {
-  hipLaunchKernelGGL(k_unpack, grid_for(B * (N / 4)), dim3(kThreads), 0, s, Z, dst, B, N, relu ? 1 : 0);
-  return hipGetLastError();
-}
-
-hipError_t dA(const float* gh1, const float* u, const float* a, bool mask, float* imgA, float* gnext, long long B,
-              long long N, hipStream_t s) {
-  hipLaunchKernelGGL(k_dA, grid_for(B * N), dim3(kThreads), 0, s, gh1, u, a, mask ? 1 : 0, imgA, gnext, B, N);
-  return hipGetLastError();
-}
-
-PermGeo perm_geo(long long N, int ew) {
-  const long long cap = kPermChunk / ew;
+PermGeo perm_geo(const Geo& g, int ew) {
+  const long long N = 2 * g.M / ew, cap = kPermChunk / ew;  // elements of a row, of a whole set
+  const long long C = N < cap ? N : cap, Q = g.M / g.R1;
   PermGeo p;
-  p.C = int(N < cap ? N : cap);
-  p.nC = int(N / p.C);
+  p.ew = ew;
+  p.lC = log2_of(C);
+  p.nC = int(N / C);
+  p.lQ = log2_of(Q);
+  p.lw = log2_of(C / (ew == 1 ? 4LL * g.R1 : g.R1));
   return p;
 }
 
-size_t perm_table_ints(long long N, int ew) {
-  const PermGeo p = perm_geo(N, ew);
-  if (p.nC == 1) return 0;
-  return size_t(3 * N + 2 * (N / kThreads) * p.nC + 3LL * p.nC * p.nC);
+size_t perm_table_ints(const Geo& g, int ew) {
+  const PermGeo p = perm_geo(g, ew);
+  const size_t N = size_t(2 * g.M / ew), nn = size_t(p.nC) * p.nC;
+  return N + N / 2 + 2 * (N / kThreads) * p.nC + 4 * nn;
 }
 
-PermTabs perm_tables_at(int* base, long long N, int ew) {
-  const PermGeo p = perm_geo(N, ew);
+PermTabs perm_tables_at(int* base, const Geo& g, int ew) {
+  const PermGeo p = perm_geo(g, ew);
+  const long long N = 2 * g.M / ew, nb = N / kThreads, nn = (long long)p.nC * p.nC;
   PermTabs t;
-  if (p.nC == 1) return t;
-  t.stride = (long long)perm_table_ints(N, ew);
-  const long long nb = N / kThreads, nn = (long long)p.nC * p.nC;
-  t.srcA = base;
-  t.gposB = t.srcA + N;
-  t.locB = t.gposB + N;
-  t.cntS = t.locB + N;
+  t.stride = (long long)perm_table_ints(g, ew);
+  t.item = reinterpret_cast<unsigned*>(base);
+  t.loc = reinterpret_cast<unsigned short*>(base + N);
+  t.cntS = base + N + N / 2;
   t.bpre = t.cntS + nb * p.nC;
   t.cnt = t.bpre + nb * p.nC;
-  t.off = t.cnt + nn;
-  t.lst = t.off + nn;
+  t.start = t.cnt + nn;
+  t.lst = t.start + nn;
+  t.delta = t.lst + nn;
   return t;
 }
 
 PermTabs perm_layer(const PermTabs& t, int l) {
-  if (t.srcA == nullptr) return t;
   const long long o = l * t.stride;
   PermTabs r = t;
-  r.srcA += o;
-  r.gposB += o;
-  r.locB += o;
+  r.item += o;
+  r.loc += 2 * o;
   r.cntS += o;
   r.bpre += o;
   r.cnt += o;
-  r.off += o;
+  r.start += o;
   r.lst += o;
+  r.delta += o;
   return r;
 }
 
-hipError_t perm_build(const int* perm, long long N, int layers, const PermTabs& t, hipStream_t s, int ew) {
-  const PermGeo p = perm_geo(N, ew);
-  if (p.nC == 1 || layers <= 0) return hipSuccess;
+hipError_t perm_build(const int* perm, const Geo& g, int ew, int layers, const PermTabs& t, hipStream_t s) {
+  if (layers <= 0) return hipSuccess;
+  const PermGeo p = perm_geo(g, ew);
+  const long long N = 2 * g.M / ew;
   const unsigned nb = unsigned(N / kThreads), nn = unsigned(p.nC * p.nC), L = unsigned(layers);
-  hipLaunchKernelGGL(k_pt_count, dim3(nb, L), dim3(kThreads), 0, s, perm, N, p.C, p.nC, t.cntS, t.stride);
+  hipLaunchKernelGGL(k_pt_count, dim3(nb, L), dim3(kThreads), 0, s, perm, N, p, t.cntS, t.stride);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_pt_blocks, dim3((nn + kThreads - 1) / kThreads, L), dim3(kThreads), 0, s, t.cntS, p.C, p.nC,
-                     t.bpre, t.cnt, t.stride);
+  hipLaunchKernelGGL(k_pt_blocks, dim3((nn + kThreads - 1) / kThreads, L), dim3(kThreads), 0, s, t.cntS, p, t.bpre,
+                     t.cnt, t.stride);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_pt_offsets, dim3(L), dim3(kThreads), 0, s, t.cnt, p.C, p.nC, t.off, t.lst, t.stride);
+  hipLaunchKernelGGL(k_pt_offsets, dim3(L), dim3(kThreads), 0, s, t.cnt, p, t.start, t.lst, t.delta, t.stride);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_pt_place, dim3(nb, L), dim3(kThreads), 0, s, perm, N, p.C, p.nC, t.bpre, t.off, t.lst,
-                     t.srcA, t.gposB, t.locB, t.stride);
+  hipLaunchKernelGGL(k_pt_place, dim3(nb, L), dim3(kThreads), 0, s, perm, N, p, t.bpre, t.start, t.lst, t.item,
+                     t.loc, t.stride);
   return hipGetLastError();
 }
 
-namespace {
-dim3 perm_grid(long long work) { return dim3(unsigned(work < 65536 ? (work < 1 ? 1 : work) : 65536)); }
-}  // namespace
-
-hipError_t permute(const float* in, float* out, float* tmp, const int* perm, const PermTabs& t, long long B,
-                   long long N, hipStream_t s) {
-  const PermGeo p = perm_geo(N, 1);
-  const long long work = B * p.nC;
-  if (p.nC == 1) {
-    hipLaunchKernelGGL(k_pt_a<float>, perm_grid(work), dim3(kPermThreads), 0, s, in, out, perm, N, p.C, p.nC, work);
-    return hipGetLastError();
+hipError_t cols(Src src, Sink sink, bool cplx, const Cols& c, long long B, const Geo& g, const float2* tw1,
+                hipStream_t s) {
+  const PermGeo pg = perm_geo(g, cplx ? 2 : 1);
+  const bool bwd = c.u != nullptr;
+  const int rb = bwd ? col_rows(B, g, pg.ew) : 1;
+  ColArgs a{c.src,   c.dst, c.Z,  c.a,    c.stash, c.u, c.part, tw1, nullptr, nullptr, nullptr, B, g.M,
+            rb, c.relu, pg};
+  if (c.pt != nullptr) {
+    a.item = c.pt->item;
+    a.loc = c.pt->loc;
+    a.delta = c.pt->delta;
   }
-  hipLaunchKernelGGL(k_pt_a<float>, perm_grid(work), dim3(kPermThreads), 0, s, in, tmp, t.srcA, N, p.C, p.nC, work);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_pt_b<float>, perm_grid(work), dim3(kPermThreads), 0, s, tmp, out, t.gposB, t.locB, N, p.C, p.nC,
-                     work);
+  const dim3 grid(unsigned((B + rb - 1) / rb * pg.nC));
+  auto is = [&](Src x, Sink y, bool w) { return src == x && sink == y && bwd == w; };
+  bool ok = false;
+  if (is(Src::rows, Sink::send, false)) ok = launch_cols<Src::rows, Sink::send, false>(cplx, g.R1, grid, a, s);
+  else if (is(Src::rows, Sink::dif, false)) ok = launch_cols<Src::rows, Sink::dif, false>(cplx, g.R1, grid, a, s);
+  else if (is(Src::gather, Sink::dif, false)) ok = launch_cols<Src::gather, Sink::dif, false>(cplx, g.R1, grid, a, s);
+  else if (is(Src::dit, Sink::send, false)) ok = launch_cols<Src::dit, Sink::send, false>(cplx, g.R1, grid, a, s);
+  else if (is(Src::dit, Sink::rows, false)) ok = launch_cols<Src::dit, Sink::rows, false>(cplx, g.R1, grid, a, s);
+  else if (is(Src::dit, Sink::dif, false)) ok = launch_cols<Src::dit, Sink::dif, false>(cplx, g.R1, grid, a, s);
+  else if (is(Src::scatter, Sink::dif, false))
+    ok = launch_cols<Src::scatter, Sink::dif, false>(cplx, g.R1, grid, a, s);
+  else if (is(Src::scatter, Sink::rows, false))
+    ok = launch_cols<Src::scatter, Sink::rows, false>(cplx, g.R1, grid, a, s);
+  else if (is(Src::dit, Sink::ret, true)) ok = launch_cols<Src::dit, Sink::ret, true>(cplx, g.R1, grid, a, s);
+  else if (is(Src::dit, Sink::rows, true)) ok = launch_cols<Src::dit, Sink::rows, true>(cplx, g.R1, grid, a, s);
+  else if (is(Src::dit, Sink::dif, true)) ok = launch_cols<Src::dit, Sink::dif, true>(cplx, g.R1, grid, a, s);
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
+}
+
+hipError_t dif2(float2* Z, long long B, const Geo& g, const float2* tw2, hipStream_t s) {
+  return part_pass<false>(Z, B, g, tw2, s);
+}
+hipError_t dit2(float2* Z, long long B, const Geo& g, const float2* tw2, hipStream_t s) {
+  return part_pass<true>(Z, B, g, tw2, s);
+}
+
+hipError_t mq(const float* D, const float* Bias, float4* Mq, int K, const Geo& g, const QuartetTabs& q,
+              hipStream_t s) {
+  int T, P;
+  seg_shape(g.L, T, P);
+  hipLaunchKernelGGL(k_mq, grid_for((long long)K * (g.M / 2)), dim3(kThreads), 0, s, D, Bias, Mq, K, g, q, T, P);
   return hipGetLastError();
 }
 
-hipError_t dA_permute(const float* gh1, const float* u, const float* a, bool mask, float* imgA, float* gnext,
-                      float* tmp, const int* perm, const PermTabs& t, long long B, long long N, hipStream_t s) {
-  const PermGeo p = perm_geo(N, 1);
-  const long long work = B * p.nC;
-  const int mk = mask ? 1 : 0;
-  if (p.nC == 1) {
-    hipLaunchKernelGGL(k_pt_bt, perm_grid(work), dim3(kPermThreads), 0, s, gh1, u, a, mk, imgA, gnext,
-                       static_cast<const int*>(nullptr), perm, N, p.C, p.nC, work);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(k_pt_bt, perm_grid(work), dim3(kPermThreads), 0, s, gh1, u, a, mk, imgA, tmp, t.gposB, t.locB,
-                     N, p.C, p.nC, work);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_pt_at<float>, perm_grid(work), dim3(kPermThreads), 0, s, tmp, gnext, t.srcA, N, p.C, p.nC, work);
+hipError_t seg_fwd(float2* Z, const float4* Mq, long long B, const Geo& g, bool bias, const char* seg_tab,
+                   hipStream_t s) {
+  const bool ok = with_seg_plan(g.L, [&]<class PL>() {
+    hipLaunchKernelGGL(k_seg_fwd<PL>, seg_grid<PL>(B * (g.R1 * g.R2 / 2)), dim3(Seg<PL>::THREADS), 0, s, Z, Mq, B, g,
+                       bias ? 1 : 0, seg_tab);
+  });
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
+}
+
+hipError_t seg_bwd(float2* Zh, float2* Zg, const float4* Mq, long long B, const Geo& g, float* part,
+                   const char* seg_tab, hipStream_t s) {
+  const int rb = seg_rows(B, g, false);
+  const bool ok = with_seg_plan(g.L, [&]<class PL>() {
+    hipLaunchKernelGGL(k_seg_bwd<PL>, seg_grid<PL>((B + rb - 1) / rb * (g.R1 * g.R2 / 2)), dim3(Seg<PL>::THREADS), 0,
+                       s, Zh, Zg, Mq, B, g, rb, part, seg_tab);
+  });
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
+}
+
+hipError_t seg_dct(const float2* Z, const float4* Mq, const Geo& g, const QuartetTabs& q, float* gB,
+                   bool accumulate, const char* seg_tab, hipStream_t s) {
+  const bool ok = with_seg_plan(g.L, [&]<class PL>() {
+    hipLaunchKernelGGL(k_seg_dct<PL>, seg_grid<PL>(g.R1 * g.R2 / 2), dim3(Seg<PL>::THREADS), 0, s, Z, Mq, g, q, gB,
+                       accumulate ? 1 : 0, seg_tab);
+  });
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
+}
+
+hipError_t dn(const float2* D, float2* Dn, int K, const Geo& g, hipStream_t s) {
+  hipLaunchKernelGGL(k_dn, grid_for((long long)K * g.M), dim3(kThreads), 0, s, D, Dn, K, g, 1.0f / float(g.M));
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------- complex launchers
-hipError_t cpermute(const float2* in, float2* out, float2* tmp, const int* perm, const PermTabs& t, long long B,
-                    long long N, hipStream_t s) {
-  const PermGeo p = perm_geo(N, 2);
-  const long long work = B * p.nC;
-  if (p.nC == 1) {
-    hipLaunchKernelGGL(k_pt_a<float2>, perm_grid(work), dim3(kPermThreads), 0, s, in, out, perm, N, p.C, p.nC, work);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(k_pt_a<float2>, perm_grid(work), dim3(kPermThreads), 0, s, in, tmp, t.srcA, N, p.C, p.nC, work);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_pt_b<float2>, perm_grid(work), dim3(kPermThreads), 0, s, tmp, out, t.gposB, t.locB, N, p.C,
-                     p.nC, work);
-  return hipGetLastError();
+hipError_t cseg_fwd(float2* Z, const float2* Dn, long long B, const Geo& g, const char* seg_tab, hipStream_t s) {
+  const bool ok = with_seg_plan(g.L, [&]<class PL>() {
+    hipLaunchKernelGGL(k_cseg_fwd<PL>, seg_grid<PL>(B * (g.R1 * g.R2)), dim3(Seg<PL>::THREADS), 0, s, Z, Dn, B, g,
+                       seg_tab);
+  });
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
-hipError_t cpermute_adjoint(const float2* in, float2* out, float2* tmp, const int* perm, const PermTabs& t,
-                            long long B, long long N, hipStream_t s) {
-  const PermGeo p = perm_geo(N, 2);
-  const long long work = B * p.nC;
-  if (p.nC == 1) {
-    hipLaunchKernelGGL(k_pt_btp<float2>, perm_grid(work), dim3(kPermThreads), 0, s, in, out,
-                       static_cast<const int*>(nullptr), perm, N, p.C, p.nC, work);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(k_pt_btp<float2>, perm_grid(work), dim3(kPermThreads), 0, s, in, tmp, t.gposB, t.locB, N, p.C,
-                     p.nC, work);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_pt_at<float2>, perm_grid(work), dim3(kPermThreads), 0, s, tmp, out, t.srcA, N, p.C, p.nC,
-                     work);
-  return hipGetLastError();
+hipError_t cseg_bwd(float2* Zh, float2* Zg, const float2* Dn, long long B, const Geo& g, float* part,
+                    const char* seg_tab, hipStream_t s) {
+  const int rb = seg_rows(B, g, true);
+  const bool ok = with_seg_plan(g.L, [&]<class PL>() {
+    hipLaunchKernelGGL(k_cseg_bwd<PL>, seg_grid<PL>((B + rb - 1) / rb * (g.R1 * g.R2)), dim3(Seg<PL>::THREADS), 0, s,
+                       Zh, Zg, Dn, B, g, rb, reinterpret_cast<float2*>(part), seg_tab);
+  });
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
-hipError_t cfft_in(const float2* src, const float2* a, float2* stash, float2* Z, long long B, const Geo& g,
-                   const float2* twM, const char* seg_tab, hipStream_t s) {
-  const dim3 block(kThreads);
-  if (g.R1 > 1) {
-    const dim3 grid = grid_for(B * (g.M / g.R1));
-    switch (g.R1) {
-      case 2: hipLaunchKernelGGL(k_cdif_in<2>, grid, block, 0, s, src, a, stash, Z, B, g.M, twM); break;
-      case 4: hipLaunchKernelGGL(k_cdif_in<4>, grid, block, 0, s, src, a, stash, Z, B, g.M, twM); break;
-      case 8: hipLaunchKernelGGL(k_cdif_in<8>, grid, block, 0, s, src, a, stash, Z, B, g.M, twM); break;
-      case 16: hipLaunchKernelGGL(k_cdif_in<16>, grid, block, 0, s, src, a, stash, Z, B, g.M, twM); break;
-      default: return hipErrorInvalidValue;
-    }
-  } else {
-    hipLaunchKernelGGL(k_cscale, grid_for(B * g.M), block, 0, s, src, a, stash, Z, B, g.M);
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (g.R2 > 1 && (e = dif(Z, B, g, g.M / g.R1, g.R2, twM, s)) != hipSuccess) return e;
-  return segments(Z, B * (g.M / g.L), g.L, false, seg_tab, s);
+// Four segment workgroups, two column workgroups on each of 256 CUs.
+int seg_rows(long long B, const Geo& g, bool cplx) {
+  return clamp_rows(B * (g.R1 * g.R2 / (cplx ? 1 : 2)) / 1024);
 }
+int col_rows(long long B, const Geo& g, int ew) { return clamp_rows(B * perm_geo(g, ew).nC / 512); }
 
-hipError_t cifft_out(float2* Z, float2* dst, long long B, const Geo& g, const float2* twM, const char* seg_tab,
-                     hipStream_t s) {
-  hipError_t e = segments(Z, B * (g.M / g.L), g.L, true, seg_tab, s);
-  if (e != hipSuccess) return e;
-  if (g.R2 > 1 && (e = dit(Z, B, g, g.M / g.R1, g.R2, twM, s)) != hipSuccess) return e;
-  const dim3 block(kThreads);
-  if (g.R1 > 1) {
-    const dim3 grid = grid_for(B * (g.M / g.R1));
-    switch (g.R1) {
-      case 2: hipLaunchKernelGGL(k_cdit_out<2>, grid, block, 0, s, Z, dst, B, g.M, twM); break;
-      case 4: hipLaunchKernelGGL(k_cdit_out<4>, grid, block, 0, s, Z, dst, B, g.M, twM); break;
-      case 8: hipLaunchKernelGGL(k_cdit_out<8>, grid, block, 0, s, Z, dst, B, g.M, twM); break;
-      case 16: hipLaunchKernelGGL(k_cdit_out<16>, grid, block, 0, s, Z, dst, B, g.M, twM); break;
-      default: return hipErrorInvalidValue;
-    }
-  } else {
-    hipLaunchKernelGGL(k_ccopy, grid_for(B * g.M), block, 0, s, Z, dst, B * g.M);
-  }
-  return hipGetLastError();
-}
-
-hipError_t cmid_fwd(float2* Z, const float2* d, long long B, const Geo& g, float invN, hipStream_t s) {
-  const long long P = (B + kColRows - 1) / kColRows;
-  hipLaunchKernelGGL(k_cmid_fwd, grid_for(P * g.M), dim3(kThreads), 0, s, Z, d, B, g, invN);
-  return hipGetLastError();
-}
-
-hipError_t cmid_bwd(const float2* Zh, float2* Zg, const float2* d, long long B, const Geo& g, float invN,
-                    float2* part, hipStream_t s) {
-  const long long P = (B + kColRows - 1) / kColRows;
-  hipLaunchKernelGGL(k_cmid_bwd, grid_for(P * g.M), dim3(kThreads), 0, s, Zh, Zg, d, B, g, invN, part);
-  return hipGetLastError();
-}
-
-hipError_t cdA(const float2* gh1, const float2* u, const float2* a, float2* imgA, float2* gu, long long B,
-               long long N, hipStream_t s) {
-  hipLaunchKernelGGL(k_cdA, grid_for(B * N), dim3(kThreads), 0, s, gh1, u, a, imgA, gu, B, N);
-  return hipGetLastError();
-}
-
-hipError_t colsum_parts(const float* part, long long B, long long W, float* out, const QuartetTabs* q,
-                        bool accumulate, hipStream_t s) {
-  const long long P = (B + kColRows - 1) / kColRows;
+hipError_t colsum_parts(const float* part, long long P, long long W, float* out, Order how, const Geo& g,
+                        const QuartetTabs* q, bool accumulate, hipStream_t s) {
+  int T, PT;
+  seg_shape(g.L, T, PT);
   const QuartetTabs qq = q ? *q : QuartetTabs{};
-  hipLaunchKernelGGL(k_colsum2, grid_for(W), dim3(kThreads), 0, s, part, P, W, out, qq, q ? 1 : 0,
-                     accumulate ? 1 : 0);
+  const dim3 grid(unsigned((W / 4 + kSumCols - 1) / kSumCols)), block(kThreads);
+  const int acc = accumulate ? 1 : 0;
+  switch (how) {
+    case Order::natural:
+      hipLaunchKernelGGL(k_colsum2<Order::natural>, grid, block, 0, s, part, P, W, out, g, qq, T, PT, acc);
+      break;
+    case Order::quartets:
+      hipLaunchKernelGGL(k_colsum2<Order::quartets>, grid, block, 0, s, part, P, W, out, g, qq, T, PT, acc);
+      break;
+    case Order::spectrum:
+      hipLaunchKernelGGL(k_colsum2<Order::spectrum>, grid, block, 0, s, part, P, W, out, g, qq, T, PT, acc);
+      break;
+  }
   return hipGetLastError();
 }
 
-hipError_t colsum(const float* img, long long B, long long W, float* part, float* out, const QuartetTabs* q,
-                  bool accumulate, hipStream_t s) {
-  const long long P = (B + kColRows - 1) / kColRows;
-  if (P > 0) {
-    hipLaunchKernelGGL(k_colsum1, grid_for(P * (W / 4)), dim3(kThreads), 0, s, img, B, W, part);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return colsum_parts(part, B, W, out, q, accumulate, s);
+hipError_t colsum(const float* img, long long B, long long W, float* part, float* out, hipStream_t s) {
+  const long long P = (B + kMaxRows - 1) / kMaxRows;
+  hipLaunchKernelGGL(k_colsum1, grid_for(P * (W / 4)), dim3(kThreads), 0, s, img, B, W, part);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  Geo g{W / 2, 4096, 2, 1};
+  return colsum_parts(part, P, W, out, Order::natural, g, nullptr, false, s);
+}
+
+bool build_seg_table(int L, std::vector<unsigned char>& host) {
+  bool ok = false;
+  (void)with_seg_plan(L, [&]<class PL>() { ok = build_complex_tables<PL>(host); });
+  return ok;
 }
 
 }  // namespace mp

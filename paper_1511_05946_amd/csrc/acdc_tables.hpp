@@ -112,32 +112,43 @@ inline bool build_real_tables(std::vector<unsigned char>& buf) {
   return true;
 }
 
-// Tables of the multi-pass path for a power-of-two width N (M = N/2):
-// W_M^e for e < M (DIF/DIT twiddles), then the quartet tables indexed by
-// quartet e < M/2 (e = 0: the self-paired quartet, else spectrum index e).
+// Tables of the multi-pass path for a power-of-two width N (M = N/2 = R1 R2
+// L): the twiddles of the first DIF pass, W_M^(n r) at [r-1][n] (r < R1, n <
+// M/R1), and of the second, W_(M/R1)^(n r) at [r-1][n] (r < R2, n < L), so
+// that neighbouring butterflies read neighbouring entries; then the quartet
+// tables indexed by quartet e < M/2 (e = 0: the self-paired quartet, else
+// spectrum index e).
 struct MpTableLayout {
-  size_t tw = 0, mk0 = 0, mk1 = 0, qidx = 0, qmask = 0, bytes = 0;
+  size_t tw1 = 0, tw2 = 0, mk0 = 0, mk1 = 0, qidx = 0, qmask = 0, bytes = 0;
 };
-inline MpTableLayout mp_table_layout(long long N) {
+inline MpTableLayout mp_table_layout(long long N, int R1, int R2, int L) {
   const size_t M = size_t(N / 2), NQ = M / 2;
   MpTableLayout l;
-  l.tw = 0;
-  l.mk0 = M * sizeof(float2);
+  l.tw1 = 0;
+  l.tw2 = size_t(R1 - 1) * (M / R1) * sizeof(float2);
+  l.mk0 = l.tw2 + size_t(R2 - 1) * L * sizeof(float2);
   l.mk1 = l.mk0 + NQ * sizeof(float4);
   l.qidx = l.mk1 + NQ * sizeof(float4);
   l.qmask = l.qidx + NQ * sizeof(int4);
   l.bytes = l.qmask + NQ * sizeof(int);
   return l;
 }
-inline bool build_mp_tables(int N, std::vector<unsigned char>& buf) {
-  const int M = N / 2, NQ = M / 2;
-  const MpTableLayout l = mp_table_layout(N);
+inline bool build_mp_tables(int N, int R1, int R2, int L, std::vector<unsigned char>& buf) {
+  const int M = N / 2, NQ = M / 2, Q = M / R1;
+  const MpTableLayout l = mp_table_layout(N, R1, R2, L);
   buf.assign(l.bytes, 0);
-  float2* tw = reinterpret_cast<float2*>(buf.data() + l.tw);
-  for (int e = 0; e < M; ++e) {
-    const HostC w = w_pow(e, M);
-    tw[e] = make_float2(float(w.re), float(w.im));
-  }
+  float2* tw = reinterpret_cast<float2*>(buf.data() + l.tw1);
+  for (int r = 1; r < R1; ++r)
+    for (int n = 0; n < Q; ++n) {
+      const HostC w = w_pow((long long)n * r, M);
+      tw[(long long)(r - 1) * Q + n] = make_float2(float(w.re), float(w.im));
+    }
+  tw = reinterpret_cast<float2*>(buf.data() + l.tw2);
+  for (int r = 1; r < R2; ++r)
+    for (int n = 0; n < L; ++n) {
+      const HostC w = w_pow((long long)n * r, Q);
+      tw[(long long)(r - 1) * L + n] = make_float2(float(w.re), float(w.im));
+    }
   float4* mk0 = reinterpret_cast<float4*>(buf.data() + l.mk0);
   float4* mk1 = reinterpret_cast<float4*>(buf.data() + l.mk1);
   int4* qidx = reinterpret_cast<int4*>(buf.data() + l.qidx);
