@@ -609,7 +609,7 @@ int launch_cplx_fwd(const CplxArgs& a, hipStream_t s) {
 struct MpTabs {
   const float2 *tw1 = nullptr, *tw2 = nullptr;
   QuartetTabs q{};
-  const char* seg = nullptr;  // the segment plan's table
+  const char *seg_f = nullptr, *seg = nullptr;  // the segment plans' tables: forward launches, others
 };
 std::map<std::pair<int, int>, void*> g_mp_tables;  // (device, N) -> device table
 
@@ -640,17 +640,21 @@ int get_mp_tables(int N, MpTabs* out) {
   const hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e);
   const mp::Geo g = mp::geo(N);
-  void *seg = nullptr, *d = nullptr;
-  // third key value 2: segment plans (0 real, 1 complex rows)
-  int rc = device_table(g_tables, std::make_tuple(dev, g.L, 2),
-                        [&](std::vector<unsigned char>& h) { return mp::build_seg_table(g.L, h); }, &seg);
-  if (rc != ACDC_OK) return rc;
+  void *seg[2] = {}, *d = nullptr;
+  int rc = ACDC_OK;
+  for (int fwd = 0; fwd < 2; ++fwd) {
+    // third key values 2 and 3: segment plans (0 real, 1 complex rows)
+    rc = device_table(g_tables, std::make_tuple(dev, g.L, 2 + fwd),
+                      [&](std::vector<unsigned char>& h) { return mp::build_seg_table(g.L, fwd != 0, h); }, &seg[fwd]);
+    if (rc != ACDC_OK) return rc;
+  }
   rc = device_table(g_mp_tables, std::make_pair(dev, N),
                     [&](std::vector<unsigned char>& h) { return build_mp_tables(N, g.R1, g.R2, g.L, h); }, &d);
   if (rc != ACDC_OK) return rc;
   const char* base = static_cast<const char*>(d);
   const MpTableLayout l = mp_table_layout(N, g.R1, g.R2, g.L);
-  out->seg = static_cast<const char*>(seg);
+  out->seg = static_cast<const char*>(seg[0]);
+  out->seg_f = static_cast<const char*>(seg[1]);
   out->tw1 = reinterpret_cast<const float2*>(base + l.tw1);
   out->tw2 = reinterpret_cast<const float2*>(base + l.tw2);
   const double qb = 1.0 / (2.0 * std::sqrt(double(N)));
@@ -807,8 +811,8 @@ struct MpCall {
   hipError_t forward_middle(float2* Z, int k) const {
     hipError_t e = mp::dif2(Z, B, g, t.tw2, s);
     if (e != hipSuccess) return e;
-    e = cplx ? mp::cseg_fwd(Z, coef + (long long)k * N, B, g, t.seg, s)
-             : mp::seg_fwd(Z, mq(k), B, g, bias, t.seg, s);
+    e = cplx ? mp::cseg_fwd(Z, coef + (long long)k * N, B, g, t.seg_f, s)
+             : mp::seg_fwd(Z, mq(k), B, g, bias, t.seg_f, s);
     return e != hipSuccess ? e : mp::dit2(Z, B, g, t.tw2, s);
   }
 };

@@ -89,6 +89,16 @@ struct GView {
     return v;
 #endif
   }
+  // zero-extended 16-bit entry
+  __host__ __device__ __forceinline__ unsigned ldu16(unsigned voff, unsigned soff) const {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, 0);
+#else
+    unsigned short v;
+    std::memcpy(&v, p + voff + soff, 2);
+    return v;
+#endif
+  }
   // 16 bytes per lane straight into LDS (buffer_load_dwordx4 ... lds): lane
   // l's bytes land at lds + 16 l, with lds the same for the whole wave.  No
   // register holds the data; the wave's vmcnt covers the copy.  The load is

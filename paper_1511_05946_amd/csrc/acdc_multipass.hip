@@ -46,20 +46,24 @@ __device__ __forceinline__ float4 relu4(float4 h) { return make_float4(relu1(h.x
 
 // ------------------------------------------------------------ permutations
 
-// Set and local position of row element i, and the element at local
-// position l of set d.
+constexpr int log2_chunk = ilog2(kPermChunk);
+
+// Set of row element i and its place in the LDS image of a column launch
+// (chunk or element js of column col at js W + col, W columns for a whole
+// set's), and the element at local position l of set d.
 __device__ __forceinline__ void part_of(const PermGeo& p, long long i, int& d, int& l) {
+  const int lW = p.lw + (log2_chunk - p.lC) + (p.ew == 1 ? 0 : -1);
   const long long Q = 1LL << p.lQ;
   if (p.ew == 1) {
     const long long q = i >> 2, j = q >> p.lQ, n = q & (Q - 1);
     const int side = n >= Q / 2 ? 1 : 0;
     const long long col = side ? Q - 1 - n : n;
     d = int(col >> p.lw);
-    l = int(((((2 * j + side) << p.lw) + (col & ((1 << p.lw) - 1))) << 2) + (i & 3));
+    l = int(((((2 * j + side) << lW) + (col & ((1 << p.lw) - 1))) << 2) + (i & 3));
   } else {
     const long long j = i >> p.lQ, n = i & (Q - 1);
     d = int(n >> p.lw);
-    l = int((j << p.lw) + (n & ((1 << p.lw) - 1)));
+    l = int((j << lW) + (n & ((1 << p.lw) - 1)));
   }
 }
 __device__ __forceinline__ long long elem_of(const PermGeo& p, int d, int l) {
@@ -167,6 +171,14 @@ __global__ __launch_bounds__(kThreads) void k_pt_place(const int* __restrict__ s
   item[((long long)c << pg.lC) + ((start[d * nC + c] + p) & mask)] = (unsigned(ls) << 8) | unsigned(d);
 }
 
+// A value the compiler takes as new each time: offsets built from it keep the
+// loads of per-layer tables inside a loop over rows.  Hoisted out of it, the
+// quartet coefficients of a thread alone would be 96 registers.
+__device__ __forceinline__ unsigned fresh(unsigned v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 // ----------------------------------------------------------------- columns
 
 struct ColArgs {
@@ -186,21 +198,18 @@ struct ColArgs {
   PermGeo pg;
 };
 
-// Loads in flight per thread where a thread follows a table: each waits for
-// its table entry, so one at a time would be bound by memory latency.
-constexpr int kBatch = 8;
-
-// f(i) for the entries i of one set's list that this thread takes: first
-// get(i) for a batch, then put(i, value) for it.
-template <int THREADS, class T, class Get, class Put>
+// The entries i of one set's list that this thread takes, BATCH of them at a
+// time: get(i) for all, then put(i, value).  A thread follows a table to HBM,
+// so one load at a time would be bound by memory latency.
+template <int THREADS, int BATCH, class T, class Get, class Put>
 __device__ __forceinline__ void for_entries(int C, Get&& get, Put&& put) {
-  if (C % (THREADS * kBatch) == 0) {
-    for (int i0 = threadIdx.x; i0 < C; i0 += THREADS * kBatch) {
-      T v[kBatch];
+  if (C % (THREADS * BATCH) == 0) {
+    for (int i0 = threadIdx.x; i0 < C; i0 += THREADS * BATCH) {
+      T v[BATCH];
 #pragma unroll
-      for (int q = 0; q < kBatch; ++q) v[q] = get(i0 + q * THREADS);
+      for (int q = 0; q < BATCH; ++q) v[q] = get(i0 + q * THREADS);
 #pragma unroll
-      for (int q = 0; q < kBatch; ++q) put(i0 + q * THREADS, v[q]);
+      for (int q = 0; q < BATCH; ++q) put(i0 + q * THREADS, v[q]);
     }
   } else {
     for (int i = threadIdx.x; i < C; i += THREADS) put(i, get(i));
@@ -221,6 +230,11 @@ constexpr bool needs_lds() {
   return SRC == Src::gather || SRC == Src::scatter || SINK == Sink::send || SINK == Sink::ret;
 }
 
+// Row accesses go through views (one 32-bit lane offset, the part that is
+// the same for all lanes in a scalar): written as 64-bit addresses per
+// access, the addresses alone took the registers of a second workgroup per
+// CU.  Fences bound what is in flight at once for the same reason.
+
 // Real rows.  A thread holds CI column pairs, R float4 chunks each: ha[j]
 // is chunk n + jQ, hb[j] chunk (Q-1-n) + jQ.  512 threads at R <= 8 (four
 // waves per SIMD with two workgroups a CU); at R = 16 a pair is 64 values
@@ -229,19 +243,26 @@ template <int R>
 constexpr int col_threads() {
   return R <= 8 ? 512 : 256;
 }
+template <int R>
+constexpr int col_waves() {
+  return R <= 8 ? 4 : 2;
+}
 
-// DWELL: rb rows in turn (the backward's image sums)
 template <int R, Src SRC, Sink SINK, bool BWD>
-__global__ __launch_bounds__(col_threads<R>()) void k_cols(ColArgs A) {
+__global__ __launch_bounds__(col_threads<R>())
+__attribute__((amdgpu_waves_per_eu(col_waves<R>()))) void k_cols(ColArgs A) {
   constexpr int THREADS = col_threads<R>(), H = R / 2;
   constexpr int CI = kPermChunk / 4 / (R * THREADS);
-  static_assert(CI >= 1 && CI * R * THREADS * 4 == kPermChunk, "a set's chunks over the threads");
+  constexpr int W = kPermChunk / 4 / R;  // LDS: chunk js of column col at js W + col
+  constexpr unsigned kMask = kPermChunk - 1;
+  static_assert(CI >= 1 && CI * THREADS == W, "a set's chunks over the threads");
   __shared__ float4 lds4[needs_lds<SRC, SINK>() ? kPermChunk / 4 : 1];
   __shared__ int dl[kPermMaxChunks];
   float* lds = reinterpret_cast<float*>(lds4);
   const PermGeo pg = A.pg;
-  const int C = 1 << pg.lC, w = 1 << pg.lw, mask = C - 1;
-  const long long M = A.M, N = 2 * M, Q = 1LL << pg.lQ;
+  const int C = 1 << pg.lC, w = 1 << pg.lw;
+  const long long M = A.M, N = 2 * M;
+  const unsigned Q = 1u << pg.lQ;
   const int c = int(blockIdx.x % unsigned(pg.nC));
   const long long p = blockIdx.x / unsigned(pg.nC);
   if constexpr (SRC == Src::scatter || SINK == Sink::send) {
@@ -249,7 +270,8 @@ __global__ __launch_bounds__(col_threads<R>()) void k_cols(ColArgs A) {
     __syncthreads();
   }
   const unsigned* item = A.item + ((long long)c << pg.lC);
-  const ushort4* loc4 = reinterpret_cast<const ushort4*>(A.loc + ((long long)c << pg.lC));
+  const GView loc = GView::of(A.loc + ((long long)c << pg.lC)), tw = GView::of(A.tw), av = GView::of(A.a);
+  const unsigned sq16 = 16u << pg.lQ, sq8 = 8u << pg.lQ;  // bytes of Q chunks, of Q spectrum values
   float4 ha[CI][H], hb[CI][H], sa[CI][H], sb[CI][H];
   if constexpr (BWD) {
 #pragma unroll
@@ -263,72 +285,75 @@ __global__ __launch_bounds__(col_threads<R>()) void k_cols(ColArgs A) {
     for (int ci = 0; ci < CI; ++ci) {
       const int col = int(threadIdx.x) + ci * THREADS;
       if (col < w) {
-        const long long n = ((long long)c << pg.lw) + col;
+        const unsigned n = fresh((unsigned(c) << pg.lw) + unsigned(col));
         f(ci, col, n, Q - 1 - n);
+        ACDC_SCHED_FENCE();
       }
     }
   };
   const long long b0 = p * A.rb, b1 = b0 + A.rb < A.B ? b0 + A.rb : A.B;
   for (long long b = b0; b < b1; ++b) {
+    const GView z = GView::of(A.Z + b * M);
     if constexpr (SRC == Src::rows) {
-      const float4* row4 = reinterpret_cast<const float4*>(A.src + b * N);
-      pairs([&](int ci, int, long long n, long long nb) {
+      const GView row = GView::of(A.src + b * N);
+      pairs([&](int ci, int, unsigned n, unsigned nb) {
 #pragma unroll
         for (int j = 0; j < H; ++j) {
-          ha[ci][j] = row4[n + j * Q];
-          hb[ci][j] = row4[nb + j * Q];
+          ha[ci][j] = row.ld4(n * 16u, j * sq16);
+          hb[ci][j] = row.ld4(nb * 16u, j * sq16);
         }
       });
     } else if constexpr (SRC == Src::gather) {
       const float4* t4 = reinterpret_cast<const float4*>(A.src + b * N + ((long long)c << pg.lC));
-      for_entries<THREADS, float4>(
+      for_entries<THREADS, 8, float4>(
           C / 4, [&](int i) { return t4[i]; }, [&](int i, float4 v) { lds4[i] = v; });
       __syncthreads();
-      pairs([&](int ci, int col, long long, long long) {
-        auto at = [&](int l4) {
-          const ushort4 s = loc4[l4];
-          return make_float4(lds[s.x & mask], lds[s.y & mask], lds[s.z & mask], lds[s.w & mask]);
+      pairs([&](int ci, int col, unsigned, unsigned) {
+        auto at = [&](int js) {
+          const int2 s = loc.ldi2(unsigned(col) * 8u, unsigned(js << pg.lw) * 8u);
+          return make_float4(lds[unsigned(s.x) & kMask], lds[(unsigned(s.x) >> 16) & kMask],
+                             lds[unsigned(s.y) & kMask], lds[(unsigned(s.y) >> 16) & kMask]);
         };
 #pragma unroll
         for (int j = 0; j < H; ++j) {
-          ha[ci][j] = at(((2 * j) << pg.lw) + col);
-          hb[ci][j] = at(((2 * j + 1) << pg.lw) + col);
+          ha[ci][j] = at(2 * j);
+          hb[ci][j] = at(2 * j + 1);
         }
       });
       if (b + 1 < b1) __syncthreads();
     } else if constexpr (SRC == Src::scatter) {
       const float* trow = A.src + b * N;
-      for_entries<THREADS, Entry<float>>(
+      const unsigned nm = unsigned(N - 1);
+      for_entries<THREADS, 16, Entry<float>>(
           C,
           [&](int i) {
             const unsigned it = item[i];
-            return Entry<float>{it, trow[(i + dl[it & 255]) & (N - 1)]};
+            return Entry<float>{it, trow[unsigned(i + dl[it & 255]) & nm]};
           },
-          [&](int, const Entry<float>& e) { lds[(e.it >> 8) & mask] = e.v; });
+          [&](int, const Entry<float>& e) { lds[(e.it >> 8) & kMask] = e.v; });
       __syncthreads();
-      pairs([&](int ci, int col, long long, long long) {
+      pairs([&](int ci, int col, unsigned, unsigned) {
 #pragma unroll
         for (int j = 0; j < H; ++j) {
-          ha[ci][j] = lds4[((2 * j) << pg.lw) + col];
-          hb[ci][j] = lds4[((2 * j + 1) << pg.lw) + col];
+          ha[ci][j] = lds4[(2 * j) * W + col];
+          hb[ci][j] = lds4[(2 * j + 1) * W + col];
         }
       });
       if (b + 1 < b1) __syncthreads();
     } else {
-      const float2* zrow = A.Z + b * M;
-      pairs([&](int ci, int, long long n, long long nb) {
+      pairs([&](int ci, int, unsigned n, unsigned nb) {
         float2 y[R], yb[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          y[r] = zrow[(r << pg.lQ) + n];
-          yb[r] = zrow[(r << pg.lQ) + nb];
+          y[r] = z.ld2(n * 8u, r * sq8);
+          yb[r] = z.ld2(nb * 8u, r * sq8);
         }
 #pragma unroll
-        for (int r = 1; r < R; ++r) {
-          y[r] = cmulc(y[r], A.tw[((r - 1) << pg.lQ) + n]);
-          yb[r] = cmulc(yb[r], A.tw[((r - 1) << pg.lQ) + nb]);
-        }
+        for (int r = 1; r < R; ++r) y[r] = cmulc(y[r], tw.ld2(n * 8u, (r - 1) * sq8));
         Dft<R, true>::run(y);
+        if constexpr (R > 8) ACDC_SCHED_FENCE();
+#pragma unroll
+        for (int r = 1; r < R; ++r) yb[r] = cmulc(yb[r], tw.ld2(nb * 8u, (r - 1) * sq8));
         Dft<R, true>::run(yb);
 #pragma unroll
         for (int j = 0; j < H; ++j) {
@@ -338,7 +363,7 @@ __global__ __launch_bounds__(col_threads<R>()) void k_cols(ColArgs A) {
       });
       if constexpr (!BWD) {
         if (A.relu) {
-          pairs([&](int ci, int, long long, long long) {
+          pairs([&](int ci, int, unsigned, unsigned) {
 #pragma unroll
             for (int j = 0; j < H; ++j) {
               ha[ci][j] = relu4(ha[ci][j]);
@@ -349,81 +374,80 @@ __global__ __launch_bounds__(col_threads<R>()) void k_cols(ColArgs A) {
       }
     }
     if constexpr (BWD) {
-      const float4* u4 = reinterpret_cast<const float4*>(A.u + b * N);
-      const float4* a4 = reinterpret_cast<const float4*>(A.a);
+      const GView uv = GView::of(A.u + b * N);
       // u = 0 exactly where the mask is off, so masking g first leaves u * g unchanged
-      auto one = [&](float4& g, float4& s, float4 u, float4 av) {
+      auto one = [&](float4& g, float4& s, float4 u, float4 a) {
         if (A.relu)
           g = make_float4(u.x > 0.f ? g.x : 0.f, u.y > 0.f ? g.y : 0.f, u.z > 0.f ? g.z : 0.f, u.w > 0.f ? g.w : 0.f);
         s = make_float4(s.x + u.x * g.x, s.y + u.y * g.y, s.z + u.z * g.z, s.w + u.w * g.w);
-        g = scale4(g, av);
+        g = scale4(g, a);
       };
-      pairs([&](int ci, int, long long n, long long nb) {
+      pairs([&](int ci, int, unsigned n, unsigned nb) {
 #pragma unroll
-        for (int j = 0; j < H; ++j) {
-          one(ha[ci][j], sa[ci][j], u4[n + j * Q], a4[n + j * Q]);
-          one(hb[ci][j], sb[ci][j], u4[nb + j * Q], a4[nb + j * Q]);
-        }
+        for (int j = 0; j < H; ++j) one(ha[ci][j], sa[ci][j], uv.ld4(n * 16u, j * sq16), av.ld4(n * 16u, j * sq16));
+        ACDC_SCHED_FENCE();
+#pragma unroll
+        for (int j = 0; j < H; ++j) one(hb[ci][j], sb[ci][j], uv.ld4(nb * 16u, j * sq16), av.ld4(nb * 16u, j * sq16));
       });
     }
     if constexpr (SINK == Sink::dif && !BWD) {
       if (A.stash != nullptr) {
-        float4* st4 = reinterpret_cast<float4*>(A.stash + b * N);
-        pairs([&](int ci, int, long long n, long long nb) {
+        const GView st = GView::of(A.stash + b * N);
+        pairs([&](int ci, int, unsigned n, unsigned nb) {
 #pragma unroll
           for (int j = 0; j < H; ++j) {
-            st4[n + j * Q] = ha[ci][j];
-            st4[nb + j * Q] = hb[ci][j];
+            st.st4(ha[ci][j], n * 16u, j * sq16);
+            st.st4(hb[ci][j], nb * 16u, j * sq16);
           }
         });
       }
       if (A.a != nullptr) {
-        const float4* a4 = reinterpret_cast<const float4*>(A.a);
-        pairs([&](int ci, int, long long n, long long nb) {
+        pairs([&](int ci, int, unsigned n, unsigned nb) {
 #pragma unroll
           for (int j = 0; j < H; ++j) {
-            ha[ci][j] = scale4(ha[ci][j], a4[n + j * Q]);
-            hb[ci][j] = scale4(hb[ci][j], a4[nb + j * Q]);
+            ha[ci][j] = scale4(ha[ci][j], av.ld4(n * 16u, j * sq16));
+            hb[ci][j] = scale4(hb[ci][j], av.ld4(nb * 16u, j * sq16));
           }
         });
       }
     }
     if constexpr (SINK == Sink::rows) {
-      float4* out4 = reinterpret_cast<float4*>(A.dst + b * N);
-      pairs([&](int ci, int, long long n, long long nb) {
+      const GView out = GView::of(A.dst + b * N);
+      pairs([&](int ci, int, unsigned n, unsigned nb) {
 #pragma unroll
         for (int j = 0; j < H; ++j) {
-          out4[n + j * Q] = ha[ci][j];
-          out4[nb + j * Q] = hb[ci][j];
+          out.st4(ha[ci][j], n * 16u, j * sq16);
+          out.st4(hb[ci][j], nb * 16u, j * sq16);
         }
       });
     } else if constexpr (SINK == Sink::send) {
-      pairs([&](int ci, int col, long long, long long) {
+      pairs([&](int ci, int col, unsigned, unsigned) {
 #pragma unroll
         for (int j = 0; j < H; ++j) {
-          lds4[((2 * j) << pg.lw) + col] = ha[ci][j];
-          lds4[((2 * j + 1) << pg.lw) + col] = hb[ci][j];
+          lds4[(2 * j) * W + col] = ha[ci][j];
+          lds4[(2 * j + 1) * W + col] = hb[ci][j];
         }
       });
       __syncthreads();
       float* trow = A.dst + b * N;
-      for_entries<THREADS, unsigned>(
+      const unsigned nm = unsigned(N - 1);
+      for_entries<THREADS, 8, unsigned>(
           C, [&](int i) { return item[i]; },
-          [&](int i, unsigned it) { trow[(i + dl[it & 255]) & (N - 1)] = lds[(it >> 8) & mask]; });
+          [&](int i, unsigned it) { trow[unsigned(i + dl[it & 255]) & nm] = lds[(it >> 8) & kMask]; });
       if (b + 1 < b1) __syncthreads();
     } else if constexpr (SINK == Sink::ret) {
-      pairs([&](int ci, int col, long long, long long) {
-        auto put = [&](int l4, float4 h) {
-          const ushort4 s = loc4[l4];
-          lds[s.x & mask] = h.x;
-          lds[s.y & mask] = h.y;
-          lds[s.z & mask] = h.z;
-          lds[s.w & mask] = h.w;
+      pairs([&](int ci, int col, unsigned, unsigned) {
+        auto put = [&](int js, float4 h) {
+          const int2 s = loc.ldi2(unsigned(col) * 8u, unsigned(js << pg.lw) * 8u);
+          lds[unsigned(s.x) & kMask] = h.x;
+          lds[(unsigned(s.x) >> 16) & kMask] = h.y;
+          lds[unsigned(s.y) & kMask] = h.z;
+          lds[(unsigned(s.y) >> 16) & kMask] = h.w;
         };
 #pragma unroll
         for (int j = 0; j < H; ++j) {
-          put(((2 * j) << pg.lw) + col, ha[ci][j]);
-          put(((2 * j + 1) << pg.lw) + col, hb[ci][j]);
+          put(2 * j, ha[ci][j]);
+          put(2 * j + 1, hb[ci][j]);
         }
       });
       __syncthreads();
@@ -431,38 +455,35 @@ __global__ __launch_bounds__(col_threads<R>()) void k_cols(ColArgs A) {
       for (int i = threadIdx.x; i < C / 4; i += THREADS) t4[i] = lds4[i];
       if (b + 1 < b1) __syncthreads();
     } else {
-      float2* zrow = A.Z + b * M;
-      pairs([&](int ci, int, long long n, long long nb) {
-        float2 x[R], xb[R];
+      pairs([&](int ci, int, unsigned n, unsigned nb) {
+        float2 x[R];
+        // one butterfly of the pair: FIRST the one of column n
+        auto bfly = [&](auto first, unsigned at) {
+          constexpr bool kFirst = decltype(first)::value;
 #pragma unroll
-        for (int j = 0; j < H; ++j) {
-          x[j] = chunk_even(ha[ci][j]);
-          xb[R - 1 - j] = chunk_odd(ha[ci][j]);
-          xb[j] = chunk_even(hb[ci][j]);
-          x[R - 1 - j] = chunk_odd(hb[ci][j]);
-        }
-        Dft<R, false>::run(x);
-        Dft<R, false>::run(xb);
+          for (int j = 0; j < H; ++j) {
+            x[j] = chunk_even(kFirst ? ha[ci][j] : hb[ci][j]);
+            x[R - 1 - j] = chunk_odd(kFirst ? hb[ci][j] : ha[ci][j]);
+          }
+          Dft<R, false>::run(x);
 #pragma unroll
-        for (int r = 1; r < R; ++r) {
-          x[r] = cmul(x[r], A.tw[((r - 1) << pg.lQ) + n]);
-          xb[r] = cmul(xb[r], A.tw[((r - 1) << pg.lQ) + nb]);
-        }
+          for (int r = 1; r < R; ++r) x[r] = cmul(x[r], tw.ld2(at * 8u, (r - 1) * sq8));
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          zrow[(r << pg.lQ) + n] = x[r];
-          zrow[(r << pg.lQ) + nb] = xb[r];
-        }
+          for (int r = 0; r < R; ++r) z.st2(x[r], at * 8u, r * sq8);
+        };
+        bfly(std::true_type{}, n);
+        ACDC_SCHED_FENCE();
+        bfly(std::false_type{}, nb);
       });
     }
   }
   if constexpr (BWD) {
-    float4* out4 = reinterpret_cast<float4*>(A.part + p * N);
-    pairs([&](int ci, int, long long n, long long nb) {
+    const GView out = GView::of(A.part + p * N);
+    pairs([&](int ci, int, unsigned n, unsigned nb) {
 #pragma unroll
       for (int j = 0; j < H; ++j) {
-        out4[n + j * Q] = sa[ci][j];
-        out4[nb + j * Q] = sb[ci][j];
+        out.st4(sa[ci][j], n * 16u, j * sq16);
+        out.st4(sb[ci][j], nb * 16u, j * sq16);
       }
     });
   }
@@ -471,16 +492,17 @@ __global__ __launch_bounds__(col_threads<R>()) void k_cols(ColArgs A) {
 // Complex rows: columns n, elements n + jQ.  Images gh1 * conj(u), and
 // dL/du = gh1 * conj(a).
 template <int R, Src SRC, Sink SINK, bool BWD>
-__global__ __launch_bounds__(512) void k_ccols(ColArgs A) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_ccols(ColArgs A) {
   constexpr int THREADS = 512, EC = kPermChunk / 2;  // elements of a whole set
-  constexpr int CI = EC / (R * THREADS);
-  static_assert(CI >= 1 && CI * R * THREADS == EC, "a set's elements over the threads");
+  constexpr int CI = EC / (R * THREADS), W = EC / R;
+  constexpr unsigned kMask = EC - 1;
+  static_assert(CI >= 1 && CI * THREADS == W, "a set's elements over the threads");
   __shared__ float4 lds4[needs_lds<SRC, SINK>() ? kPermChunk / 4 : 1];
   __shared__ int dl[kPermMaxChunks];
   float2* lds = reinterpret_cast<float2*>(lds4);
   const PermGeo pg = A.pg;
-  const int C = 1 << pg.lC, w = 1 << pg.lw, mask = C - 1;
-  const long long M = A.M, Q = 1LL << pg.lQ;
+  const int C = 1 << pg.lC, w = 1 << pg.lw;
+  const long long M = A.M;
   const int c = int(blockIdx.x % unsigned(pg.nC));
   const long long p = blockIdx.x / unsigned(pg.nC);
   if constexpr (SRC == Src::scatter || SINK == Sink::send) {
@@ -488,8 +510,8 @@ __global__ __launch_bounds__(512) void k_ccols(ColArgs A) {
     __syncthreads();
   }
   const unsigned* item = A.item + ((long long)c << pg.lC);
-  const unsigned short* loc = A.loc + ((long long)c << pg.lC);
-  const float2* a2 = reinterpret_cast<const float2*>(A.a);
+  const GView loc = GView::of(A.loc + ((long long)c << pg.lC)), tw = GView::of(A.tw), av = GView::of(A.a);
+  const unsigned sq8 = 8u << pg.lQ, nm = unsigned(M - 1);
   float2 h[CI][R], s[CI][R];
   if constexpr (BWD) {
 #pragma unroll
@@ -501,126 +523,129 @@ __global__ __launch_bounds__(512) void k_ccols(ColArgs A) {
 #pragma unroll
     for (int ci = 0; ci < CI; ++ci) {
       const int col = int(threadIdx.x) + ci * THREADS;
-      if (col < w) f(ci, col, ((long long)c << pg.lw) + col);
+      if (col < w) {
+        f(ci, col, fresh(((unsigned(c) << pg.lw) + unsigned(col)) * 8u));
+        ACDC_SCHED_FENCE();
+      }
     }
   };
   const long long b0 = p * A.rb, b1 = b0 + A.rb < A.B ? b0 + A.rb : A.B;
   for (long long b = b0; b < b1; ++b) {
+    const GView z = GView::of(A.Z + b * M);
     if constexpr (SRC == Src::rows) {
-      const float2* row = reinterpret_cast<const float2*>(A.src) + b * M;
-      columns([&](int ci, int, long long n) {
+      const GView row = GView::of(A.src + 2 * b * M);
+      columns([&](int ci, int, unsigned n8) {
 #pragma unroll
-        for (int j = 0; j < R; ++j) h[ci][j] = row[n + j * Q];
+        for (int j = 0; j < R; ++j) h[ci][j] = row.ld2(n8, j * sq8);
       });
     } else if constexpr (SRC == Src::gather) {
       const float4* t4 = reinterpret_cast<const float4*>(A.src + 2 * (b * M + ((long long)c << pg.lC)));
-      for_entries<THREADS, float4>(
+      for_entries<THREADS, 8, float4>(
           C / 2, [&](int i) { return t4[i]; }, [&](int i, float4 v) { lds4[i] = v; });
       __syncthreads();
-      columns([&](int ci, int col, long long) {
+      columns([&](int ci, int col, unsigned) {
 #pragma unroll
-        for (int j = 0; j < R; ++j) h[ci][j] = lds[loc[(j << pg.lw) + col] & mask];
+        for (int j = 0; j < R; ++j) h[ci][j] = lds[loc.ldu16(unsigned(col) * 2u, unsigned(j << pg.lw) * 2u) & kMask];
       });
       if (b + 1 < b1) __syncthreads();
     } else if constexpr (SRC == Src::scatter) {
       const float2* trow = reinterpret_cast<const float2*>(A.src) + b * M;
-      for_entries<THREADS, Entry<float2>>(
+      for_entries<THREADS, 16, Entry<float2>>(
           C,
           [&](int i) {
             const unsigned it = item[i];
-            return Entry<float2>{it, trow[(i + dl[it & 255]) & (M - 1)]};
+            return Entry<float2>{it, trow[unsigned(i + dl[it & 255]) & nm]};
           },
-          [&](int, const Entry<float2>& e) { lds[(e.it >> 8) & mask] = e.v; });
+          [&](int, const Entry<float2>& e) { lds[(e.it >> 8) & kMask] = e.v; });
       __syncthreads();
-      columns([&](int ci, int col, long long) {
+      columns([&](int ci, int col, unsigned) {
 #pragma unroll
-        for (int j = 0; j < R; ++j) h[ci][j] = lds[(j << pg.lw) + col];
+        for (int j = 0; j < R; ++j) h[ci][j] = lds[j * W + col];
       });
       if (b + 1 < b1) __syncthreads();
     } else {
-      const float2* zrow = A.Z + b * M;
-      columns([&](int ci, int, long long n) {
+      columns([&](int ci, int, unsigned n8) {
         float2 y[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) y[r] = zrow[(r << pg.lQ) + n];
+        for (int r = 0; r < R; ++r) y[r] = z.ld2(n8, r * sq8);
 #pragma unroll
-        for (int r = 1; r < R; ++r) y[r] = cmulc(y[r], A.tw[((r - 1) << pg.lQ) + n]);
+        for (int r = 1; r < R; ++r) y[r] = cmulc(y[r], tw.ld2(n8, (r - 1) * sq8));
         Dft<R, true>::run(y);
 #pragma unroll
         for (int j = 0; j < R; ++j) h[ci][j] = y[j];
       });
     }
     if constexpr (BWD) {
-      const float2* u2 = reinterpret_cast<const float2*>(A.u) + b * M;
-      columns([&](int ci, int, long long n) {
+      const GView uv = GView::of(A.u + 2 * b * M);
+      columns([&](int ci, int, unsigned n8) {
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-          const float2 img = cmulc(h[ci][j], u2[n + j * Q]);
+          if (j == R / 2) ACDC_SCHED_FENCE();
+          const float2 img = cmulc(h[ci][j], uv.ld2(n8, j * sq8));
           s[ci][j] = make_float2(s[ci][j].x + img.x, s[ci][j].y + img.y);
-          h[ci][j] = cmulc(h[ci][j], a2[n + j * Q]);
+          h[ci][j] = cmulc(h[ci][j], av.ld2(n8, j * sq8));
         }
       });
     }
     if constexpr (SINK == Sink::dif && !BWD) {
       if (A.stash != nullptr) {
-        float2* st = reinterpret_cast<float2*>(A.stash) + b * M;
-        columns([&](int ci, int, long long n) {
+        const GView st = GView::of(A.stash + 2 * b * M);
+        columns([&](int ci, int, unsigned n8) {
 #pragma unroll
-          for (int j = 0; j < R; ++j) st[n + j * Q] = h[ci][j];
+          for (int j = 0; j < R; ++j) st.st2(h[ci][j], n8, j * sq8);
         });
       }
       if (A.a != nullptr) {
-        columns([&](int ci, int, long long n) {
+        columns([&](int ci, int, unsigned n8) {
 #pragma unroll
-          for (int j = 0; j < R; ++j) h[ci][j] = cmul(h[ci][j], a2[n + j * Q]);
+          for (int j = 0; j < R; ++j) h[ci][j] = cmul(h[ci][j], av.ld2(n8, j * sq8));
         });
       }
     }
     if constexpr (SINK == Sink::rows) {
-      float2* out = reinterpret_cast<float2*>(A.dst) + b * M;
-      columns([&](int ci, int, long long n) {
+      const GView out = GView::of(A.dst + 2 * b * M);
+      columns([&](int ci, int, unsigned n8) {
 #pragma unroll
-        for (int j = 0; j < R; ++j) out[n + j * Q] = h[ci][j];
+        for (int j = 0; j < R; ++j) out.st2(h[ci][j], n8, j * sq8);
       });
     } else if constexpr (SINK == Sink::send) {
-      columns([&](int ci, int col, long long) {
+      columns([&](int ci, int col, unsigned) {
 #pragma unroll
-        for (int j = 0; j < R; ++j) lds[(j << pg.lw) + col] = h[ci][j];
+        for (int j = 0; j < R; ++j) lds[j * W + col] = h[ci][j];
       });
       __syncthreads();
       float2* trow = reinterpret_cast<float2*>(A.dst) + b * M;
-      for_entries<THREADS, unsigned>(
+      for_entries<THREADS, 8, unsigned>(
           C, [&](int i) { return item[i]; },
-          [&](int i, unsigned it) { trow[(i + dl[it & 255]) & (M - 1)] = lds[(it >> 8) & mask]; });
+          [&](int i, unsigned it) { trow[unsigned(i + dl[it & 255]) & nm] = lds[(it >> 8) & kMask]; });
       if (b + 1 < b1) __syncthreads();
     } else if constexpr (SINK == Sink::ret) {
-      columns([&](int ci, int col, long long) {
+      columns([&](int ci, int col, unsigned) {
 #pragma unroll
-        for (int j = 0; j < R; ++j) lds[loc[(j << pg.lw) + col] & mask] = h[ci][j];
+        for (int j = 0; j < R; ++j) lds[loc.ldu16(unsigned(col) * 2u, unsigned(j << pg.lw) * 2u) & kMask] = h[ci][j];
       });
       __syncthreads();
       float4* t4 = reinterpret_cast<float4*>(A.dst + 2 * (b * M + ((long long)c << pg.lC)));
       for (int i = threadIdx.x; i < C / 2; i += THREADS) t4[i] = lds4[i];
       if (b + 1 < b1) __syncthreads();
     } else {
-      float2* zrow = A.Z + b * M;
-      columns([&](int ci, int, long long n) {
+      columns([&](int ci, int, unsigned n8) {
         float2 x[R];
 #pragma unroll
         for (int j = 0; j < R; ++j) x[j] = h[ci][j];
         Dft<R, false>::run(x);
 #pragma unroll
-        for (int r = 1; r < R; ++r) x[r] = cmul(x[r], A.tw[((r - 1) << pg.lQ) + n]);
+        for (int r = 1; r < R; ++r) x[r] = cmul(x[r], tw.ld2(n8, (r - 1) * sq8));
 #pragma unroll
-        for (int r = 0; r < R; ++r) zrow[(r << pg.lQ) + n] = x[r];
+        for (int r = 0; r < R; ++r) z.st2(x[r], n8, r * sq8);
       });
     }
   }
   if constexpr (BWD) {
-    float2* out = reinterpret_cast<float2*>(A.part) + p * M;
-    columns([&](int ci, int, long long n) {
+    const GView out = GView::of(A.part + 2 * p * M);
+    columns([&](int ci, int, unsigned n8) {
 #pragma unroll
-      for (int j = 0; j < R; ++j) out[n + j * Q] = s[ci][j];
+      for (int j = 0; j < R; ++j) out.st2(s[ci][j], n8, j * sq8);
     });
   }
 }
@@ -651,19 +676,22 @@ __global__ __launch_bounds__(kThreads) void k_part(float2* __restrict__ Z, long 
 }
 
 // ---------------------------------------------------------------- segments
-// Segment plans: 16 (8) values per thread, one butterfly per thread in the
-// first and last pass, so that frequency k2 = t + T s sits in register s of
-// lane t.  Small register arrays keep four waves per SIMD where the complex
-// rows of the fused kernels (32 values) run two.
+// Segment plans: one butterfly per thread in the first and last pass, so that
+// frequency k2 = t + T s sits in register s of lane t.  8 values per thread;
+// at 4096 points the forward takes 16 (one exchange less, a fifth fewer
+// operations; complex rows 78 -> 69 us, real ones 102 -> 92 us for 134 MB
+// of rows), which in the backward, with several arrays and the image sums
+// in registers, spills (real 181 -> 294 us) or gains nothing (complex).
 using SP64 = ComplexPlan<64, 8, 8, 8>;
 using SP128 = ComplexPlan<128, 16, 8, 2, 8>;
-using SP256 = ComplexPlan<256, 16, 16, 16>;
-using SP512 = ComplexPlan<512, 32, 16, 2, 16>;
-using SP1024 = ComplexPlan<1024, 64, 16, 4, 16>;
+using SP256 = ComplexPlan<256, 32, 8, 4, 8>;
+using SP512 = ComplexPlan<512, 64, 8, 8, 8>;
+using SP1024 = ComplexPlan<1024, 128, 8, 4, 4, 8>;
 using SP2048 = ComplexPlan<2048, 128, 16, 8, 16>;
-using SP4096 = ComplexPlan<4096, 256, 16, 16, 16>;
+using SP4096 = ComplexPlan<4096, 512, 8, 8, 8, 8>;
+using SP4096F = ComplexPlan<4096, 256, 16, 16, 16>;
 
-template <class F>
+template <bool FWD, class F>
 bool with_seg_plan(int L, F&& f) {
   switch (L) {
     case 64: f.template operator()<SP64>(); return true;
@@ -672,19 +700,91 @@ bool with_seg_plan(int L, F&& f) {
     case 512: f.template operator()<SP512>(); return true;
     case 1024: f.template operator()<SP1024>(); return true;
     case 2048: f.template operator()<SP2048>(); return true;
-    case 4096: f.template operator()<SP4096>(); return true;
+    case 4096:
+      if constexpr (FWD) f.template operator()<SP4096F>();
+      else f.template operator()<SP4096>();
+      return true;
     default: return false;
   }
 }
 
+// The segment launches loop over rows and are bound by arithmetic and LDS
+// about as much as by HBM, so a thread keeps what does not change between
+// rows in registers: the twiddles of all passes (the plans' radices are
+// palindromes or the inverse loads its own), and for complex rows d / N.
+// Several arrays (h and g, the two segments of a pair) run pass by pass
+// together, each with its own slab, for two barriers per exchange in all.
 template <class PL>
 struct Seg {
   using O = CplxOps<PL>;
   static constexpr int T = PL::T, P = PL::P, L = PL::N;
   static_assert(O::B0 == 1 && O::BL == 1 && O::KIND == 0, "register s of lane t holds t + T s at both ends");
+  static_assert(PL::palindrome(), "both directions share their twiddles");
   static constexpr int GROUPS = T < 64 ? 64 / T : 1;  // segments (pairs) per workgroup
   static constexpr int THREADS = T < 64 ? 64 : T;
   static constexpr int SLAB = PL::SLAB;
+  static constexpr int NP = PL::NPASS;
+
+  // Twiddles of passes 1 .. NP-1 for lane t, and of the last pass for the
+  // reversed lane T-1-t.
+  struct Tw {
+    PassTw<PL, false, 1, 0, 0> w1;
+    PassTw<PL, false, 2, 0, 0> w2;
+    PassTw<PL, false, 3, 0, 0> w3;
+    __device__ __forceinline__ void load(unsigned t, GView tab) {
+      w1.load(t, tab);
+      if constexpr (NP > 2) w2.load(t, tab);
+      if constexpr (NP > 3) w3.load(t, tab);
+    }
+  };
+  template <int PASS, bool INV, int Q>
+  __device__ __forceinline__ static void twiddle(float2 (&x)[P], const PassTw<PL, false, Q, 0, 0>& w) {
+    constexpr int r = PL::radix(PASS, INV), b = P / r;
+#pragma unroll
+    for (int beta = 0; beta < b; ++beta)
+#pragma unroll
+      for (int i = 1; i < r; ++i) x[beta * r + i] = ctw<INV>(x[beta * r + i], w.w[beta * (r - 1) + i - 1]);
+  }
+  // One pass over NA arrays; with REV the odd arrays' spectra are held with
+  // the lanes reversed (their forward last pass and inverse first pass run
+  // at lane T-1-t).
+  template <bool INV, int PASS, int NA, bool REV, class Ctx>
+  __device__ __forceinline__ static void pass(Ctx& ctx, float2 (&x)[NA][P], unsigned t, float2* slab, const Tw& tw,
+                                              const Tw& rt) {
+    using G = PassGeo<PL, INV, PASS, 0, 0>;
+    const G geo(t), rev(T - 1 - t);
+    auto geo_of = [&](int a) -> const G& { return REV && (a & 1) && (INV ? PASS == 0 : PASS == NP - 1) ? rev : geo; };
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+      const bool r = REV && (a & 1) && !INV && PASS == NP - 1;
+      if constexpr (PASS > 0) geo_of(a).read(x[a], slab + a * (SLAB / 2));
+      if constexpr (PASS == 1) twiddle<PASS, INV>(x[a], r ? rt.w1 : tw.w1);
+      if constexpr (PASS == 2) twiddle<PASS, INV>(x[a], r ? rt.w2 : tw.w2);
+      if constexpr (PASS == 3) twiddle<PASS, INV>(x[a], r ? rt.w3 : tw.w3);
+      G::dft(x[a]);
+      if constexpr (NA > 2) ACDC_SCHED_FENCE();
+    }
+    if constexpr (PASS < NP - 1) {
+      ctx.sync_row();
+#pragma unroll
+      for (int a = 0; a < NA; ++a) geo_of(a).write(x[a], slab + a * (SLAB / 2));
+      ctx.sync_row();
+    }
+  }
+  template <bool INV, int NA, bool REV, class Ctx>
+  __device__ __forceinline__ static void fft(Ctx& ctx, float2 (&x)[NA][P], unsigned t, float2* slab, const Tw& tw,
+                                             const Tw& rt) {
+    pass<INV, 0, NA, REV>(ctx, x, t, slab, tw, rt);
+    pass<INV, 1, NA, REV>(ctx, x, t, slab, tw, rt);
+    if constexpr (NP > 2) pass<INV, 2, NA, REV>(ctx, x, t, slab, tw, rt);
+    if constexpr (NP > 3) pass<INV, 3, NA, REV>(ctx, x, t, slab, tw, rt);
+  }
+  __device__ __forceinline__ static void load(const float2* seg, float2 (&x)[P], unsigned t) {
+    O::template ld_row<false>(GView::of(seg), 0u, x, t);
+  }
+  __device__ __forceinline__ static void store(float2* seg, float2 (&x)[P], unsigned t) {
+    O::template st_row<true>(GView::of(seg), 0u, x, t);
+  }
 };
 
 // Pair p (of S/2) of a real row's segments: Z[k] in one has its Makhoul
@@ -714,14 +814,16 @@ __host__ __device__ __forceinline__ void seg_pair(const Geo& g, int p, int& sa, 
   sb = g.R2 - 1 - x;
 }
 
-// Quartet of lane t, slot s (of P) of pair p: its number e, where e = 0 is
-// the self-paired (Z[0], Z[M/2]) and otherwise Z[e] pairs with Z[M-e].
-__host__ __device__ __forceinline__ long long quartet_of(const Geo& g, int p, int s, int t, int T, int P) {
+// Quartet at place k2 of pair p: its number e, where e = 0 is the self-paired
+// (Z[0], Z[M/2]) and otherwise Z[e] pairs with Z[M-e].  In a generic pair it
+// is the quartet of segment A's k2, in pair 0 those of segment 0 come first
+// (k2 < L/2), then the other segment's.
+__host__ __device__ __forceinline__ long long quartet_of(const Geo& g, int p, int k2) {
   const long long S = (long long)g.R1 * g.R2;
-  if (p == 0) return s < P / 2 ? S * (t + T * s) : S / 2 + S * (t + T * (s - P / 2));
+  if (p == 0) return k2 < g.L / 2 ? S * k2 : S / 2 + S * (k2 - g.L / 2);
   int sa, sb;
   seg_pair(g, p, sa, sb);
-  const long long k = sa / g.R2 + (long long)g.R1 * (sa % g.R2 + (long long)g.R2 * (t + T * s));
+  const long long k = sa / g.R2 + (long long)g.R1 * (sa % g.R2 + (long long)g.R2 * k2);
   return k < g.M / 2 ? k : g.M - k;
 }
 
@@ -733,31 +835,15 @@ __device__ __forceinline__ long long spec_index(const Geo& g, long long q) {
   return r1 + (long long)g.R1 * (r2 + (long long)g.R2 * k2);
 }
 
-// The lanes of one pair: segment A in v (lane t), segment B in w with the
-// lanes reversed (lane T-1-t).  Then register s of v and register P-1-s of w
-// hold k2 and L-1-k2, Makhoul partners in a generic pair.  Slot s has
-// (Z[e], Z[M-e]) = (v[s], w[P-1-s]) for s < P/2 and the other way round from
-// there on, where k > M/2.
+// The lanes of one pair, x[0] = segment A (lane t), x[1] = segment B, whose
+// spectrum is held with the lanes reversed.  Then register s of x[0] and
+// register P-1-s of x[1] hold k2 and L-1-k2, Makhoul partners in a generic
+// pair.  Slot s has (Z[e], Z[M-e]) = (x[0][s], x[1][P-1-s]) for s < P/2 and
+// the other way round from there on, where k > M/2.
 template <class PL>
 struct PairOps {
   using G = Seg<PL>;
   static constexpr int T = PL::T, P = PL::P, L = PL::N;
-  template <bool INV, class Ctx>
-  __device__ __forceinline__ static void fft(Ctx& ctx, float2 (&v)[P], float2 (&w)[P], unsigned t, float2* slab,
-                                             GView tab) {
-    G::O::template fft<INV>(ctx, v, t, slab, tab);
-    G::O::template fft<INV>(ctx, w, T - 1 - t, slab, tab);
-  }
-  __device__ __forceinline__ static void load(const float2* row, int sa, int sb, float2 (&v)[P], float2 (&w)[P],
-                                              unsigned t) {
-    G::O::template ld_row<false>(GView::of(row + (long long)sa * L), 0u, v, t);
-    G::O::template ld_row<false>(GView::of(row + (long long)sb * L), 0u, w, T - 1 - t);
-  }
-  __device__ __forceinline__ static void store(float2* row, int sa, int sb, float2 (&v)[P], float2 (&w)[P],
-                                               unsigned t) {
-    G::O::template st_row<true>(GView::of(row + (long long)sa * L), 0u, v, t);
-    G::O::template st_row<true>(GView::of(row + (long long)sb * L), 0u, w, T - 1 - t);
-  }
   static __device__ __forceinline__ float2& zk(float2 (&v)[P], float2 (&w)[P], int s) {
     return s < P / 2 ? v[s] : w[P - 1 - s];
   }
@@ -765,179 +851,198 @@ struct PairOps {
     return s < P / 2 ? w[P - 1 - s] : v[s];
   }
   // Pair 0: the partners lie in other lanes of the same segment.  Through
-  // the slab, one segment after the other: segment 0's quartets q = t + T s
-  // (k2 = q, L-q; q = 0: 0, L/2) into slots s < P/2, segment B's (q, L-1-q)
-  // into the others; and back.
+  // two slabs: segment 0's quartets q = t + T s (k2 = q, L-q; q = 0: 0, L/2)
+  // into slots s < P/2, segment B's (q, L-1-q) into the others; and back.
   template <class Ctx>
   __device__ __forceinline__ static void to_quartets(Ctx& ctx, float2 (&v)[P], float2 (&w)[P], unsigned t,
                                                      float2* slab) {
-    float2 a[P / 2], b[P / 2], c[P / 2], d[P / 2];
+    float2* const slab2 = slab + G::SLAB / 2;
     ctx.sync_row();
 #pragma unroll
-    for (int s = 0; s < P; ++s) slab[t + T * s] = v[s];
+    for (int s = 0; s < P; ++s) {
+      slab[t + T * s] = v[s];
+      slab2[T - 1 - t + T * s] = w[s];
+    }
     ctx.sync_row();
 #pragma unroll
     for (int s = 0; s < P / 2; ++s) {
       const unsigned q = t + T * s;
-      a[s] = slab[q];
-      b[s] = slab[q == 0 ? L / 2 : L - q];
-    }
-    ctx.sync_row();
-#pragma unroll
-    for (int s = 0; s < P; ++s) slab[T - 1 - t + T * s] = w[s];
-    ctx.sync_row();
-#pragma unroll
-    for (int s = 0; s < P / 2; ++s) {
-      const unsigned q = t + T * s;
-      c[s] = slab[q];
-      d[s] = slab[L - 1 - q];
-    }
-#pragma unroll
-    for (int s = 0; s < P / 2; ++s) {
-      zk(v, w, s) = a[s];
-      zm(v, w, s) = b[s];
-    }
-#pragma unroll
-    for (int s = P / 2; s < P; ++s) {
-      zk(v, w, s) = c[s - P / 2];
-      zm(v, w, s) = d[s - P / 2];
+      zk(v, w, s) = slab[q];
+      zm(v, w, s) = slab[q == 0 ? L / 2 : L - q];
+      zk(v, w, s + P / 2) = slab2[q];
+      zm(v, w, s + P / 2) = slab2[L - 1 - q];
     }
   }
   template <class Ctx>
   __device__ __forceinline__ static void from_quartets(Ctx& ctx, float2 (&v)[P], float2 (&w)[P], unsigned t,
                                                        float2* slab) {
-    float2 nv[P], nw[P];
+    float2* const slab2 = slab + G::SLAB / 2;
     ctx.sync_row();
 #pragma unroll
     for (int s = 0; s < P / 2; ++s) {
       const unsigned q = t + T * s;
       slab[q] = zk(v, w, s);
       slab[q == 0 ? L / 2 : L - q] = zm(v, w, s);
+      slab2[q] = zk(v, w, s + P / 2);
+      slab2[L - 1 - q] = zm(v, w, s + P / 2);
     }
     ctx.sync_row();
-#pragma unroll
-    for (int s = 0; s < P; ++s) nv[s] = slab[t + T * s];
-    ctx.sync_row();
-#pragma unroll
-    for (int s = P / 2; s < P; ++s) {
-      const unsigned q = t + T * (s - P / 2);
-      slab[q] = zk(v, w, s);
-      slab[L - 1 - q] = zm(v, w, s);
-    }
-    ctx.sync_row();
-#pragma unroll
-    for (int s = 0; s < P; ++s) nw[s] = slab[T - 1 - t + T * s];
 #pragma unroll
     for (int s = 0; s < P; ++s) {
-      v[s] = nv[s];
-      w[s] = nw[s];
+      v[s] = slab[t + T * s];
+      w[s] = slab2[T - 1 - t + T * s];
     }
   }
 };
 
+// What a workgroup's group of lanes works on: rows b0 .. b1 of unit `unit`
+// (a segment or pair; `units` a row), blocks of rb rows.  Groups past the
+// end repeat the first unit without storing.
+struct SegWork {
+  bool valid;
+  int unit;
+  long long blk, b0, b1;
+  __device__ __forceinline__ SegWork(long long id, int units, long long B, int rb) {
+    const long long nblk = (B + rb - 1) / rb;
+    valid = id < nblk * units;
+    unit = valid ? int(id % units) : 0;
+    blk = valid ? id / units : 0;
+    b0 = blk * rb;
+    b1 = b0 + rb < B ? b0 + rb : B;
+  }
+};
+
+// Waves per SIMD of the forward launches: what the values, the twiddles and
+// (complex) d of a thread leave room for.
+template <class PL>
+constexpr int seg_fwd_waves() {
+  return PL::P == 8 ? 4 : 2;
+}
+
 // Forward: segment FFTs of a pair, the quartet maps, segment IFFTs.
 template <class PL>
-__global__ __launch_bounds__(Seg<PL>::THREADS) void k_seg_fwd(float2* __restrict__ Z, const float4* __restrict__ Mq,
-                                                              long long B, Geo g, int bias,
-                                                              const char* __restrict__ tab) {
+__global__ __launch_bounds__(Seg<PL>::THREADS) __attribute__((amdgpu_waves_per_eu(seg_fwd_waves<PL>()))) void k_seg_fwd(
+    float2* __restrict__ Z, const float4* __restrict__ Mq, long long B, Geo g, int rb, int bias,
+    const char* __restrict__ tab) {
   using G = Seg<PL>;
   using Q = PairOps<PL>;
   constexpr int T = PL::T, P = PL::P;
-  __shared__ float lds[G::GROUPS * G::SLAB];
+  __shared__ float lds[G::GROUPS * 2 * G::SLAB];
   const unsigned t = threadIdx.x % T, grp = threadIdx.x / T;
-  float2* slab = reinterpret_cast<float2*>(lds + grp * G::SLAB);
-  const int np = g.R1 * g.R2 / 2;
-  const long long id = (long long)blockIdx.x * G::GROUPS + grp;
-  const bool valid = id < B * np;
-  const long long b = valid ? id / np : 0;
-  const int p = valid ? int(id % np) : 0;
+  float2* slab = reinterpret_cast<float2*>(lds + grp * 2 * G::SLAB);
+  const SegWork wk((long long)blockIdx.x * G::GROUPS + grp, g.R1 * g.R2 / 2, B, rb);
+  const int p = wk.unit;
   int sa, sb;
   seg_pair(g, p, sa, sb);
-  float2* row = Z + b * g.M;
   DevCtx<T> ctx;
-  const GView tw = GView::of(tab);
-  float2 v[P], w[P];
-  Q::load(row, sa, sb, v, w, t);
-  Q::template fft<false>(ctx, v, w, t, slab, tw);
-  if (p == 0) Q::to_quartets(ctx, v, w, t, slab);
+  typename G::Tw tw, rt;
+  tw.load(t, GView::of(tab));
+  rt.load(T - 1 - t, GView::of(tab));
   const GView mq = GView::of(Mq + (long long)p * PL::N * kMqRows);
+  for (long long b = wk.b0; b < wk.b1; ++b) {
+    float2* const za = Z + b * g.M + (long long)sa * PL::N;
+    float2* const zb = Z + b * g.M + (long long)sb * PL::N;
+    const unsigned t16 = fresh(t * 16u);
+    float2 x[2][P];
+    G::load(za, x[0], t);
+    G::load(zb, x[1], t);
+    G::template fft<false, 2, true>(ctx, x, t, slab, tw, rt);
+    if (p == 0) Q::to_quartets(ctx, x[0], x[1], t, slab);
 #pragma unroll
-  for (int s = 0; s < P; ++s) {
-    float2& zk = Q::zk(v, w, s);
-    float2& zm = Q::zm(v, w, s);
-    const float4 c0 = mq.ld4(t * 16u, unsigned((s * kMqRows + 0) * T * 16));
-    const float4 c1 = mq.ld4(t * 16u, unsigned((s * kMqRows + 1) * T * 16));
-    quartet_back(quartet_split(zk, zm, make_float2(c1.z, c1.w)), c0, c1, zk, zm);
-    if (bias) {
-      const float4 c3 = mq.ld4(t * 16u, unsigned((s * kMqRows + 3) * T * 16));
-      zk = make_float2(zk.x + c3.x, zk.y + c3.y);
-      zm = make_float2(zm.x + c3.z, zm.y + c3.w);
+    for (int s = 0; s < P; ++s) {
+      if (s % 2 == 0) ACDC_SCHED_FENCE();
+      float2& zk = Q::zk(x[0], x[1], s);
+      float2& zm = Q::zm(x[0], x[1], s);
+      const float4 c0 = mq.ld4(t16, unsigned((0 * PL::N + s * T) * 16));
+      const float4 c1 = mq.ld4(t16, unsigned((1 * PL::N + s * T) * 16));
+      quartet_back(quartet_split(zk, zm, make_float2(c1.z, c1.w)), c0, c1, zk, zm);
+      if (bias) {
+        const float4 c3 = mq.ld4(t16, unsigned((3 * PL::N + s * T) * 16));
+        zk = make_float2(zk.x + c3.x, zk.y + c3.y);
+        zm = make_float2(zm.x + c3.z, zm.y + c3.w);
+      }
+    }
+    if (p == 0) Q::from_quartets(ctx, x[0], x[1], t, slab);
+    G::template fft<true, 2, true>(ctx, x, t, slab, tw, rt);
+    if (wk.valid) {
+      G::store(za, x[0], t);
+      G::store(zb, x[1], t);
     }
   }
-  if (p == 0) Q::from_quartets(ctx, v, w, t, slab);
-  Q::template fft<true>(ctx, v, w, t, slab, tw);
-  if (valid) Q::store(row, sa, sb, v, w, t);
 }
 
 // Backward: rb rows in turn.  Segment FFTs of h and g, the images H*G (dL/dd)
 // summed over the rows, g's quartets through the D maps, its segment IFFTs.
 template <class PL>
-__global__ __launch_bounds__(Seg<PL>::THREADS) void k_seg_bwd(const float2* __restrict__ Zh, float2* __restrict__ Zg,
-                                                              const float4* __restrict__ Mq, long long B, Geo g,
-                                                              int rb, float* __restrict__ part,
-                                                              const char* __restrict__ tab) {
+__global__ __launch_bounds__(Seg<PL>::THREADS) __attribute__((amdgpu_waves_per_eu(2))) void k_seg_bwd(
+    const float2* __restrict__ Zh, float2* __restrict__ Zg, const float4* __restrict__ Mq, long long B, Geo g, int rb,
+    float* __restrict__ part, const char* __restrict__ tab) {
   using G = Seg<PL>;
   using Q = PairOps<PL>;
   constexpr int T = PL::T, P = PL::P;
-  __shared__ float lds[G::GROUPS * G::SLAB];
+  __shared__ float lds[G::GROUPS * 2 * G::SLAB];
   const unsigned t = threadIdx.x % T, grp = threadIdx.x / T;
-  float2* slab = reinterpret_cast<float2*>(lds + grp * G::SLAB);
-  const int np = g.R1 * g.R2 / 2;
-  const long long nblk = (B + rb - 1) / rb, id = (long long)blockIdx.x * G::GROUPS + grp;
-  const bool valid = id < nblk * np;
-  const long long blk = valid ? id / np : 0;
-  const int p = valid ? int(id % np) : 0;
+  float2* slab = reinterpret_cast<float2*>(lds + grp * 2 * G::SLAB);
+  const SegWork wk((long long)blockIdx.x * G::GROUPS + grp, g.R1 * g.R2 / 2, B, rb);
+  const int p = wk.unit;
   int sa, sb;
   seg_pair(g, p, sa, sb);
   DevCtx<T> ctx;
-  const GView tw = GView::of(tab);
+  typename G::Tw tw, rt;
+  tw.load(t, GView::of(tab));
+  rt.load(T - 1 - t, GView::of(tab));
   const GView mq = GView::of(Mq + (long long)p * PL::N * kMqRows);
   float4 sum[P];
 #pragma unroll
   for (int s = 0; s < P; ++s) sum[s] = make_float4(0.f, 0.f, 0.f, 0.f);
-  const long long b0 = blk * rb, b1 = b0 + rb < B ? b0 + rb : B;
-  for (long long b = b0; b < b1; ++b) {
-    float2 hv[P], hw[P], gv[P], gw[P];
-    Q::load(Zh + b * g.M, sa, sb, hv, hw, t);
-    Q::load(Zg + b * g.M, sa, sb, gv, gw, t);
-    Q::template fft<false>(ctx, hv, hw, t, slab, tw);
-    Q::template fft<false>(ctx, gv, gw, t, slab, tw);
-    if (p == 0) {
-      Q::to_quartets(ctx, hv, hw, t, slab);
-      Q::to_quartets(ctx, gv, gw, t, slab);
+  // pair 0 on a path of its own: joined inside the row, its exchanges cost
+  // every pair registers (47 spilled at two waves per SIMD)
+  auto rows = [&](auto special) {
+  for (long long b = wk.b0; b < wk.b1; ++b) {
+    const long long oa = b * g.M + (long long)sa * PL::N, ob = b * g.M + (long long)sb * PL::N;
+    const unsigned t16 = fresh(t * 16u);
+    float2 h[2][P], x[2][P];
+    G::load(Zh + oa, h[0], t);
+    G::load(Zh + ob, h[1], t);
+    G::load(Zg + oa, x[0], t);
+    G::load(Zg + ob, x[1], t);
+    G::template fft<false, 2, true>(ctx, h, t, slab, tw, rt);
+    ACDC_SCHED_FENCE();
+    G::template fft<false, 2, true>(ctx, x, t, slab, tw, rt);
+    ACDC_SCHED_FENCE();
+    if constexpr (special.value) {
+      Q::to_quartets(ctx, h[0], h[1], t, slab);
+      Q::to_quartets(ctx, x[0], x[1], t, slab);
     }
 #pragma unroll
     for (int s = 0; s < P; ++s) {
-      const float4 c0 = mq.ld4(t * 16u, unsigned((s * kMqRows + 0) * T * 16));
-      const float4 c1 = mq.ld4(t * 16u, unsigned((s * kMqRows + 1) * T * 16));
-      const float4 c2 = mq.ld4(t * 16u, unsigned((s * kMqRows + 2) * T * 16));
+      if (s % 2 == 0) ACDC_SCHED_FENCE();
+      const float4 c0 = mq.ld4(t16, unsigned((0 * PL::N + s * T) * 16));
+      const float4 c1 = mq.ld4(t16, unsigned((1 * PL::N + s * T) * 16));
+      const float4 c2 = mq.ld4(t16, unsigned((2 * PL::N + s * T) * 16));
       const float2 wt = make_float2(c1.z, c1.w), qa = make_float2(c2.x, c2.y), qbr = make_float2(c2.z, c2.w);
-      float2& gk = Q::zk(gv, gw, s);
-      float2& gm = Q::zm(gv, gw, s);
+      float2& gk = Q::zk(x[0], x[1], s);
+      float2& gm = Q::zm(x[0], x[1], s);
       float H[4], X[4];
-      quartet_post(quartet_split(Q::zk(hv, hw, s), Q::zm(hv, hw, s), wt), qa, qbr, H);
+      quartet_post(quartet_split(Q::zk(h[0], h[1], s), Q::zm(h[0], h[1], s), wt), qa, qbr, H);
       const Split sg = quartet_split(gk, gm, wt);
       quartet_post(sg, qa, qbr, X);
       sum[s] = make_float4(sum[s].x + H[0] * X[0], sum[s].y + H[1] * X[1], sum[s].z + H[2] * X[2],
                            sum[s].w + H[3] * X[3]);
       quartet_back(sg, c0, c1, gk, gm);
     }
-    if (p == 0) Q::from_quartets(ctx, gv, gw, t, slab);
-    Q::template fft<true>(ctx, gv, gw, t, slab, tw);
-    if (valid) Q::store(Zg + b * g.M, sa, sb, gv, gw, t);
+    if constexpr (special.value) Q::from_quartets(ctx, x[0], x[1], t, slab);
+    G::template fft<true, 2, true>(ctx, x, t, slab, tw, rt);
+    if (wk.valid) {
+      G::store(Zg + oa, x[0], t);
+      G::store(Zg + ob, x[1], t);
+    }
   }
-  if (!valid) return;
-  float4* out = reinterpret_cast<float4*>(part + blk * 2 * g.M) + (long long)p * PL::N;
+  };
+  if (p == 0) rows(std::true_type{});
+  else rows(std::false_type{});
+  if (!wk.valid) return;
+  float4* out = reinterpret_cast<float4*>(part + wk.blk * 2 * g.M) + (long long)p * PL::N;
 #pragma unroll
   for (int s = 0; s < P; ++s) out[T * s + t] = sum[s];
 }
@@ -951,125 +1056,131 @@ __global__ __launch_bounds__(Seg<PL>::THREADS) void k_seg_dct(const float2* __re
   using G = Seg<PL>;
   using Q = PairOps<PL>;
   constexpr int T = PL::T, P = PL::P;
-  __shared__ float lds[G::GROUPS * G::SLAB];
+  __shared__ float lds[G::GROUPS * 2 * G::SLAB];
   const unsigned t = threadIdx.x % T, grp = threadIdx.x / T;
-  float2* slab = reinterpret_cast<float2*>(lds + grp * G::SLAB);
-  const int np = g.R1 * g.R2 / 2, id = int(blockIdx.x) * G::GROUPS + int(grp);
-  const bool valid = id < np;
-  const int p = valid ? id : 0;
+  float2* slab = reinterpret_cast<float2*>(lds + grp * 2 * G::SLAB);
+  const SegWork wk((long long)blockIdx.x * G::GROUPS + grp, g.R1 * g.R2 / 2, 1, 1);
+  const int p = wk.unit;
   int sa, sb;
   seg_pair(g, p, sa, sb);
   DevCtx<T> ctx;
-  float2 v[P], w[P];
-  Q::load(Z, sa, sb, v, w, t);
-  Q::template fft<false>(ctx, v, w, t, slab, GView::of(tab));
-  if (p == 0) Q::to_quartets(ctx, v, w, t, slab);
+  typename G::Tw tw, rt;
+  tw.load(t, GView::of(tab));
+  rt.load(T - 1 - t, GView::of(tab));
+  float2 x[2][P];
+  G::load(Z + (long long)sa * PL::N, x[0], t);
+  G::load(Z + (long long)sb * PL::N, x[1], t);
+  G::template fft<false, 2, true>(ctx, x, t, slab, tw, rt);
+  if (p == 0) Q::to_quartets(ctx, x[0], x[1], t, slab);
   const GView mq = GView::of(Mq + (long long)p * PL::N * kMqRows);
 #pragma unroll
   for (int s = 0; s < P; ++s) {
-    const float4 c1 = mq.ld4(t * 16u, unsigned((s * kMqRows + 1) * T * 16));
-    const float4 c2 = mq.ld4(t * 16u, unsigned((s * kMqRows + 2) * T * 16));
+    const float4 c1 = mq.ld4(t * 16u, unsigned((1 * PL::N + s * T) * 16));
+    const float4 c2 = mq.ld4(t * 16u, unsigned((2 * PL::N + s * T) * 16));
     float X[4];
-    quartet_post(quartet_split(Q::zk(v, w, s), Q::zm(v, w, s), make_float2(c1.z, c1.w)), make_float2(c2.x, c2.y),
-                 make_float2(c2.z, c2.w), X);
+    quartet_post(quartet_split(Q::zk(x[0], x[1], s), Q::zm(x[0], x[1], s), make_float2(c1.z, c1.w)),
+                 make_float2(c2.x, c2.y), make_float2(c2.z, c2.w), X);
     X[1] = -X[1];
-    const long long e = quartet_of(g, p, s, int(t), T, P);
+    const long long e = quartet_of(g, p, int(t) + T * s);
     const int4 idx = q.qidx[e];
     const int sm = (q.qmask[e] >> 4) & 0xF;
     const int id4[4] = {idx.x, idx.y, idx.z, idx.w};
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      if (valid && (sm & (1 << j))) put1(out + id4[j], X[j], accumulate != 0);
+      if (wk.valid && (sm & (1 << j))) put1(out + id4[j], X[j], accumulate != 0);
   }
 }
 
 // Complex rows: segment FFT, * d / N (Dn in storage order), segment IFFT.
+// The next row is loaded while one is transformed.
 template <class PL>
-__global__ __launch_bounds__(Seg<PL>::THREADS) void k_cseg_fwd(float2* __restrict__ Z, const float2* __restrict__ Dn,
-                                                               long long B, Geo g, const char* __restrict__ tab) {
+__global__ __launch_bounds__(Seg<PL>::THREADS) __attribute__((amdgpu_waves_per_eu(seg_fwd_waves<PL>()))) void k_cseg_fwd(
+    float2* __restrict__ Z, const float2* __restrict__ Dn, long long B, Geo g, int rb, const char* __restrict__ tab) {
   using G = Seg<PL>;
-  using O = typename G::O;
   constexpr int T = PL::T, P = PL::P;
   __shared__ float lds[G::GROUPS * G::SLAB];
   const unsigned t = threadIdx.x % T, grp = threadIdx.x / T;
   float2* slab = reinterpret_cast<float2*>(lds + grp * G::SLAB);
-  const int ns = g.R1 * g.R2;
-  const long long id = (long long)blockIdx.x * G::GROUPS + grp;
-  const bool valid = id < B * ns;
-  const long long seg = valid ? id : 0;
-  const GView z = GView::of(Z + seg * PL::N), tw = GView::of(tab);
-  const GView dn = GView::of(Dn + (seg % ns) * PL::N);
+  const SegWork wk((long long)blockIdx.x * G::GROUPS + grp, g.R1 * g.R2, B, rb);
+  const GView dn = GView::of(Dn + (long long)wk.unit * PL::N);
   DevCtx<T> ctx;
-  float2 v[P];
-  O::template ld_row<false>(z, 0u, v, t);
-  O::template fft<false>(ctx, v, t, slab, tw);
+  typename G::Tw tw;
+  tw.load(t, GView::of(tab));
+  float2 d[P], n[1][P];
 #pragma unroll
-  for (int s = 0; s < P; ++s) v[s] = cmul(v[s], dn.ld2(t * 8u, unsigned(T * s) * 8u));
-  O::template fft<true>(ctx, v, t, slab, tw);
-  if (valid) O::template st_row<true>(z, 0u, v, t);
+  for (int s = 0; s < P; ++s) d[s] = dn.ld2(t * 8u, unsigned(T * s) * 8u);
+  float2* z = Z + wk.b0 * g.M + (long long)wk.unit * PL::N;
+  G::load(z, n[0], t);
+  for (long long b = wk.b0; b < wk.b1; ++b, z += g.M) {
+    float2 x[1][P];
+#pragma unroll
+    for (int s = 0; s < P; ++s) x[0][s] = n[0][s];
+    if (b + 1 < wk.b1) G::load(z + g.M, n[0], t);
+    ACDC_SCHED_FENCE();
+    G::template fft<false, 1, false>(ctx, x, t, slab, tw, tw);
+#pragma unroll
+    for (int s = 0; s < P; ++s) x[0][s] = cmul(x[0][s], d[s]);
+    G::template fft<true, 1, false>(ctx, x, t, slab, tw, tw);
+    if (wk.valid) G::store(z, x[0], t);
+  }
 }
 
 // Backward, rb rows in turn: gh3 = FFT(g) / N, images gh3 * conj(h2) summed
 // over the rows (storage order), then gh3 * conj(d) and its segment IFFT.
 // N is a power of two, so dividing the sum is exact.
 template <class PL>
-__global__ __launch_bounds__(Seg<PL>::THREADS) void k_cseg_bwd(const float2* __restrict__ Zh, float2* __restrict__ Zg,
-                                                               const float2* __restrict__ Dn, long long B, Geo g,
-                                                               int rb, float2* __restrict__ part,
-                                                               const char* __restrict__ tab) {
+__global__ __launch_bounds__(Seg<PL>::THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_cseg_bwd(
+    const float2* __restrict__ Zh, float2* __restrict__ Zg, const float2* __restrict__ Dn, long long B, Geo g, int rb,
+    float2* __restrict__ part, const char* __restrict__ tab) {
   using G = Seg<PL>;
-  using O = typename G::O;
   constexpr int T = PL::T, P = PL::P;
-  __shared__ float lds[G::GROUPS * G::SLAB];
+  __shared__ float lds[G::GROUPS * 2 * G::SLAB];
   const unsigned t = threadIdx.x % T, grp = threadIdx.x / T;
-  float2* slab = reinterpret_cast<float2*>(lds + grp * G::SLAB);
-  const int ns = g.R1 * g.R2;
-  const long long nblk = (B + rb - 1) / rb, id = (long long)blockIdx.x * G::GROUPS + grp;
-  const bool valid = id < nblk * ns;
-  const long long blk = valid ? id / ns : 0;
-  const int sg = valid ? int(id % ns) : 0;
-  const GView tw = GView::of(tab), dn = GView::of(Dn + (long long)sg * PL::N);
+  float2* slab = reinterpret_cast<float2*>(lds + grp * 2 * G::SLAB);
+  const SegWork wk((long long)blockIdx.x * G::GROUPS + grp, g.R1 * g.R2, B, rb);
+  const GView dn = GView::of(Dn + (long long)wk.unit * PL::N);
   DevCtx<T> ctx;
+  typename G::Tw tw;
+  tw.load(t, GView::of(tab));
   float2 sum[P];
 #pragma unroll
   for (int s = 0; s < P; ++s) sum[s] = make_float2(0.f, 0.f);
-  const long long b0 = blk * rb, b1 = b0 + rb < B ? b0 + rb : B;
-  for (long long b = b0; b < b1; ++b) {
-    const long long at = b * g.M + (long long)sg * PL::N;
-    float2 h[P], v[P];
-    O::template ld_row<false>(GView::of(Zh + at), 0u, h, t);
-    O::template ld_row<false>(GView::of(Zg + at), 0u, v, t);
-    O::template fft<false>(ctx, h, t, slab, tw);
-    O::template fft<false>(ctx, v, t, slab, tw);
+  for (long long b = wk.b0; b < wk.b1; ++b) {
+    const long long at = b * g.M + (long long)wk.unit * PL::N;
+    const unsigned t8 = fresh(t * 8u);
+    float2 x[2][P];
+    G::load(Zh + at, x[0], t);
+    G::load(Zg + at, x[1], t);
+    G::template fft<false, 2, false>(ctx, x, t, slab, tw, tw);
+    float2 y[1][P];
 #pragma unroll
     for (int s = 0; s < P; ++s) {
-      const float2 img = cmulc(v[s], h[s]);
+      const float2 img = cmulc(x[1][s], x[0][s]);
       sum[s] = make_float2(sum[s].x + img.x, sum[s].y + img.y);
-      v[s] = cmulc(v[s], dn.ld2(t * 8u, unsigned(T * s) * 8u));
+      y[0][s] = cmulc(x[1][s], dn.ld2(t8, unsigned(T * s) * 8u));
     }
-    O::template fft<true>(ctx, v, t, slab, tw);
-    if (valid) O::template st_row<true>(GView::of(Zg + at), 0u, v, t);
+    G::template fft<true, 1, false>(ctx, y, t, slab, tw, tw);
+    if (wk.valid) G::store(Zg + at, y[0], t);
   }
-  if (!valid) return;
+  if (!wk.valid) return;
   const float inv = 1.0f / float(g.M);
-  float2* out = part + blk * g.M + (long long)sg * PL::N;
+  float2* out = part + wk.blk * g.M + (long long)wk.unit * PL::N;
 #pragma unroll
   for (int s = 0; s < P; ++s) out[T * s + t] = make_float2(sum[s].x * inv, sum[s].y * inv);
 }
 
-// Per-layer quartet coefficients, [K][pair][slot][kMqRows][T].
+// Per-layer quartet coefficients, [K][pair][kMqRows][k2].
 __global__ __launch_bounds__(kThreads) void k_mq(const float* __restrict__ D, const float* __restrict__ Bias,
-                                                 float4* __restrict__ Mq, int K, Geo g, QuartetTabs q, int T, int P) {
+                                                 float4* __restrict__ Mq, int K, Geo g, QuartetTabs q) {
   const long long NQ = g.M / 2, total = (long long)K * NQ, N = 2 * g.M;
   for (long long i = gindex(); i < total; i += gstride()) {
     const long long k = i / NQ, r = i % NQ;
-    const int p = int(r / g.L), s = int(r % g.L) / T, t = int(r % T);
-    const int e = int(quartet_of(g, p, s, t, T, P));
+    const int p = int(r / g.L), k2 = int(r % g.L);
     float4 row[kMqRows];
-    quartet_coeffs(D + k * N, Bias ? Bias + k * N : nullptr, q, e, row);
-    float4* out = Mq + (i - t) * kMqRows + t;
+    quartet_coeffs(D + k * N, Bias ? Bias + k * N : nullptr, q, int(quartet_of(g, p, k2)), row);
+    float4* out = Mq + (i - k2) * kMqRows + k2;
 #pragma unroll
-    for (int c = 0; c < kMqRows; ++c) out[c * T] = row[c];
+    for (int c = 0; c < kMqRows; ++c) out[c * g.L] = row[c];
   }
 }
 
@@ -1107,7 +1218,7 @@ __global__ __launch_bounds__(kThreads) void k_colsum1(const float* __restrict__ 
 constexpr int kSumPh = 8, kSumCols = kThreads / kSumPh;
 template <Order HOW>
 __global__ __launch_bounds__(kThreads) void k_colsum2(const float* __restrict__ part, long long P, long long W,
-                                                      float* __restrict__ out, Geo g, QuartetTabs q, int T, int PT,
+                                                      float* __restrict__ out, Geo g, QuartetTabs q,
                                                       int accumulate) {
   __shared__ float4 ph[kSumPh][kSumCols];
   const int lane = threadIdx.x % kSumCols, f = threadIdx.x / kSumCols;
@@ -1128,8 +1239,7 @@ __global__ __launch_bounds__(kThreads) void k_colsum2(const float* __restrict__ 
   if constexpr (HOW == Order::natural) {
     put4(reinterpret_cast<float4*>(out) + w4, s, acc);
   } else if constexpr (HOW == Order::quartets) {
-    const int p = int(w4 / g.L), sl = int(w4 % g.L) / T, t = int(w4 % T);
-    const long long e = quartet_of(g, p, sl, t, T, PT);
+    const long long e = quartet_of(g, int(w4 / g.L), int(w4 % g.L));
     const int m = (q.qmask[e] >> 4) & 0xF;
     const int4 idx = q.qidx[e];
     if (m & 1) put1(out + idx.x, s.x, acc);
@@ -1150,21 +1260,6 @@ int log2_of(long long v) {
   int l = 0;
   while ((1LL << (l + 1)) <= v) ++l;
   return l;
-}
-
-// T and P of the segment plan of L points.
-void seg_shape(int L, int& T, int& P) {
-  T = P = 1;
-  (void)with_seg_plan(L, [&]<class PL>() {
-    T = PL::T;
-    P = PL::P;
-  });
-}
-
-template <class K>
-hipError_t launch(K&& k) {
-  k();
-  return hipGetLastError();
 }
 
 template <class F>
@@ -1329,17 +1424,16 @@ hipError_t dit2(float2* Z, long long B, const Geo& g, const float2* tw2, hipStre
 
 hipError_t mq(const float* D, const float* Bias, float4* Mq, int K, const Geo& g, const QuartetTabs& q,
               hipStream_t s) {
-  int T, P;
-  seg_shape(g.L, T, P);
-  hipLaunchKernelGGL(k_mq, grid_for((long long)K * (g.M / 2)), dim3(kThreads), 0, s, D, Bias, Mq, K, g, q, T, P);
+  hipLaunchKernelGGL(k_mq, grid_for((long long)K * (g.M / 2)), dim3(kThreads), 0, s, D, Bias, Mq, K, g, q);
   return hipGetLastError();
 }
 
 hipError_t seg_fwd(float2* Z, const float4* Mq, long long B, const Geo& g, bool bias, const char* seg_tab,
                    hipStream_t s) {
-  const bool ok = with_seg_plan(g.L, [&]<class PL>() {
-    hipLaunchKernelGGL(k_seg_fwd<PL>, seg_grid<PL>(B * (g.R1 * g.R2 / 2)), dim3(Seg<PL>::THREADS), 0, s, Z, Mq, B, g,
-                       bias ? 1 : 0, seg_tab);
+  const int rb = seg_rows(B, g, false);
+  const bool ok = with_seg_plan<true>(g.L, [&]<class PL>() {
+    hipLaunchKernelGGL(k_seg_fwd<PL>, seg_grid<PL>((B + rb - 1) / rb * (g.R1 * g.R2 / 2)), dim3(Seg<PL>::THREADS), 0,
+                       s, Z, Mq, B, g, rb, bias ? 1 : 0, seg_tab);
   });
   return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
@@ -1347,7 +1441,7 @@ hipError_t seg_fwd(float2* Z, const float4* Mq, long long B, const Geo& g, bool 
 hipError_t seg_bwd(float2* Zh, float2* Zg, const float4* Mq, long long B, const Geo& g, float* part,
                    const char* seg_tab, hipStream_t s) {
   const int rb = seg_rows(B, g, false);
-  const bool ok = with_seg_plan(g.L, [&]<class PL>() {
+  const bool ok = with_seg_plan<false>(g.L, [&]<class PL>() {
     hipLaunchKernelGGL(k_seg_bwd<PL>, seg_grid<PL>((B + rb - 1) / rb * (g.R1 * g.R2 / 2)), dim3(Seg<PL>::THREADS), 0,
                        s, Zh, Zg, Mq, B, g, rb, part, seg_tab);
   });
@@ -1356,7 +1450,7 @@ hipError_t seg_bwd(float2* Zh, float2* Zg, const float4* Mq, long long B, const 
 
 hipError_t seg_dct(const float2* Z, const float4* Mq, const Geo& g, const QuartetTabs& q, float* gB,
                    bool accumulate, const char* seg_tab, hipStream_t s) {
-  const bool ok = with_seg_plan(g.L, [&]<class PL>() {
+  const bool ok = with_seg_plan<false>(g.L, [&]<class PL>() {
     hipLaunchKernelGGL(k_seg_dct<PL>, seg_grid<PL>(g.R1 * g.R2 / 2), dim3(Seg<PL>::THREADS), 0, s, Z, Mq, g, q, gB,
                        accumulate ? 1 : 0, seg_tab);
   });
@@ -1369,9 +1463,10 @@ hipError_t dn(const float2* D, float2* Dn, int K, const Geo& g, hipStream_t s) {
 }
 
 hipError_t cseg_fwd(float2* Z, const float2* Dn, long long B, const Geo& g, const char* seg_tab, hipStream_t s) {
-  const bool ok = with_seg_plan(g.L, [&]<class PL>() {
-    hipLaunchKernelGGL(k_cseg_fwd<PL>, seg_grid<PL>(B * (g.R1 * g.R2)), dim3(Seg<PL>::THREADS), 0, s, Z, Dn, B, g,
-                       seg_tab);
+  const int rb = seg_rows(B, g, true);
+  const bool ok = with_seg_plan<true>(g.L, [&]<class PL>() {
+    hipLaunchKernelGGL(k_cseg_fwd<PL>, seg_grid<PL>((B + rb - 1) / rb * (g.R1 * g.R2)), dim3(Seg<PL>::THREADS), 0, s,
+                       Z, Dn, B, g, rb, seg_tab);
   });
   return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
@@ -1379,35 +1474,33 @@ hipError_t cseg_fwd(float2* Z, const float2* Dn, long long B, const Geo& g, cons
 hipError_t cseg_bwd(float2* Zh, float2* Zg, const float2* Dn, long long B, const Geo& g, float* part,
                     const char* seg_tab, hipStream_t s) {
   const int rb = seg_rows(B, g, true);
-  const bool ok = with_seg_plan(g.L, [&]<class PL>() {
+  const bool ok = with_seg_plan<false>(g.L, [&]<class PL>() {
     hipLaunchKernelGGL(k_cseg_bwd<PL>, seg_grid<PL>((B + rb - 1) / rb * (g.R1 * g.R2)), dim3(Seg<PL>::THREADS), 0, s,
                        Zh, Zg, Dn, B, g, rb, reinterpret_cast<float2*>(part), seg_tab);
   });
   return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
-// Four segment workgroups, two column workgroups on each of 256 CUs.
+// Two workgroups on each of 256 CUs.
 int seg_rows(long long B, const Geo& g, bool cplx) {
-  return clamp_rows(B * (g.R1 * g.R2 / (cplx ? 1 : 2)) / 1024);
+  return clamp_rows(B * (g.R1 * g.R2 / (cplx ? 1 : 2)) / 512);
 }
 int col_rows(long long B, const Geo& g, int ew) { return clamp_rows(B * perm_geo(g, ew).nC / 512); }
 
 hipError_t colsum_parts(const float* part, long long P, long long W, float* out, Order how, const Geo& g,
                         const QuartetTabs* q, bool accumulate, hipStream_t s) {
-  int T, PT;
-  seg_shape(g.L, T, PT);
   const QuartetTabs qq = q ? *q : QuartetTabs{};
   const dim3 grid(unsigned((W / 4 + kSumCols - 1) / kSumCols)), block(kThreads);
   const int acc = accumulate ? 1 : 0;
   switch (how) {
     case Order::natural:
-      hipLaunchKernelGGL(k_colsum2<Order::natural>, grid, block, 0, s, part, P, W, out, g, qq, T, PT, acc);
+      hipLaunchKernelGGL(k_colsum2<Order::natural>, grid, block, 0, s, part, P, W, out, g, qq, acc);
       break;
     case Order::quartets:
-      hipLaunchKernelGGL(k_colsum2<Order::quartets>, grid, block, 0, s, part, P, W, out, g, qq, T, PT, acc);
+      hipLaunchKernelGGL(k_colsum2<Order::quartets>, grid, block, 0, s, part, P, W, out, g, qq, acc);
       break;
     case Order::spectrum:
-      hipLaunchKernelGGL(k_colsum2<Order::spectrum>, grid, block, 0, s, part, P, W, out, g, qq, T, PT, acc);
+      hipLaunchKernelGGL(k_colsum2<Order::spectrum>, grid, block, 0, s, part, P, W, out, g, qq, acc);
       break;
   }
   return hipGetLastError();
@@ -1422,9 +1515,10 @@ hipError_t colsum(const float* img, long long B, long long W, float* part, float
   return colsum_parts(part, P, W, out, Order::natural, g, nullptr, false, s);
 }
 
-bool build_seg_table(int L, std::vector<unsigned char>& host) {
+bool build_seg_table(int L, bool fwd, std::vector<unsigned char>& host) {
   bool ok = false;
-  (void)with_seg_plan(L, [&]<class PL>() { ok = build_complex_tables<PL>(host); });
+  auto build = [&]<class PL>() { ok = build_complex_tables<PL>(host); };
+  (void)(fwd ? with_seg_plan<true>(L, build) : with_seg_plan<false>(L, build));
   return ok;
 }
 

@@ -114,7 +114,7 @@ hipError_t dit2(float2* Z, long long B, const Geo& g, const float2* tw2, hipStre
 
 // Segment launches, in place.
 // Real rows: Mq holds the quartet coefficients of all layers in the order
-// the segment kernels read them, [K][pair][slot][kMqRows][T] (mq).
+// the segment kernels read them, [K][pair][kMqRows][k2] (mq).
 hipError_t mq(const float* D, const float* Bias, float4* Mq, int K, const Geo& g, const QuartetTabs& q,
               hipStream_t s);
 hipError_t seg_fwd(float2* Z, const float4* Mq, long long B, const Geo& g, bool bias, const char* seg_tab,
@@ -150,8 +150,9 @@ hipError_t colsum_parts(const float* part, long long P, long long W, float* out,
 // part, then the block sums.  W is a multiple of 4.
 hipError_t colsum(const float* img, long long B, long long W, float* part, float* out, hipStream_t s);
 
-// Constant table of the segment plan of L points (fill: host bytes).
-bool build_seg_table(int L, std::vector<unsigned char>& host);
+// Constant table of the segment plan of L points (fill: host bytes): the
+// forward launches' (seg_fwd, cseg_fwd), or the other launches'.
+bool build_seg_table(int L, bool fwd, std::vector<unsigned char>& host);
 
 }  // namespace mp
 }  // namespace acdc

@@ -6,12 +6,12 @@ GPU parity tests (every element, same tolerance)."""
 import pytest
 
 from oracle import acdc_oracle as O
-from paper_1511_05946_amd.workloads import FLAG_BIAS
+from paper_1511_05946_amd.workloads import FLAG_BIAS, FLAG_MULTIPASS
 from tests.test_gpu_parity import acdc, run_case  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
-P, R, CX = O.FLAG_PERM, O.FLAG_RELU, O.FLAG_COMPLEX
+P, R, CX, MP = O.FLAG_PERM, O.FLAG_RELU, O.FLAG_COMPLEX, FLAG_MULTIPASS
 
 
 # Narrow rows: one tile holds 256 (N = 8, 16) down to 16 rows (N = 512; up to
@@ -23,3 +23,33 @@ P, R, CX = O.FLAG_PERM, O.FLAG_RELU, O.FLAG_COMPLEX
                                        (64, 129, CX | P), (256, 65, CX | P)])
 def test_narrow_tile_sums(acdc, N, B, flags):  # noqa: F811
     run_case(acdc, N, 3, B, flags, seed=N + B)
+
+
+# Multi-pass rows: every segment plan (M / L = 2 up to N = 16384), the first
+# DIF radix 2 to 16, a second level (N = 2^18), one permutation set a row or
+# several; without permutations the DIT and DIF passes join in one launch.
+@pytest.mark.parametrize("N,K,B,flags", [(512, 3, 3, P | R | FLAG_BIAS | MP), (1024, 2, 3, R | MP),
+                                         (2048, 2, 5, P | FLAG_BIAS | MP), (8192, 3, 3, P | R | FLAG_BIAS | MP),
+                                         (16384, 2, 3, R | FLAG_BIAS | MP), (32768, 3, 2, R | MP),
+                                         (65536, 3, 3, R | FLAG_BIAS), (131072, 2, 2, P), (131072, 3, 2, FLAG_BIAS),
+                                         (1 << 18, 3, 2, 0), (512, 3, 3, CX | MP), (1024, 2, 3, CX | P | MP),
+                                         (2048, 2, 3, CX | P | MP), (8192, 3, 2, CX | P | MP), (32768, 3, 2, CX),
+                                         (131072, 2, 2, CX | P), (1 << 18, 2, 1, CX)])
+def test_multipass_plans(acdc, N, K, B, flags):  # noqa: F811
+    run_case(acdc, N, K, B, flags, seed=N % 1000 + B + flags)
+
+
+# Row blocks of the image sums: B rows x units / 512 rows a block, 1 to 16
+# (N = 65536: 4 pairs and 4 sets; N = 512: one pair and set; complex 32768: 8
+# segments and 4 sets), whole and ragged.
+@pytest.mark.parametrize("N,K,B,flags", [(65536, 1, 259, P), (512, 1, 1023, P | MP), (512, 2, 1537, P | MP),
+                                         (256, 2, 9001, FLAG_BIAS | MP), (32768, 1, 131, CX | P),
+                                         (512, 2, 4099, CX | MP)])
+def test_multipass_row_block_edges(acdc, N, K, B, flags):  # noqa: F811
+    run_case(acdc, N, K, B, flags, seed=N % 1000 + B)
+
+
+def test_multipass_tables_rebuilt_per_layer(acdc):  # noqa: F811
+    # five layers' permutation tables at the widest row are past 256 MB, so
+    # each layer's are built in turn; 256 sets a row
+    run_case(acdc, 1 << 22, 5, 1, P, seed=3)
