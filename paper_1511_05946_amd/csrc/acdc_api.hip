@@ -103,12 +103,21 @@ __attribute__((amdgpu_waves_per_eu(Launch<PL>::FWD_WPE))) void k_real_fwd(RealAr
   }
 }
 
-template <class PL, bool BIAS>
-__global__ __launch_bounds__(Launch<PL>::BWD_THREADS)
+// Persistent accumulation over tiles: whole tiles of the unbiased plans that
+// have it.
+template <class PL, bool BIAS, int ROWS>
+constexpr bool bwd_acc() {
+  return Launch<PL>::BWD_ACC && !BIAS && ROWS == Launch<PL>::BWD_ROWS;
+}
+
+// ROWS: rows per workgroup (bwd_rows)
+template <class PL, bool BIAS, int ROWS>
+__global__ __launch_bounds__(ROWS * PL::T)
 __attribute__((amdgpu_waves_per_eu(Launch<PL>::BWD_WPE))) void k_real_bwd(RealArgs a, long long ntiles) {
   using L = Launch<PL>;
-  constexpr bool ACC = L::BWD_ACC && !BIAS;
-  __shared__ float lds[L::BWD_LDS_FLOATS + (ACC ? L::ACC_FLOATS : 0)];
+  constexpr bool ACC = bwd_acc<PL, BIAS, ROWS>();
+  constexpr int LDS_FLOATS = ROWS * L::BWD_SLAB + L::BWD_TW_FLOATS;
+  __shared__ float lds[LDS_FLOATS + (ACC ? L::ACC_FLOATS : 0)];
   const int tid = threadIdx.x;
   const unsigned t = unsigned(tid) % PL::T;
   int r = tid / PL::T;
@@ -123,34 +132,34 @@ __attribute__((amdgpu_waves_per_eu(Launch<PL>::BWD_WPE))) void k_real_bwd(RealAr
       // persistent: workgroup w runs tiles w, w + G, ... (G = gridDim.x) and
       // adds them, in that order, into partial slot w
       static_assert(!L::BWD_TW_LDS, "persistent backward reads its twiddles from global memory");
-      float* const old = lds + L::BWD_LDS_FLOATS;
+      float* const old = lds + LDS_FLOATS;
       const unsigned w = blockIdx.x, nt = unsigned(ntiles);  // tiles < 2^31: batch <= 2^40 / N rows and N >= 1024
       for (unsigned tile = w; tile < nt; tile += gridDim.x)
-        real_backward_row<PL, L::BWD_ROWS, BIAS, true>(ctx, a, t, (long long)tile * L::BWD_ROWS, unsigned(r), tid,
+        real_backward_row<PL, ROWS, BIAS, true>(ctx, a, t, (long long)tile * ROWS, unsigned(r), tid,
                                                        w, rows, slab, GView::of(a.tab), tile == w ? nullptr : old);
     } else if constexpr (L::BWD_TW_LDS) {
       // one tile per workgroup, one partial slot per tile
       const long long tile = blockIdx.x;
       float* twl = lds;
-      copy_twiddles<PL>(twl, a.tab, tid, L::BWD_THREADS);
+      copy_twiddles<PL>(twl, a.tab, tid, ROWS * PL::T);
       ctx.sync_all();
-      real_backward_row<PL, L::BWD_ROWS, BIAS>(ctx, a, t, tile * L::BWD_ROWS, unsigned(r), tid, tile, rows, slab,
+      real_backward_row<PL, ROWS, BIAS>(ctx, a, t, tile * ROWS, unsigned(r), tid, tile, rows, slab,
                                                LdsView::of(twl));
     } else {
       const long long tile = blockIdx.x;
-      real_backward_row<PL, L::BWD_ROWS, BIAS>(ctx, a, t, tile * L::BWD_ROWS, unsigned(r), tid, tile, rows, slab,
+      real_backward_row<PL, ROWS, BIAS>(ctx, a, t, tile * ROWS, unsigned(r), tid, tile, rows, slab,
                                                GView::of(a.tab));
     }
   };
-  if constexpr (L::BWD_GROUP_SYNC) {
+  if constexpr (L::group_sync(ROWS)) {
     // rows of several waves meet at their own LDS counter (GroupCtx)
     using G = GroupCtx<PL::T>;
-    __shared__ unsigned words[G::kWords * L::BWD_ROWS];
-    if (tid < G::kWords * L::BWD_ROWS) words[tid] = 0u;
+    __shared__ unsigned words[G::kWords * ROWS];
+    if (tid < G::kWords * ROWS) words[tid] = 0u;
     DevCtx<PL::T>::lds_barrier();
     G ctx(&words[G::kWords * r]);
     body(ctx);
-    G::report(words, L::BWD_ROWS, tid, &sync_timeouts);
+    G::report(words, ROWS, tid, &sync_timeouts);
   } else {
     DevCtx<PL::T> ctx;
     body(ctx);
@@ -212,27 +221,27 @@ __attribute__((amdgpu_waves_per_eu(Launch<PL>::FWD_WPE))) void k_cplx_fwd(CplxAr
   cplx_forward_row<PL>(ctx, a, t, (long long)blockIdx.x * L::FWD_ROWS, unsigned(r), lds + r * L::FWD_SLAB);
 }
 
-template <class PL>
-__global__ __launch_bounds__(Launch<PL>::BWD_THREADS)
+template <class PL, int ROWS>
+__global__ __launch_bounds__(ROWS * PL::T)
 __attribute__((amdgpu_waves_per_eu(Launch<PL>::BWD_WPE))) void k_cplx_bwd(CplxArgs a) {
   using L = Launch<PL>;
-  __shared__ float lds[L::BWD_ROWS * L::BWD_SLAB];
+  __shared__ float lds[ROWS * L::BWD_SLAB];
   const int tid = threadIdx.x;
   const unsigned t = unsigned(tid) % PL::T;
   int r = tid / PL::T;
   if constexpr (PL::T >= 64) r = __builtin_amdgcn_readfirstlane(r);  // one row per whole wave
-  if constexpr (L::BWD_GROUP_SYNC) {
+  if constexpr (L::group_sync(ROWS)) {
     using G = GroupCtx<PL::T>;
-    __shared__ unsigned words[G::kWords * L::BWD_ROWS];
-    if (tid < G::kWords * L::BWD_ROWS) words[tid] = 0u;
+    __shared__ unsigned words[G::kWords * ROWS];
+    if (tid < G::kWords * ROWS) words[tid] = 0u;
     DevCtx<PL::T>::lds_barrier();
     G ctx(&words[G::kWords * r]);
-    cplx_backward_row<PL, L::BWD_ROWS>(ctx, a, t, (long long)blockIdx.x * L::BWD_ROWS, unsigned(r), tid,
+    cplx_backward_row<PL, ROWS>(ctx, a, t, (long long)blockIdx.x * ROWS, unsigned(r), tid,
                                        (long long)blockIdx.x, lds, lds + r * L::BWD_SLAB);
-    G::report(words, L::BWD_ROWS, tid, &sync_timeouts);
+    G::report(words, ROWS, tid, &sync_timeouts);
   } else {
     DevCtx<PL::T> ctx;
-    cplx_backward_row<PL, L::BWD_ROWS>(ctx, a, t, (long long)blockIdx.x * L::BWD_ROWS, unsigned(r), tid,
+    cplx_backward_row<PL, ROWS>(ctx, a, t, (long long)blockIdx.x * ROWS, unsigned(r), tid,
                                        (long long)blockIdx.x, lds, lds + r * L::BWD_SLAB);
   }
 }
@@ -476,7 +485,14 @@ long long fwd_blocks(int64_t batch) {
 }
 template <class PL>
 long long bwd_tiles(int64_t batch) {
-  return (batch + Launch<PL>::BWD_ROWS - 1) / Launch<PL>::BWD_ROWS;
+  return (batch + bwd_rows<PL>(batch) - 1) / bwd_rows<PL>(batch);
+}
+// f.template operator()<ROWS>() for the call's rows per backward workgroup.
+template <class PL, class F>
+void with_bwd_rows(int64_t batch, F&& f) {
+  using L = Launch<PL>;
+  if (L::BWD_ROWS_FEW != L::BWD_ROWS && bwd_rows<PL>(batch) == L::BWD_ROWS_FEW) f.template operator()<L::BWD_ROWS_FEW>();
+  else f.template operator()<L::BWD_ROWS>();
 }
 
 // Rows per forward workgroup of the plans with several waves per workgroup
@@ -539,7 +555,11 @@ WsLayout bwd_layout(int64_t batch, int32_t N, int32_t K, uint32_t flags, bool ha
   WsLayout w;
   const bool bias = (flags & kFlagBias) != 0;
   auto f = [&]<class PL>() {
-    const long long tiles = bwd_tiles<PL>(batch);
+    // a buffer sized for one batch also serves the smaller ones, whose tiles
+    // may be more (at most kCus, see bwd_rows)
+    long long tiles = bwd_tiles<PL>(batch);
+    if (Launch<PL>::BWD_ROWS_FEW != Launch<PL>::BWD_ROWS && batch > kCus * Launch<PL>::BWD_ROWS_FEW && tiles < kCus)
+      tiles = kCus;
     w.partial = align256(size_t(tiles) * K * partial_entries4<PL>(bias) * sizeof(float4));
     if constexpr (!PL::kComplex) {
       // the bias gradient's DCT reads w, qa, qb' from the quartet table
@@ -765,8 +785,7 @@ MpBwdWs mp_bwd_ws(int64_t batch, int32_t N, int32_t K, uint32_t flags, bool have
   w.zhg = take(2 * rows);
   w.tmp = take(perm_on ? rows : 0);
   auto blocks = [&](int rb) { return size_t((batch + rb - 1) / rb); };
-  const size_t nseg = blocks(mp::seg_rows(batch, g, cplx)), ncol = blocks(mp::col_rows(batch, g, mp_ew(flags)));
-  w.part = take((nseg > ncol ? nseg : ncol) * rowb);
+  w.part = take(size_t(mp::max_blocks(batch, g, mp_ew(flags))) * rowb);
   w.zsum = take(bias ? rowb : 0);
   w.partB = take(bias ? blocks(mp::kMaxRows) * rowb : 0);
   w.stash = take(have_saved ? 0 : saved_floats(batch, N, K, flags) * sizeof(float));
@@ -1050,7 +1069,8 @@ extern "C" int acdc_prepare(int32_t N, uint32_t flags) {
     (void)resident_workgroups(reinterpret_cast<const void*>(&k_real_fwd<PL, false>), Launch<PL>::FWD_THREADS);
     (void)resident_workgroups(reinterpret_cast<const void*>(&k_real_fwd<PL, true>), Launch<PL>::FWD_THREADS);
     if constexpr (Launch<PL>::BWD_ACC)
-      (void)resident_workgroups(reinterpret_cast<const void*>(&k_real_bwd<PL, false>), Launch<PL>::BWD_THREADS);
+      (void)resident_workgroups(reinterpret_cast<const void*>(&k_real_bwd<PL, false, Launch<PL>::BWD_ROWS>),
+                                Launch<PL>::BWD_THREADS);
   });
   return ACDC_OK;
 }
@@ -1194,7 +1214,9 @@ extern "C" int acdc_backward(const float* x, const float* grad_y, const float* A
         hipError_t e;
         {
           ProfScope prof(1, s);
-          hipLaunchKernelGGL(k_cplx_bwd<PL>, dim3(unsigned(tiles)), dim3(L::BWD_THREADS), 0, s, a);
+          with_bwd_rows<PL>(batch, [&]<int ROWS>() {
+            hipLaunchKernelGGL((k_cplx_bwd<PL, ROWS>), dim3(unsigned(tiles)), dim3(ROWS * PL::T), 0, s, a);
+          });
           e = hipGetLastError();
         }
         if (e != hipSuccess) {
@@ -1224,9 +1246,11 @@ extern "C" int acdc_backward(const float* x, const float* grad_y, const float* A
       // partial slots: one per tile, or one per resident workgroup of the
       // persistent (accumulating) unbiased backward
       const long long slots =
-          (L::BWD_ACC && !bias_on)
-              ? persistent_grid(
-                    resident_workgroups(reinterpret_cast<const void*>(&k_real_bwd<PL, false>), L::BWD_THREADS).n, tiles)
+          (L::BWD_ACC && !bias_on && bwd_rows<PL>(batch) == L::BWD_ROWS)
+              ? persistent_grid(resident_workgroups(reinterpret_cast<const void*>(&k_real_bwd<PL, false, L::BWD_ROWS>),
+                                                    L::BWD_THREADS)
+                                    .n,
+                                tiles)
               : tiles;
       float4* Mq = reinterpret_cast<float4*>(ws + w.off_mq);
       int4* P16 = batch > 0 ? perm16_of<PL>(Mq, K, flags) : nullptr;
@@ -1246,10 +1270,13 @@ extern "C" int acdc_backward(const float* x, const float* grad_y, const float* A
         hipError_t e;
         {
           ProfScope prof(1, s);
-          if (bias_on)
-            hipLaunchKernelGGL((k_real_bwd<PL, true>), dim3(unsigned(tiles)), dim3(L::BWD_THREADS), 0, s, a, tiles);
-          else
-            hipLaunchKernelGGL((k_real_bwd<PL, false>), dim3(unsigned(slots)), dim3(L::BWD_THREADS), 0, s, a, tiles);
+          with_bwd_rows<PL>(batch, [&]<int ROWS>() {
+            const dim3 block(ROWS * PL::T);
+            if (bias_on)
+              hipLaunchKernelGGL((k_real_bwd<PL, true, ROWS>), dim3(unsigned(tiles)), block, 0, s, a, tiles);
+            else
+              hipLaunchKernelGGL((k_real_bwd<PL, false, ROWS>), dim3(unsigned(slots)), block, 0, s, a, tiles);
+          });
           e = hipGetLastError();
         }
         if (e != hipSuccess) {

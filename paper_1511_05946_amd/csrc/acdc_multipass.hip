@@ -1481,11 +1481,26 @@ hipError_t cseg_bwd(float2* Zh, float2* Zg, const float2* Dn, long long B, const
   return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
-// Two workgroups on each of 256 CUs.
-int seg_rows(long long B, const Geo& g, bool cplx) {
-  return clamp_rows(B * (g.R1 * g.R2 / (cplx ? 1 : 2)) / 512);
+namespace {
+// Workgroups of a whole row block, and the blocks that make two of them on
+// each of 256 CUs.
+constexpr long long kWant = 512;
+long long seg_units(const Geo& g, bool cplx) { return g.R1 * g.R2 / (cplx ? 1 : 2); }
+}  // namespace
+
+int seg_rows(long long B, const Geo& g, bool cplx) { return clamp_rows(B * seg_units(g, cplx) / kWant); }
+int col_rows(long long B, const Geo& g, int ew) { return clamp_rows(B * perm_geo(g, ew).nC / kWant); }
+// With u units a row there are at most B blocks, fewer than 2 kWant / u while
+// blocks have fewer than kMaxRows rows, and B / kMaxRows from there on.
+long long max_blocks(long long B, const Geo& g, int ew) {
+  long long most = (B + kMaxRows - 1) / kMaxRows;
+  for (long long u : {seg_units(g, ew == 2), (long long)perm_geo(g, ew).nC}) {
+    const long long few = (2 * kWant + u - 1) / u + 1;
+    const long long n = B < few ? B : few;
+    most = n > most ? n : most;
+  }
+  return most;
 }
-int col_rows(long long B, const Geo& g, int ew) { return clamp_rows(B * perm_geo(g, ew).nC / 512); }
 
 hipError_t colsum_parts(const float* part, long long P, long long W, float* out, Order how, const Geo& g,
                         const QuartetTabs* q, bool accumulate, hipStream_t s) {

@@ -138,6 +138,9 @@ hipError_t cseg_bwd(float2* Zh, float2* Zg, const float2* Dn, long long B, const
 constexpr int kMaxRows = 16;
 int seg_rows(long long B, const Geo& g, bool cplx);
 int col_rows(long long B, const Geo& g, int ew);
+// An upper bound of the blocks of either for every batch up to B (sizes the
+// block sums: a workspace of one batch serves the smaller ones).
+long long max_blocks(long long B, const Geo& g, int ew);
 
 // Fixed-order sums over row blocks: out[w] (+)= sum over p of part[p][w] in
 // block order, column w being in the order of the launch that wrote it.

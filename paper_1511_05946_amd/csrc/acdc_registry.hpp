@@ -124,8 +124,11 @@ struct Launch {
       : PL::T == 192                    ? ACDC_BWD_ROWS_T192
       : (PL::kComplex && PL::T == 128)  ? ACDC_BWD_ROWS_CPLX_T128
                                         : (TW_LDS ? WIDE_ROWS : (PL::T >= ACDC_BWD_THREADS ? 1 : ACDC_BWD_THREADS / PL::T));
+  // Half the rows per backward workgroup, for batches that leave CUs idle at
+  // BWD_ROWS (see bwd_rows); only where those fill eight waves, or six.
+  static constexpr int BWD_ROWS_FEW = BWD_ROWS > 1 && BWD_ROWS * PL::T > 256 ? BWD_ROWS / 2 : BWD_ROWS;
   static constexpr bool BWD_TW_LDS = TW_LDS && ACDC_TW_LDS_BWD;
-  static constexpr bool BWD_GROUP_SYNC = ACDC_GROUP_SYNC && PL::T > 64 && PL::T % 64 == 0 && BWD_ROWS > 1;
+  static constexpr bool group_sync(int rows) { return ACDC_GROUP_SYNC && PL::T > 64 && PL::T % 64 == 0 && rows > 1; }
   static constexpr int FWD_THREADS = FWD_ROWS * PL::T;
   static constexpr int BWD_THREADS = BWD_ROWS * PL::T;
   static constexpr int TW_FLOATS = TW_LDS ? PL::TW_FLOAT2 * 2 : 0;  // LDS copy of the twiddles
@@ -152,6 +155,21 @@ struct Launch {
   static_assert(FWD_LDS_BYTES <= kLdsBytes && BWD_LDS_BYTES <= kLdsBytes, "LDS budget");
   static_assert(BWD_THREADS <= 1024 && FWD_THREADS <= 1024, "workgroup size");
 };
+
+// Rows per backward workgroup (one partial of the parameter gradients each):
+// BWD_ROWS, or half of them while that still leaves every CU at most one
+// workgroup.  Eight waves put two on each SIMD of half the CUs where four
+// put one on each SIMD of twice as many; the partials, twice as many, are
+// few at such batches.  Depends on the batch alone (it sizes the workspace).
+// Forward and backward, K = 8 (part of it the forward's own spread): N = 4096,
+// 300 rows 269 -> 206 us, 1100 rows 287 -> 273; N = 9216, 100 rows 271 -> 229;
+// complex N = 1024, 2000 rows 374 -> 281, N = 4096, 500 rows 267 -> 246.
+constexpr long long kCus = 256;
+template <class PL>
+constexpr int bwd_rows(long long batch) {
+  using L = Launch<PL>;
+  return batch <= kCus * L::BWD_ROWS_FEW ? L::BWD_ROWS_FEW : L::BWD_ROWS;
+}
 
 // ACDC_ONLY_N=<width> instantiates a single real plan and ACDC_ONLY_CN a
 // single complex plan (quick development builds); ACDC_PLAN_SUBSET

@@ -25,6 +25,32 @@ def test_narrow_tile_sums(acdc, N, B, flags):  # noqa: F811
     run_case(acdc, N, 3, B, flags, seed=N + B)
 
 
+# Backward workgroups of half the rows while those leave every CU at most one
+# workgroup (256 of them): the last such batch and the first beyond it.
+@pytest.mark.parametrize("N,few,flags", [(4096, 4, P | R | FLAG_BIAS), (8192, 2, P), (9216, 1, P), (16384, 1, P | FLAG_BIAS),
+                                         (64, 64, CX | P), (1024, 8, CX | P), (4096, 2, CX)])
+def test_backward_rows_rule(acdc, N, few, flags):  # noqa: F811
+    for B in (256 * few, 256 * few + 1):
+        run_case(acdc, N, 2 if flags & R else 1, B, flags, seed=N + B)
+
+
+def test_workspace_of_a_batch_serves_smaller_ones(acdc):  # noqa: F811
+    # one workspace for a whole epoch: its last, ragged batch may run more
+    # (smaller) backward workgroups than the full ones
+    import torch
+    N, K = 4096, 2
+    full = torch.zeros(1100, N, device="cuda")
+    ws = torch.empty(acdc.backward_workspace_bytes(full, K, 0, have_saved=True), dtype=torch.uint8, device="cuda")
+    x = torch.randn(1003, N, device="cuda")
+    A, D = torch.ones(K, N, device="cuda"), torch.ones(K, N, device="cuda")
+    _, saved = acdc.forward(x, A, D, None, 0, save=True)
+    gx, gA, _ = acdc.backward(x, x, A, D, None, 0, saved=saved, workspace=ws)
+    # identity layers: dL/dx = x, dL/da = sum of x^2 over the rows
+    ref = (x.double() ** 2).sum(0)
+    assert float((gx - x).abs().max()) < 1e-5
+    assert float(((gA.double() - ref) / ref).abs().max()) < 1e-5
+
+
 # Multi-pass rows: every segment plan (M / L = 2 up to N = 16384), the first
 # DIF radix 2 to 16, a second level (N = 2^18), one permutation set a row or
 # several; without permutations the DIT and DIF passes join in one launch.
