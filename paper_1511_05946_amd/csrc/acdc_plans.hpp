@@ -58,7 +58,9 @@ constexpr int ilog2(int v) {
   return l;
 }
 
-template <int N_, int T_, int R0_, int R1_, int R2_ = 1, int R3_ = 1>
+// PAD_: log2 of the elements per pad slot of the LDS slab, where another
+// value than the first radix ran faster (0: the first radix).
+template <int N_, int T_, int R0_, int R1_, int R2_ = 1, int R3_ = 1, int PAD_ = 0>
 struct RealPlan {
   static constexpr bool kComplex = false;
   static constexpr int N = N_;
@@ -94,7 +96,7 @@ struct RealPlan {
   // so each thread would hold one precomputed address per output (about 48
   // VGPRs, spilled) instead of one base per butterfly.
   static constexpr int PADSH =
-      !ACDC_LDS_PAD ? 30 : (ilog2(R0_) >= 2 && (1 << ilog2(R0_)) == R0_ ? ilog2(R0_) : 30);
+      !ACDC_LDS_PAD ? 30 : PAD_ > 0 ? PAD_ : (ilog2(R0_) >= 2 && (1 << ilog2(R0_)) == R0_ ? ilog2(R0_) : 30);
   static constexpr int FFT_FLOATS = 2 * (M + (M >> PADSH));
   static constexpr int SLAB = cmax(cmax(N, QF), FFT_FLOATS);  // LDS floats per row
   // twiddle table (float2) offsets: forward passes 1.., then inverse passes

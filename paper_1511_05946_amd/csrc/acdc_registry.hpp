@@ -13,12 +13,28 @@ namespace acdc {
 using RP8 = RealPlan<8, 1, 2, 2>;
 using RP16 = RealPlan<16, 1, 2, 4>;
 using RP32 = RealPlan<32, 2, 4, 4>;
-using RP64 = RealPlan<64, 2, 4, 8>;
-using RP128 = RealPlan<128, 4, 8, 8>;
-using RP256 = RealPlan<256, 4, 16, 8>;
-using RP512 = RealPlan<512, 16, 8, 4, 8>;  // 16 complex values per thread
+//
+// Few values per thread keep a row's serial chain through the layers short,
+// which is the time of a small batch, and leave registers for more waves; a
+// third pass costs a large batch an exchange.  Step (forward + backward, K =
+// 8) with the plans before and now:
+//   N = 64    8 values per thread instead of 16: 64 rows 95 -> 59 us, 200000
+//             rows 536 -> 456
+//   N = 256   8 instead of 32: 64 rows 153 -> 59, 60000 rows 516 -> 498
+//   N = 2048  16 instead of 32, workgroups of four rows: 16 rows 183 -> 101,
+//             2500 rows 267 -> 211, 16384 rows (K = 12) 1780 -> 1732
+// and not for N = 128 (4 4 4: 100000 rows 404 -> 469), 8192 (8 8 8 8 on 256
+// threads: 4096 rows 1457 -> 1865) and 16384 (512 threads: 1892 -> 2611).
+// The slabs of these rows are padded by one slot per 16 (N = 512: 32)
+// elements, not by the first radix: at 64 and 256 that was 3 and 7 % of a
+// large batch, at 512 (3 %) and 128 (2 %) it is all there is to gain; at 1024,
+// 4096, 8192 and 16384 other pads than the first radix lose 1 to 30 %.
+using RP64 = RealPlan<64, 4, 4, 2, 4, 1, 4>;
+using RP128 = RealPlan<128, 4, 8, 8, 1, 1, 4>;
+using RP256 = RealPlan<256, 16, 4, 8, 4, 1, 4>;
+using RP512 = RealPlan<512, 16, 8, 4, 8, 1, 5>;  // 16 complex values per thread
 using RP1024 = RealPlan<1024, 32, 8, 8, 8>;  // 16 complex values per thread: 125 VGPRs forward, 4 waves per SIMD
-using RP2048 = RealPlan<2048, 32, 16, 4, 16>;
+using RP2048 = RealPlan<2048, 64, 8, 16, 8, 1, 4>;
 using RP4096 = RealPlan<4096, 64, 16, 8, 16>;
 using RP8192 = RealPlan<8192, 128, 16, 16, 16>;
 using RP9216 = RealPlan<9216, 192, 12, 8, 4, 12>;
@@ -37,7 +53,9 @@ using CP1024 = ComplexPlan<1024, 32, 32, 32>;
 using CP2048 = ComplexPlan<2048, 64, 32, 2, 32>;
 using CP4096 = ComplexPlan<4096, 128, 16, 16, 16>;  // two butterflies per thread at both ends: adjacent pairs
 using CP8192 = ComplexPlan<8192, 256, 32, 8, 32>;
-using CP16384 = ComplexPlan<16384, 512, 32, 16, 32>;
+// radix 32 at the ends spilled: backward (K = 8) 1024 rows 2866 -> 2083 us,
+// 16 rows 371 -> 265, forward unchanged
+using CP16384 = ComplexPlan<16384, 512, 16, 8, 8, 16>;
 
 // Rows per workgroup.  Forward rows are independent; backward rows of one
 // workgroup are reduced together into one partial of dL/da, dL/dd.
@@ -67,7 +85,7 @@ using CP16384 = ComplexPlan<16384, 512, 32, 16, 32>;
 #ifndef ACDC_TW_LDS_T
 #define ACDC_TW_LDS_T 0
 #endif
-// Rows per backward workgroup for real rows of 32 threads (N = 1024, 2048):
+// Rows per backward workgroup for real rows of 32 threads (N = 1024):
 // 8 (four waves, three workgroups per CU at 3 waves per SIMD) ran the
 // backward 6-8 % faster than 16, more than the doubled partials cost.
 #ifndef ACDC_BWD_ROWS_T32
@@ -114,7 +132,12 @@ template <class PL>
 struct Launch {
   static constexpr int FWD_SLAB = PL::kComplex ? PL::SLAB : cmax(PL::N, PL::FFT_FLOATS);  // floats per row
   static constexpr int BWD_SLAB = PL::SLAB;
-  static constexpr int WIDE_ROWS = PL::T <= 16 ? ACDC_NARROW_THREADS / PL::T : PL::T <= 64 ? 512 / PL::T : 1;
+  // (N = 2048: 256 threads, two workgroups a CU with their twiddle copies;
+  // with 512 the forward of 2500 rows took 94 us instead of 75)
+  static constexpr int WIDE_ROWS = PL::T <= 16                     ? ACDC_NARROW_THREADS / PL::T
+                                   : PL::T == 64 && PL::N <= 2048 ? 256 / PL::T
+                                   : PL::T <= 64                   ? 512 / PL::T
+                                                                   : 1;
   static constexpr bool TW_LDS = ACDC_TW_LDS && !PL::kComplex && (PL::T <= 64 || PL::T == ACDC_TW_LDS_T) &&
                                  WIDE_ROWS * PL::SLAB * 4 + PL::TW_FLOAT2 * 8 <= kLdsBytes;
   static constexpr int FWD_ROWS =

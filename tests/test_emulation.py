@@ -80,6 +80,10 @@ def test_real_small(emu, N, flags):
     check(emu, N, 3, 9, flags, seed=N)
 
 
+def test_real_2048_four_rows_a_workgroup(emu):
+    check(emu, 2048, 2, 6, O.FLAG_PERM | O.FLAG_RELU | FLAG_BIAS, seed=2048, with_saved=True)
+
+
 @pytest.mark.parametrize("N", [8, 16, 64, 256, 1024])
 def test_complex_small(emu, N):
     check(emu, N, 2, 5, O.FLAG_COMPLEX | O.FLAG_PERM, seed=N)
