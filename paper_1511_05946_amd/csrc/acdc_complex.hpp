@@ -318,6 +318,7 @@ __host__ __device__ void cplx_forward_row(Ctx& ctx, const CplxArgs& a, unsigned 
     // stash u_k: u_1..u_{K-1} in slots 0..K-2, and with PERM u_0 in slot K-1
     if (a.saved != nullptr && (k > 0 || (a.flags & 1u)) && valid)
       O::store(GView::of(a.saved + ((long long)(k > 0 ? k - 1 : a.K - 1) * a.batch + row0) * RS), roff, v, t);
+    if (a.y == nullptr && k == a.K - 1) break;  // recompute: only the layer inputs are wanted
     if constexpr (AHEAD) {
       O::template mul_diag<false, false>(v, dg, 1.0f, t);
       O::template fft<false>(ctx, v, t, slab2, tab, [&] { O::template ld_diag<true>(dg, dk, t); });
