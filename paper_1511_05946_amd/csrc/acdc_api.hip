@@ -74,11 +74,16 @@ __device__ __forceinline__ void copy_twiddles(float* dst, const char* tab, int t
 // The forward kernel is persistent: workgroup b handles row groups (tiles)
 // b, b + gridDim.x, ... of `rpw` rows (fwd_rows).  Rows are independent, so
 // results do not depend on the grid size or on rpw.
-template <class PL, bool BIAS>
-__global__ __launch_bounds__(Launch<PL>::FWD_THREADS)
-__attribute__((amdgpu_waves_per_eu(Launch<PL>::FWD_WPE))) void k_real_fwd(RealArgs a, long long ntiles, int rpw) {
+constexpr int kAloneThreads = 256;
+// ALONE: at most one wave per SIMD (fwd_rows), workgroups of kAloneThreads.
+// K = 12, without and with: N = 4096, 16 rows 101 and 93 us, 1024 x 700 rows
+// 48 and 44, 64 x 500 22 and 21.
+template <class PL, bool BIAS, bool ALONE>
+__global__ __launch_bounds__(ALONE ? kAloneThreads : Launch<PL>::FWD_THREADS)
+__attribute__((amdgpu_waves_per_eu(ALONE ? 1 : Launch<PL>::FWD_WPE))) void k_real_fwd(RealArgs a, long long ntiles, int rpw) {
   using L = Launch<PL>;
-  __shared__ float lds[L::FWD_LDS_FLOATS];
+  constexpr int THREADS = ALONE ? kAloneThreads : L::FWD_THREADS;
+  __shared__ float lds[L::TW_FLOATS + THREADS / PL::T * L::FWD_SLAB];
   DevCtx<PL::T> ctx;
   const int tid = threadIdx.x;
   const unsigned t = unsigned(tid) % PL::T;
@@ -90,12 +95,12 @@ __attribute__((amdgpu_waves_per_eu(Launch<PL>::FWD_WPE))) void k_real_fwd(RealAr
   float* slab = rows + r * L::FWD_SLAB;
   if constexpr (L::TW_LDS) {
     float* twl = lds;
-    copy_twiddles<PL>(twl, a.tab, tid, L::FWD_THREADS);
+    copy_twiddles<PL>(twl, a.tab, tid, THREADS);
     ctx.sync_all();
     if (r >= rpw) return;  // whole waves, which have no row: no barrier follows
     const LdsView tw = LdsView::of(twl);
     for (long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x)
-      real_forward_row<PL, BIAS>(ctx, a, t, tile * rpw, unsigned(r), slab, tw);
+      real_forward_row<PL, BIAS, ALONE>(ctx, a, t, tile * rpw, unsigned(r), slab, tw);
   } else {
     const GView tw = GView::of(a.tab);
     for (long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x)
@@ -598,12 +603,20 @@ int launch_real_mq(const float* D, const float* Bias, float4* Mq, int K, const c
 
 template <class PL, bool BIAS>
 void launch_real_fwd_k(const RealArgs& a, hipStream_t s, bool remember) {
-  const Resident res = resident_workgroups(reinterpret_cast<const void*>(&k_real_fwd<PL, BIAS>),
-                                           Launch<PL>::FWD_THREADS, remember);
+  using L = Launch<PL>;
+  const Resident res = resident_workgroups(reinterpret_cast<const void*>(&k_real_fwd<PL, BIAS, false>),
+                                           L::FWD_THREADS, remember);
   const int rpw = fwd_rows<PL>(a.batch, res.cus);
   const long long tiles = (a.batch + rpw - 1) / rpw;
-  hipLaunchKernelGGL((k_real_fwd<PL, BIAS>), dim3(unsigned(persistent_grid(res.n, tiles))), dim3(Launch<PL>::FWD_THREADS), 0, s, a, tiles,
-                     rpw);
+  if constexpr (L::TW_LDS) {
+    if (rpw * PL::T <= kAloneThreads && tiles <= res.cus) {
+      hipLaunchKernelGGL((k_real_fwd<PL, BIAS, true>), dim3(unsigned(tiles)), dim3(kAloneThreads), 0, s, a, tiles,
+                         rpw);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_real_fwd<PL, BIAS, false>), dim3(unsigned(persistent_grid(res.n, tiles))),
+                     dim3(L::FWD_THREADS), 0, s, a, tiles, rpw);
 }
 
 template <class PL>
@@ -1066,8 +1079,8 @@ extern "C" int acdc_prepare(int32_t N, uint32_t flags) {
   if (rc != ACDC_OK || (flags & kFlagComplex)) return rc;
   // cache the persistent grids, so that later calls look them up
   dispatch_real(N, [&]<class PL>() {
-    (void)resident_workgroups(reinterpret_cast<const void*>(&k_real_fwd<PL, false>), Launch<PL>::FWD_THREADS);
-    (void)resident_workgroups(reinterpret_cast<const void*>(&k_real_fwd<PL, true>), Launch<PL>::FWD_THREADS);
+    (void)resident_workgroups(reinterpret_cast<const void*>(&k_real_fwd<PL, false, false>), Launch<PL>::FWD_THREADS);
+    (void)resident_workgroups(reinterpret_cast<const void*>(&k_real_fwd<PL, true, false>), Launch<PL>::FWD_THREADS);
     if constexpr (Launch<PL>::BWD_ACC)
       (void)resident_workgroups(reinterpret_cast<const void*>(&k_real_bwd<PL, false, Launch<PL>::BWD_ROWS>),
                                 Launch<PL>::BWD_THREADS);

@@ -429,10 +429,11 @@ struct RealOps {
     for (int r = 0; r < NR; ++r)
       tb.m[slot][r] = mq.ld4(t * 16u, unsigned((slot * kMqRows + MqTabs<NR, R2>::row(r)) * T * 16));
   }
-  template <int NR, int R2>
+  // the first PF slots, or with ALL every slot
+  template <bool ALL = false, int NR, int R2>
   __host__ __device__ __forceinline__ static void load_mhead(MqTabs<NR, R2>& tb, unsigned t, GView mq) {
 #pragma unroll
-    for (int s = 0; s < MqTabs<NR, R2>::PF; ++s) load_mslot(tb, s, t, mq);
+    for (int s = 0; s < (ALL ? NSL : MqTabs<NR, R2>::PF); ++s) load_mslot(tb, s, t, mq);
   }
   // Forward middle's table: c0, c1, plus c3 with a bias.
   template <bool BIAS>
@@ -453,9 +454,9 @@ struct RealOps {
   // Forward middle of a layer, in place per quartet slot: Z (frequency
   // layout) -> DCT-II quartet -> * d (+ b) -> DCT-III pre-twiddle -> Z', as
   // split + sym_back (32 operations per slot; 4 more add the bias term).
-  template <bool BIAS>
+  template <bool BIAS, bool ALL = false>
   __host__ __device__ __forceinline__ static void mid(float2 (&v)[P], unsigned t, GView mq, FwdTabs<BIAS>& tb) {
-    constexpr int PFM = FwdTabs<BIAS>::PF;
+    constexpr int PFM = ALL ? NSL : FwdTabs<BIAS>::PF;  // slots loaded ahead (load_mhead)
     const bool sp = (t == 0);
     permute0(v, sp);
 #pragma unroll
@@ -555,8 +556,11 @@ struct RealArgs {
 };
 
 // BIAS: the layers add the D-domain bias (Sec. 6.2), carried by row c3 of
-// the quartet table.
-template <class PL, bool BIAS, class Ctx, class TW>
+// the quartet table.  ALONE: the wave has its SIMD to itself, so nothing else
+// hides its loads, but it has twice the registers: a layer's coefficients
+// are all loaded at its start, and the next layer's indices and diagonal
+// before this one's inverse FFT.
+template <class PL, bool BIAS, bool ALONE = false, class Ctx, class TW>
 __host__ __device__ void real_forward_row(Ctx& ctx, const RealArgs& a, unsigned t, long long row0, unsigned rr,
                                           float* slab, TW tab) {
   using O = RealOps<PL>;
@@ -571,10 +575,17 @@ __host__ __device__ void real_forward_row(Ctx& ctx, const RealArgs& a, unsigned 
   int4 idx[NCH];
   float4 av[NCH];
   O::load(GView::of(a.x + row0 * N), roff, v, L, valid);
+  auto load_layer = [&](int k) {
+    if (permute) O::template load_idx<false>(idx, GView::of(a.perm + (long long)k * N), L, t);
+    O::load_vec(av, GView::of(a.A + (long long)k * N), L);
+  };
+  if constexpr (ALONE) load_layer(0);
   for (int k = 0; k < a.K; ++k) {
     const GView ak = GView::of(a.A + (long long)k * N);
     const GView mq = GView::of(a.Mq + (long long)k * NSL * kMqRows * T);
-    if (permute) {
+    if constexpr (ALONE) {
+      if (permute) O::template gather<false>(ctx, v, L, slab, idx, [] {});
+    } else if (permute) {
       O::template load_idx<false>(idx, GView::of(a.perm + (long long)k * N), L, t);
       O::template gather<false>(ctx, v, L, slab, idx, [&] { O::load_vec(av, ak, L); });
     } else {
@@ -588,8 +599,18 @@ __host__ __device__ void real_forward_row(Ctx& ctx, const RealArgs& a, unsigned 
     if (a.y == nullptr && k == a.K - 1) break;  // recompute: only the layer inputs are wanted
     O::scale(v, av);
     typename O::template FwdTabs<BIAS> tb;
-    O::template fft<false>(ctx, v, t, slab2, tab, [&] { O::load_mhead(tb, t, mq); });
-    O::template mid<BIAS>(v, t, mq, tb);
+    if constexpr (ALONE) {
+      O::template load_mhead<true>(tb, t, mq);
+      ACDC_SCHED_FENCE();
+    }
+    O::template fft<false>(ctx, v, t, slab2, tab, [&] {
+      if constexpr (!ALONE) O::load_mhead(tb, t, mq);
+    });
+    O::template mid<BIAS, ALONE>(v, t, mq, tb);
+    if constexpr (ALONE) {
+      load_layer(k + 1 < a.K ? k + 1 : k);
+      ACDC_SCHED_FENCE();
+    }
     O::template fft<true>(ctx, v, t, slab2, tab, [] {});
     if ((a.flags & kFlagRelu) && k < a.K - 1) O::relu(v);
   }
