@@ -682,13 +682,17 @@ __global__ __launch_bounds__(kThreads) void k_part(float2* __restrict__ Z, long 
 // operations; complex rows 78 -> 69 us, real ones 102 -> 92 us for 134 MB
 // of rows), which in the backward, with several arrays and the image sums
 // in registers, spills (real 181 -> 294 us) or gains nothing (complex).
-using SP64 = ComplexPlan<64, 8, 8, 8>;
-using SP128 = ComplexPlan<128, 16, 8, 2, 8>;
-using SP256 = ComplexPlan<256, 32, 8, 4, 8>;
-using SP512 = ComplexPlan<512, 64, 8, 8, 8>;
-using SP1024 = ComplexPlan<1024, 128, 8, 4, 4, 8>;
+// Slabs are padded by one slot per 16 elements: an LDS access of 8 bytes a
+// lane runs 16 lanes at a time over 32 banks, so 16 neighbouring elements
+// must not hold a pad (pads of 8, the first radix: 3 % slower in the
+// backward).
+using SP64 = ComplexPlan<64, 8, 8, 8, 1, 1, 4>;
+using SP128 = ComplexPlan<128, 16, 8, 2, 8, 1, 4>;
+using SP256 = ComplexPlan<256, 32, 8, 4, 8, 1, 4>;
+using SP512 = ComplexPlan<512, 64, 8, 8, 8, 1, 4>;
+using SP1024 = ComplexPlan<1024, 128, 8, 4, 4, 8, 4>;
 using SP2048 = ComplexPlan<2048, 128, 16, 8, 16>;
-using SP4096 = ComplexPlan<4096, 512, 8, 8, 8, 8>;
+using SP4096 = ComplexPlan<4096, 512, 8, 8, 8, 8, 4>;
 using SP4096F = ComplexPlan<4096, 256, 16, 16, 16>;
 
 template <bool FWD, class F>

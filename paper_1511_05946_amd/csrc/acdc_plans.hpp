@@ -150,7 +150,7 @@ struct RealPlan {
   static_assert(R0 % 2 == 0, "first pass radix must be even");
 };
 
-template <int N_, int T_, int R0_, int R1_, int R2_ = 1, int R3_ = 1>
+template <int N_, int T_, int R0_, int R1_, int R2_ = 1, int R3_ = 1, int PAD_ = 0>
 struct ComplexPlan {
   static constexpr bool kComplex = true;
   static constexpr int N = N_;  // complex points per row
@@ -170,7 +170,7 @@ struct ComplexPlan {
     return s;
   }
   static constexpr int PADSH =
-      !ACDC_LDS_PAD ? 30 : (ilog2(R0_) >= 2 && (1 << ilog2(R0_)) == R0_ ? ilog2(R0_) : 30);
+      !ACDC_LDS_PAD ? 30 : PAD_ > 0 ? PAD_ : (ilog2(R0_) >= 2 && (1 << ilog2(R0_)) == R0_ ? ilog2(R0_) : 30);
   static constexpr int FFT_FLOATS = 2 * (N_ + (N_ >> PADSH));
   static constexpr int SLAB = FFT_FLOATS;  // LDS floats per row
   // Twiddles of a pass are stored in pairs (inputs i, i+1) so one 16-byte
