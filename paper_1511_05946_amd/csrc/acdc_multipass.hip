@@ -1181,7 +1181,8 @@ __global__ __launch_bounds__(kThreads) void k_mq(const float* __restrict__ D, co
     const long long k = i / NQ, r = i % NQ;
     const int p = int(r / g.L), k2 = int(r % g.L);
     float4 row[kMqRows];
-    quartet_coeffs(D + k * N, Bias ? Bias + k * N : nullptr, q, int(quartet_of(g, p, k2)), row);
+    const int e = int(quartet_of(g, p, k2));
+    quartet_coeffs(D + k * N, Bias ? Bias + k * N : nullptr, q, e, quartet_idx(int(N), e == 0 ? -2 : e), row);
     float4* out = Mq + (i - k2) * kMqRows + k2;
 #pragma unroll
     for (int c = 0; c < kMqRows; ++c) out[c * g.L] = row[c];

@@ -13,6 +13,8 @@
 // without the real-to-complex packing.
 #pragma once
 
+#include <hip/hip_runtime.h>
+
 #include <cstdint>
 
 #ifndef ACDC_TAB_PF
@@ -209,5 +211,24 @@ struct ComplexPlan {
   static_assert(P % R0_ == 0 && P % R1_ == 0 && P % R2_ == 0 && P % R3_ == 0,
                 "each radix must divide the per-thread register count");
 };
+
+// Spectrum index k handled by quartet slot `slot` of thread t, or -2 for
+// slot 0 of thread 0, which carries the two self-paired values Z[0] and
+// Z[M/2] and yields X[0], X[M], X[3M/2], X[M/2].
+template <class PL>
+__host__ __device__ inline int real_slot_k(int t, int slot) {
+  constexpr int RL = PL::RL, NB = PL::NB, T = PL::T;
+  const int q = slot / RL, i = slot % RL;
+  const int p = t + T * q;
+  if (p != 0) return p + i * NB;
+  if (i == 0) return -2;
+  return i < RL / 2 ? i * NB : NB / 2 + i * NB;
+}
+
+// DCT indices of the quartet of spectrum index k (-2: the self-paired one).
+__host__ __device__ inline int4 quartet_idx(int N, int k) {
+  const int M = N / 2;
+  return k == -2 ? make_int4(0, M, 3 * M / 2, M / 2) : make_int4(k, N - k, M - k, M + k);
+}
 
 }  // namespace acdc

@@ -265,8 +265,8 @@ inline bool dispatch_complex(int N, F&& f) {
 }
 
 // The per-entry quartet tables of a width N: Makhoul twiddle blocks mk0,
-// mk1, the four DCT indices of each entry and their masks (low nibble: the
-// d values to read; high nibble: the image values to store).  The fused
+// mk1, the four DCT indices of each entry and their masks (high nibble: the
+// image values to store).  The fused
 // plans index them by slot entry e = slot*T + t, the multi-pass path by the
 // quartet number; entry 0 is the self-paired quartet (Z[0], Z[M/2]) in both.
 struct QuartetTabs {
@@ -284,12 +284,11 @@ __host__ __device__ __forceinline__ QuartetTabs quartet_tabs(const char* tab) {
                      reinterpret_cast<const int*>(tab + PL::OFF_QMASK), RealOps<PL>::kQbRe, RealOps<PL>::kQbIm};
 }
 
-// A layer vector (d or b) at the four quartet indices of entry e.
-__host__ __device__ __forceinline__ float4 quartet_gather(const float* Vk, const QuartetTabs& q, int e) {
-  const int4 idx = q.qidx[e];
-  const int m = q.qmask[e] & 0xF;
-  return make_float4((m & 1) ? Vk[idx.x] : 0.f, (m & 2) ? Vk[idx.y] : 0.f, (m & 4) ? Vk[idx.z] : 0.f,
-                     (m & 8) ? Vk[idx.w] : 0.f);
+// A layer vector (d or b) at the four indices of a quartet.  The callers
+// compute the indices: read from the table (qidx) they were one more memory
+// latency ahead of these loads, in launches that are nothing but latency.
+__host__ __device__ __forceinline__ float4 quartet_gather(const float* Vk, int4 idx) {
+  return make_float4(Vk[idx.x], Vk[idx.y], Vk[idx.z], Vk[idx.w]);
 }
 
 // Quartet coefficients of layer k at slot entry e = slot*T + t.
@@ -323,10 +322,10 @@ __host__ __device__ inline QuartetD qd_mulc(QuartetD a, QuartetD w) {  // a * co
   return QuartetD{a.x * w.x + a.y * w.y, a.y * w.x - a.x * w.y};
 }
 __host__ __device__ inline void quartet_coeffs(const float* Dk, const float* Bk, const QuartetTabs& q, int e,
-                                               float4 (&out)[kMqRows]) {
+                                               int4 idx, float4 (&out)[kMqRows]) {
   const float4 m0 = q.mk0[e];
   const float4 m1 = q.mk1[e];
-  const float4 d = quartet_gather(Dk, q, e);
+  const float4 d = quartet_gather(Dk, idx);
   const QuartetD qa{m0.z, m0.w}, qb{m1.x, m1.y}, qap{m1.z, m1.w};
   // thread 0's slot 0 carries the self-paired values; its pre-twiddle uses
   // exp(i pi/8) / (2 sqrt(N))
@@ -358,7 +357,7 @@ __host__ __device__ inline void quartet_coeffs(const float* Dk, const float* Bk,
   // after the 2x2 maps.
   out[3] = make_float4(0.f, 0.f, 0.f, 0.f);
   if (Bk != nullptr) {
-    const float4 b = quartet_gather(Bk, q, e);
+    const float4 b = quartet_gather(Bk, idx);
     const QuartetD ap = qd_mul(QuartetD{b.x, -double(b.y)}, qap);
     const QuartetD bp = qd_mulc(QuartetD{double(b.z) + b.w, double(b.w) - b.z}, qbp);
     const QuartetD S{ap.x + bp.x, ap.y + bp.y}, Dd{ap.x - bp.x, ap.y - bp.y};
@@ -370,7 +369,7 @@ __host__ __device__ inline void quartet_coeffs(const float* Dk, const float* Bk,
 template <class PL>
 __host__ __device__ inline void real_mq_entry(const float* Dk, const float* Bk, const char* tab, int e,
                                               float4 (&out)[kMqRows]) {
-  quartet_coeffs(Dk, Bk, quartet_tabs<PL>(tab), e, out);
+  quartet_coeffs(Dk, Bk, quartet_tabs<PL>(tab), e, quartet_idx(PL::N, real_slot_k<PL>(e % PL::T, e / PL::T)), out);
 }
 
 // Fixed-order batch reduction of the per-tile partials.  Entry e (a float4)

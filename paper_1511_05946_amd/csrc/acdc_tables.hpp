@@ -42,19 +42,6 @@ inline void fill_fft_twiddles(float2* tw) {
   }
 }
 
-// Spectrum index k handled by quartet slot `slot` of thread t, or -2 for
-// slot 0 of thread 0, which carries the two self-paired values Z[0] and
-// Z[M/2] and yields X[0], X[M], X[3M/2], X[M/2].
-template <class PL>
-inline int real_slot_k(int t, int slot) {
-  constexpr int RL = PL::RL, NB = PL::NB, T = PL::T;
-  const int q = slot / RL, i = slot % RL;
-  const int p = t + T * q;
-  if (p != 0) return p + i * NB;
-  if (i == 0) return -2;
-  return i < RL / 2 ? i * NB : NB / 2 + i * NB;
-}
-
 // Makhoul coefficients and DCT indices of the quartet of spectrum index k
 // (k = -2: the self-paired quartet (Z[0], Z[M/2])), for width N.
 inline void quartet_entry(int N, int k, float4& mk0, float4& mk1, int (&idx)[4]) {
@@ -66,10 +53,6 @@ inline void quartet_entry(int N, int k, float4& mk0, float4& mk1, int (&idx)[4])
     const double c8 = q8.re, s8 = -q8.im;
     mk0 = make_float4(0.f, 1.f, float(s0 / 2), float(-s0 / 2));
     mk1 = make_float4(float(s * (c8 + s8) / 4), float(s * (c8 - s8) / 4), float(s0 / 2), float(s0 / 2));
-    idx[0] = 0;
-    idx[1] = M;
-    idx[2] = 3 * M / 2;
-    idx[3] = M / 2;
   } else {
     const double sk = (k == 0) ? s0 : s;
     const HostC w = w_pow(k, N);        // W_N^k
@@ -77,11 +60,12 @@ inline void quartet_entry(int N, int k, float4& mk0, float4& mk1, int (&idx)[4])
     const double fa = sk / 2, fb = s / (2 * std::sqrt(2.0)), fp = 1.0 / (2.0 * M * sk);
     mk0 = make_float4(float(w.re), float(w.im), float(fa * q.re), float(fa * q.im));
     mk1 = make_float4(float(fb * q.re), float(fb * q.im), float(fp * q.re), float(-fp * q.im));
-    idx[0] = k;
-    idx[1] = N - k;
-    idx[2] = M - k;
-    idx[3] = M + k;
   }
+  const int4 i4 = quartet_idx(N, k);
+  idx[0] = i4.x;
+  idx[1] = i4.y;
+  idx[2] = i4.z;
+  idx[3] = i4.w;
 }
 
 // Returns false if the quartet slots do not cover every DCT index exactly once.
