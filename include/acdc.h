@@ -122,9 +122,9 @@ int acdc_prepare(int32_t N, uint32_t flags);
 size_t acdc_saved_bytes(int64_t batch, int32_t N, int32_t K, uint32_t flags);
 
 /* Bytes of workspace acdc_forward needs (the per-layer quartet coefficients
- * built from D; on the multi-pass path also the packed spectra, a layer
- * buffer and, with ACDC_FLAG_PERM, a buffer for the permuted layer input and
- * the permutation tables that each call builds on the device from perm).
+ * built from D; on the multi-pass path also the spectra and, with
+ * ACDC_FLAG_PERM, the rows between the two halves of a permutation and the
+ * permutation tables that each call builds on the device from perm).
  * Host only. */
 size_t acdc_forward_workspace_size(int64_t batch, int32_t N, int32_t K, uint32_t flags);
 
@@ -134,7 +134,8 @@ size_t acdc_forward_workspace_size(int64_t batch, int32_t N, int32_t K, uint32_t
  * behind the bias gradient (ACDC_FLAG_BIAS), and -- when have_saved is 0 and
  * acdc_saved_bytes(...) is not 0 -- room to recompute the layer inputs (the
  * paper's recompute policy, Sec. 5.3).  The multi-pass path adds its
- * spectra, layer buffers, row-block sums and permutation tables. */
+ * spectra, row-block sums and permutation tables.  Never less for a larger
+ * batch: a workspace of one batch serves the smaller ones. */
 size_t acdc_backward_workspace_size(int64_t batch, int32_t N, int32_t K, uint32_t flags, int have_saved);
 
 /* Forward cascade: y = cascade(x).  `bias` is read with ACDC_FLAG_BIAS and
@@ -173,8 +174,8 @@ int acdc_forward_noalloc(const float* x, float* y, const float* A, const float* 
  * batch, in a fixed order that depends only on the call's shapes (batch,
  * N, K, flags) and the device (workgroups sum their rows, and the partials
  * are then added in 4 or 8 fixed tile phases, 8 for the smaller gradients;
- * at N = 9216 each resident workgroup first adds its tiles into one
- * partial), and with
+ * at N = 9216 and more than 256 rows each resident workgroup first adds its
+ * tiles into one partial), and with
  * ACDC_FLAG_BIAS grad_bias = dL/db_k (bias and grad_bias are then required,
  * and ignored otherwise).  The parameter gradients are overwritten, or with
  * ACDC_FLAG_ACCUMULATE added to what the arrays hold.  `saved` is the buffer

@@ -2,7 +2,7 @@
 //
 // Kernels (one instantiation per supported width):
 //   k_real_mq      per-layer quartet coefficients of the layer middle (tiny)
-//   k_real_fwd     forward cascade, ROWS rows per workgroup, all K layers
+//   k_real_fwd     forward cascade, up to FWD_ROWS rows per workgroup, all K layers
 //                  fused, rows kept in registers + one LDS slab per row
 //   k_real_bwd     backward cascade with the reduction of dL/da, dL/dd over
 //                  the workgroup's rows into one partial per tile, or
