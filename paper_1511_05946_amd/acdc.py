@@ -232,7 +232,7 @@ def forward(x, A, D, perm=None, flags: int = 0, save: bool = False, out=None, sa
     ws = _workspace(workspace, ws_bytes, device)
     if workspace is not None:
         _validate({"workspace": ws}, cplx, device)
-    rc = _call(lib().acdc_forward, device, x.data_ptr(), out.data_ptr(), A.data_ptr(), D.data_ptr(), _ptr(bias),
+    rc = _call(lib().acdc_forward, device, x.data_ptr(), out.data_ptr(), A.data_ptr(), _ptr(D), _ptr(bias),
                _ptr(perm), B, N, K, flags, saved.data_ptr() if (saved is not None and saved.numel() > 0) else None,
                _nbytes(saved), ws.data_ptr(), ws_bytes)
     _check(rc, "acdc_forward")
@@ -279,9 +279,9 @@ def backward(x, grad_y, A, D, perm=None, flags: int = 0, saved=None, bias=None, 
     ws = _workspace(workspace, ws_bytes, device)
     if workspace is not None:
         _validate({"workspace": ws}, cplx, device)
-    rc = _call(lib().acdc_backward, device, x.data_ptr(), grad_y.data_ptr(), A.data_ptr(), D.data_ptr(), _ptr(bias),
-               _ptr(perm), saved.data_ptr() if use_saved else None, _nbytes(saved), gx.data_ptr(), gA.data_ptr(),
-               gD.data_ptr(), _ptr(gB), B, N, K, flags, ws.data_ptr(), ws_bytes)
+    rc = _call(lib().acdc_backward, device, x.data_ptr(), _ptr(grad_y), A.data_ptr(), _ptr(D), _ptr(bias),
+               _ptr(perm), saved.data_ptr() if use_saved else None, _nbytes(saved), gx.data_ptr(), _ptr(gA),
+               _ptr(gD), _ptr(gB), B, N, K, flags, ws.data_ptr(), ws_bytes)
     _check(rc, "acdc_backward")
     return (gx, gA, gD, gB) if bias is not None else (gx, gA, gD)
 

@@ -250,6 +250,25 @@ def test_binding_checks_shapes_before_any_library_call(L):
             acdc.backward(**args)
 
 
+def test_binding_leaves_missing_tensors_to_the_library(L, monkeypatch):
+    # A None where a tensor belongs reaches the library as a null pointer:
+    # refused with its status, or unread where there is nothing to do (an
+    # empty batch reads no D in the forward and no grad_y in the backward).
+    torch = pytest.importorskip("torch")
+    import paper_1511_05946_amd.acdc as acdc
+    monkeypatch.setattr(acdc, "_call", lambda fn, device, *args: fn(*args, None))   # no device: host checks only
+    N, K = 64, 2
+    A, g = torch.ones(K, N), torch.zeros(K, N)
+    x, none = torch.zeros(3, N), torch.zeros(0, N)
+    with pytest.raises(acdc.ACDCError, match="invalid argument"):
+        acdc.forward(x, A, None)
+    for gy, D, grads in ((None, A, None), (x, None, (g, g.clone())), (x, A, (None, g)), (x, A, (g, None))):
+        with pytest.raises(acdc.ACDCError, match="invalid argument"):
+            acdc.backward(x, gy, A, D, grads=grads)
+    y, _ = acdc.forward(none, A, None)
+    assert y.shape == (0, N)
+
+
 def test_noalloc_forward_rejects_on_the_host(L):
     # acdc_forward_noalloc refuses, before any HIP call, what its fixed
     # scratch array cannot hold (more than 2^20 layer-elements of real rows)
