@@ -46,37 +46,6 @@ __device__ __forceinline__ float4 relu4(float4 h) { return make_float4(relu1(h.x
 
 // ------------------------------------------------------------ permutations
 
-constexpr int log2_chunk = ilog2(kPermChunk);
-
-// Set of row element i and its place in the LDS image of a column launch
-// (chunk or element js of column col at js W + col, W columns for a whole
-// set's), and the element at local position l of set d.
-__device__ __forceinline__ void part_of(const PermGeo& p, long long i, int& d, int& l) {
-  const int lW = p.lw + (log2_chunk - p.lC) + (p.ew == 1 ? 0 : -1);
-  const long long Q = 1LL << p.lQ;
-  if (p.ew == 1) {
-    const long long q = i >> 2, j = q >> p.lQ, n = q & (Q - 1);
-    const int side = n >= Q / 2 ? 1 : 0;
-    const long long col = side ? Q - 1 - n : n;
-    d = int(col >> p.lw);
-    l = int(((((2 * j + side) << lW) + (col & ((1 << p.lw) - 1))) << 2) + (i & 3));
-  } else {
-    const long long j = i >> p.lQ, n = i & (Q - 1);
-    d = int(n >> p.lw);
-    l = int((j << lW) + (n & ((1 << p.lw) - 1)));
-  }
-}
-__device__ __forceinline__ long long elem_of(const PermGeo& p, int d, int l) {
-  const long long Q = 1LL << p.lQ;
-  if (p.ew == 1) {
-    const int l4 = l >> 2, js = l4 >> p.lw;
-    const long long col = ((long long)d << p.lw) + (l4 & ((1 << p.lw) - 1));
-    const long long n = (js & 1) ? Q - 1 - col : col;
-    return ((((long long)(js >> 1) << p.lQ) + n) << 2) + (l & 3);
-  }
-  return ((long long)(l >> p.lw) << p.lQ) + ((long long)d << p.lw) + (l & ((1 << p.lw) - 1));
-}
-
 // Table build, a counting sort of the destinations by source set.  Step 1:
 // per block of kThreads destinations (all of one set d), the count of each
 // source set: cntS[blk][c].  Every step handles layer blockIdx.y (step 3: x).
@@ -236,22 +205,16 @@ constexpr bool needs_lds() {
 // CU.  Fences bound what is in flight at once for the same reason.
 
 // Real rows.  A thread holds CI column pairs, R float4 chunks each: ha[j]
-// is chunk n + jQ, hb[j] chunk (Q-1-n) + jQ.  512 threads at R <= 8 (four
-// waves per SIMD with two workgroups a CU); at R = 16 a pair is 64 values
-// and a set of 16384 floats has 256 pairs.
-template <int R>
-constexpr int col_threads() {
-  return R <= 8 ? 512 : 256;
-}
+// is chunk n + jQ, hb[j] chunk (Q-1-n) + jQ.
 template <int R>
 constexpr int col_waves() {
   return R <= 8 ? 4 : 2;
 }
 
 template <int R, Src SRC, Sink SINK, bool BWD>
-__global__ __launch_bounds__(col_threads<R>())
+__global__ __launch_bounds__(col_threads(R, 1))
 __attribute__((amdgpu_waves_per_eu(col_waves<R>()))) void k_cols(ColArgs A) {
-  constexpr int THREADS = col_threads<R>(), H = R / 2;
+  constexpr int THREADS = col_threads(R, 1), H = R / 2;
   constexpr int CI = kPermChunk / 4 / (R * THREADS);
   constexpr int W = kPermChunk / 4 / R;  // LDS: chunk js of column col at js W + col
   constexpr unsigned kMask = kPermChunk - 1;
@@ -492,8 +455,8 @@ __attribute__((amdgpu_waves_per_eu(col_waves<R>()))) void k_cols(ColArgs A) {
 // Complex rows: columns n, elements n + jQ.  Images gh1 * conj(u), and
 // dL/du = gh1 * conj(a).
 template <int R, Src SRC, Sink SINK, bool BWD>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_ccols(ColArgs A) {
-  constexpr int THREADS = 512, EC = kPermChunk / 2;  // elements of a whole set
+__global__ __launch_bounds__(col_threads(R, 2)) __attribute__((amdgpu_waves_per_eu(4))) void k_ccols(ColArgs A) {
+  constexpr int THREADS = col_threads(R, 2), EC = kPermChunk / 2;  // elements of a whole set
   constexpr int CI = EC / (R * THREADS), W = EC / R;
   constexpr unsigned kMask = EC - 1;
   static_assert(CI >= 1 && CI * THREADS == W, "a set's elements over the threads");
@@ -790,54 +753,6 @@ struct Seg {
     O::template st_row<true>(GView::of(seg), 0u, x, t);
   }
 };
-
-// Pair p (of S/2) of a real row's segments: Z[k] in one has its Makhoul
-// partner Z[M-k] in the other, at L-1-k2.  Pair 0 is the two segments that
-// hold their own partners, segment 0 (at L-k2) and one more (at L-1-k2).
-__host__ __device__ __forceinline__ void seg_pair(const Geo& g, int p, int& sa, int& sb) {
-  if (p == 0) {
-    sa = 0;
-    sb = g.R2 == 1 ? g.R1 / 2 : g.R2 / 2;
-    return;
-  }
-  int x = p - 1;
-  if (x < (g.R1 / 2 - 1) * g.R2) {
-    const int r1 = 1 + x / g.R2, r2 = x % g.R2;
-    sa = r1 * g.R2 + r2;
-    sb = (g.R1 - r1) * g.R2 + (g.R2 - 1 - r2);
-    return;
-  }
-  x -= (g.R1 / 2 - 1) * g.R2;
-  if (x < g.R2 / 2) {
-    sa = (g.R1 / 2) * g.R2 + x;
-    sb = (g.R1 / 2) * g.R2 + (g.R2 - 1 - x);
-    return;
-  }
-  x -= g.R2 / 2;
-  sa = 1 + x;
-  sb = g.R2 - 1 - x;
-}
-
-// Quartet at place k2 of pair p: its number e, where e = 0 is the self-paired
-// (Z[0], Z[M/2]) and otherwise Z[e] pairs with Z[M-e].  In a generic pair it
-// is the quartet of segment A's k2, in pair 0 those of segment 0 come first
-// (k2 < L/2), then the other segment's.
-__host__ __device__ __forceinline__ long long quartet_of(const Geo& g, int p, int k2) {
-  const long long S = (long long)g.R1 * g.R2;
-  if (p == 0) return k2 < g.L / 2 ? S * k2 : S / 2 + S * (k2 - g.L / 2);
-  int sa, sb;
-  seg_pair(g, p, sa, sb);
-  const long long k = sa / g.R2 + (long long)g.R1 * (sa % g.R2 + (long long)g.R2 * k2);
-  return k < g.M / 2 ? k : g.M - k;
-}
-
-// Spectrum index of storage position q.
-__device__ __forceinline__ long long spec_index(const Geo& g, long long q) {
-  const long long S1 = g.M / g.R1;
-  const long long r1 = q / S1, rem = q % S1;
-  const long long r2 = rem / g.L, k2 = rem % g.L;
-  return r1 + (long long)g.R1 * (r2 + (long long)g.R2 * k2);
-}
 
 // The lanes of one pair, x[0] = segment A (lane t), x[1] = segment B, whose
 // spectrum is held with the lanes reversed.  Then register s of x[0] and
@@ -1261,12 +1176,6 @@ __global__ __launch_bounds__(kThreads) void k_colsum2(const float* __restrict__ 
   }
 }
 
-int log2_of(long long v) {
-  int l = 0;
-  while ((1LL << (l + 1)) <= v) ++l;
-  return l;
-}
-
 template <class F>
 bool with_r1(int R1, F&& f) {
   switch (R1) {
@@ -1281,8 +1190,8 @@ bool with_r1(int R1, F&& f) {
 template <Src SRC, Sink SINK, bool BWD>
 bool launch_cols(bool cplx, int R1, dim3 grid, const ColArgs& a, hipStream_t s) {
   return with_r1(R1, [&]<int R>() {
-    if (cplx) hipLaunchKernelGGL((k_ccols<R, SRC, SINK, BWD>), grid, dim3(512), 0, s, a);
-    else hipLaunchKernelGGL((k_cols<R, SRC, SINK, BWD>), grid, dim3(col_threads<R>()), 0, s, a);
+    if (cplx) hipLaunchKernelGGL((k_ccols<R, SRC, SINK, BWD>), grid, dim3(col_threads(R, 2)), 0, s, a);
+    else hipLaunchKernelGGL((k_cols<R, SRC, SINK, BWD>), grid, dim3(col_threads(R, 1)), 0, s, a);
   });
 }
 
@@ -1309,31 +1218,7 @@ dim3 seg_grid(long long units) {
   return dim3(unsigned((units + Seg<PL>::GROUPS - 1) / Seg<PL>::GROUPS));
 }
 
-int clamp_rows(long long n) { return n < 1 ? 1 : n > kMaxRows ? kMaxRows : int(n); }
-
 }  // namespace
-
-Geo geo(long long N) {
-  Geo g;
-  g.M = N / 2;
-  g.L = int(g.M / 2 < 4096 ? g.M / 2 : 4096);
-  const long long ratio = g.M / g.L;
-  g.R1 = int(ratio <= 16 ? ratio : 16);
-  g.R2 = int(ratio / g.R1);
-  return g;
-}
-
-PermGeo perm_geo(const Geo& g, int ew) {
-  const long long N = 2 * g.M / ew, cap = kPermChunk / ew;  // elements of a row, of a whole set
-  const long long C = N < cap ? N : cap, Q = g.M / g.R1;
-  PermGeo p;
-  p.ew = ew;
-  p.lC = log2_of(C);
-  p.nC = int(N / C);
-  p.lQ = log2_of(Q);
-  p.lw = log2_of(C / (ew == 1 ? 4LL * g.R1 : g.R1));
-  return p;
-}
 
 size_t perm_table_ints(const Geo& g, int ew) {
   const PermGeo p = perm_geo(g, ew);
@@ -1393,15 +1278,16 @@ hipError_t cols(Src src, Sink sink, bool cplx, const Cols& c, long long B, const
                 hipStream_t s) {
   const PermGeo pg = perm_geo(g, cplx ? 2 : 1);
   const bool bwd = c.u != nullptr;
-  const int rb = bwd ? col_rows(B, g, pg.ew) : 1;
+  const ColGrid cg = col_grid(B, g, pg.ew, bwd);
+  if (cg.groups * cg.threads >= 1LL << 32) return hipErrorInvalidValue;
   ColArgs a{c.src,   c.dst, c.Z,  c.a,    c.stash, c.u, c.part, tw1, nullptr, nullptr, nullptr, B, g.M,
-            rb, c.relu, pg};
+            cg.rb, c.relu, pg};
   if (c.pt != nullptr) {
     a.item = c.pt->item;
     a.loc = c.pt->loc;
     a.delta = c.pt->delta;
   }
-  const dim3 grid(unsigned((B + rb - 1) / rb * pg.nC));
+  const dim3 grid(unsigned(cg.groups));
   auto is = [&](Src x, Sink y, bool w) { return src == x && sink == y && bwd == w; };
   bool ok = false;
   if (is(Src::rows, Sink::send, false)) ok = launch_cols<Src::rows, Sink::send, false>(cplx, g.R1, grid, a, s);
@@ -1484,27 +1370,6 @@ hipError_t cseg_bwd(float2* Zh, float2* Zg, const float2* Dn, long long B, const
                        Zh, Zg, Dn, B, g, rb, reinterpret_cast<float2*>(part), seg_tab);
   });
   return ok ? hipGetLastError() : hipErrorInvalidValue;
-}
-
-namespace {
-// Workgroups of a whole row block, and the blocks that make two of them on
-// each of 256 CUs.
-constexpr long long kWant = 512;
-long long seg_units(const Geo& g, bool cplx) { return g.R1 * g.R2 / (cplx ? 1 : 2); }
-}  // namespace
-
-int seg_rows(long long B, const Geo& g, bool cplx) { return clamp_rows(B * seg_units(g, cplx) / kWant); }
-int col_rows(long long B, const Geo& g, int ew) { return clamp_rows(B * perm_geo(g, ew).nC / kWant); }
-// With u units a row there are at most B blocks, fewer than 2 kWant / u while
-// blocks have fewer than kMaxRows rows, and B / kMaxRows from there on.
-long long max_blocks(long long B, const Geo& g, int ew) {
-  long long most = (B + kMaxRows - 1) / kMaxRows;
-  for (long long u : {seg_units(g, ew == 2), (long long)perm_geo(g, ew).nC}) {
-    const long long few = (2 * kWant + u - 1) / u + 1;
-    const long long n = B < few ? B : few;
-    most = n > most ? n : most;
-  }
-  return most;
 }
 
 hipError_t colsum_parts(const float* part, long long P, long long W, float* out, Order how, const Geo& g,

@@ -30,19 +30,11 @@
 #include <cstdint>
 #include <vector>
 
+#include "acdc_mp_geo.hpp"
 #include "acdc_registry.hpp"
 
 namespace acdc {
 namespace mp {
-
-// Geometry of one row's M-point FFT: M = R1 * R2 * L, R1 in {2, 4, 8, 16},
-// R2 in {1, 2, ..., 32} (1 = no pass), L the in-LDS segment length, a power
-// of two from 64 to 4096.
-struct Geo {
-  long long M;
-  int L, R1, R2;
-};
-Geo geo(long long N);  // of real rows of width N (complex rows of N / 2 elements)
 
 // Permutations between column sets.  A set ("chunk") holds the elements of w
 // neighbouring columns: for complex rows m = n + j Q (Q = M / R1, j < R1) of
@@ -60,13 +52,6 @@ Geo geo(long long N);  // of real rows of width N (complex rows of N / 2 element
 // values sourced from set c, back to their places in it).  Every HBM access
 // is contiguous, or in runs of C / nC elements.  Table entries are masked
 // into range, so a malformed permutation cannot address outside its row.
-constexpr int kPermChunk = 16384;                       // floats: 64 KB of LDS
-constexpr int kPermMaxChunks = (1 << 22) / kPermChunk;  // the widest row
-struct PermGeo {
-  int lQ, lw, lC, nC;  // log2 of Q, w, C; sets per row
-  int ew;              // floats per element: 1 real, 2 complex
-};
-PermGeo perm_geo(const Geo& g, int ew);
 // One layer's tables (layer l's sit stride ints further on):
 //   item[cC + i]   entry i of set c's list, ordered by destination set d:
 //                  (local source index << 8) | d
@@ -131,16 +116,6 @@ hipError_t dn(const float2* D, float2* Dn, int K, const Geo& g, hipStream_t s);
 hipError_t cseg_fwd(float2* Z, const float2* Dn, long long B, const Geo& g, const char* seg_tab, hipStream_t s);
 hipError_t cseg_bwd(float2* Zh, float2* Zg, const float2* Dn, long long B, const Geo& g, float* part,
                     const char* seg_tab, hipStream_t s);
-
-// Rows per block of the image sums of the segment and column launches: one
-// block is one workgroup's loop, so few enough to leave every CU several
-// workgroups, and at most kMaxRows.
-constexpr int kMaxRows = 16;
-int seg_rows(long long B, const Geo& g, bool cplx);
-int col_rows(long long B, const Geo& g, int ew);
-// An upper bound of the blocks of either for every batch up to B (sizes the
-// block sums: a workspace of one batch serves the smaller ones).
-long long max_blocks(long long B, const Geo& g, int ew);
 
 // Fixed-order sums over row blocks: out[w] (+)= sum over p of part[p][w] in
 // block order, column w being in the order of the launch that wrote it.

@@ -11,6 +11,7 @@
 #include <thread>
 #include <vector>
 
+#include "../../paper_1511_05946_amd/csrc/acdc_mp_geo.hpp"
 #include "../../paper_1511_05946_amd/csrc/acdc_registry.hpp"
 
 using namespace acdc;
@@ -333,4 +334,13 @@ extern "C" int acdc_emu_reduce4(const float* partial, long long ntiles, long lon
     return PH;
   };
   return red_phases(n4) == 8 ? run.template operator()<8>() : run.template operator()<4>();
+}
+
+// Geometry of the multi-pass rows of N elements (ew = 1 real, 2 complex).
+// out: rows in turn, threads of a workgroup, workgroups of a column launch.
+extern "C" void acdc_emu_mp_col_grid(long long batch, int N, int ew, int sums, long long* out) {
+  const mp::ColGrid c = mp::col_grid(batch, mp::geo((long long)N * ew), ew, sums != 0);
+  out[0] = c.rb;
+  out[1] = c.threads;
+  out[2] = c.groups;
 }

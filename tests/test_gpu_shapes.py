@@ -6,7 +6,7 @@ GPU parity tests (every element, same tolerance)."""
 import pytest
 
 from oracle import acdc_oracle as O
-from paper_1511_05946_amd.workloads import FLAG_BIAS, FLAG_MULTIPASS
+from paper_1511_05946_amd.workloads import FLAG_BIAS, FLAG_MULTIPASS, make_bias, make_inputs
 from tests.test_gpu_parity import acdc, run_case  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -73,6 +73,27 @@ def test_multipass_plans(acdc, N, K, B, flags):  # noqa: F811
                                          (512, 2, 4099, CX | MP)])
 def test_multipass_row_block_edges(acdc, N, K, B, flags):  # noqa: F811
     run_case(acdc, N, K, B, flags, seed=N % 1000 + B)
+
+
+# Column launches whose workgroups take several rows in turn: more rows than
+# the grid has workgroups (65536, of up to 64 rows at N = 256).  Rows are
+# independent, so copies of a few rows give those rows' results, bit for bit.
+@pytest.mark.parametrize("N,B,flags", [(256, 64 * 65536 + 3, P | R | FLAG_BIAS | MP), (256, 32 * 65536 + 3, CX | P | MP),
+                                       (65536, 16387, P | R), (32768, 16387, CX)])
+def test_multipass_more_rows_than_workgroups(acdc, N, B, flags):  # noqa: F811
+    import torch
+    K, few, fl = 2, 7, flags & ~CX
+    x, A, D, perm, gy = (torch.from_numpy(t).cuda() for t in make_inputs(N, K, few, flags, N + 1))
+    bias = torch.from_numpy(make_bias(N, K, N)).cuda() if flags & FLAG_BIAS else None
+    y0, s0 = acdc.forward(x, A, D, perm, fl, save=True, bias=bias)
+    gx0 = acdc.backward(x, gy, A, D, perm, fl, saved=s0, bias=bias)[0]
+    n = -(-B // few)
+    whole = lambda t: t.repeat(n, 1)[:B].contiguous()  # noqa: E731
+    y, s = acdc.forward(whole(x), A, D, perm, fl, save=True, bias=bias)
+    assert torch.equal(y, whole(y0))
+    del y
+    gx = acdc.backward(whole(x), whole(gy), A, D, perm, fl, saved=s, bias=bias)[0]
+    assert torch.equal(gx, whole(gx0))
 
 
 def test_multipass_tables_rebuilt_per_layer(acdc):  # noqa: F811
