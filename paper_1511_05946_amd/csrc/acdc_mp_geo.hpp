@@ -139,6 +139,14 @@ constexpr long long kWant = 512;
 inline int clamp_rows(long long n) { return n < 1 ? 1 : n > kMaxRows ? kMaxRows : int(n); }
 inline long long seg_units(const Geo& g, bool cplx) { return g.R1 * g.R2 / (cplx ? 1 : 2); }
 inline int seg_rows(long long B, const Geo& g, bool cplx) { return clamp_rows(B * seg_units(g, cplx) / kWant); }
+// The forward segment launches keep no sums, so their rows in turn follow the
+// threads alone: plans of few threads (8 at L = 64, eight units a workgroup)
+// counted by units left most of the chip idle (N = 256, 8000 rows, K = 4: 63
+// workgroups of one wave, 150 us a layer).
+constexpr int seg_fwd_threads(int L) { return L <= 1024 ? L / 8 : L / 16; }
+inline int seg_fwd_rows(long long B, const Geo& g, bool cplx) {
+  return clamp_rows(B * seg_units(g, cplx) * seg_fwd_threads(g.L) / (kWant * 256));
+}
 inline int col_rows(long long B, const Geo& g, int ew) { return clamp_rows(B * perm_geo(g, ew).nC / kWant); }
 // An upper bound of the blocks of either for every batch up to B (sizes the
 // block sums: a workspace of one batch serves the smaller ones).  With u
@@ -154,28 +162,39 @@ inline long long max_blocks(long long B, const Geo& g, int ew) {
   return most;
 }
 
-// Column launch over B rows: a workgroup takes one column set of rb rows in
-// turn; workgroups in all.  With image sums (sums) the rows are their block;
-// the other launches keep nothing from row to row, so a row is a workgroup
-// of its own up to kColGroups of them.  Past that the rows in turn grow with
-// the batch: HIP takes fewer than 2^32 threads a launch, which one workgroup
-// of 512 threads per row reaches at 2^23 rows.
 // Threads of a workgroup: 512 at R <= 8 (four waves per SIMD with two
 // workgroups a CU); a real row's column pair at R = 16 is 64 values, and a
 // set of 16384 floats has 256 pairs.
 constexpr int col_threads(int R1, int ew) { return ew == 1 && R1 > 8 ? 256 : 512; }
+
+// Column launch over B rows: a workgroup takes one column set of rw rows side
+// by side and rb times as many in turn.
+//   rw  Rows of fewer than kPermChunk floats leave columns of a workgroup
+//       empty: at N = 256, R1 = 2, a row has 32 column pairs for 512 threads.
+//       The launches without image sums fill them with further rows (narrow)
+//       while that leaves kWant workgroups.  Forward, K = 4, one row a
+//       workgroup and packed: see k_cols.
+//   rb  With image sums the rows of their block (col_rows).  The other
+//       launches keep nothing from row to row, so one, up to kColGroups
+//       workgroups; past that it grows with the batch: HIP takes fewer than
+//       2^32 threads a launch, which one workgroup of 512 threads per row
+//       reaches at 2^23 rows.
+constexpr bool narrow(int R1, bool sums) { return R1 == 2 && !sums; }
 constexpr long long kColGroups = 65536;
 struct ColGrid {
-  int rb, threads;
+  int rw, rb, threads;
   long long groups;
 };
 inline ColGrid col_grid(long long B, const Geo& g, int ew, bool sums) {
-  const long long nC = perm_geo(g, ew).nC;
-  const long long rb = sums ? col_rows(B, g, ew) : (B * nC + kColGroups - 1) / kColGroups;
+  const PermGeo p = perm_geo(g, ew);
+  const long long full = narrow(g.R1, sums) ? (kPermChunk / ew) >> p.lC : 1, share = B / kWant;
+  const long long rw = share < 1 ? 1 : share < full ? share : full, sets = (B + rw - 1) / rw * p.nC;
+  const long long rb = sums ? col_rows(B, g, ew) : (sets + kColGroups - 1) / kColGroups;
   ColGrid c;
+  c.rw = int(rw);
   c.rb = int(rb < 1 ? 1 : rb);
   c.threads = col_threads(g.R1, ew);
-  c.groups = (B + c.rb - 1) / c.rb * nC;
+  c.groups = (B + c.rb * rw - 1) / (c.rb * rw) * p.nC;
   return c;
 }
 

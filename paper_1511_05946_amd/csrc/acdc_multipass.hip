@@ -163,7 +163,7 @@ struct ColArgs {
   const unsigned short* loc;
   const int* delta;
   long long B, M;
-  int rb, relu;
+  int rw, rb, relu;
   PermGeo pg;
 };
 
@@ -211,7 +211,11 @@ constexpr int col_waves() {
   return R <= 8 ? 4 : 2;
 }
 
-template <int R, Src SRC, Sink SINK, bool BWD>
+// NARROW: A.rw > 1 rows side by side, column col being row col / w's (a
+// template of its own: the row arithmetic costs every entry of a list).
+// N = 256, K = 4, 40000 rows, forward with permutations and ReLU, segment
+// launches as at the time: 1665 us with a row a workgroup, 776 with 64.
+template <int R, Src SRC, Sink SINK, bool BWD, bool NARROW>
 __global__ __launch_bounds__(col_threads(R, 1))
 __attribute__((amdgpu_waves_per_eu(col_waves<R>()))) void k_cols(ColArgs A) {
   constexpr int THREADS = col_threads(R, 1), H = R / 2;
@@ -242,40 +246,52 @@ __attribute__((amdgpu_waves_per_eu(col_waves<R>()))) void k_cols(ColArgs A) {
 #pragma unroll
       for (int j = 0; j < H; ++j) sa[ci][j] = sb[ci][j] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  // f(ci, col, n, nb): this thread's column pairs
+  // LDS place of entry i of the step's lists whose place in its own row's set
+  // is ls: row i / C's columns start at column w i / C.  (For a malformed perm
+  // ls is any value.)
+  auto at_row = [&](unsigned ls, int i) {
+    return (ls + (NARROW ? unsigned(i >> pg.lC) << (pg.lw + 2) : 0u)) & kMask;
+  };
+  int nr = 1;  // rows side by side in this step
+  // f(ci, col, n, nb, o): this thread's column pairs, and the byte offset of
+  // its row from the step's first one (the same in rows and spectra)
   auto pairs = [&](auto&& f) {
 #pragma unroll
     for (int ci = 0; ci < CI; ++ci) {
       const int col = int(threadIdx.x) + ci * THREADS;
-      if (col < w) {
-        const unsigned n = fresh((unsigned(c) << pg.lw) + unsigned(col));
-        f(ci, col, n, Q - 1 - n);
+      const int row = NARROW ? col >> pg.lw : 0;
+      if (NARROW ? row < nr : col < w) {
+        const unsigned n = fresh((unsigned(c) << pg.lw) + unsigned(col - (row << pg.lw)));
+        f(ci, col, n, Q - 1 - n, NARROW ? unsigned(row) << (pg.lC + 2) : 0u);
         ACDC_SCHED_FENCE();
       }
     }
   };
-  const long long b0 = p * A.rb, b1 = b0 + A.rb < A.B ? b0 + A.rb : A.B;
-  for (long long b = b0; b < b1; ++b) {
+  const long long rw = NARROW ? A.rw : 1, b0 = p * A.rb * rw, b1 = b0 + A.rb * rw < A.B ? b0 + A.rb * rw : A.B;
+  for (long long b = b0; b < b1; b += rw) {
+    if constexpr (NARROW) nr = int(b1 - b < rw ? b1 - b : rw);
+    const int total = NARROW ? nr << pg.lC : C;  // elements of this step's (rows of one) set
     const GView z = GView::of(A.Z + b * M);
     if constexpr (SRC == Src::rows) {
       const GView row = GView::of(A.src + b * N);
-      pairs([&](int ci, int, unsigned n, unsigned nb) {
+      pairs([&](int ci, int, unsigned n, unsigned nb, unsigned o) {
 #pragma unroll
         for (int j = 0; j < H; ++j) {
-          ha[ci][j] = row.ld4(n * 16u, j * sq16);
-          hb[ci][j] = row.ld4(nb * 16u, j * sq16);
+          ha[ci][j] = row.ld4(n * 16u + o, j * sq16);
+          hb[ci][j] = row.ld4(nb * 16u + o, j * sq16);
         }
       });
     } else if constexpr (SRC == Src::gather) {
       const float4* t4 = reinterpret_cast<const float4*>(A.src + b * N + ((long long)c << pg.lC));
       for_entries<THREADS, 8, float4>(
-          C / 4, [&](int i) { return t4[i]; }, [&](int i, float4 v) { lds4[i] = v; });
+          total / 4, [&](int i) { return t4[i]; }, [&](int i, float4 v) { lds4[i] = v; });
       __syncthreads();
-      pairs([&](int ci, int col, unsigned, unsigned) {
+      pairs([&](int ci, int col, unsigned, unsigned, unsigned o) {
+        const unsigned f = o / 4;  // the row's place in LDS
         auto at = [&](int js) {
-          const int2 s = loc.ldi2(unsigned(col) * 8u, unsigned(js << pg.lw) * 8u);
-          return make_float4(lds[unsigned(s.x) & kMask], lds[(unsigned(s.x) >> 16) & kMask],
-                             lds[unsigned(s.y) & kMask], lds[(unsigned(s.y) >> 16) & kMask]);
+          const int2 s = loc.ldi2(unsigned(NARROW ? col & (w - 1) : col) * 8u, unsigned(js << pg.lw) * 8u);
+          return make_float4(lds[(unsigned(s.x) + f) & kMask], lds[((unsigned(s.x) >> 16) + f) & kMask],
+                             lds[(unsigned(s.y) + f) & kMask], lds[((unsigned(s.y) >> 16) + f) & kMask]);
         };
 #pragma unroll
         for (int j = 0; j < H; ++j) {
@@ -283,33 +299,34 @@ __attribute__((amdgpu_waves_per_eu(col_waves<R>()))) void k_cols(ColArgs A) {
           hb[ci][j] = at(2 * j + 1);
         }
       });
-      if (b + 1 < b1) __syncthreads();
+      if (b + rw < b1) __syncthreads();
     } else if constexpr (SRC == Src::scatter) {
       const float* trow = A.src + b * N;
       const unsigned nm = unsigned(N - 1);
       for_entries<THREADS, 16, Entry<float>>(
-          C,
+          total,
           [&](int i) {
-            const unsigned it = item[i];
-            return Entry<float>{it, trow[unsigned(i + dl[it & 255]) & nm]};
+            const int r = NARROW ? i >> pg.lC : 0, e = i - (r << pg.lC);
+            const unsigned it = item[e];
+            return Entry<float>{it, trow[(unsigned(e + dl[it & 255]) & nm) + (unsigned(r) << pg.lC)]};
           },
-          [&](int, const Entry<float>& e) { lds[(e.it >> 8) & kMask] = e.v; });
+          [&](int i, const Entry<float>& e) { lds[at_row(e.it >> 8, i)] = e.v; });
       __syncthreads();
-      pairs([&](int ci, int col, unsigned, unsigned) {
+      pairs([&](int ci, int col, unsigned, unsigned, unsigned) {
 #pragma unroll
         for (int j = 0; j < H; ++j) {
           ha[ci][j] = lds4[(2 * j) * W + col];
           hb[ci][j] = lds4[(2 * j + 1) * W + col];
         }
       });
-      if (b + 1 < b1) __syncthreads();
+      if (b + rw < b1) __syncthreads();
     } else {
-      pairs([&](int ci, int, unsigned n, unsigned nb) {
+      pairs([&](int ci, int, unsigned n, unsigned nb, unsigned o) {
         float2 y[R], yb[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          y[r] = z.ld2(n * 8u, r * sq8);
-          yb[r] = z.ld2(nb * 8u, r * sq8);
+          y[r] = z.ld2(n * 8u + o, r * sq8);
+          yb[r] = z.ld2(nb * 8u + o, r * sq8);
         }
 #pragma unroll
         for (int r = 1; r < R; ++r) y[r] = cmulc(y[r], tw.ld2(n * 8u, (r - 1) * sq8));
@@ -326,7 +343,7 @@ __attribute__((amdgpu_waves_per_eu(col_waves<R>()))) void k_cols(ColArgs A) {
       });
       if constexpr (!BWD) {
         if (A.relu) {
-          pairs([&](int ci, int, unsigned, unsigned) {
+          pairs([&](int ci, int, unsigned, unsigned, unsigned) {
 #pragma unroll
             for (int j = 0; j < H; ++j) {
               ha[ci][j] = relu4(ha[ci][j]);
@@ -345,7 +362,7 @@ __attribute__((amdgpu_waves_per_eu(col_waves<R>()))) void k_cols(ColArgs A) {
         s = make_float4(s.x + u.x * g.x, s.y + u.y * g.y, s.z + u.z * g.z, s.w + u.w * g.w);
         g = scale4(g, a);
       };
-      pairs([&](int ci, int, unsigned n, unsigned nb) {
+      pairs([&](int ci, int, unsigned n, unsigned nb, unsigned) {
 #pragma unroll
         for (int j = 0; j < H; ++j) one(ha[ci][j], sa[ci][j], uv.ld4(n * 16u, j * sq16), av.ld4(n * 16u, j * sq16));
         ACDC_SCHED_FENCE();
@@ -356,16 +373,16 @@ __attribute__((amdgpu_waves_per_eu(col_waves<R>()))) void k_cols(ColArgs A) {
     if constexpr (SINK == Sink::dif && !BWD) {
       if (A.stash != nullptr) {
         const GView st = GView::of(A.stash + b * N);
-        pairs([&](int ci, int, unsigned n, unsigned nb) {
+        pairs([&](int ci, int, unsigned n, unsigned nb, unsigned o) {
 #pragma unroll
           for (int j = 0; j < H; ++j) {
-            st.st4(ha[ci][j], n * 16u, j * sq16);
-            st.st4(hb[ci][j], nb * 16u, j * sq16);
+            st.st4(ha[ci][j], n * 16u + o, j * sq16);
+            st.st4(hb[ci][j], nb * 16u + o, j * sq16);
           }
         });
       }
       if (A.a != nullptr) {
-        pairs([&](int ci, int, unsigned n, unsigned nb) {
+        pairs([&](int ci, int, unsigned n, unsigned nb, unsigned) {
 #pragma unroll
           for (int j = 0; j < H; ++j) {
             ha[ci][j] = scale4(ha[ci][j], av.ld4(n * 16u, j * sq16));
@@ -376,15 +393,15 @@ __attribute__((amdgpu_waves_per_eu(col_waves<R>()))) void k_cols(ColArgs A) {
     }
     if constexpr (SINK == Sink::rows) {
       const GView out = GView::of(A.dst + b * N);
-      pairs([&](int ci, int, unsigned n, unsigned nb) {
+      pairs([&](int ci, int, unsigned n, unsigned nb, unsigned o) {
 #pragma unroll
         for (int j = 0; j < H; ++j) {
-          out.st4(ha[ci][j], n * 16u, j * sq16);
-          out.st4(hb[ci][j], nb * 16u, j * sq16);
+          out.st4(ha[ci][j], n * 16u + o, j * sq16);
+          out.st4(hb[ci][j], nb * 16u + o, j * sq16);
         }
       });
     } else if constexpr (SINK == Sink::send) {
-      pairs([&](int ci, int col, unsigned, unsigned) {
+      pairs([&](int ci, int col, unsigned, unsigned, unsigned) {
 #pragma unroll
         for (int j = 0; j < H; ++j) {
           lds4[(2 * j) * W + col] = ha[ci][j];
@@ -395,11 +412,14 @@ __attribute__((amdgpu_waves_per_eu(col_waves<R>()))) void k_cols(ColArgs A) {
       float* trow = A.dst + b * N;
       const unsigned nm = unsigned(N - 1);
       for_entries<THREADS, 8, unsigned>(
-          C, [&](int i) { return item[i]; },
-          [&](int i, unsigned it) { trow[unsigned(i + dl[it & 255]) & nm] = lds[(it >> 8) & kMask]; });
-      if (b + 1 < b1) __syncthreads();
+          total, [&](int i) { return item[NARROW ? i & (C - 1) : i]; },
+          [&](int i, unsigned it) {
+            const int r = NARROW ? i >> pg.lC : 0, e = i - (r << pg.lC);
+            trow[(unsigned(e + dl[it & 255]) & nm) + (unsigned(r) << pg.lC)] = lds[at_row(it >> 8, i)];
+          });
+      if (b + rw < b1) __syncthreads();
     } else if constexpr (SINK == Sink::ret) {
-      pairs([&](int ci, int col, unsigned, unsigned) {
+      pairs([&](int ci, int col, unsigned, unsigned, unsigned) {
         auto put = [&](int js, float4 h) {
           const int2 s = loc.ldi2(unsigned(col) * 8u, unsigned(js << pg.lw) * 8u);
           lds[unsigned(s.x) & kMask] = h.x;
@@ -416,9 +436,9 @@ __attribute__((amdgpu_waves_per_eu(col_waves<R>()))) void k_cols(ColArgs A) {
       __syncthreads();
       float4* t4 = reinterpret_cast<float4*>(A.dst + b * N + ((long long)c << pg.lC));
       for (int i = threadIdx.x; i < C / 4; i += THREADS) t4[i] = lds4[i];
-      if (b + 1 < b1) __syncthreads();
+      if (b + rw < b1) __syncthreads();
     } else {
-      pairs([&](int ci, int, unsigned n, unsigned nb) {
+      pairs([&](int ci, int, unsigned n, unsigned nb, unsigned o) {
         float2 x[R];
         // one butterfly of the pair: FIRST the one of column n
         auto bfly = [&](auto first, unsigned at) {
@@ -432,7 +452,7 @@ __attribute__((amdgpu_waves_per_eu(col_waves<R>()))) void k_cols(ColArgs A) {
 #pragma unroll
           for (int r = 1; r < R; ++r) x[r] = cmul(x[r], tw.ld2(at * 8u, (r - 1) * sq8));
 #pragma unroll
-          for (int r = 0; r < R; ++r) z.st2(x[r], at * 8u, r * sq8);
+          for (int r = 0; r < R; ++r) z.st2(x[r], at * 8u + o, r * sq8);
         };
         bfly(std::true_type{}, n);
         ACDC_SCHED_FENCE();
@@ -442,7 +462,7 @@ __attribute__((amdgpu_waves_per_eu(col_waves<R>()))) void k_cols(ColArgs A) {
   }
   if constexpr (BWD) {
     const GView out = GView::of(A.part + p * N);
-    pairs([&](int ci, int, unsigned n, unsigned nb) {
+    pairs([&](int ci, int, unsigned n, unsigned nb, unsigned) {
 #pragma unroll
       for (int j = 0; j < H; ++j) {
         out.st4(sa[ci][j], n * 16u, j * sq16);
@@ -454,7 +474,7 @@ __attribute__((amdgpu_waves_per_eu(col_waves<R>()))) void k_cols(ColArgs A) {
 
 // Complex rows: columns n, elements n + jQ.  Images gh1 * conj(u), and
 // dL/du = gh1 * conj(a).
-template <int R, Src SRC, Sink SINK, bool BWD>
+template <int R, Src SRC, Sink SINK, bool BWD, bool NARROW>
 __global__ __launch_bounds__(col_threads(R, 2)) __attribute__((amdgpu_waves_per_eu(4))) void k_ccols(ColArgs A) {
   constexpr int THREADS = col_threads(R, 2), EC = kPermChunk / 2;  // elements of a whole set
   constexpr int CI = EC / (R * THREADS), W = EC / R;
@@ -482,55 +502,63 @@ __global__ __launch_bounds__(col_threads(R, 2)) __attribute__((amdgpu_waves_per_
 #pragma unroll
       for (int j = 0; j < R; ++j) s[ci][j] = make_float2(0.f, 0.f);
   }
+  auto at_row = [&](unsigned ls, int i) { return (ls + (NARROW ? unsigned(i >> pg.lC) << pg.lw : 0u)) & kMask; };
+  int nr = 1;
   auto columns = [&](auto&& f) {
 #pragma unroll
     for (int ci = 0; ci < CI; ++ci) {
       const int col = int(threadIdx.x) + ci * THREADS;
-      if (col < w) {
-        f(ci, col, fresh(((unsigned(c) << pg.lw) + unsigned(col)) * 8u));
+      const int row = NARROW ? col >> pg.lw : 0;
+      if (NARROW ? row < nr : col < w) {
+        f(ci, col, fresh(((unsigned(c) << pg.lw) + unsigned(col - (row << pg.lw))) * 8u),
+          NARROW ? unsigned(row) << (pg.lC + 3) : 0u);
         ACDC_SCHED_FENCE();
       }
     }
   };
-  const long long b0 = p * A.rb, b1 = b0 + A.rb < A.B ? b0 + A.rb : A.B;
-  for (long long b = b0; b < b1; ++b) {
+  const long long rw = NARROW ? A.rw : 1, b0 = p * A.rb * rw, b1 = b0 + A.rb * rw < A.B ? b0 + A.rb * rw : A.B;
+  for (long long b = b0; b < b1; b += rw) {
+    if constexpr (NARROW) nr = int(b1 - b < rw ? b1 - b : rw);
+    const int total = NARROW ? nr << pg.lC : C;
     const GView z = GView::of(A.Z + b * M);
     if constexpr (SRC == Src::rows) {
       const GView row = GView::of(A.src + 2 * b * M);
-      columns([&](int ci, int, unsigned n8) {
+      columns([&](int ci, int, unsigned n8, unsigned o) {
 #pragma unroll
-        for (int j = 0; j < R; ++j) h[ci][j] = row.ld2(n8, j * sq8);
+        for (int j = 0; j < R; ++j) h[ci][j] = row.ld2(n8 + o, j * sq8);
       });
     } else if constexpr (SRC == Src::gather) {
       const float4* t4 = reinterpret_cast<const float4*>(A.src + 2 * (b * M + ((long long)c << pg.lC)));
       for_entries<THREADS, 8, float4>(
-          C / 2, [&](int i) { return t4[i]; }, [&](int i, float4 v) { lds4[i] = v; });
+          total / 2, [&](int i) { return t4[i]; }, [&](int i, float4 v) { lds4[i] = v; });
       __syncthreads();
-      columns([&](int ci, int col, unsigned) {
+      columns([&](int ci, int col, unsigned, unsigned o) {
 #pragma unroll
-        for (int j = 0; j < R; ++j) h[ci][j] = lds[loc.ldu16(unsigned(col) * 2u, unsigned(j << pg.lw) * 2u) & kMask];
+        for (int j = 0; j < R; ++j)
+          h[ci][j] = lds[(loc.ldu16(unsigned(NARROW ? col & (w - 1) : col) * 2u, unsigned(j << pg.lw) * 2u) + o / 8) & kMask];
       });
-      if (b + 1 < b1) __syncthreads();
+      if (b + rw < b1) __syncthreads();
     } else if constexpr (SRC == Src::scatter) {
       const float2* trow = reinterpret_cast<const float2*>(A.src) + b * M;
-      for_entries<THREADS, 16, Entry<float2>>(
-          C,
+      for_entries<THREADS, NARROW ? 8 : 16, Entry<float2>>(
+          total,
           [&](int i) {
-            const unsigned it = item[i];
-            return Entry<float2>{it, trow[unsigned(i + dl[it & 255]) & nm]};
+            const int r = NARROW ? i >> pg.lC : 0, e = i - (r << pg.lC);
+            const unsigned it = item[e];
+            return Entry<float2>{it, trow[(unsigned(e + dl[it & 255]) & nm) + (unsigned(r) << pg.lC)]};
           },
-          [&](int, const Entry<float2>& e) { lds[(e.it >> 8) & kMask] = e.v; });
+          [&](int i, const Entry<float2>& e) { lds[at_row(e.it >> 8, i)] = e.v; });
       __syncthreads();
-      columns([&](int ci, int col, unsigned) {
+      columns([&](int ci, int col, unsigned, unsigned o) {
 #pragma unroll
         for (int j = 0; j < R; ++j) h[ci][j] = lds[j * W + col];
       });
-      if (b + 1 < b1) __syncthreads();
+      if (b + rw < b1) __syncthreads();
     } else {
-      columns([&](int ci, int, unsigned n8) {
+      columns([&](int ci, int, unsigned n8, unsigned o) {
         float2 y[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) y[r] = z.ld2(n8, r * sq8);
+        for (int r = 0; r < R; ++r) y[r] = z.ld2(n8 + o, r * sq8);
 #pragma unroll
         for (int r = 1; r < R; ++r) y[r] = cmulc(y[r], tw.ld2(n8, (r - 1) * sq8));
         Dft<R, true>::run(y);
@@ -540,7 +568,7 @@ __global__ __launch_bounds__(col_threads(R, 2)) __attribute__((amdgpu_waves_per_
     }
     if constexpr (BWD) {
       const GView uv = GView::of(A.u + 2 * b * M);
-      columns([&](int ci, int, unsigned n8) {
+      columns([&](int ci, int, unsigned n8, unsigned o) {
 #pragma unroll
         for (int j = 0; j < R; ++j) {
           if (j == R / 2) ACDC_SCHED_FENCE();
@@ -553,13 +581,13 @@ __global__ __launch_bounds__(col_threads(R, 2)) __attribute__((amdgpu_waves_per_
     if constexpr (SINK == Sink::dif && !BWD) {
       if (A.stash != nullptr) {
         const GView st = GView::of(A.stash + 2 * b * M);
-        columns([&](int ci, int, unsigned n8) {
+        columns([&](int ci, int, unsigned n8, unsigned o) {
 #pragma unroll
-          for (int j = 0; j < R; ++j) st.st2(h[ci][j], n8, j * sq8);
+          for (int j = 0; j < R; ++j) st.st2(h[ci][j], n8 + o, j * sq8);
         });
       }
       if (A.a != nullptr) {
-        columns([&](int ci, int, unsigned n8) {
+        columns([&](int ci, int, unsigned n8, unsigned o) {
 #pragma unroll
           for (int j = 0; j < R; ++j) h[ci][j] = cmul(h[ci][j], av.ld2(n8, j * sq8));
         });
@@ -567,32 +595,35 @@ __global__ __launch_bounds__(col_threads(R, 2)) __attribute__((amdgpu_waves_per_
     }
     if constexpr (SINK == Sink::rows) {
       const GView out = GView::of(A.dst + 2 * b * M);
-      columns([&](int ci, int, unsigned n8) {
+      columns([&](int ci, int, unsigned n8, unsigned o) {
 #pragma unroll
-        for (int j = 0; j < R; ++j) out.st2(h[ci][j], n8, j * sq8);
+        for (int j = 0; j < R; ++j) out.st2(h[ci][j], n8 + o, j * sq8);
       });
     } else if constexpr (SINK == Sink::send) {
-      columns([&](int ci, int col, unsigned) {
+      columns([&](int ci, int col, unsigned, unsigned o) {
 #pragma unroll
         for (int j = 0; j < R; ++j) lds[j * W + col] = h[ci][j];
       });
       __syncthreads();
       float2* trow = reinterpret_cast<float2*>(A.dst) + b * M;
       for_entries<THREADS, 8, unsigned>(
-          C, [&](int i) { return item[i]; },
-          [&](int i, unsigned it) { trow[unsigned(i + dl[it & 255]) & nm] = lds[(it >> 8) & kMask]; });
-      if (b + 1 < b1) __syncthreads();
+          total, [&](int i) { return item[NARROW ? i & (C - 1) : i]; },
+          [&](int i, unsigned it) {
+            const int r = NARROW ? i >> pg.lC : 0, e = i - (r << pg.lC);
+            trow[(unsigned(e + dl[it & 255]) & nm) + (unsigned(r) << pg.lC)] = lds[at_row(it >> 8, i)];
+          });
+      if (b + rw < b1) __syncthreads();
     } else if constexpr (SINK == Sink::ret) {
-      columns([&](int ci, int col, unsigned) {
+      columns([&](int ci, int col, unsigned, unsigned o) {
 #pragma unroll
         for (int j = 0; j < R; ++j) lds[loc.ldu16(unsigned(col) * 2u, unsigned(j << pg.lw) * 2u) & kMask] = h[ci][j];
       });
       __syncthreads();
       float4* t4 = reinterpret_cast<float4*>(A.dst + 2 * (b * M + ((long long)c << pg.lC)));
       for (int i = threadIdx.x; i < C / 2; i += THREADS) t4[i] = lds4[i];
-      if (b + 1 < b1) __syncthreads();
+      if (b + rw < b1) __syncthreads();
     } else {
-      columns([&](int ci, int, unsigned n8) {
+      columns([&](int ci, int, unsigned n8, unsigned o) {
         float2 x[R];
 #pragma unroll
         for (int j = 0; j < R; ++j) x[j] = h[ci][j];
@@ -600,13 +631,13 @@ __global__ __launch_bounds__(col_threads(R, 2)) __attribute__((amdgpu_waves_per_
 #pragma unroll
         for (int r = 1; r < R; ++r) x[r] = cmul(x[r], tw.ld2(n8, (r - 1) * sq8));
 #pragma unroll
-        for (int r = 0; r < R; ++r) z.st2(x[r], n8, r * sq8);
+        for (int r = 0; r < R; ++r) z.st2(x[r], n8 + o, r * sq8);
       });
     }
   }
   if constexpr (BWD) {
     const GView out = GView::of(A.part + 2 * p * M);
-    columns([&](int ci, int, unsigned n8) {
+    columns([&](int ci, int, unsigned n8, unsigned o) {
 #pragma unroll
       for (int j = 0; j < R; ++j) out.st2(s[ci][j], n8, j * sq8);
     });
@@ -674,6 +705,9 @@ bool with_seg_plan(int L, F&& f) {
     default: return false;
   }
 }
+static_assert(SP64::T == seg_fwd_threads(64) && SP1024::T == seg_fwd_threads(1024) &&
+                  SP2048::T == seg_fwd_threads(2048) && SP4096F::T == seg_fwd_threads(4096),
+              "the forward plans' threads");
 
 // The segment launches loop over rows and are bound by arithmetic and LDS
 // about as much as by HBM, so a thread keeps what does not change between
@@ -1190,8 +1224,14 @@ bool with_r1(int R1, F&& f) {
 template <Src SRC, Sink SINK, bool BWD>
 bool launch_cols(bool cplx, int R1, dim3 grid, const ColArgs& a, hipStream_t s) {
   return with_r1(R1, [&]<int R>() {
-    if (cplx) hipLaunchKernelGGL((k_ccols<R, SRC, SINK, BWD>), grid, dim3(col_threads(R, 2)), 0, s, a);
-    else hipLaunchKernelGGL((k_cols<R, SRC, SINK, BWD>), grid, dim3(col_threads(R, 1)), 0, s, a);
+    auto launch = [&]<bool NARROW>() {
+      if (cplx) hipLaunchKernelGGL((k_ccols<R, SRC, SINK, BWD, NARROW>), grid, dim3(col_threads(R, 2)), 0, s, a);
+      else hipLaunchKernelGGL((k_cols<R, SRC, SINK, BWD, NARROW>), grid, dim3(col_threads(R, 1)), 0, s, a);
+    };
+    if constexpr (narrow(R, BWD)) {
+      if (a.rw > 1) return launch.template operator()<true>();
+    }
+    launch.template operator()<false>();
   });
 }
 
@@ -1281,7 +1321,7 @@ hipError_t cols(Src src, Sink sink, bool cplx, const Cols& c, long long B, const
   const ColGrid cg = col_grid(B, g, pg.ew, bwd);
   if (cg.groups * cg.threads >= 1LL << 32) return hipErrorInvalidValue;
   ColArgs a{c.src,   c.dst, c.Z,  c.a,    c.stash, c.u, c.part, tw1, nullptr, nullptr, nullptr, B, g.M,
-            cg.rb, c.relu, pg};
+            cg.rw, cg.rb, c.relu, pg};
   if (c.pt != nullptr) {
     a.item = c.pt->item;
     a.loc = c.pt->loc;
@@ -1321,7 +1361,7 @@ hipError_t mq(const float* D, const float* Bias, float4* Mq, int K, const Geo& g
 
 hipError_t seg_fwd(float2* Z, const float4* Mq, long long B, const Geo& g, bool bias, const char* seg_tab,
                    hipStream_t s) {
-  const int rb = seg_rows(B, g, false);
+  const int rb = seg_fwd_rows(B, g, false);
   const bool ok = with_seg_plan<true>(g.L, [&]<class PL>() {
     hipLaunchKernelGGL(k_seg_fwd<PL>, seg_grid<PL>((B + rb - 1) / rb * (g.R1 * g.R2 / 2)), dim3(Seg<PL>::THREADS), 0,
                        s, Z, Mq, B, g, rb, bias ? 1 : 0, seg_tab);
@@ -1354,7 +1394,7 @@ hipError_t dn(const float2* D, float2* Dn, int K, const Geo& g, hipStream_t s) {
 }
 
 hipError_t cseg_fwd(float2* Z, const float2* Dn, long long B, const Geo& g, const char* seg_tab, hipStream_t s) {
-  const int rb = seg_rows(B, g, true);
+  const int rb = seg_fwd_rows(B, g, true);
   const bool ok = with_seg_plan<true>(g.L, [&]<class PL>() {
     hipLaunchKernelGGL(k_cseg_fwd<PL>, seg_grid<PL>((B + rb - 1) / rb * (g.R1 * g.R2)), dim3(Seg<PL>::THREADS), 0, s,
                        Z, Dn, B, g, rb, seg_tab);

@@ -337,10 +337,12 @@ extern "C" int acdc_emu_reduce4(const float* partial, long long ntiles, long lon
 }
 
 // Geometry of the multi-pass rows of N elements (ew = 1 real, 2 complex).
-// out: rows in turn, threads of a workgroup, workgroups of a column launch.
+// out: rows in turn, threads of a workgroup, workgroups, rows side by side of a
+// column launch.
 extern "C" void acdc_emu_mp_col_grid(long long batch, int N, int ew, int sums, long long* out) {
   const mp::ColGrid c = mp::col_grid(batch, mp::geo((long long)N * ew), ew, sums != 0);
   out[0] = c.rb;
   out[1] = c.threads;
   out[2] = c.groups;
+  out[3] = c.rw;
 }

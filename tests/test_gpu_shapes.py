@@ -3,6 +3,7 @@
 Each case runs through the same comparison with the fp64 oracle as the other
 GPU parity tests (every element, same tolerance)."""
 
+import numpy as np
 import pytest
 
 from oracle import acdc_oracle as O
@@ -73,6 +74,17 @@ def test_multipass_plans(acdc, N, K, B, flags):  # noqa: F811
                                          (512, 2, 4099, CX | MP)])
 def test_multipass_row_block_edges(acdc, N, K, B, flags):  # noqa: F811
     run_case(acdc, N, K, B, flags, seed=N % 1000 + B)
+
+
+# Narrow multi-pass rows share a column workgroup from 1024 rows on (B / 512
+# rows side by side, at most those of 16384 floats): the last batch of one row
+# a workgroup, whole and ragged last workgroups, the most rows there are.
+@pytest.mark.parametrize("N,B,flags", [(256, 1023, P | R | MP), (256, 1027, P | R | FLAG_BIAS | MP),
+                                       (256, 40000, P | MP), (2048, 4101, P | R | MP), (8192, 1025, P | FLAG_BIAS | MP),
+                                       (256, 1025, CX | P | MP), (512, 20001, CX | P | MP), (2048, 3000, CX | MP)])
+def test_multipass_narrow_rows_share_workgroups(acdc, N, B, flags):  # noqa: F811
+    rows = np.unique(np.concatenate([np.arange(0, B, max(1, B // 120)), np.arange(max(0, B - 70), B)]))
+    run_case(acdc, N, 3, B, flags, seed=N + B, rows=rows)
 
 
 # Column launches whose workgroups take several rows in turn: more rows than

@@ -26,7 +26,7 @@ def emu():
 
 
 def col_grid(emu, B, N, ew, sums):
-    out = (ctypes.c_longlong * 3)()
+    out = (ctypes.c_longlong * 4)()
     emu.acdc_emu_mp_col_grid(B, N, ew, sums, out)
     return tuple(out)
 
@@ -40,13 +40,16 @@ def test_column_launches_fit_any_batch(emu, N, ew):
     for B in (1, 2, 511, 65535, 65536, 65537, 1 << 23, (1 << 23) + 1, (1 << 40) // N):
         if B > (1 << 40) // N:
             continue
-        rb, threads, groups = col_grid(emu, B, N, ew, 0)
+        rb, threads, groups, rw = col_grid(emu, B, N, ew, 0)
         sets = max(1, N * ew // 16384)
-        assert rb >= 1 and groups == -(-B // rb) * sets
+        assert rb >= 1 and groups == -(-B // (rb * rw)) * sets
         assert groups * threads < 1 << 32
-        if B * sets <= 65536:
-            assert rb == 1                          # a workgroup for every row and set
+        # rows side by side: what fits a set of 16384 floats, and only while
+        # every CU has two workgroups
+        assert 1 <= rw <= max(1, 16384 // (N * ew)) and (rw == 1 or B // rw >= 512)
+        if -(-B // rw) * sets <= 65536:
+            assert rb == 1                          # a workgroup of its own for every rw rows and set
         if B <= (1 << 36) // (N * ew):
-            rb, threads, groups = col_grid(emu, B, N, ew, 1)
-            assert 1 <= rb <= 16 and groups == -(-B // rb) * sets
+            rb, threads, groups, rw = col_grid(emu, B, N, ew, 1)
+            assert rw == 1 and 1 <= rb <= 16 and groups == -(-B // rb) * sets
             assert groups * threads < 1 << 32
