@@ -777,8 +777,8 @@ MpFwdWs mp_fwd_ws(int64_t batch, int32_t N, int32_t K, uint32_t flags) {
 
 // Backward workspace: the coefficients, the h and g spectra (contiguous:
 // the second-level passes take both), the rows between the halves of a
-// permutation, the row-block sums, with a bias the batch sum of g's spectra
-// and its block sums, the recompute stash and the permutation tables.  At
+// permutation, the row-block sums, with a bias every layer's batch sum of g's
+// spectra and their block sums, the recompute stash and the permutation tables.  At
 // least as large as earlier releases' layout, as in the forward.
 struct MpBwdWs {
   size_t coef = 0, zhg = 0, tmp = 0, part = 0, zsum = 0, partB = 0, stash = 0, ptab = 0, total = 0;
@@ -799,7 +799,7 @@ MpBwdWs mp_bwd_ws(int64_t batch, int32_t N, int32_t K, uint32_t flags, bool have
   w.tmp = take(perm_on ? rows : 0);
   auto blocks = [&](int rb) { return size_t((batch + rb - 1) / rb); };
   w.part = take(size_t(mp::max_blocks(batch, g, mp_ew(flags))) * rowb);
-  w.zsum = take(bias ? rowb : 0);
+  w.zsum = take(bias ? size_t(K) * rowb : 0);
   w.partB = take(bias ? blocks(mp::kMaxRows) * rowb : 0);
   w.stash = take(have_saved ? 0 : saved_floats(batch, N, K, flags) * sizeof(float));
   w.ptab = take(mp_perm_bytes(g, K, flags));
@@ -932,7 +932,7 @@ int mp_forward(const float* x, float* y, const float* A, const float* D, const f
 // launch sums the dL/dd images and leaves the inverse's segments in Zg; the
 // column launch after it sums the dL/da images and takes g * a through the
 // adjoint permutation to the next layer's Zg.  dL/db_k is the DCT-II of the
-// batch sum of g, taken on its spectrum.
+// batch sum of g, taken on its spectrum, for all layers at the end.
 int mp_backward(const float* x, const float* grad_y, const float* A, const float* D, const float* bias,
                 const int32_t* perm, const float* saved, float* grad_x, float* grad_A, float* grad_D,
                 float* grad_bias, int64_t batch, int32_t N, int32_t K, uint32_t flags, bool have_saved,
@@ -992,11 +992,7 @@ int mp_backward(const float* x, const float* grad_y, const float* A, const float
       MP_TRY(m.cols(Src::rows, Sink::dif, c));
     }
     MP_TRY(mp::dif2(Zh, 2 * batch, g, m.t.tw2, s));
-    if (m.bias) {
-      MP_TRY(mp::colsum(reinterpret_cast<const float*>(Zg), batch, m.W, partB, zsum, s));
-      MP_TRY(mp::seg_dct(reinterpret_cast<const float2*>(zsum), m.mq(k), g, m.t.q, grad_bias + k * m.W, acc, m.t.seg,
-                         s));
-    }
+    if (m.bias) MP_TRY(mp::colsum(reinterpret_cast<const float*>(Zg), batch, m.W, partB, zsum + k * m.W, s));
     if (m.cplx) MP_TRY(mp::cseg_bwd(Zh, Zg, m.coef + (long long)k * N, batch, g, part, m.t.seg, s));
     else MP_TRY(mp::seg_bwd(Zh, Zg, m.mq(k), batch, g, part, m.t.seg, s));
     MP_TRY(mp::colsum_parts(part, pseg, m.W, gD, order, g, &m.t.q, acc, s));
@@ -1029,6 +1025,7 @@ int mp_backward(const float* x, const float* grad_y, const float* A, const float
       MP_TRY(m.cols(Src::scatter, k == 0 ? Sink::rows : Sink::dif, d));
     }
   }
+  if (m.bias) MP_TRY(mp::seg_dct(reinterpret_cast<const float2*>(zsum), m.mq(0), K, g, grad_bias, acc, m.t.seg, s));
   return ACDC_OK;
 }
 

@@ -114,13 +114,16 @@ __host__ __device__ __forceinline__ void seg_pair(const Geo& g, int p, int& sa, 
 // (Z[0], Z[M/2]) and otherwise Z[e] pairs with Z[M-e].  In a generic pair it
 // is the quartet of segment A's k2, in pair 0 those of segment 0 come first
 // (k2 < L/2), then the other segment's.
-__host__ __device__ __forceinline__ long long quartet_of(const Geo& g, int p, int k2) {
+__host__ __device__ __forceinline__ long long quartet_of(const Geo& g, int p, int sa, int k2) {
   const long long S = (long long)g.R1 * g.R2;
   if (p == 0) return k2 < g.L / 2 ? S * k2 : S / 2 + S * (k2 - g.L / 2);
+  const long long k = sa / g.R2 + (long long)g.R1 * (sa % g.R2) + S * k2;
+  return k < g.M / 2 ? k : g.M - k;
+}
+__host__ __device__ __forceinline__ long long quartet_of(const Geo& g, int p, int k2) {
   int sa, sb;
   seg_pair(g, p, sa, sb);
-  const long long k = sa / g.R2 + (long long)g.R1 * (sa % g.R2 + (long long)g.R2 * k2);
-  return k < g.M / 2 ? k : g.M - k;
+  return quartet_of(g, p, sa, k2);
 }
 
 // Spectrum index of storage position q.

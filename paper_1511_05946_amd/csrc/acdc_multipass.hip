@@ -1000,10 +1000,16 @@ __global__ __launch_bounds__(Seg<PL>::THREADS) __attribute__((amdgpu_waves_per_e
   for (int s = 0; s < P; ++s) out[T * s + t] = sum[s];
 }
 
-// DCT-II outputs of one row whose DIF passes are done (the bias gradient).
+// DCT-II outputs of one row per layer whose DIF passes are done (the bias
+// gradients): out[k] (+)= those of Z[k].  Latency is all there is, so one
+// launch takes every layer, all table loads are issued before the FFT, and
+// the DCT indices are computed: read per slot between the stores, which the
+// compiler cannot move loads across, they took 15 to 20 us, and a launch per
+// layer at that.  N = 65536, K = 4, one row with biases, backward 271 -> 190
+// us.
 template <class PL>
 __global__ __launch_bounds__(Seg<PL>::THREADS) void k_seg_dct(const float2* __restrict__ Z,
-                                                              const float4* __restrict__ Mq, Geo g, QuartetTabs q,
+                                                              const float4* __restrict__ Mq, int K, Geo g,
                                                               float* __restrict__ out, int accumulate,
                                                               const char* __restrict__ tab) {
   using G = Seg<PL>;
@@ -1012,35 +1018,51 @@ __global__ __launch_bounds__(Seg<PL>::THREADS) void k_seg_dct(const float2* __re
   __shared__ float lds[G::GROUPS * 2 * G::SLAB];
   const unsigned t = threadIdx.x % T, grp = threadIdx.x / T;
   float2* slab = reinterpret_cast<float2*>(lds + grp * 2 * G::SLAB);
-  const SegWork wk((long long)blockIdx.x * G::GROUPS + grp, g.R1 * g.R2 / 2, 1, 1);
+  const SegWork wk((long long)blockIdx.x * G::GROUPS + grp, g.R1 * g.R2 / 2, K, 1);
   const int p = wk.unit;
   int sa, sb;
   seg_pair(g, p, sa, sb);
+  const float2* z = Z + wk.blk * g.M;
   DevCtx<T> ctx;
   typename G::Tw tw, rt;
+  float2 x[2][P];
+  G::load(z + (long long)sa * PL::N, x[0], t);
+  G::load(z + (long long)sb * PL::N, x[1], t);
   tw.load(t, GView::of(tab));
   rt.load(T - 1 - t, GView::of(tab));
-  float2 x[2][P];
-  G::load(Z + (long long)sa * PL::N, x[0], t);
-  G::load(Z + (long long)sb * PL::N, x[1], t);
-  G::template fft<false, 2, true>(ctx, x, t, slab, tw, rt);
-  if (p == 0) Q::to_quartets(ctx, x[0], x[1], t, slab);
-  const GView mq = GView::of(Mq + (long long)p * PL::N * kMqRows);
+  const GView mq = GView::of(Mq + wk.blk * (g.M / 2) * kMqRows + (long long)p * PL::N * kMqRows);
+  float4 c1[P], c2[P];
 #pragma unroll
   for (int s = 0; s < P; ++s) {
-    const float4 c1 = mq.ld4(t * 16u, unsigned((1 * PL::N + s * T) * 16));
-    const float4 c2 = mq.ld4(t * 16u, unsigned((2 * PL::N + s * T) * 16));
-    float X[4];
-    quartet_post(quartet_split(Q::zk(x[0], x[1], s), Q::zm(x[0], x[1], s), make_float2(c1.z, c1.w)),
-                 make_float2(c2.x, c2.y), make_float2(c2.z, c2.w), X);
-    X[1] = -X[1];
-    const long long e = quartet_of(g, p, int(t) + T * s);
-    const int4 idx = q.qidx[e];
-    const int sm = (q.qmask[e] >> 4) & 0xF;
-    const int id4[4] = {idx.x, idx.y, idx.z, idx.w};
+    c1[s] = mq.ld4(t * 16u, unsigned((1 * PL::N + s * T) * 16));
+    c2[s] = mq.ld4(t * 16u, unsigned((2 * PL::N + s * T) * 16));
+  }
+  ACDC_SCHED_FENCE();
+  G::template fft<false, 2, true>(ctx, x, t, slab, tw, rt);
+  if (p == 0) Q::to_quartets(ctx, x[0], x[1], t, slab);
+  if (!wk.valid) return;
+  float X[P][4], old[P][4];
+  int4 id[P];
+  out += wk.blk * 2 * g.M;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (wk.valid && (sm & (1 << j))) put1(out + id4[j], X[j], accumulate != 0);
+  for (int s = 0; s < P; ++s) {
+    const int e = int(quartet_of(g, p, sa, int(t) + T * s));
+    id[s] = quartet_idx(int(2 * g.M), e == 0 ? -2 : e);
+    quartet_post(quartet_split(Q::zk(x[0], x[1], s), Q::zm(x[0], x[1], s), make_float2(c1[s].z, c1[s].w)),
+                 make_float2(c2[s].x, c2[s].y), make_float2(c2[s].z, c2[s].w), X[s]);
+    X[s][1] = -X[s][1];
+  }
+#pragma unroll
+  for (int s = 0; s < P; ++s) {
+    const int i4[4] = {id[s].x, id[s].y, id[s].z, id[s].w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) old[s][j] = accumulate ? out[i4[j]] : 0.f;
+  }
+#pragma unroll
+  for (int s = 0; s < P; ++s) {
+    const int i4[4] = {id[s].x, id[s].y, id[s].z, id[s].w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) out[i4[j]] = accumulate ? old[s][j] + X[s][j] : X[s][j];
   }
 }
 
@@ -1379,11 +1401,11 @@ hipError_t seg_bwd(float2* Zh, float2* Zg, const float4* Mq, long long B, const 
   return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
-hipError_t seg_dct(const float2* Z, const float4* Mq, const Geo& g, const QuartetTabs& q, float* gB,
-                   bool accumulate, const char* seg_tab, hipStream_t s) {
+hipError_t seg_dct(const float2* Z, const float4* Mq, int K, const Geo& g, float* gB, bool accumulate,
+                   const char* seg_tab, hipStream_t s) {
   const bool ok = with_seg_plan<false>(g.L, [&]<class PL>() {
-    hipLaunchKernelGGL(k_seg_dct<PL>, seg_grid<PL>(g.R1 * g.R2 / 2), dim3(Seg<PL>::THREADS), 0, s, Z, Mq, g, q, gB,
-                       accumulate ? 1 : 0, seg_tab);
+    hipLaunchKernelGGL(k_seg_dct<PL>, seg_grid<PL>((long long)K * (g.R1 * g.R2 / 2)), dim3(Seg<PL>::THREADS), 0, s, Z,
+                       Mq, K, g, gB, accumulate ? 1 : 0, seg_tab);
   });
   return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
@@ -1432,11 +1454,13 @@ hipError_t colsum_parts(const float* part, long long P, long long W, float* out,
 }
 
 hipError_t colsum(const float* img, long long B, long long W, float* part, float* out, hipStream_t s) {
+  Geo g{W / 2, 4096, 2, 1};
+  // few rows: one launch, each phase taking the rows of a block
+  if (B <= kSumPh * kMaxRows) return colsum_parts(img, B, W, out, Order::natural, g, nullptr, false, s);
   const long long P = (B + kMaxRows - 1) / kMaxRows;
   hipLaunchKernelGGL(k_colsum1, grid_for(P * (W / 4)), dim3(kThreads), 0, s, img, B, W, part);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  Geo g{W / 2, 4096, 2, 1};
   return colsum_parts(part, P, W, out, Order::natural, g, nullptr, false, s);
 }
 

@@ -108,9 +108,10 @@ hipError_t seg_fwd(float2* Z, const float4* Mq, long long B, const Geo& g, bool 
 // Zg <- the inverse FFT's segments of DCT-III's input.
 hipError_t seg_bwd(float2* Zh, float2* Zg, const float4* Mq, long long B, const Geo& g, float* part,
                    const char* seg_tab, hipStream_t s);
-// gB (+)= the DCT-II whose first-level spectrum (DIF passes done) is Z, one row.
-hipError_t seg_dct(const float2* Z, const float4* Mq, const Geo& g, const QuartetTabs& q, float* gB,
-                   bool accumulate, const char* seg_tab, hipStream_t s);
+// gB[k] (+)= the DCT-II whose spectrum after the DIF passes is Z[k], one row
+// per layer; Mq as above (all K layers).
+hipError_t seg_dct(const float2* Z, const float4* Mq, int K, const Geo& g, float* gB, bool accumulate,
+                   const char* seg_tab, hipStream_t s);
 // Complex rows: Dn holds d / N of all layers in storage order, [K][M] (dn).
 hipError_t dn(const float2* D, float2* Dn, int K, const Geo& g, hipStream_t s);
 hipError_t cseg_fwd(float2* Z, const float2* Dn, long long B, const Geo& g, const char* seg_tab, hipStream_t s);
@@ -125,7 +126,8 @@ enum class Order { natural, quartets, spectrum };
 hipError_t colsum_parts(const float* part, long long P, long long W, float* out, Order how, const Geo& g,
                         const QuartetTabs* q, bool accumulate, hipStream_t s);
 // out[w] = sum over the B rows of img[b][w]: blocks of kMaxRows rows into
-// part, then the block sums.  W is a multiple of 4.
+// part, then the block sums (up to 128 rows the rows themselves in their
+// place).  W is a multiple of 4.
 hipError_t colsum(const float* img, long long B, long long W, float* part, float* out, hipStream_t s);
 
 // Constant table of the segment plan of L points (fill: host bytes): the
