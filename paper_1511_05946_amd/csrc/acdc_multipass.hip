@@ -872,11 +872,12 @@ constexpr int seg_fwd_waves() {
   return PL::P == 8 ? 4 : 2;
 }
 
-// Forward: segment FFTs of a pair, the quartet maps, segment IFFTs.
-template <class PL>
+// Forward: segment FFTs of a pair, the quartet maps, segment IFFTs.  BIAS: a
+// template, since a branch on it per slot kept every slot's c3 load from
+// being issued with the others (N = 65536, one row: 15 -> 20 us a launch).
+template <class PL, bool BIAS>
 __global__ __launch_bounds__(Seg<PL>::THREADS) __attribute__((amdgpu_waves_per_eu(seg_fwd_waves<PL>()))) void k_seg_fwd(
-    float2* __restrict__ Z, const float4* __restrict__ Mq, long long B, Geo g, int rb, int bias,
-    const char* __restrict__ tab) {
+    float2* __restrict__ Z, const float4* __restrict__ Mq, long long B, Geo g, int rb, const char* __restrict__ tab) {
   using G = Seg<PL>;
   using Q = PairOps<PL>;
   constexpr int T = PL::T, P = PL::P;
@@ -908,9 +909,10 @@ __global__ __launch_bounds__(Seg<PL>::THREADS) __attribute__((amdgpu_waves_per_e
       float2& zm = Q::zm(x[0], x[1], s);
       const float4 c0 = mq.ld4(t16, unsigned((0 * PL::N + s * T) * 16));
       const float4 c1 = mq.ld4(t16, unsigned((1 * PL::N + s * T) * 16));
+      float4 c3;
+      if constexpr (BIAS) c3 = mq.ld4(t16, unsigned((3 * PL::N + s * T) * 16));
       quartet_back(quartet_split(zk, zm, make_float2(c1.z, c1.w)), c0, c1, zk, zm);
-      if (bias) {
-        const float4 c3 = mq.ld4(t16, unsigned((3 * PL::N + s * T) * 16));
+      if constexpr (BIAS) {
         zk = make_float2(zk.x + c3.x, zk.y + c3.y);
         zm = make_float2(zm.x + c3.z, zm.y + c3.w);
       }
@@ -1385,8 +1387,9 @@ hipError_t seg_fwd(float2* Z, const float4* Mq, long long B, const Geo& g, bool 
                    hipStream_t s) {
   const int rb = seg_fwd_rows(B, g, false);
   const bool ok = with_seg_plan<true>(g.L, [&]<class PL>() {
-    hipLaunchKernelGGL(k_seg_fwd<PL>, seg_grid<PL>((B + rb - 1) / rb * (g.R1 * g.R2 / 2)), dim3(Seg<PL>::THREADS), 0,
-                       s, Z, Mq, B, g, rb, bias ? 1 : 0, seg_tab);
+    const dim3 grid = seg_grid<PL>((B + rb - 1) / rb * (g.R1 * g.R2 / 2)), block(Seg<PL>::THREADS);
+    if (bias) hipLaunchKernelGGL((k_seg_fwd<PL, true>), grid, block, 0, s, Z, Mq, B, g, rb, seg_tab);
+    else hipLaunchKernelGGL((k_seg_fwd<PL, false>), grid, block, 0, s, Z, Mq, B, g, rb, seg_tab);
   });
   return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
