@@ -126,6 +126,30 @@ __host__ __device__ __forceinline__ long long quartet_of(const Geo& g, int p, in
   return quartet_of(g, p, sa, k2);
 }
 
+// The inverse: pair and place of quartet e.
+__host__ __device__ __forceinline__ void quartet_place(const Geo& g, long long e, int& p, int& k2) {
+  const int S = g.R1 * g.R2, c = int(e % S), r1 = c % g.R1, r2 = c / g.R1;
+  k2 = int(e / S);
+  if (c == 0 || c == S / 2) {
+    p = 0;
+    if (c != 0) k2 += g.L / 2;
+    return;
+  }
+  const int H = 1 + (g.R1 / 2 - 1) * g.R2;  // the first pair inside r1 = R1 / 2
+  bool second;                              // e lies in the pair's segment B
+  if (r1 == 0) {
+    second = r2 > g.R2 / 2;
+    p = H + g.R2 / 2 + (second ? g.R2 - 1 - r2 : r2 - 1);
+  } else if (r1 == g.R1 / 2) {
+    second = r2 >= g.R2 / 2;
+    p = H + (second ? g.R2 - 1 - r2 : r2);
+  } else {
+    second = r1 > g.R1 / 2;
+    p = second ? 1 + (g.R1 - r1 - 1) * g.R2 + g.R2 - 1 - r2 : 1 + (r1 - 1) * g.R2 + r2;
+  }
+  if (second) k2 = g.L - 1 - k2;
+}
+
 // Spectrum index of storage position q.
 __host__ __device__ __forceinline__ long long spec_index(const Geo& g, long long q) {
   const long long S1 = g.M / g.R1;

@@ -1146,19 +1146,43 @@ __global__ __launch_bounds__(Seg<PL>::THREADS) __attribute__((amdgpu_waves_per_e
   for (int s = 0; s < P; ++s) out[T * s + t] = make_float2(sum[s].x * inv, sum[s].y * inv);
 }
 
-// Per-layer quartet coefficients, [K][pair][kMqRows][k2].
+// Per-layer quartet coefficients, [K][pair][kMqRows][k2].  A pair's quartets
+// lie S = R1 R2 apart in the tables and in D, so a workgroup takes a tile of
+// cw neighbouring quartets in each of kThreads / cw places k2 and turns it in
+// LDS: it reads runs of cw entries and writes runs of neighbouring places.
+// N = 2^22 (S = 512), K = 4: 619 us with a thread for each place in order
+// (every read a cache line of its own), 112 with the tiles.
+constexpr int kMqTile = 16;
 __global__ __launch_bounds__(kThreads) void k_mq(const float* __restrict__ D, const float* __restrict__ Bias,
                                                  float4* __restrict__ Mq, int K, Geo g, QuartetTabs q) {
-  const long long NQ = g.M / 2, total = (long long)K * NQ, N = 2 * g.M;
-  for (long long i = gindex(); i < total; i += gstride()) {
-    const long long k = i / NQ, r = i % NQ;
-    const int p = int(r / g.L), k2 = int(r % g.L);
-    float4 row[kMqRows];
-    const int e = int(quartet_of(g, p, k2));
-    quartet_coeffs(D + k * N, Bias ? Bias + k * N : nullptr, q, e, quartet_idx(int(N), e == 0 ? -2 : e), row);
-    float4* out = Mq + (i - k2) * kMqRows + k2;
+  __shared__ float4 tile[kMqRows][kThreads];
+  const int S = g.R1 * g.R2, cw = S < kMqTile ? S : kMqTile, kw = kThreads / cw, places = g.L / 2;
+  const int tc = S / cw, tk = (places + kw - 1) / kw;  // tiles of a layer
+  const long long NQ = g.M / 2, N = 2 * g.M, total = (long long)K * tc * tk;
+  const int tid = threadIdx.x;
+  for (long long i = blockIdx.x; i < total; i += gridDim.x) {
+    const long long k = i / (tc * tk);
+    const int r = int(i % (tc * tk)), c0 = r % tc * cw, k0 = r / tc * kw;
+    {
+      const int c = tid % cw, kk = tid / cw;
+      if (k0 + kk < places) {
+        const int e = c0 + c + S * (k0 + kk);
+        float4 row[kMqRows];
+        quartet_coeffs(D + k * N, Bias ? Bias + k * N : nullptr, q, e, quartet_idx(int(N), e == 0 ? -2 : e), row);
 #pragma unroll
-    for (int c = 0; c < kMqRows; ++c) out[c * g.L] = row[c];
+        for (int j = 0; j < kMqRows; ++j) tile[j][c * kw + kk] = row[j];
+      }
+    }
+    __syncthreads();
+    const int c = tid / kw, kk = tid % kw;
+    if (k0 + kk < places) {
+      int p, k2;
+      quartet_place(g, c0 + c + (long long)S * (k0 + kk), p, k2);
+      float4* out = Mq + (k * NQ + (long long)p * g.L) * kMqRows + k2;
+#pragma unroll
+      for (int j = 0; j < kMqRows; ++j) out[j * g.L] = tile[j][tid];
+    }
+    __syncthreads();
   }
 }
 
@@ -1379,7 +1403,9 @@ hipError_t dit2(float2* Z, long long B, const Geo& g, const float2* tw2, hipStre
 
 hipError_t mq(const float* D, const float* Bias, float4* Mq, int K, const Geo& g, const QuartetTabs& q,
               hipStream_t s) {
-  hipLaunchKernelGGL(k_mq, grid_for((long long)K * (g.M / 2)), dim3(kThreads), 0, s, D, Bias, Mq, K, g, q);
+  // a layer's M / 2 quartets, or one tile's threads where it has fewer
+  const long long n = (long long)K * (g.M / 2 > kThreads ? g.M / 2 : kThreads);
+  hipLaunchKernelGGL(k_mq, grid_for(n), dim3(kThreads), 0, s, D, Bias, Mq, K, g, q);
   return hipGetLastError();
 }
 

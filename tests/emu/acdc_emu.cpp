@@ -346,3 +346,17 @@ extern "C" void acdc_emu_mp_col_grid(long long batch, int N, int ew, int sums, l
   out[2] = c.groups;
   out[3] = c.rw;
 }
+
+// Quartets of a row's M-point FFT by pair and place: out[p][k2] = the quartet
+// there, and back[e] = pair L + place of quartet e.  Returns L.
+extern "C" int acdc_emu_mp_quartets(int N, int ew, long long* out, long long* back) {
+  const mp::Geo g = mp::geo((long long)N * ew);
+  for (int p = 0; p < g.R1 * g.R2 / 2; ++p)
+    for (int k2 = 0; k2 < g.L; ++k2) out[(long long)p * g.L + k2] = mp::quartet_of(g, p, k2);
+  for (long long e = 0; e < g.M / 2; ++e) {
+    int p, k2;
+    mp::quartet_place(g, e, p, k2);
+    back[e] = (long long)p * g.L + k2;
+  }
+  return g.L;
+}

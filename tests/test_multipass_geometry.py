@@ -1,4 +1,4 @@
-"""Launch sizes of the multi-pass rows (no GPU): the headers' own code, built
+"""Launch sizes and index algebra of the multi-pass rows (no GPU): the headers' own code, built
 for the host with the CPU emulation."""
 
 import ctypes
@@ -6,6 +6,7 @@ import os
 import shutil
 import sys
 
+import numpy as np
 import pytest
 
 sys.path.insert(0, os.path.join(os.path.dirname(__file__), "emu"))
@@ -22,6 +23,7 @@ def emu():
     import build_emu
     L = ctypes.CDLL(build_emu.build())
     L.acdc_emu_mp_col_grid.argtypes = [ctypes.c_longlong, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
+    L.acdc_emu_mp_quartets.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
     return L
 
 
@@ -53,3 +55,14 @@ def test_column_launches_fit_any_batch(emu, N, ew):
             rb, threads, groups, rw = col_grid(emu, B, N, ew, 1)
             assert rw == 1 and 1 <= rb <= 16 and groups == -(-B // rb) * sets
             assert groups * threads < 1 << 32
+
+
+@pytest.mark.parametrize("N", REAL)
+def test_quartet_places(emu, N):
+    # every quartet has one place, and the map from quartets to places is
+    # the inverse of the one from places to quartets
+    n = N // 4
+    out, back = np.full(n, -1, np.int64), np.full(n, -1, np.int64)
+    emu.acdc_emu_mp_quartets(N, 1, out.ctypes.data, back.ctypes.data)
+    assert np.array_equal(np.sort(out), np.arange(n))
+    assert np.array_equal(out[back], np.arange(n))
