@@ -12,8 +12,10 @@ namespace acdc {
 namespace mp {
 
 // Geometry of one row's M-point FFT: M = R1 * R2 * L, R1 in {2, 4, 8, 16},
-// R2 in {1, 2, ..., 32} (1 = no pass), L the in-LDS segment length, a power
-// of two from 64 to 4096.
+// R2 in {1, 2, ..., 32} (1 = no pass), L the in-LDS segment length, 64 to 1024
+// or 4096.  (2048, for M = 4096, has no plan of 8 values a thread that reads
+// the same forwards and backwards, and with 16 on 128 threads a row is a long
+// chain: see with_seg_plan.)
 struct Geo {
   long long M;
   int L, R1, R2;
@@ -22,7 +24,7 @@ struct Geo {
 inline Geo geo(long long N) {
   Geo g;
   g.M = N / 2;
-  g.L = int(g.M / 2 < 4096 ? g.M / 2 : 4096);
+  g.L = g.M >= 8192 ? 4096 : g.M >= 2048 ? 1024 : int(g.M / 2);
   const long long ratio = g.M / g.L;
   g.R1 = int(ratio <= 16 ? ratio : 16);
   g.R2 = int(ratio / g.R1);

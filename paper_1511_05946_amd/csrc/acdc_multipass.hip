@@ -685,7 +685,6 @@ using SP128 = ComplexPlan<128, 16, 8, 2, 8, 1, 4>;
 using SP256 = ComplexPlan<256, 32, 8, 4, 8, 1, 4>;
 using SP512 = ComplexPlan<512, 64, 8, 8, 8, 1, 4>;
 using SP1024 = ComplexPlan<1024, 128, 8, 4, 4, 8, 4>;
-using SP2048 = ComplexPlan<2048, 128, 16, 8, 16>;
 using SP4096 = ComplexPlan<4096, 512, 8, 8, 8, 8, 4>;
 using SP4096F = ComplexPlan<4096, 256, 16, 16, 16>;
 
@@ -697,7 +696,6 @@ bool with_seg_plan(int L, F&& f) {
     case 256: f.template operator()<SP256>(); return true;
     case 512: f.template operator()<SP512>(); return true;
     case 1024: f.template operator()<SP1024>(); return true;
-    case 2048: f.template operator()<SP2048>(); return true;
     case 4096:
       if constexpr (FWD) f.template operator()<SP4096F>();
       else f.template operator()<SP4096>();
@@ -706,7 +704,7 @@ bool with_seg_plan(int L, F&& f) {
   }
 }
 static_assert(SP64::T == seg_fwd_threads(64) && SP1024::T == seg_fwd_threads(1024) &&
-                  SP2048::T == seg_fwd_threads(2048) && SP4096F::T == seg_fwd_threads(4096),
+                  SP4096F::T == seg_fwd_threads(4096),
               "the forward plans' threads");
 
 // The segment launches loop over rows and are bound by arithmetic and LDS
