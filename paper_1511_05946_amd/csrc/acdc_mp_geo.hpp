@@ -12,10 +12,14 @@ namespace acdc {
 namespace mp {
 
 // Geometry of one row's M-point FFT: M = R1 * R2 * L, R1 in {2, 4, 8, 16},
-// R2 in {1, 2, ..., 32} (1 = no pass), L the in-LDS segment length, 64 to 1024
-// or 4096.  (2048, for M = 4096, has no plan of 8 values a thread that reads
-// the same forwards and backwards, and with 16 on 128 threads a row is a long
-// chain: see with_seg_plan.)
+// R2 in {1, 2, ..., 32} (1 = no pass), L the in-LDS segment length: 1024 from M
+// = 2048 to 8192, 4096 from 16384 on.  K = 4, forward and backward from the
+// stored layer inputs, other lengths against these: M = 4096 in segments of
+// 2048 (16 values on each of 128 threads) one row 108 and 210 us, 89 and 134
+// so; M = 8192 in segments of 4096 one row 131 and 181 against 98 and 157,
+// 1000 rows 479 and 979 against 470 and 963; M = 16384 in segments of 1024 one
+// row 130 and 188 against 146 and 199, but 1000 rows 1019 and 1851 against 976
+// and 1716.
 struct Geo {
   long long M;
   int L, R1, R2;
@@ -24,7 +28,7 @@ struct Geo {
 inline Geo geo(long long N) {
   Geo g;
   g.M = N / 2;
-  g.L = g.M >= 8192 ? 4096 : g.M >= 2048 ? 1024 : int(g.M / 2);
+  g.L = g.M >= 16384 ? 4096 : g.M >= 2048 ? 1024 : int(g.M / 2);
   const long long ratio = g.M / g.L;
   g.R1 = int(ratio <= 16 ? ratio : 16);
   g.R2 = int(ratio / g.R1);
