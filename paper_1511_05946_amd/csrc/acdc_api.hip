@@ -750,9 +750,7 @@ struct MpPerm {
 };
 
 // Forward workspace: the layers' coefficients, the spectra, and with PERM
-// the rows between the two halves of a permutation and the tables.  The
-// total is at least that of earlier releases' layout (three buffers of rows
-// with PERM, two without), which callers may have sized by hand.
+// the rows between the two halves of a permutation and the tables.
 struct MpFwdWs {
   size_t coef = 0, z = 0, tmp = 0, ptab = 0, total = 0;
 };
@@ -771,15 +769,14 @@ MpFwdWs mp_fwd_ws(int64_t batch, int32_t N, int32_t K, uint32_t flags) {
   w.z = take(rows);
   w.tmp = take(perm_on ? rows : 0);
   w.ptab = take(mp_perm_bytes(g, K, flags));
-  w.total = off + rows;
+  w.total = off;
   return w;
 }
 
 // Backward workspace: the coefficients, the h and g spectra (contiguous:
 // the second-level passes take both), the rows between the halves of a
 // permutation, the row-block sums, with a bias every layer's batch sum of g's
-// spectra and their block sums, the recompute stash and the permutation tables.  At
-// least as large as earlier releases' layout, as in the forward.
+// spectra and their block sums, the recompute stash and the permutation tables.
 struct MpBwdWs {
   size_t coef = 0, zhg = 0, tmp = 0, part = 0, zsum = 0, partB = 0, stash = 0, ptab = 0, total = 0;
 };
@@ -792,7 +789,7 @@ MpBwdWs mp_bwd_ws(int64_t batch, int32_t N, int32_t K, uint32_t flags, bool have
     return o;
   };
   const mp::Geo g = mp_geo(N, flags);
-  const bool cplx = (flags & kFlagComplex) != 0, perm_on = (flags & kFlagPerm) != 0, bias = (flags & kFlagBias) != 0;
+  const bool perm_on = (flags & kFlagPerm) != 0, bias = (flags & kFlagBias) != 0;
   const size_t rowb = size_t(2 * g.M) * sizeof(float), rows = size_t(batch) * rowb;
   w.coef = take(mp_coef_bytes(N, K, flags));
   w.zhg = take(2 * rows);
@@ -803,8 +800,7 @@ MpBwdWs mp_bwd_ws(int64_t batch, int32_t N, int32_t K, uint32_t flags, bool have
   w.partB = take(bias ? blocks(mp::kMaxRows) * rowb : 0);
   w.stash = take(have_saved ? 0 : saved_floats(batch, N, K, flags) * sizeof(float));
   w.ptab = take(mp_perm_bytes(g, K, flags));
-  const size_t before = (cplx && perm_on ? 6 : 5) * rows + (have_saved ? 0 : saved_floats(batch, N, K, flags) * 4);
-  w.total = off > before ? off : align256(before);
+  w.total = off;
   return w;
 }
 

@@ -185,21 +185,30 @@ def test_multipass_workspace_sizes(L):
     MP = 32
     B, N, K = 64, 65536, 4
     rows_real, rows_cx = B * N * 4, B * N * 8  # bytes of one batch of rows
-    # forward: spectra and layer buffer, plus the permuted input with PERM
-    assert L.acdc_forward_workspace_size(B, N, K, PERM) >= 3 * rows_real
-    assert L.acdc_forward_workspace_size(B, N, K, CX | PERM) >= 3 * rows_cx
+    # what the calls use and no more.  Per layer: the coefficients (16 N
+    # bytes real, 8 N complex) and, with PERM, tables of under 2 N ints
+    layers_real, layers_cx = K * N * (16 + 8), K * N * (8 + 8)
+    # forward: the spectra, plus the rows between the halves of a permutation
+    for flags, rows, layers in ((PERM, rows_real, layers_real), (CX | PERM, rows_cx, layers_cx)):
+        assert 2 * rows <= L.acdc_forward_workspace_size(B, N, K, flags) <= 2 * rows + layers
+        assert rows <= L.acdc_forward_workspace_size(B, N, K, flags & ~PERM) <= rows + layers
+        # backward: the h and g spectra, the same rows, and row-block sums
+        # (one row each, at most B blocks); the recompute stash when nothing
+        # is saved; the batch sums of g and their blocks of 16 with a bias
+        assert 3 * rows <= L.acdc_backward_workspace_size(B, N, K, flags, 1) <= 4 * rows + layers
+    assert (L.acdc_backward_workspace_size(B, N, K, PERM | BIAS, 1)
+            <= 4 * rows_real + layers_real + (K + B // 16) * N * 4)
     assert L.acdc_forward_workspace_size(B, N, K, CX) < L.acdc_forward_workspace_size(B, N, K, CX | PERM)
-    # backward: the h and g spectra (one batch each), dL/dv, the next g, the
-    # dL/da image (+ dL/du before the complex adjoint permutation), and the
-    # recompute stash when nothing is saved
-    assert L.acdc_backward_workspace_size(B, N, K, PERM, 1) >= 5 * rows_real
-    assert L.acdc_backward_workspace_size(B, N, K, CX | PERM, 1) >= 6 * rows_cx
     saved = L.acdc_saved_bytes(B, N, K, CX | PERM)
     assert saved == K * rows_cx
     assert (L.acdc_backward_workspace_size(B, N, K, CX | PERM, 0)
             >= L.acdc_backward_workspace_size(B, N, K, CX | PERM, 1) + saved)
     # forcing the multi-pass path at a fused width needs more workspace
     assert L.acdc_forward_workspace_size(B, 4096, K, CX | PERM | MP) > L.acdc_forward_workspace_size(B, 4096, K, CX | PERM)
+    # a workspace of one batch serves the smaller ones, at any width
+    for n, flags in ((256, PERM | MP), (8192, BIAS | MP), (65536, PERM | BIAS), (1 << 20, CX | PERM)):
+        sizes = [L.acdc_backward_workspace_size(b, n, K, flags, 0) for b in list(range(1, 70)) + list(range(70, 9000, 41))]
+        assert sizes == sorted(sizes)
     # unsupported: complex rows past 2^21
     assert L.acdc_forward_workspace_size(B, 1 << 22, K, CX) == 0
 

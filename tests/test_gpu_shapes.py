@@ -112,3 +112,37 @@ def test_multipass_tables_rebuilt_per_layer(acdc):  # noqa: F811
     # five layers' permutation tables at the widest row are past 256 MB, so
     # each layer's are built in turn; 256 sets a row
     run_case(acdc, 1 << 22, 5, 1, P, seed=3)
+
+
+@pytest.mark.parametrize("N,B,flags", [(256, 1100, P | R | FLAG_BIAS | MP), (8192, 37, P | FLAG_BIAS | MP),
+                                       (65536, 37, P | R | FLAG_BIAS), (65536, 150, R | FLAG_BIAS), (4096, 37, CX | P | MP),
+                                       (1 << 18, 3, CX | P), (131072, 5, CX)])
+def test_multipass_workspace_holds_all(acdc, N, B, flags):  # noqa: F811
+    # a workspace of exactly the stated size, all NaN patterns, between bytes
+    # that no call may change; the results are those of a roomy one
+    import torch
+    K, fl = 3, flags & ~CX
+    x, A, D, perm, gy = (torch.from_numpy(t).cuda() for t in make_inputs(N, K, B, flags, N + B))
+    bias = torch.from_numpy(make_bias(N, K, N)).cuda() if flags & FLAG_BIAS else None
+
+    def space(need, roomy):
+        buf = torch.full((need * (2 if roomy else 1) + 8192,), 255, dtype=torch.uint8, device="cuda")
+        return buf, buf[4096: buf.numel() - 4096]
+
+    def untouched(buf):
+        return bool((buf[:4096] == 255).all()) and bool((buf[-4096:] == 255).all())
+
+    outs = []
+    for roomy in (False, True):
+        buf, ws = space(acdc.forward_workspace_bytes(x, K, fl, bias), roomy)
+        y, saved = acdc.forward(x, A, D, perm, fl, save=True, bias=bias, workspace=ws)
+        assert untouched(buf)
+        got = [y, saved]
+        for have in (True, False):
+            buf, ws = space(acdc.backward_workspace_bytes(x, K, fl, have, bias), roomy)
+            got += acdc.backward(x, gy, A, D, perm, fl, saved=saved if have else None, bias=bias, workspace=ws)
+            assert untouched(buf)
+        outs.append(got)
+    for tight, wide in zip(*outs):
+        assert bool(torch.isfinite(torch.view_as_real(tight) if tight.is_complex() else tight).all())
+        assert torch.equal(tight, wide)
