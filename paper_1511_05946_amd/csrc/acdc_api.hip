@@ -692,7 +692,7 @@ int get_mp_tables(int N, MpTabs* out) {
   out->tw2 = reinterpret_cast<const float2*>(base + l.tw2);
   const double qb = 1.0 / (2.0 * std::sqrt(double(N)));
   out->q = QuartetTabs{reinterpret_cast<const float4*>(base + l.mk0), reinterpret_cast<const float4*>(base + l.mk1),
-                       reinterpret_cast<const int4*>(base + l.qidx), reinterpret_cast<const int*>(base + l.qmask),
+                       reinterpret_cast<const int4*>(base + l.qidx),
                        float(0.9238795325112867561 * qb), float(0.3826834323650897717 * qb)};
   return ACDC_OK;
 }

@@ -1254,12 +1254,11 @@ __global__ __launch_bounds__(kThreads) void k_colsum2(const float* __restrict__ 
     put4(reinterpret_cast<float4*>(out) + w4, s, acc);
   } else if constexpr (HOW == Order::quartets) {
     const long long e = quartet_of(g, int(w4 / g.L), int(w4 % g.L));
-    const int m = (q.qmask[e] >> 4) & 0xF;
     const int4 idx = q.qidx[e];
-    if (m & 1) put1(out + idx.x, s.x, acc);
-    if (m & 2) put1(out + idx.y, s.y, acc);
-    if (m & 4) put1(out + idx.z, s.z, acc);
-    if (m & 8) put1(out + idx.w, s.w, acc);
+    put1(out + idx.x, s.x, acc);
+    put1(out + idx.y, s.y, acc);
+    put1(out + idx.z, s.z, acc);
+    put1(out + idx.w, s.w, acc);
   } else {
     float2* o = reinterpret_cast<float2*>(out);
     const long long k0 = spec_index(g, 2 * w4), k1 = spec_index(g, 2 * w4 + 1);

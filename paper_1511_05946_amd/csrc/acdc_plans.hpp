@@ -134,12 +134,11 @@ struct RealPlan {
   }
   static constexpr int TW_FLOAT2 = tw_total();
   // table block layout in bytes: [fft twiddles][mk0 float4 NSL*T][mk1 float4 NSL*T]
-  //                             [qidx int4 NSL*T][qmask int NSL*T]
+  //                             [qidx int4 NSL*T]
   static constexpr int OFF_MK0 = ((TW_FLOAT2 * 8 + 255) / 256) * 256;
   static constexpr int OFF_MK1 = OFF_MK0 + NSL * T * 16;
   static constexpr int OFF_QIDX = OFF_MK1 + NSL * T * 16;
-  static constexpr int OFF_QMASK = OFF_QIDX + NSL * T * 16;
-  static constexpr int TABLE_BYTES = ((OFF_QMASK + NSL * T * 4 + 255) / 256) * 256;
+  static constexpr int TABLE_BYTES = ((OFF_QIDX + NSL * T * 16 + 255) / 256) * 256;
 
   static_assert(N % 4 == 0, "N must be a multiple of 4");
   static_assert(M % T == 0, "threads must divide the row");

@@ -644,6 +644,8 @@ __host__ __device__ void real_backward_row(Ctx& ctx, const RealArgs& a, unsigned
   static_assert(!O::XL || ROWS % 4 == 0, "rows of 16 lanes fill whole waves");
   constexpr int SROWS = O::XL ? ROWS / 4 : ROWS;
   constexpr int SSTRIDE = O::XL ? 4 * PL::SLAB : PL::SLAB;
+  static_assert(!ACC || (sum_phases<SROWS, THREADS, QF>() == 1 && sum_phases<SROWS, THREADS, N>() == 1),
+                "sums in phases leave out the earlier tiles' values");
   const unsigned rw = rr % 4u;  // row within its wave (XL)
   float* const wimg = lds + (rr - rw) * PL::SLAB;
   // A row past the batch end reads the block's first row for u_k but starts
@@ -780,7 +782,7 @@ __host__ __device__ void real_dct_row(Ctx& ctx, const float* S, float* out, cons
   O::template fft<false>(ctx, v, t, reinterpret_cast<float2*>(slab), tab, [] {});
   O::permute0(v, t == 0);
   const GView mq = GView::of(Mq);
-  const GView qi = GView::of(tabc + PL::OFF_QIDX), qm = GView::of(tabc + PL::OFF_QMASK);
+  const GView qi = GView::of(tabc + PL::OFF_QIDX);
   // One row a workgroup: latency is all there is, so the table loads of a
   // group of slots are issued together and the stores, which the compiler
   // cannot move loads across, follow them (slot by slot a row of N = 4096 took
@@ -791,12 +793,10 @@ __host__ __device__ void real_dct_row(Ctx& ctx, const float* S, float* out, cons
   for (int s0 = 0; s0 < PL::NSL; s0 += GR) {
     float X[GR][4];
     int4 idx[GR];
-    int sm[GR];
 #pragma unroll
     for (int j = 0; j < GR; ++j) {
       const int slot = s0 + j;
       idx[j] = qi.ldi4(t * 16u, unsigned(slot * T * 16));
-      sm[j] = (qm.ldi1(t * 4u, unsigned(slot * T * 4)) >> 4) & 0xF;
     }
 #pragma unroll
     for (int j = 0; j < GR; ++j) {
@@ -811,8 +811,7 @@ __host__ __device__ void real_dct_row(Ctx& ctx, const float* S, float* out, cons
     for (int j = 0; j < GR; ++j) {
       const int id[4] = {idx[j].x, idx[j].y, idx[j].z, idx[j].w};
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-        if (sm[j] & (1 << c)) out[id[c]] = accumulate ? out[id[c]] + X[j][c] : X[j][c];
+      for (int c = 0; c < 4; ++c) out[id[c]] = accumulate ? out[id[c]] + X[j][c] : X[j][c];
     }
   }
 }

@@ -183,7 +183,10 @@ struct Launch {
 // BWD_ROWS, or half of them while that still leaves every CU at most one
 // workgroup.  Eight waves put two on each SIMD of half the CUs where four
 // put one on each SIMD of twice as many; the partials, twice as many, are
-// few at such batches.  Depends on the batch alone (it sizes the workspace).
+// few at such batches.  Depends on the batch alone: it sizes the workspace,
+// which callers may ask for without a device, so the CUs are the MI355X's
+// (where the device has others, as in a partition of it, the rule only picks
+// the other of two valid tile sizes).
 // Forward and backward, K = 8 (part of it the forward's own spread): N = 4096,
 // 300 rows 269 -> 206 us, 1100 rows 287 -> 273; N = 9216, 100 rows 271 -> 229;
 // complex N = 1024, 2000 rows 374 -> 281, N = 4096, 500 rows 267 -> 246.
@@ -265,15 +268,14 @@ inline bool dispatch_complex(int N, F&& f) {
 }
 
 // The per-entry quartet tables of a width N: Makhoul twiddle blocks mk0,
-// mk1, the four DCT indices of each entry and their masks (high nibble: the
-// image values to store).  The fused
-// plans index them by slot entry e = slot*T + t, the multi-pass path by the
-// quartet number; entry 0 is the self-paired quartet (Z[0], Z[M/2]) in both.
+// mk1 and the four DCT indices of each entry (all entries' together cover
+// every index once: the builders check it).  The fused plans index them by
+// slot entry e = slot*T + t, the multi-pass path by the quartet number; entry
+// 0 is the self-paired quartet (Z[0], Z[M/2]) in both.
 struct QuartetTabs {
   const float4* mk0;
   const float4* mk1;
   const int4* qidx;
-  const int* qmask;
   float qb0_re, qb0_im;  // entry 0's DCT-III pre-twiddle exp(i pi/8) / (2 sqrt(N))
 };
 template <class PL>
@@ -281,7 +283,7 @@ __host__ __device__ __forceinline__ QuartetTabs quartet_tabs(const char* tab) {
   return QuartetTabs{reinterpret_cast<const float4*>(tab + PL::OFF_MK0),
                      reinterpret_cast<const float4*>(tab + PL::OFF_MK1),
                      reinterpret_cast<const int4*>(tab + PL::OFF_QIDX),
-                     reinterpret_cast<const int*>(tab + PL::OFF_QMASK), RealOps<PL>::kQbRe, RealOps<PL>::kQbIm};
+                     RealOps<PL>::kQbRe, RealOps<PL>::kQbIm};
 }
 
 // A layer vector (d or b) at the four indices of a quartet.  The callers
@@ -437,13 +439,12 @@ __host__ __device__ __forceinline__ void real_reduce_store4(float4 s, int k, int
     put4(reinterpret_cast<float4*>(gA + (long long)k * PL::N) + e4, s, accumulate);
   } else if (e4 < (PL::N + PL::QF) / 4) {
     const int st = e4 - PL::N / 4;
-    const int sm = (reinterpret_cast<const int*>(tab + PL::OFF_QMASK)[st] >> 4) & 0xF;
     const int4 idx = reinterpret_cast<const int4*>(tab + PL::OFF_QIDX)[st];
     float* gd = gD + (long long)k * PL::N;
-    if (sm & 1) put1(gd + idx.x, s.x, accumulate);
-    if (sm & 2) put1(gd + idx.y, s.y, accumulate);
-    if (sm & 4) put1(gd + idx.z, s.z, accumulate);
-    if (sm & 8) put1(gd + idx.w, s.w, accumulate);
+    put1(gd + idx.x, s.x, accumulate);
+    put1(gd + idx.y, s.y, accumulate);
+    put1(gd + idx.z, s.z, accumulate);
+    put1(gd + idx.w, s.w, accumulate);
   } else {
     reinterpret_cast<float4*>(gS + (long long)k * PL::N)[e4 - (PL::N + PL::QF) / 4] = s;
   }

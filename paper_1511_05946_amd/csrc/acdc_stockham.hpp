@@ -306,8 +306,9 @@ constexpr int sum_phases() {
 // (sum_phases) each phase's consecutive rows, then the phase sums in phase
 // order.  A phase's sum replaces its first row's entry, which no other
 // thread reads, until the second stage.  With `old` (LDS, NFL floats) the
-// sum is added to it afterwards: old + (row 0 + ... ).  Called by every
-// thread; the trip count is a compile-time constant.
+// sum is added to it afterwards: old + (row 0 + ... ); not in phases, where
+// the caller asserts that it passes none.  Called by every thread; the trip
+// count is a compile-time constant.
 template <int ROWS, int SLAB, int THREADS, int NFL, class Ctx>
 __host__ __device__ __forceinline__ void sum_rows(Ctx& ctx, float* lds, GView out, int tid,
                                                   const float* old = nullptr) {

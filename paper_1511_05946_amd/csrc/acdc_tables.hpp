@@ -77,7 +77,6 @@ inline bool build_real_tables(std::vector<unsigned char>& buf) {
   float4* mk0 = reinterpret_cast<float4*>(buf.data() + PL::OFF_MK0);
   float4* mk1 = reinterpret_cast<float4*>(buf.data() + PL::OFF_MK1);
   int4* qidx = reinterpret_cast<int4*>(buf.data() + PL::OFF_QIDX);
-  int* qmask = reinterpret_cast<int*>(buf.data() + PL::OFF_QMASK);
   std::vector<int> cover(N, 0);
   for (int slot = 0; slot < NSL; ++slot)
     for (int t = 0; t < T; ++t) {
@@ -89,7 +88,6 @@ inline bool build_real_tables(std::vector<unsigned char>& buf) {
         cover[idx[c]]++;
       }
       qidx[e] = make_int4(idx[0], idx[1], idx[2], idx[3]);
-      qmask[e] = 0xF | (0xF << 4);
     }
   for (int n = 0; n < N; ++n)
     if (cover[n] != 1) return false;
@@ -103,7 +101,7 @@ inline bool build_real_tables(std::vector<unsigned char>& buf) {
 // tables indexed by quartet e < M/2 (e = 0: the self-paired quartet, else
 // spectrum index e).
 struct MpTableLayout {
-  size_t tw1 = 0, tw2 = 0, mk0 = 0, mk1 = 0, qidx = 0, qmask = 0, bytes = 0;
+  size_t tw1 = 0, tw2 = 0, mk0 = 0, mk1 = 0, qidx = 0, bytes = 0;
 };
 inline MpTableLayout mp_table_layout(long long N, int R1, int R2, int L) {
   const size_t M = size_t(N / 2), NQ = M / 2;
@@ -113,8 +111,7 @@ inline MpTableLayout mp_table_layout(long long N, int R1, int R2, int L) {
   l.mk0 = l.tw2 + size_t(R2 - 1) * L * sizeof(float2);
   l.mk1 = l.mk0 + NQ * sizeof(float4);
   l.qidx = l.mk1 + NQ * sizeof(float4);
-  l.qmask = l.qidx + NQ * sizeof(int4);
-  l.bytes = l.qmask + NQ * sizeof(int);
+  l.bytes = l.qidx + NQ * sizeof(int4);
   return l;
 }
 inline bool build_mp_tables(int N, int R1, int R2, int L, std::vector<unsigned char>& buf) {
@@ -136,7 +133,6 @@ inline bool build_mp_tables(int N, int R1, int R2, int L, std::vector<unsigned c
   float4* mk0 = reinterpret_cast<float4*>(buf.data() + l.mk0);
   float4* mk1 = reinterpret_cast<float4*>(buf.data() + l.mk1);
   int4* qidx = reinterpret_cast<int4*>(buf.data() + l.qidx);
-  int* qmask = reinterpret_cast<int*>(buf.data() + l.qmask);
   std::vector<int> cover(N, 0);
   for (int e = 0; e < NQ; ++e) {
     int idx[4];
@@ -146,7 +142,6 @@ inline bool build_mp_tables(int N, int R1, int R2, int L, std::vector<unsigned c
       cover[idx[c]]++;
     }
     qidx[e] = make_int4(idx[0], idx[1], idx[2], idx[3]);
-    qmask[e] = 0xF | (0xF << 4);
   }
   for (int n = 0; n < N; ++n)
     if (cover[n] != 1) return false;
