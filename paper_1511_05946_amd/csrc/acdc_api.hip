@@ -74,10 +74,7 @@ __device__ __forceinline__ void copy_twiddles(float* dst, const char* tab, int t
 // The forward kernel is persistent: workgroup b handles row groups (tiles)
 // b, b + gridDim.x, ... of `rpw` rows (fwd_rows).  Rows are independent, so
 // results do not depend on the grid size or on rpw.
-constexpr int kAloneThreads = 256;
-// ALONE: at most one wave per SIMD (fwd_rows), workgroups of kAloneThreads.
-// K = 12, without and with: N = 4096, 16 rows 101 and 93 us, 1024 x 700 rows
-// 48 and 44, 64 x 500 22 and 21.
+// ALONE: see fwd_alone.
 template <class PL, bool BIAS, bool ALONE>
 __global__ __launch_bounds__(ALONE ? kAloneThreads : Launch<PL>::FWD_THREADS)
 __attribute__((amdgpu_waves_per_eu(ALONE ? 1 : Launch<PL>::FWD_WPE))) void k_real_fwd(RealArgs a, long long ntiles, int rpw) {
@@ -500,30 +497,6 @@ void with_bwd_rows(int64_t batch, F&& f) {
   else f.template operator()<L::BWD_ROWS>();
 }
 
-// Rows per forward workgroup of the plans with several waves per workgroup
-// (twiddles in LDS): all of FWD_ROWS once the batch gives every CU one such
-// workgroup; below that the waves are spread evenly over the CUs.  A row is
-// a serial chain through all K layers, and two waves on one SIMD take twice
-// as long for it while other CUs idle.  K = 12, without and with the spread:
-// N = 4096, 16 rows 128 and 101 us (two workgroups of 8 waves, 16 of one),
-// 700 rows 136 and 110; N = 1024, 700 rows 68 and 47; N = 64, 128 rows 46
-// and 36.  (Spreading over every resident workgroup instead, several to a
-// CU, ran N = 1024 x 4096 rows 1.6 % slower: more copies of the twiddles.)
-template <class PL>
-int fwd_rows(int64_t batch, int cus) {
-  using L = Launch<PL>;
-  if constexpr (!L::TW_LDS) {
-    return L::FWD_ROWS;
-  } else {
-    constexpr int RW = 64 / PL::T;             // rows per wave
-    constexpr int WAVES = L::FWD_ROWS / RW;
-    static_assert(PL::T <= 64 && L::FWD_ROWS % RW == 0, "whole waves of rows");
-    if (cus <= 0) return L::FWD_ROWS;
-    const long long waves = (batch + RW - 1) / RW, each = (waves + cus - 1) / cus;
-    return int(each < WAVES ? each : WAVES) * RW;
-  }
-}
-
 size_t elem_floats(uint32_t flags) { return (flags & kFlagComplex) ? 2 : 1; }
 
 // Floats of the `saved` buffer: the layer inputs u_1..u_{K-1}, preceded by
@@ -609,7 +582,7 @@ void launch_real_fwd_k(const RealArgs& a, hipStream_t s, bool remember) {
   const int rpw = fwd_rows<PL>(a.batch, res.cus);
   const long long tiles = (a.batch + rpw - 1) / rpw;
   if constexpr (L::TW_LDS) {
-    if (rpw * PL::T <= kAloneThreads && tiles <= res.cus) {
+    if (fwd_alone<PL>(a.batch, rpw, res.cus)) {
       hipLaunchKernelGGL((k_real_fwd<PL, BIAS, true>), dim3(unsigned(tiles)), dim3(kAloneThreads), 0, s, a, tiles,
                          rpw);
       return;

@@ -197,6 +197,40 @@ constexpr int bwd_rows(long long batch) {
   return batch <= kCus * L::BWD_ROWS_FEW ? L::BWD_ROWS_FEW : L::BWD_ROWS;
 }
 
+// Rows per forward workgroup of the plans with several waves per workgroup
+// (twiddles in LDS): all of FWD_ROWS once the batch gives every CU one such
+// workgroup; below that the waves are spread evenly over the CUs.  A row is
+// a serial chain through all K layers, and two waves on one SIMD take twice
+// as long for it while other CUs idle.  K = 12, without and with the spread:
+// N = 4096, 16 rows 128 and 101 us (two workgroups of 8 waves, 16 of one),
+// 700 rows 136 and 110; N = 1024, 700 rows 68 and 47; N = 64, 128 rows 46
+// and 36.  (Spreading over every resident workgroup instead, several to a
+// CU, ran N = 1024 x 4096 rows 1.6 % slower: more copies of the twiddles.)
+template <class PL>
+constexpr int fwd_rows(long long batch, int cus) {
+  using L = Launch<PL>;
+  if constexpr (!L::TW_LDS) {
+    return L::FWD_ROWS;
+  } else {
+    constexpr int RW = 64 / PL::T;             // rows per wave
+    constexpr int WAVES = L::FWD_ROWS / RW;
+    static_assert(PL::T <= 64 && L::FWD_ROWS % RW == 0, "whole waves of rows");
+    if (cus <= 0) return L::FWD_ROWS;
+    const long long waves = (batch + RW - 1) / RW, each = (waves + cus - 1) / cus;
+    return int(each < WAVES ? each : WAVES) * RW;
+  }
+}
+
+// One wave a SIMD (real_forward_row's ALONE), in workgroups of kAloneThreads:
+// where fwd_rows leaves every CU at most one such workgroup.  K = 12, without
+// and with: N = 4096, 16 rows 101 and 93 us, 1024 x 700 rows 48 and 44, 64 x
+// 500 22 and 21.
+constexpr int kAloneThreads = 256;
+template <class PL>
+constexpr bool fwd_alone(long long batch, int rpw, int cus) {
+  return Launch<PL>::TW_LDS && rpw * PL::T <= kAloneThreads && (batch + rpw - 1) / rpw <= cus;
+}
+
 // ACDC_ONLY_N=<width> instantiates a single real plan and ACDC_ONLY_CN a
 // single complex plan (quick development builds); ACDC_PLAN_SUBSET
 // instantiates real plans 8, 64, 1024, 4096, 9216 and complex plans 16, 256,

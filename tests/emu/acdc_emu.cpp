@@ -107,23 +107,40 @@ std::vector<int4> packed_perm(const int* perm, int K, unsigned flags) {
   return p;
 }
 
-template <class PL, bool BIAS>
-void real_fwd_k(const RealArgs& a, const std::vector<unsigned char>& tab) {
+// The launches of small batches on a device of 256 CUs (the forward's fewer
+// rows per workgroup and its ALONE form, the backward's BWD_ROWS_FEW) where
+// the batch has them; otherwise every batch runs as a large one does.
+bool g_small_batch = false;
+
+template <class PL, bool BIAS, bool ALONE>
+void real_fwd_rows(const RealArgs& a, const std::vector<unsigned char>& tab, int rpw) {
   using L = Launch<PL>;
-  const long long nwg = (a.batch + L::FWD_ROWS - 1) / L::FWD_ROWS;
-  std::vector<float> lds((size_t)L::FWD_LDS_FLOATS);
+  const long long nwg = (a.batch + rpw - 1) / rpw;
+  const int wg_rows = (ALONE ? kAloneThreads : L::FWD_THREADS) / PL::T;
+  std::vector<float> lds((size_t)L::TW_FLOATS + (size_t)wg_rows * L::FWD_SLAB);
   float* twl = lds.data();
   float* rows = lds.data() + L::TW_FLOATS;
   if (L::TW_LDS) std::memcpy(twl, tab.data(), (size_t)PL::TW_FLOAT2 * 8);
+  // the workgroup's waves past rpw rows have nothing to do
   for (long long wg = 0; wg < nwg; ++wg)
-    run_wg(L::FWD_THREADS, [&](HostCtx& ctx, int tid) {
+    run_wg(rpw * PL::T, [&](HostCtx& ctx, int tid) {
       const int r = tid / PL::T, t = tid % PL::T;
       float* slab = rows + (size_t)r * L::FWD_SLAB;
       if constexpr (L::TW_LDS)
-        real_forward_row<PL, BIAS>(ctx, a, unsigned(t), wg * L::FWD_ROWS, unsigned(r), slab, LdsView::of(twl));
+        real_forward_row<PL, BIAS, ALONE>(ctx, a, unsigned(t), wg * rpw, unsigned(r), slab, LdsView::of(twl));
       else
-        real_forward_row<PL, BIAS>(ctx, a, unsigned(t), wg * L::FWD_ROWS, unsigned(r), slab, GView::of(tab.data()));
+        real_forward_row<PL, BIAS>(ctx, a, unsigned(t), wg * rpw, unsigned(r), slab, GView::of(tab.data()));
     });
+}
+
+template <class PL, bool BIAS>
+void real_fwd_k(const RealArgs& a, const std::vector<unsigned char>& tab) {
+  using L = Launch<PL>;
+  const int rpw = g_small_batch ? fwd_rows<PL>(a.batch, int(kCus)) : L::FWD_ROWS;
+  if constexpr (L::TW_LDS) {
+    if (g_small_batch && fwd_alone<PL>(a.batch, rpw, int(kCus))) return real_fwd_rows<PL, BIAS, true>(a, tab, rpw);
+  }
+  real_fwd_rows<PL, BIAS, false>(a, tab, rpw);
 }
 
 template <class PL>
@@ -140,35 +157,43 @@ void real_fwd(const float* x, float* y, const float* A, const float* D, const fl
 // many resident workgroups as tiles).
 long long g_bwd_slots = 0;
 
-template <class PL, bool BIAS>
+// f.template operator()<ROWS>() for the rows per backward workgroup.
+template <class PL, class F>
+void with_rows(long long batch, F&& f) {
+  using L = Launch<PL>;
+  if (g_small_batch && bwd_rows<PL>(batch) == L::BWD_ROWS_FEW) f.template operator()<L::BWD_ROWS_FEW>();
+  else f.template operator()<L::BWD_ROWS>();
+}
+
+template <class PL, bool BIAS, int ROWS>
 constexpr bool emu_acc() {
-  return Launch<PL>::BWD_ACC && !BIAS;
+  return Launch<PL>::BWD_ACC && !BIAS && ROWS == Launch<PL>::BWD_ROWS;
 }
 
 // Partial slots of a backward over ntiles tiles.
-template <class PL, bool BIAS>
+template <class PL, bool BIAS, int ROWS>
 long long bwd_slots(long long ntiles) {
-  return (emu_acc<PL, BIAS>() && g_bwd_slots > 0 && g_bwd_slots < ntiles) ? g_bwd_slots : ntiles;
+  return (emu_acc<PL, BIAS, ROWS>() && g_bwd_slots > 0 && g_bwd_slots < ntiles) ? g_bwd_slots : ntiles;
 }
 
-template <class PL, bool BIAS>
+template <class PL, bool BIAS, int ROWS>
 void real_bwd_k(const RealArgs& a, long long ntiles, float* lds, const std::vector<unsigned char>& tab) {
   using L = Launch<PL>;
-  const long long slots = bwd_slots<PL, BIAS>(ntiles);
+  const long long slots = bwd_slots<PL, BIAS, ROWS>(ntiles);
   // workgroup w runs tiles w, w + slots, ... in turn, as the persistent
   // kernel does, adding them into slot w (its LDS kept across its tiles)
   for (long long w = 0; w < slots; ++w)
     for (long long tile = w; tile < ntiles; tile += slots)
-      run_wg(L::BWD_THREADS, [&](HostCtx& ctx, int tid) {
+      run_wg(ROWS * PL::T, [&](HostCtx& ctx, int tid) {
         const int r = tid / PL::T, t = tid % PL::T;
         float* slab = lds + (size_t)r * L::BWD_SLAB;
-        if constexpr (emu_acc<PL, BIAS>())
-          real_backward_row<PL, L::BWD_ROWS, BIAS, true>(ctx, a, unsigned(t), tile * L::BWD_ROWS, unsigned(r), tid, w,
-                                                         lds, slab, GView::of(tab.data()),
-                                                         tile == w ? nullptr : lds + L::BWD_LDS_FLOATS);
+        if constexpr (emu_acc<PL, BIAS, ROWS>())
+          real_backward_row<PL, ROWS, BIAS, true>(ctx, a, unsigned(t), tile * ROWS, unsigned(r), tid, w, lds, slab,
+                                                  GView::of(tab.data()),
+                                                  tile == w ? nullptr : lds + L::BWD_LDS_FLOATS);
         else
-          real_backward_row<PL, L::BWD_ROWS, BIAS>(ctx, a, unsigned(t), tile * L::BWD_ROWS, unsigned(r), tid, w, lds,
-                                                   slab, GView::of(tab.data()));
+          real_backward_row<PL, ROWS, BIAS>(ctx, a, unsigned(t), tile * ROWS, unsigned(r), tid, w, lds, slab,
+                                            GView::of(tab.data()));
       });
 }
 
@@ -189,8 +214,11 @@ void real_bwd(const float* x, const float* gy, const float* A, const float* D, c
     saved = saved_buf.data();
   }
   const std::vector<float4> mq = quartet_coefficients<PL>(D, bias ? B : nullptr, K, tab);
-  const long long ntiles = (batch + L::BWD_ROWS - 1) / L::BWD_ROWS;
-  const long long slots = bias ? bwd_slots<PL, true>(ntiles) : bwd_slots<PL, false>(ntiles);
+  long long ntiles = 0, slots = 0;
+  with_rows<PL>(batch, [&]<int ROWS>() {
+    ntiles = (batch + ROWS - 1) / ROWS;
+    slots = bias ? bwd_slots<PL, true, ROWS>(ntiles) : bwd_slots<PL, false, ROWS>(ntiles);
+  });
   const long long PS4 = partial_entries4<PL>(bias);
   std::vector<float> partial((size_t)slots * K * PS4 * 4);
   const std::vector<int4> p16 = packed_perm<PL>(perm, K, flags);
@@ -198,8 +226,10 @@ void real_bwd(const float* x, const float* gy, const float* A, const float* D, c
              (const char*)tab.data(), batch, K, flags};
   a.perm16 = p16.empty() ? nullptr : p16.data();
   std::vector<float> lds((size_t)L::BWD_LDS_FLOATS + L::ACC_FLOATS);
-  if (bias) real_bwd_k<PL, true>(a, ntiles, lds.data(), tab);
-  else real_bwd_k<PL, false>(a, ntiles, lds.data(), tab);
+  with_rows<PL>(batch, [&]<int ROWS>() {
+    if (bias) real_bwd_k<PL, true, ROWS>(a, ntiles, lds.data(), tab);
+    else real_bwd_k<PL, false, ROWS>(a, ntiles, lds.data(), tab);
+  });
   std::vector<float> gS(bias ? (size_t)K * PL::N : 0);
   reduce_all<PL>(partial.data(), slots, K, PS4, [&](float4 s, int k, int e4) {
     real_reduce_store4<PL>(s, k, e4, gA, gD, gS.data(), (const char*)tab.data(), acc);
@@ -241,18 +271,21 @@ void cplx_bwd(const float* x, const float* gy, const float* A, const float* D, c
     cplx_fwd<PL>(x, nullptr, A, D, perm, batch, K, flags, saved_buf.data(), tab);
     saved = saved_buf.data();
   }
-  const long long ntiles = (batch + L::BWD_ROWS - 1) / L::BWD_ROWS;
+  long long ntiles = 0;
+  with_rows<PL>(batch, [&]<int ROWS>() { ntiles = (batch + ROWS - 1) / ROWS; });
   const long long PS = 4LL * PL::N;
   std::vector<float> partial((size_t)ntiles * K * PS);
   CplxArgs a{x, nullptr, A, D, perm, const_cast<float*>(saved), gy, gx, partial.data(),
              (const char*)tab.data(), batch, K, flags};
   std::vector<float> lds((size_t)L::BWD_ROWS * L::BWD_SLAB);
-  for (long long wg = 0; wg < ntiles; ++wg)
-    run_wg(L::BWD_THREADS, [&](HostCtx& ctx, int tid) {
-      const int r = tid / PL::T, t = tid % PL::T;
-      cplx_backward_row<PL, L::BWD_ROWS>(ctx, a, unsigned(t), wg * L::BWD_ROWS, unsigned(r), tid, wg, lds.data(),
-                                         lds.data() + (size_t)r * L::BWD_SLAB);
-    });
+  with_rows<PL>(batch, [&]<int ROWS>() {
+    for (long long wg = 0; wg < ntiles; ++wg)
+      run_wg(ROWS * PL::T, [&](HostCtx& ctx, int tid) {
+        const int r = tid / PL::T, t = tid % PL::T;
+        cplx_backward_row<PL, ROWS>(ctx, a, unsigned(t), wg * ROWS, unsigned(r), tid, wg, lds.data(),
+                                    lds.data() + (size_t)r * L::BWD_SLAB);
+      });
+  });
   reduce_all<PL>(partial.data(), ntiles, K, partial_entries4<PL>(), [&](float4 s, int k, int e4) {
     cplx_reduce_store4<PL>(s, k, e4, gA, gD, (flags & kFlagAccumulate) != 0);
   });
@@ -319,6 +352,28 @@ extern "C" int acdc_emu_set_backward_slots(long long slots, int N) {
   return acc;
 }
 
+// Run the launches of small batches (see g_small_batch).
+extern "C" void acdc_emu_set_small_batch(int on) { g_small_batch = on != 0; }
+
+// Rules of the fused launches on 256 CUs: rows per backward workgroup, rows
+// per forward workgroup, and whether the forward runs its ALONE form.
+extern "C" int acdc_emu_rows(long long batch, int N, unsigned flags, int* out) {
+  int rc = -2;
+  auto f = [&]<class PL>() {
+    out[0] = bwd_rows<PL>(batch);
+    out[1] = Launch<PL>::FWD_ROWS;
+    out[2] = 0;
+    if constexpr (!PL::kComplex) {
+      out[1] = fwd_rows<PL>(batch, int(kCus));
+      out[2] = fwd_alone<PL>(batch, out[1], int(kCus)) ? 1 : 0;
+    }
+    rc = 0;
+  };
+  if (flags & kFlagComplex) dispatch_complex(N, f);
+  else dispatch_real(N, f);
+  return rc;
+}
+
 // The fixed-order batch reduction alone: out[e] (float4 e < n4) = the sum
 // over ntiles tiles of partial[t][e], in the kernels' order (red_phases(n4)
 // tile phases, grouped loads, phases added in order).  Returns the number of
@@ -359,4 +414,31 @@ extern "C" int acdc_emu_mp_quartets(int N, int ew, long long* out, long long* ba
     back[e] = (long long)p * g.L + k2;
   }
   return g.L;
+}
+
+// Column sets of a row of N elements: set and LDS place of every element
+// (part_of), and the element at every local position of every set (elem_of).
+// Returns the elements of a set.
+extern "C" int acdc_emu_mp_sets(int N, int ew, long long* set, long long* place, long long* elem) {
+  const mp::PermGeo p = mp::perm_geo(mp::geo((long long)N * ew), ew);
+  for (long long i = 0; i < N; ++i) {
+    int d, l;
+    mp::part_of(p, i, d, l);
+    set[i] = d;
+    place[i] = l;
+  }
+  for (int d = 0; d < p.nC; ++d)
+    for (int l = 0; l < (1 << p.lC); ++l) elem[((long long)d << p.lC) + l] = mp::elem_of(p, d, l);
+  return 1 << p.lC;
+}
+
+// The M-point FFT of such a row: spectrum index of every storage position, the
+// segments of every pair ([S/2][2]), and (R1, R2, L).
+extern "C" void acdc_emu_mp_spectrum(int N, int ew, long long* spec, int* pairs, int* geo) {
+  const mp::Geo g = mp::geo((long long)N * ew);
+  for (long long q = 0; q < g.M; ++q) spec[q] = mp::spec_index(g, q);
+  for (int p = 0; p < g.R1 * g.R2 / 2; ++p) mp::seg_pair(g, p, pairs[2 * p], pairs[2 * p + 1]);
+  geo[0] = g.R1;
+  geo[1] = g.R2;
+  geo[2] = g.L;
 }

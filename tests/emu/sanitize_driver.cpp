@@ -5,7 +5,8 @@
 //   1. the kernels' __host__ __device__ row bodies in the CPU emulation
 //      (acdc_emu.cpp) on small cascades of every flag combination, ragged
 //      last workgroups included (and persistent backward workgroups that
-//      add several tiles into one partial), and checks determinism and that
+//      add several tiles into one partial, and the launches of small
+//      batches), and checks determinism and that
 //      the saved and recompute backwards agree bit for bit;
 //   2. the C ABI's host-side argument validation and size arithmetic
 //      (acdc_api.hip, compiled for the host only) on bad, extreme and
@@ -156,6 +157,14 @@ int main() {
       {4096, 1, 3, kFlagComplex},
   };
   for (const Case& c : cases) run_case(c);
+  // the launches of small batches (one wave a SIMD with loads ahead, fewer rows
+  // a workgroup), ragged last workgroups included
+  acdc_emu_set_small_batch(1);
+  for (const Case& c : {Case{64, 2, 19, kFlagPerm | kFlagRelu | kFlagBias}, Case{1024, 2, 5, kFlagPerm},
+                        Case{4096, 2, 5, kFlagPerm | kFlagRelu}, Case{9216, 2, 2, kFlagPerm},
+                        Case{256, 2, 33, kFlagComplex | kFlagPerm}, Case{4096, 1, 3, kFlagComplex}})
+    run_case(c);
+  acdc_emu_set_small_batch(0);
   // the persistent accumulating backward: 3 tiles of 2 rows over 2 slots
   CHECK(acdc_emu_set_backward_slots(2, 9216) == 1);
   run_case({9216, 2, 5, kFlagPerm});

@@ -12,6 +12,27 @@ TOL_COMPLEX = 2e-4
 RELU_DELTA = 1e-5
 
 
+# Rows per backward workgroup (one partial of the parameter gradients each) of
+# the fused widths: the first while the batch fills at most one such workgroup
+# on each of 256 CUs, the second beyond (checked against the headers' own rule
+# in test_emulation.py).
+BWD_ROWS_REAL = {8: (256, 256), 16: (256, 256), 32: (128, 128), 64: (64, 64), 128: (64, 64), 256: (16, 16),
+                 512: (16, 16), 1024: (8, 8), 2048: (4, 4), 4096: (4, 8), 8192: (2, 4), 9216: (1, 2), 16384: (1, 2),
+                 32768: (1, 1)}
+BWD_ROWS_COMPLEX = {8: (256, 512), 16: (256, 512), 32: (128, 256), 64: (64, 128), 128: (32, 64), 256: (32, 64),
+                    512: (16, 32), 1024: (8, 16), 2048: (4, 8), 4096: (2, 4), 8192: (1, 2), 16384: (1, 1)}
+# The largest batch whose forward runs one wave on each SIMD of 256 CUs (its
+# ALONE form), for the widths whose rows share a workgroup.
+FWD_ALONE_MAX = {8: 65536, 16: 65536, 32: 32768, 64: 16384, 128: 16384, 256: 4096, 512: 4096, 1024: 2048,
+                 2048: 1024, 4096: 1024}
+
+
+def bwd_tiles(N: int, B: int, complex_: bool = False) -> int:
+    few, full = (BWD_ROWS_COMPLEX if complex_ else BWD_ROWS_REAL)[N]
+    rows = few if B <= 256 * few else full
+    return -(-B // rows)
+
+
 def rel_err(got, ref) -> float:
     """max_i |got_i - ref_i| / max(|ref_i|, rms(ref over the group)), groups =
     rows (last axis).  Handles complex arrays through their modulus."""

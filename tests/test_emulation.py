@@ -16,7 +16,8 @@ import pytest
 
 from oracle import acdc_oracle as O
 from paper_1511_05946_amd.workloads import FLAG_ACCUMULATE, FLAG_BIAS, make_bias, make_inputs
-from tests.helpers import TOL_COMPLEX, TOL_REAL, rel_err, relu_safe_rows
+from tests.helpers import (BWD_ROWS_COMPLEX, BWD_ROWS_REAL, FWD_ALONE_MAX, TOL_COMPLEX, TOL_REAL, bwd_tiles, rel_err,
+                           relu_safe_rows)
 
 sys.path.insert(0, os.path.join(os.path.dirname(__file__), "emu"))
 
@@ -34,6 +35,8 @@ def emu():
                                     ctypes.c_int, ctypes.c_uint]
     L.acdc_emu_set_backward_slots.argtypes = [ctypes.c_longlong, ctypes.c_int]
     L.acdc_emu_set_backward_slots.restype = ctypes.c_int
+    L.acdc_emu_set_small_batch.argtypes = [ctypes.c_int]
+    L.acdc_emu_rows.argtypes = [ctypes.c_longlong, ctypes.c_int, ctypes.c_uint, ctypes.c_void_p]
     return L
 
 
@@ -87,6 +90,42 @@ def test_real_2048_four_rows_a_workgroup(emu):
 @pytest.mark.parametrize("N", [8, 16, 64, 256, 1024])
 def test_complex_small(emu, N):
     check(emu, N, 2, 5, O.FLAG_COMPLEX | O.FLAG_PERM, seed=N)
+
+
+# The launches that small batches run on 256 CUs: the forward with fewer rows a
+# workgroup and, up to N = 4096, loads ahead at one wave a SIMD; backward
+# workgroups of half the rows from N = 4096 (complex: every width).  Two
+# workgroups, the last one ragged.
+@pytest.mark.parametrize("N,B,flags", [(64, 19, O.FLAG_PERM | O.FLAG_RELU | FLAG_BIAS), (256, 7, O.FLAG_PERM),
+                                       (1024, 3, O.FLAG_PERM | O.FLAG_RELU), (2048, 3, O.FLAG_PERM | FLAG_BIAS),
+                                       (4096, 5, O.FLAG_PERM | O.FLAG_RELU), (4096, 2, FLAG_BIAS),
+                                       (9216, 2, O.FLAG_PERM | O.FLAG_RELU), (8192, 3, 0),
+                                       (64, 65, O.FLAG_COMPLEX | O.FLAG_PERM), (1024, 9, O.FLAG_COMPLEX),
+                                       (4096, 3, O.FLAG_COMPLEX | O.FLAG_PERM)])
+def test_small_batch_launches(emu, N, B, flags):
+    emu.acdc_emu_set_small_batch(1)
+    try:
+        check(emu, N, 3 if N < 4096 else 2, B, flags, seed=N + B, with_saved=N != 8192)
+    finally:
+        emu.acdc_emu_set_small_batch(0)
+
+
+def test_launch_row_rules(emu):
+    # the rules as the GPU tests state them
+    def rows(B, N, flags):
+        out = (ctypes.c_int * 3)()
+        assert emu.acdc_emu_rows(B, N, flags, out) == 0
+        return out[0], out[2]
+
+    for flags, table in ((0, BWD_ROWS_REAL), (O.FLAG_COMPLEX, BWD_ROWS_COMPLEX)):
+        for N, (few, full) in table.items():
+            for B in (1, 256 * few, 256 * few + 1, 100003):
+                r, alone = rows(B, N, flags)
+                assert -(-B // r) == bwd_tiles(N, B, flags != 0)
+                assert alone == (flags == 0 and B <= FWD_ALONE_MAX.get(N, 0))
+            for B in (FWD_ALONE_MAX.get(N, 0), FWD_ALONE_MAX.get(N, 0) + 1):
+                if B > 1 and flags == 0:
+                    assert rows(B, N, flags)[1] == (B == FWD_ALONE_MAX[N])
 
 
 @pytest.mark.parametrize("flags", [O.FLAG_COMPLEX, O.FLAG_COMPLEX | O.FLAG_PERM])

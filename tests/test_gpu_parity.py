@@ -13,7 +13,7 @@ import pytest
 from oracle import acdc_oracle as O
 from paper_1511_05946_amd.workloads import (FLAG_ACCUMULATE, FLAG_BIAS, FLAG_MULTIPASS, WORKLOADS, make_bias,
                                             make_inputs)
-from tests.helpers import TOL_COMPLEX, TOL_REAL, rel_err, relu_safe_rows  # noqa: F401
+from tests.helpers import TOL_COMPLEX, TOL_REAL, bwd_tiles, rel_err, relu_safe_rows  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -200,21 +200,27 @@ def test_workloads_full_size_sampled(acdc, name):
 # at 4P tiles or more, as every benchmark batch has (128 to 1024 tiles); these
 # cases compare the
 # batch-summed dL/da, dL/dd (and dL/db) with the oracle at such tile counts.
+# Batches of at most 256 tiles of half the rows run those (see bwd_tiles), so
+# the kernels of the benchmarks' large batches need batches past that.
 @pytest.mark.parametrize("N,K,B,flags,tiles", [
     (1024, 12, 4096, P, 512),                    # acdc_n1024_k12_perm at its full batch (8 rows per tile)
-    (4096, 12, 256, P, 32),                      # the headline width and depth, 8 rows per tile
-    (4096, 12, 256, P | R, 32),                  # ... with ReLU (GPU decisions)
-    (4096, 12, 256, P | R | FLAG_BIAS, 32),      # ... with the D-domain bias
-    (4096, 8, 128, CX | P, 32),                  # afdf_n4096_k8_perm's width and depth (4 rows per tile)
-    (9216, 16, 64, P | R, 32),                   # acdc_n9216_k16_perm_relu's width and depth (2 rows per tile)
-    (9216, 16, 64, P, 32),                       # ... without ReLU: every stash slot, the K = 16 partials
+    (4096, 12, 256, P, 64),                      # the headline width and depth, small batches: 4 rows per tile
+    (4096, 12, 256, P | R, 64),                  # ... with ReLU (GPU decisions)
+    (4096, 12, 256, P | R | FLAG_BIAS, 64),      # ... with the D-domain bias
+    (4096, 12, 1029, P, 129),                    # the headline kernel, 8 rows per tile, a ragged last tile
+    (4096, 12, 1025, P | R, 129),                # ... with ReLU, one batch past the rule
+    (4096, 8, 128, CX | P, 64),                  # afdf_n4096_k8_perm's width and depth, small batches: 2 rows per tile
+    (4096, 8, 517, CX | P, 130),                 # ... and its kernel, 4 rows per tile
+    (9216, 16, 64, P | R, 64),                   # acdc_n9216_k16_perm_relu's width and depth, small batches: 1 row
+    (9216, 16, 64, P, 64),                       # ... without ReLU: every stash slot, the K = 16 partials
+    (9216, 16, 517, P | R, 259),                 # ... and its persistent kernel, 2 rows per tile
     (9216, 2, 1100, P, 550),                     # more tiles than resident workgroups (256 on MI355X): the
                                                  # persistent backward adds 2 or 3 tiles into each partial
     (9216, 1, 513, P, 257),                      # one tile more than the resident workgroups, a ragged last
                                                  # tile, a single layer: one workgroup adds a second tile
 ])
 def test_reduction_many_tiles(acdc, N, K, B, flags, tiles):
-    print(f"[case] reduction over {tiles} tiles", flush=True)
+    assert bwd_tiles(N, B, bool(flags & CX)) == tiles
     run_case(acdc, N, K, B, flags, seed=500 + N + K + flags)
 
 
@@ -424,8 +430,8 @@ def test_multipass_fused_widths(acdc, N):
 @pytest.mark.parametrize("N,K,B,flags", [(65536, 2, 3, P | R | FLAG_BIAS), (1 << 18, 2, 2, P | FLAG_BIAS),
                                          (1 << 20, 2, 2, P | FLAG_BIAS), (1 << 22, 4, 2, P | FLAG_BIAS)])
 def test_multipass_wide_rows(acdc, N, K, B, flags):
-    # 65536: one radix-4 pass; 2^18: one radix-16 pass; 2^20: radix-16 then
-    # radix-4; 2^22: radix 16 twice, and permutation tables too large to
+    # 65536: one radix-8 pass; 2^18: radix 16, then 2; 2^20: radix 16, then
+    # 8; 2^22: radix 16, then 32, and permutation tables too large to
     # build for all 4 layers at once (rebuilt per layer).  Rows of 2^18 and
     # more nearly always hold a ReLU decision within 1e-5 rms of zero, so
     # those run without ReLU.
@@ -433,8 +439,9 @@ def test_multipass_wide_rows(acdc, N, K, B, flags):
 
 
 def test_multipass_row_blocks(acdc):
-    # the backward sums images over blocks of 16 rows: 37 rows give two
-    # whole blocks and a ragged one; 4 permutation chunks per row
+    # the backward sums images over blocks of rows, of one row each at this
+    # batch (test_multipass_row_block_edges has longer ones); 4 column sets
+    # per row
     run_case(acdc, 65536, 2, 37, P | FLAG_BIAS, seed=76)
 
 
@@ -483,16 +490,15 @@ def test_multipass_accumulate_and_determinism(acdc):
 
 @pytest.mark.parametrize("N,K,B", [(32768, 2, 3), (65536, 2, 2), (1 << 20, 2, 2)])
 def test_multipass_complex_wide(acdc, N, K, B):
-    # past the fused complex cap (16384): 32768 (one radix-4 DIF pass, 4
-    # permutation chunks of 8192 complex), 65536 (radix 8), 2^20 (radix 16,
-    # then radix 8; 128 chunks)
+    # past the fused complex cap (16384): 32768 (one radix-8 DIF pass, 4
+    # column sets of 8192 complex), 65536 (radix 16), 2^20 (radix 16, then
+    # 16; 128 sets)
     run_case(acdc, N, K, B, CX | P, seed=N + 11)
 
 
 @pytest.mark.parametrize("N", [256, 4096, 16384])
 def test_multipass_complex_fused_widths(acdc, N):
-    # the fused complex widths forced through the multi-pass path (no DIF
-    # pass up to 8192)
+    # the fused complex widths forced through the multi-pass path
     run_case(acdc, N, 3, 21, CX | P | MP, seed=N + 13)
 
 

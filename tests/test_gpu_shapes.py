@@ -8,7 +8,8 @@ import pytest
 
 from oracle import acdc_oracle as O
 from paper_1511_05946_amd.workloads import FLAG_BIAS, FLAG_MULTIPASS, make_bias, make_inputs
-from tests.test_gpu_parity import acdc, run_case  # noqa: F401
+from tests.helpers import FWD_ALONE_MAX, TOL_REAL, rel_err
+from tests.test_gpu_parity import acdc, host, run_case  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -35,6 +36,46 @@ def test_backward_rows_rule(acdc, N, few, flags):  # noqa: F811
         run_case(acdc, N, 2 if flags & R else 1, B, flags, seed=N + B)
 
 
+# Forward workgroups: one wave a SIMD with loads ahead (ALONE) up to a batch
+# per width, whole workgroups beyond, and a persistent loop over tiles where
+# they are more than the device holds.  The last batch of the first form, the
+# first of the second, and one of several tiles a workgroup.  Rows are
+# independent, so copies of a few rows (checked against the oracle) give those
+# rows' results bit for bit in either form; the parameter gradients are the
+# oracle's with each row's gradient times its copies.
+@pytest.mark.parametrize("N,flags", [(8, P | FLAG_BIAS), (32, P), (64, P | FLAG_BIAS), (64, P | R), (128, P),
+                                     (256, P | FLAG_BIAS), (256, R), (512, P), (1024, P | R | FLAG_BIAS),
+                                     (2048, P | FLAG_BIAS), (2048, P | R), (4096, P)])
+def test_forward_rows_rule(acdc, N, flags):  # noqa: F811
+    import torch
+    K, few = 3, 11
+    many = {8: 600011, 32: 400009, 64: 200003, 128: 200003, 256: 60013, 512: 60013, 1024: 30011, 2048: 20011,
+            4096: 5003}[N]
+    run_case(acdc, N, K, few, flags, seed=N)
+    x, A, D, perm, gy = make_inputs(N, K, few, flags, N)
+    bias = make_bias(N, K, N) if flags & FLAG_BIAS else None
+    xt, At, Dt, pt, gt = (torch.from_numpy(t).cuda() for t in (x, A, D, perm, gy))
+    bt = torch.from_numpy(bias).cuda() if bias is not None else None
+    y0, s0 = acdc.forward(xt, At, Dt, pt, flags, save=True, bias=bt)
+    u0 = acdc.saved_layer_inputs(s0, xt, K, flags)
+    gx0 = acdc.backward(xt, gt, At, Dt, pt, flags, saved=s0, bias=bt)[0]
+    for B in (FWD_ALONE_MAX[N], FWD_ALONE_MAX[N] + 1, many):
+        print(f"[case] N={N} B={B} flags={flags}", flush=True)
+        whole = lambda t: t.repeat(-(-B // few), 1)[:B].contiguous()  # noqa: E731
+        xs = whole(xt)
+        y, s = acdc.forward(xs, At, Dt, pt, flags, save=True, bias=bt)
+        assert torch.equal(y, whole(y0))
+        for a, b in zip(acdc.saved_layer_inputs(s, xs, K, flags), u0):
+            assert torch.equal(a, whole(b))
+        got = acdc.backward(xs, whole(gt), At, Dt, pt, flags, saved=s, bias=bt)
+        assert torch.equal(got[0], whole(gx0))
+        if not flags & R:
+            copies = np.bincount(np.arange(B) % few, minlength=few).astype(np.float64)[:, None]
+            ref = O.backward(x, gy * copies, A, D, perm, flags & 7, B=bias)
+            for g, r in zip(got[1:], ref[1:]):
+                assert rel_err(host(g), r) < TOL_REAL
+
+
 def test_workspace_of_a_batch_serves_smaller_ones(acdc):  # noqa: F811
     # one workspace for a whole epoch: its last, ragged batch may run more
     # (smaller) backward workgroups than the full ones
@@ -52,16 +93,18 @@ def test_workspace_of_a_batch_serves_smaller_ones(acdc):  # noqa: F811
     assert float(((gA.double() - ref) / ref).abs().max()) < 1e-5
 
 
-# Multi-pass rows: every segment plan (M / L = 2 up to N = 16384), the first
-# DIF radix 2 to 16, a second level (N = 2^18), one permutation set a row or
-# several; without permutations the DIT and DIF passes join in one launch.
+# Multi-pass rows: every segment plan, the first DIF radix 2 to 16, a second
+# level (N = 2^18; 2^21 complex: radix 32, 256 permutation sets), one
+# permutation set a row or several; without permutations the DIT and DIF passes
+# join in one launch.
 @pytest.mark.parametrize("N,K,B,flags", [(512, 3, 3, P | R | FLAG_BIAS | MP), (1024, 2, 3, R | MP),
                                          (2048, 2, 5, P | FLAG_BIAS | MP), (8192, 3, 3, P | R | FLAG_BIAS | MP),
                                          (16384, 2, 3, R | FLAG_BIAS | MP), (32768, 3, 2, R | MP),
                                          (65536, 3, 3, R | FLAG_BIAS), (131072, 2, 2, P), (131072, 3, 2, FLAG_BIAS),
                                          (1 << 18, 3, 2, 0), (512, 3, 3, CX | MP), (1024, 2, 3, CX | P | MP),
                                          (2048, 2, 3, CX | P | MP), (8192, 3, 2, CX | P | MP), (32768, 3, 2, CX),
-                                         (131072, 2, 2, CX | P), (1 << 18, 2, 1, CX)])
+                                         (131072, 2, 2, CX | P), (1 << 18, 2, 1, CX), (16384, 2, 3, CX | P | MP),
+                                         (1 << 21, 2, 1, CX | P), (1 << 21, 2, 1, CX), (16384, 3, 3, P | MP)])
 def test_multipass_plans(acdc, N, K, B, flags):  # noqa: F811
     run_case(acdc, N, K, B, flags, seed=N % 1000 + B + flags)
 
