@@ -134,8 +134,9 @@ size_t acdc_forward_workspace_size(int64_t batch, int32_t N, int32_t K, uint32_t
  * behind the bias gradient (ACDC_FLAG_BIAS), and -- when have_saved is 0 and
  * acdc_saved_bytes(...) is not 0 -- room to recompute the layer inputs (the
  * paper's recompute policy, Sec. 5.3).  The multi-pass path adds its
- * spectra, row-block sums and permutation tables.  Never less for a larger
- * batch: a workspace of one batch serves the smaller ones. */
+ * spectra, row-block sums, rows between the halves of a permutation and
+ * permutation tables.  Never less for a larger batch: a workspace of one
+ * batch serves the smaller ones. */
 size_t acdc_backward_workspace_size(int64_t batch, int32_t N, int32_t K, uint32_t flags, int have_saved);
 
 /* Forward cascade: y = cascade(x).  `bias` is read with ACDC_FLAG_BIAS and

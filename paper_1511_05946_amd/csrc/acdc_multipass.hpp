@@ -52,6 +52,9 @@ namespace mp {
 // values sourced from set c, back to their places in it).  Every HBM access
 // is contiguous, or in runs of C / nC elements.  Table entries are masked
 // into range, so a malformed permutation cannot address outside its row.
+// Rows of one set (N <= 16384 floats) take the same launches; their list
+// follows the destinations.
+//
 // One layer's tables (layer l's sit stride ints further on):
 //   item[cC + i]   entry i of set c's list, ordered by destination set d:
 //                  (local source index << 8) | d
